@@ -4,6 +4,7 @@
 #include <stdio.h>
 #include <stdlib.h>
 #include <string.h>
+#include <algorithm>
 #include <new>
 
 #include "vf_internal.h"
@@ -100,7 +101,8 @@ size_t carve_model(vf_model *m, char *base) {
     m->draw = (DrawDesc *)cv.take(sizeof(DrawDesc) * VF_MAX_BATCH);
     m->draw_sums = (double *)cv.take((size_t)VF_MAX_BATCH * VF_STAT_CHUNKS * 8);
     m->scratch_i32 = (int32_t *)cv.take(64 * 4);
-    m->ss = (float *)cv.take((d / 16) * 64 * 4);
+    m->ss_ld = c.dtype == VF_F32 ? (int)std::max(R, (size_t)64) : 64;
+    m->ss = (float *)cv.take((d / 16) * (size_t)m->ss_ld * 4);
     m->counters = (int32_t *)cv.take(VF_N_COUNTERS * 4);
     m->topk_cand_v = (float *)cv.take((size_t)R * vf_topk_max_slices(c) * VF_TOPK_MAX * 4);
     m->topk_cand_i = (int32_t *)cv.take((size_t)R * vf_topk_max_slices(c) * VF_TOPK_MAX * 4);
@@ -130,6 +132,10 @@ SeqDesc describe(const vf_seq *s, int row0, int nrows) {
 int run_layers(vf_model *m, const Batch &b, const int32_t *tokens, int *tail_parts, hipStream_t st,
                bool tree = false) {
     const vf_config &c = m->cfg;
+    if (c.dtype == VF_F32) {
+        *tail_parts = 0;
+        return vf_run_layers_f32(m, b, tokens, tree, st);
+    }
     const int rows = b.total_rows, R = rows;  // partials are laid out with ld = rows of this call
     const int d = c.d_model, F = c.d_ffn, nq = c.n_q_heads * c.head_dim, nkv = c.n_kv_heads * c.head_dim;
     int rc;
@@ -177,6 +183,7 @@ int run_layers(vf_model *m, const Batch &b, const int32_t *tokens, int *tail_par
 int run_head(vf_model *m, int rows, int tail_parts, int row_lo, int row_hi, float *out, hipStream_t st) {
     const vf_config &c = m->cfg;
     int rc;
+    if (c.dtype == VF_F32) return vf_run_head_f32(m, row_lo, row_hi, out, st);
     { ProfScope ps(m, VF_SITE_SMALL, st);
       if ((rc = vf_launch_norm(m, m->final_norm, m->x, m->part, tail_parts, rows, rows, st))) return rc; }
     GemmPlan p = vf_gemm_plan(m, c.vocab, c.d_model, rows, 1);
@@ -264,6 +271,7 @@ int vf_model_create(const vf_config *cfg, const vf_weights *w, void *packed_dev,
     // activation buffers start at zero so that padding rows of a 16-row block are finite
     TRYHIP(hipMemsetAsync(m->h, 0, (size_t)((char *)m->base + m->bytes - (char *)m->h), st));
     if (c.dtype == VF_BF16) TRY(vf_fused_init(m, m->fz_ws, st));
+    else TRY(vf_f32_init(m));
     TRY(vf_accept_static_init());  // device address of the static acceptance scratch on this GPU
 #undef TRY
 #undef TRYHIP
@@ -449,11 +457,11 @@ int vf_prefill_chunk_topk(vf_model *m, vf_seq *s, const int32_t *tokens_dev, int
     b.s[0] = describe(s, 0, n_tokens);
     int tail = 0, rc;
     if ((rc = run_layers(m, b, tokens_dev, &tail, st))) return rc;
-    { ProfScope ps(m, VF_SITE_SMALL, st);
-      if ((rc = vf_launch_norm(m, m->final_norm, m->x, m->part, tail, n_tokens, n_tokens, st))) return rc; }
     GemmPlan p = vf_gemm_plan(m, c.vocab, c.d_model, n_tokens, 1);
     const float *last_row;
     if (p.tnb) {
+        { ProfScope ps(m, VF_SITE_SMALL, st);
+          if ((rc = vf_launch_norm(m, m->final_norm, m->x, m->part, tail, n_tokens, n_tokens, st))) return rc; }
         // many rows: the candidates leave the GEMM's epilogue, one list per (row, column tile)
         const int n_tiles = (c.vocab / 16 + p.tnb - 1) / p.tnb;
         p.topk = top_k;
@@ -470,9 +478,7 @@ int vf_prefill_chunk_topk(vf_model *m, vf_seq *s, const int32_t *tokens_dev, int
         }
         last_row = m->logits;
     } else {
-        { ProfScope ps(m, VF_SITE_HEAD, st);
-          if ((rc = vf_launch_gemm(m, m->lm_head, m->x, m->logits, c.vocab, c.d_model, n_tokens, 0, n_tokens, n_tokens,
-                                   p, st))) return rc; }
+        if ((rc = run_head(m, n_tokens, tail, 0, n_tokens, m->logits, st))) return rc;
         if ((rc = vf_launch_topk_slices(m, m->logits, n_tokens, top_k, st))) return rc;
         if ((rc = vf_launch_topk_merge(m, n_tokens, VF_STAT_CHUNKS, top_k, topk_logit_dev, topk_id_dev, st))) return rc;
         last_row = m->logits + (size_t)(n_tokens - 1) * c.vocab;

@@ -11,9 +11,9 @@ namespace {
 constexpr int ATT_THREADS = 128;  // query items (row, head-in-group) per workgroup
 constexpr int ATT_TK = 32;        // keys staged in LDS at a time
 
-template <typename T, int HD>
+template <int HD>
 __global__ __launch_bounds__(ATT_THREADS) void attn_partial_kernel(
-    Batch b, int layer, const T *__restrict__ q, float *__restrict__ part, int hq, int hkv, int n_splits,
+    Batch b, int layer, const bf16_t *__restrict__ q, float *__restrict__ part, int hq, int hkv, int n_splits,
     int chunk, float scale, const tree_mask_t *__restrict__ anc) {
     __shared__ float ks[ATT_TK][HD];
     __shared__ float vs[ATT_TK][HD];
@@ -40,11 +40,11 @@ __global__ __launch_bounds__(ATT_THREADS) void attn_partial_kernel(
     float qv[HD], o[HD];
 #pragma unroll
     for (int d = 0; d < HD; ++d) {
-        qv[d] = valid ? to_f32(q[((size_t)row * hq + head) * HD + d]) * scale : 0.f;
+        qv[d] = valid ? (float)(q[((size_t)row * hq + head) * HD + d]) * scale : 0.f;
         o[d] = 0.f;
     }
     float mx = -INFINITY, l = 0.f;
-    const T *kv = reinterpret_cast<const T *>(s.kv);
+    const bf16_t *kv = reinterpret_cast<const bf16_t *>(s.kv);
 
     for (int t0 = k_begin; t0 < k_end; t0 += ATT_TK) {
         const int nt = min(ATT_TK, k_end - t0);
@@ -52,11 +52,11 @@ __global__ __launch_bounds__(ATT_THREADS) void attn_partial_kernel(
         const int page = kv_page(s, t0), tin0 = t0 % VF_TILE;  // a 32-key tile never straddles a 64 tile
         for (int i = threadIdx.x; i < nt * HD; i += ATT_THREADS) {
             int t = i / HD, d = i % HD;
-            ks[t][d] = to_f32(kv[kv_k_index(layer, s.n_pages, page, hkv, kvh, tin0 + t, d, HD)]);
+            ks[t][d] = (float)(kv[kv_k_index(layer, s.n_pages, page, hkv, kvh, tin0 + t, d, HD)]);
         }
         for (int i = threadIdx.x; i < nt * HD; i += ATT_THREADS) {
             int d = i / nt, t = i % nt;
-            vs[t][d] = to_f32(kv[kv_v_index(layer, s.n_pages, page, hkv, kvh, tin0 + t, d, HD)]);
+            vs[t][d] = (float)(kv[kv_v_index(layer, s.n_pages, page, hkv, kvh, tin0 + t, d, HD)]);
         }
         __syncthreads();
         if (!valid) continue;
@@ -87,8 +87,8 @@ __global__ __launch_bounds__(ATT_THREADS) void attn_partial_kernel(
     for (int d = 0; d < HD; ++d) out[2 + d] = o[d];
 }
 
-template <typename T, int HD>
-__global__ __launch_bounds__(HD) void attn_combine_kernel(const float *__restrict__ part, T *__restrict__ o,
+template <int HD>
+__global__ __launch_bounds__(HD) void attn_combine_kernel(const float *__restrict__ part, bf16_t *__restrict__ o,
                                                           int hq, int n_splits, int ncb) {
     const int row = blockIdx.x / hq, head = blockIdx.x % hq, d = threadIdx.x;
     const float *p = part + ((size_t)row * hq + head) * n_splits * (HD + 2);
@@ -100,10 +100,10 @@ __global__ __launch_bounds__(HD) void attn_combine_kernel(const float *__restric
         L += p[s * (HD + 2) + 1] * w;
         acc += p[s * (HD + 2) + 2 + d] * w;
     }
-    o[act_index<T>(row, head * HD + d, hq * HD, ncb)] = from_f32<T>(acc / L);
+    o[xfrag_index(row, head * HD + d, ncb)] = (bf16_t)(acc / L);
 }
 
-template <typename T, int HD>
+template <int HD>
 int launch(const vf_model *m, const Batch &b, int layer, const tree_mask_t *anc, hipStream_t st) {
     const vf_config &c = m->cfg;
     const int group = c.n_q_heads / c.n_kv_heads;
@@ -121,13 +121,13 @@ int launch(const vf_model *m, const Batch &b, int layer, const tree_mask_t *anc,
     int chunk = (max_keys + n_splits - 1) / n_splits;
     chunk = (chunk + VF_TILE - 1) / VF_TILE * VF_TILE;
     const float scale = 1.0f / sqrtf((float)HD);
-    hipLaunchKernelGGL((attn_partial_kernel<T, HD>), dim3(tiles, n_splits, b.n_seqs * c.n_kv_heads),
-                       dim3(ATT_THREADS), 0, st, b, layer, (const T *)m->q, m->attn_part, c.n_q_heads,
+    hipLaunchKernelGGL((attn_partial_kernel<HD>), dim3(tiles, n_splits, b.n_seqs * c.n_kv_heads),
+                       dim3(ATT_THREADS), 0, st, b, layer, (const bf16_t *)m->q, m->attn_part, c.n_q_heads,
                        c.n_kv_heads, n_splits, chunk, scale, anc);
     VF_LAUNCH_CHECK("attn_partial");
     const int ncb = (b.total_rows + 15) >> 4;
-    hipLaunchKernelGGL((attn_combine_kernel<T, HD>), dim3(b.total_rows * c.n_q_heads), dim3(HD), 0, st,
-                       m->attn_part, (T *)m->o, c.n_q_heads, n_splits, ncb);
+    hipLaunchKernelGGL((attn_combine_kernel<HD>), dim3(b.total_rows * c.n_q_heads), dim3(HD), 0, st,
+                       m->attn_part, (bf16_t *)m->o, c.n_q_heads, n_splits, ncb);
     VF_LAUNCH_CHECK("attn_combine");
     return VF_OK;
 }
@@ -136,13 +136,8 @@ int launch(const vf_model *m, const Batch &b, int layer, const tree_mask_t *anc,
 
 int vf_launch_attention(const vf_model *m, const Batch &b, int layer, const tree_mask_t *anc, hipStream_t st) {
     const vf_config &c = m->cfg;
-    if (c.dtype == VF_BF16) {
-        if (m->fast_path && !anc) return vf_launch_attention_rows(m, b, layer, st);  // MFMA kernel
-        if (c.head_dim == 64) return launch<bf16_t, 64>(m, b, layer, anc, st);
-        if (c.head_dim == 128) return launch<bf16_t, 128>(m, b, layer, anc, st);
-    } else {
-        if (c.head_dim == 64) return launch<float, 64>(m, b, layer, anc, st);
-        if (c.head_dim == 128) return launch<float, 128>(m, b, layer, anc, st);
-    }
+    if (m->fast_path && !anc) return vf_launch_attention_rows(m, b, layer, st);  // MFMA kernel
+    if (c.head_dim == 64) return launch<64>(m, b, layer, anc, st);
+    if (c.head_dim == 128) return launch<128>(m, b, layer, anc, st);
     return vf_fail(VF_ERR_UNSUPPORTED, "head_dim %d (built for 64 and 128)", c.head_dim);
 }

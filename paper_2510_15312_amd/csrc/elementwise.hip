@@ -61,14 +61,13 @@ __global__ void rope_table_kernel(float *__restrict__ cosv, float *__restrict__ 
 
 // ---- forward pass helpers -----------------------------------------------------------------------
 
-template <typename T>
-__global__ void embed_kernel(const T *__restrict__ E, const int32_t *__restrict__ tokens, Batch b,
+__global__ void embed_kernel(const bf16_t *__restrict__ E, const int32_t *__restrict__ tokens, Batch b,
                              float *__restrict__ h, int d, int vocab) {
     const int row = blockIdx.x;
     int tok = tokens[row];
     if (tok == VF_PENDING) tok = b.s[find_seq(b, row)].state[1];
     if (tok < 0 || tok >= vocab) tok = 0;
-    for (int k = threadIdx.x; k < d; k += blockDim.x) h[(size_t)row * d + k] = to_f32(E[w_index<T>(tok, k, d)]);
+    for (int k = threadIdx.x; k < d; k += blockDim.x) h[(size_t)row * d + k] = (float)E[wfrag_index(tok, k, d)];
 }
 
 __device__ inline float block_sum(float v, float *red) {
@@ -82,11 +81,10 @@ __device__ inline float block_sum(float v, float *red) {
     return s;
 }
 
-// h[row] += sum of partials (if any); x[row] = T(rmsnorm(h[row]) * gain) in activation layout.
-template <typename T>
+// h[row] += sum of partials (if any); x[row] = bf16(rmsnorm(h[row]) * gain) in activation layout.
 __global__ __launch_bounds__(256) void norm_kernel(float *__restrict__ h, const float *__restrict__ part,
                                                    int nparts, int ld_rows, const float *__restrict__ gain,
-                                                   T *__restrict__ x, int d, int ncb, float eps) {
+                                                   bf16_t *__restrict__ x, int d, int ncb, float eps) {
     __shared__ float red[4];
     const int row = blockIdx.x;
     float ss = 0.f;
@@ -99,10 +97,10 @@ __global__ __launch_bounds__(256) void norm_kernel(float *__restrict__ h, const 
     ss = block_sum(ss, red);
     const float inv = 1.0f / sqrtf(ss / (float)d + eps);
     for (int k = threadIdx.x; k < d; k += 256)
-        x[act_index<T>(row, k, d, ncb)] = from_f32<T>(h[(size_t)row * d + k] * inv * gain[k]);
+        x[xfrag_index(row, k, ncb)] = (bf16_t)(h[(size_t)row * d + k] * inv * gain[k]);
 }
 
-// The same for bf16 activations with d a multiple of 8: a thread owns runs of eight consecutive
+// The same for d up to 4096: a thread owns runs of eight consecutive
 // elements (one 16-byte piece of an activation fragment), keeps them in registers between the
 // sum of squares and the scaling, and stores the piece whole.
 template <int VPT>
@@ -164,10 +162,9 @@ __global__ __launch_bounds__(256) void norm_bf16_vec_kernel(float *__restrict__ 
 // QKV epilogue: one thread per (row, head, rotary pair).  Heads 0..Hq-1 are q, then Hkv k heads,
 // then Hkv v heads (v is not rotated).  Pair = elements (i, i + hd/2) of a head; the packed
 // q and k weight rows (and biases) hold a pair in neighbouring columns 2i, 2i+1.
-template <typename T>
 __global__ void qkv_finish_kernel(const float *__restrict__ part, int nparts, int ld_rows, Batch b, int layer,
                                   const float *__restrict__ bias, const float *__restrict__ cosv,
-                                  const float *__restrict__ sinv, T *__restrict__ q, int hq, int hkv, int hd,
+                                  const float *__restrict__ sinv, bf16_t *__restrict__ q, int hq, int hkv, int hd,
                                   const int32_t *__restrict__ depth) {
     const int half = hd >> 1;
     const int heads = hq + 2 * hkv;
@@ -198,28 +195,27 @@ __global__ void qkv_finish_kernel(const float *__restrict__ part, int nparts, in
         v0 = r0; v1 = r1;
     }
     if (head < hq) {
-        T *qr = q + ((size_t)row * hq + head) * hd;
-        qr[i] = from_f32<T>(v0);
-        qr[i + half] = from_f32<T>(v1);
+        bf16_t *qr = q + ((size_t)row * hq + head) * hd;
+        qr[i] = (bf16_t)(v0);
+        qr[i + half] = (bf16_t)(v1);
         return;
     }
-    T *kv = reinterpret_cast<T *>(s.kv);
+    bf16_t *kv = reinterpret_cast<bf16_t *>(s.kv);
     const int page = kv_page(s, slot), tin = slot % VF_TILE;
     if (head < hq + hkv) {
         const int kh = head - hq;
-        kv[kv_k_index(layer, s.n_pages, page, hkv, kh, tin, i, hd)] = from_f32<T>(v0);
-        kv[kv_k_index(layer, s.n_pages, page, hkv, kh, tin, i + half, hd)] = from_f32<T>(v1);
+        kv[kv_k_index(layer, s.n_pages, page, hkv, kh, tin, i, hd)] = (bf16_t)(v0);
+        kv[kv_k_index(layer, s.n_pages, page, hkv, kh, tin, i + half, hd)] = (bf16_t)(v1);
     } else {
         const int vh = head - hq - hkv;
-        kv[kv_v_index(layer, s.n_pages, page, hkv, vh, tin, i, hd)] = from_f32<T>(v0);
-        kv[kv_v_index(layer, s.n_pages, page, hkv, vh, tin, i + half, hd)] = from_f32<T>(v1);
+        kv[kv_v_index(layer, s.n_pages, page, hkv, vh, tin, i, hd)] = (bf16_t)(v0);
+        kv[kv_v_index(layer, s.n_pages, page, hkv, vh, tin, i + half, hd)] = (bf16_t)(v1);
     }
 }
 
-// a[row, f] = T(silu(gate) * up); the gate/up GEMM output interleaves 16-wide blocks: block 2j is
+// a[row, f] = bf16(silu(gate) * up); the gate/up GEMM output interleaves 16-wide blocks: block 2j is
 // gate rows 16j.., block 2j+1 the matching up rows.
-template <typename T>
-__global__ void swiglu_kernel(const float *__restrict__ part, int nparts, int ld_rows, T *__restrict__ a,
+__global__ void swiglu_kernel(const float *__restrict__ part, int nparts, int ld_rows, bf16_t *__restrict__ a,
                               int rows, int F, int ncb) {
     size_t idx = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
     if (idx >= (size_t)rows * F) return;
@@ -232,17 +228,7 @@ __global__ void swiglu_kernel(const float *__restrict__ part, int nparts, int ld
         u += pr[nu];
     }
     const float sg = g / (1.0f + expf(-g));
-    a[act_index<T>(row, f, F, ncb)] = from_f32<T>(sg * u);
-}
-
-__global__ void reduce_rows_kernel(const float *__restrict__ part, int nparts, int ld_rows, int N, int row_lo,
-                                   int nrows, float *__restrict__ out, int out_ld) {
-    size_t idx = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
-    if (idx >= (size_t)nrows * N) return;
-    const int r = (int)(idx / N), n = (int)(idx % N);
-    float v = 0.f;
-    for (int p = 0; p < nparts; ++p) v += part[((size_t)p * ld_rows + row_lo + r) * N + n];
-    out[(size_t)r * out_ld + n] = v;
+    a[xfrag_index(row, f, ncb)] = (bf16_t)(sg * u);
 }
 
 __global__ void state_set_kernel(int32_t *state, int idx, int32_t value) { state[idx] = value; }
@@ -367,12 +353,8 @@ int vf_launch_rope_table(const vf_model *m, hipStream_t st) {
 }
 
 int vf_launch_embed(const vf_model *m, const Batch &b, const int32_t *tokens, hipStream_t st) {
-    if (m->cfg.dtype == VF_BF16)
-        hipLaunchKernelGGL(embed_kernel<bf16_t>, dim3(b.total_rows), dim3(256), 0, st, (const bf16_t *)m->embed,
-                           tokens, b, m->h, m->cfg.d_model, m->cfg.vocab);
-    else
-        hipLaunchKernelGGL(embed_kernel<float>, dim3(b.total_rows), dim3(256), 0, st, (const float *)m->embed,
-                           tokens, b, m->h, m->cfg.d_model, m->cfg.vocab);
+    hipLaunchKernelGGL(embed_kernel, dim3(b.total_rows), dim3(256), 0, st, (const bf16_t *)m->embed, tokens, b, m->h,
+                       m->cfg.d_model, m->cfg.vocab);
     VF_LAUNCH_CHECK("embed");
     return VF_OK;
 }
@@ -381,18 +363,15 @@ int vf_launch_norm(const vf_model *m, const float *gain, void *x_out, const floa
                    int ld_rows, hipStream_t st) {
     const int ncb = (rows + 15) >> 4;
     const int d = m->cfg.d_model;
-    if (m->cfg.dtype == VF_BF16 && d % 8 == 0 && d <= 2048)
+    if (d <= 2048)
         hipLaunchKernelGGL(norm_bf16_vec_kernel<1>, dim3(rows), dim3(256), 0, st, m->h, part, nparts, ld_rows, gain,
                            (u32x4_t *)x_out, d, ncb, m->cfg.rms_eps);
-    else if (m->cfg.dtype == VF_BF16 && d % 8 == 0 && d <= 4096)
+    else if (d <= 4096)
         hipLaunchKernelGGL(norm_bf16_vec_kernel<2>, dim3(rows), dim3(256), 0, st, m->h, part, nparts, ld_rows, gain,
                            (u32x4_t *)x_out, d, ncb, m->cfg.rms_eps);
-    else if (m->cfg.dtype == VF_BF16)
-        hipLaunchKernelGGL(norm_kernel<bf16_t>, dim3(rows), dim3(256), 0, st, m->h, part, nparts, ld_rows, gain,
-                           (bf16_t *)x_out, m->cfg.d_model, ncb, m->cfg.rms_eps);
     else
-        hipLaunchKernelGGL(norm_kernel<float>, dim3(rows), dim3(256), 0, st, m->h, part, nparts, ld_rows, gain,
-                           (float *)x_out, m->cfg.d_model, ncb, m->cfg.rms_eps);
+        hipLaunchKernelGGL(norm_kernel, dim3(rows), dim3(256), 0, st, m->h, part, nparts, ld_rows, gain, (bf16_t *)x_out, d, ncb,
+                           m->cfg.rms_eps);
     VF_LAUNCH_CHECK("norm");
     return VF_OK;
 }
@@ -401,39 +380,18 @@ int vf_launch_qkv_finish(const vf_model *m, const Batch &b, int layer, const flo
                          int ld_rows, const int32_t *depth, hipStream_t st) {
     const vf_config &c = m->cfg;
     const int total = b.total_rows * (c.n_q_heads + 2 * c.n_kv_heads) * (c.head_dim / 2);
-    const float *bias = c.qkv_bias ? m->layers[layer].bqkv : nullptr;
-    if (c.dtype == VF_BF16)
-        hipLaunchKernelGGL(qkv_finish_kernel<bf16_t>, dim3(nblocks(total, 256)), dim3(256), 0, st, part, nparts,
-                           ld_rows, b, layer, bias, m->rope_cos, m->rope_sin, (bf16_t *)m->q, c.n_q_heads,
-                           c.n_kv_heads, c.head_dim, depth);
-    else
-        hipLaunchKernelGGL(qkv_finish_kernel<float>, dim3(nblocks(total, 256)), dim3(256), 0, st, part, nparts,
-                           ld_rows, b, layer, bias, m->rope_cos, m->rope_sin, (float *)m->q, c.n_q_heads,
-                           c.n_kv_heads, c.head_dim, depth);
+    hipLaunchKernelGGL(qkv_finish_kernel, dim3(nblocks(total, 256)), dim3(256), 0, st, part, nparts, ld_rows, b, layer,
+                       c.qkv_bias ? m->layers[layer].bqkv : nullptr, m->rope_cos, m->rope_sin, (bf16_t *)m->q, c.n_q_heads,
+                       c.n_kv_heads, c.head_dim, depth);
     VF_LAUNCH_CHECK("qkv_finish");
     return VF_OK;
 }
 
 int vf_launch_swiglu(const vf_model *m, const float *part, int nparts, int rows, int ld_rows, hipStream_t st) {
     const int F = m->cfg.d_ffn, ncb = (rows + 15) >> 4;
-    const size_t total = (size_t)rows * F;
-    if (m->cfg.dtype == VF_BF16)
-        hipLaunchKernelGGL(swiglu_kernel<bf16_t>, dim3(nblocks(total, 256)), dim3(256), 0, st, part, nparts,
-                           ld_rows, (bf16_t *)m->a, rows, F, ncb);
-    else
-        hipLaunchKernelGGL(swiglu_kernel<float>, dim3(nblocks(total, 256)), dim3(256), 0, st, part, nparts,
-                           ld_rows, (float *)m->a, rows, F, ncb);
+    hipLaunchKernelGGL(swiglu_kernel, dim3(nblocks((size_t)rows * F, 256)), dim3(256), 0, st, part, nparts, ld_rows,
+                       (bf16_t *)m->a, rows, F, ncb);
     VF_LAUNCH_CHECK("swiglu");
-    return VF_OK;
-}
-
-int vf_launch_reduce_rows(const vf_model *, const float *part, int nparts, int N, int row_lo, int row_hi,
-                          int ld_rows, float *out, int out_ld, hipStream_t st) {
-    const int nrows = row_hi - row_lo;
-    if (nrows <= 0) return VF_OK;
-    hipLaunchKernelGGL(reduce_rows_kernel, dim3(nblocks((size_t)nrows * N, 256)), dim3(256), 0, st, part, nparts,
-                       ld_rows, N, row_lo, nrows, out, out_ld);
-    VF_LAUNCH_CHECK("reduce_rows");
     return VF_OK;
 }
 

@@ -370,32 +370,6 @@ void gemm_rows_kernel(const u32x4 *__restrict__ Wp, const u32x4 *__restrict__ Xp
     }
 }
 
-// float32 model: plain fused-multiply-add GEMM, one wavefront per output column, 8 rows at a time.
-__global__ __launch_bounds__(256) void gemm_f32_kernel(const float *__restrict__ W,
-                                                        const float *__restrict__ X,
-                                                        float *__restrict__ out, int N, int K,
-                                                        int row_lo, int row_hi) {
-    const int lane = threadIdx.x & 63;
-    const int n = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (n >= N) return;
-    const float *wr = W + (size_t)n * K;
-    for (int r0 = row_lo; r0 < row_hi; r0 += 8) {
-        float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-        for (int k = lane; k < K; k += 64) {
-            float wv = wr[k];
-#pragma unroll
-            for (int i = 0; i < 8; ++i)
-                if (r0 + i < row_hi) acc[i] = fmaf(wv, X[(size_t)(r0 + i) * K + k], acc[i]);
-        }
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            float v = acc[i];
-            for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-            if (lane == 0 && r0 + i < row_hi) out[(size_t)(r0 + i) * N + n] = v;
-        }
-    }
-}
-
 template <int NB>
 int launch_bf16(const vf_model *m, const void *W, const void *X, float *part, int N, int K, int ncb,
                 int row_lo, int row_hi, int ld_rows, GemmPlan plan, hipStream_t st) {
@@ -475,12 +449,6 @@ int vf_launch_gemm(const vf_model *m, const void *W, const void *X, float *part,
             go(gemm_rows_kernel<4, 8, 2, ROWS_NW_NARROW, ROWS_SETS_NARROW, ROWS_EPI_PARTIAL>, ROWS_NW_NARROW);
         }
         VF_LAUNCH_CHECK("gemm_rows");
-        return VF_OK;
-    }
-    if (m->cfg.dtype == VF_F32) {
-        hipLaunchKernelGGL(gemm_f32_kernel, dim3((N + 3) / 4), dim3(256), 0, st, (const float *)W,
-                           (const float *)X, part, N, K, row_lo, row_hi);
-        VF_LAUNCH_CHECK("gemm_f32");
         return VF_OK;
     }
     const int ncb = (rows_total + 15) >> 4;

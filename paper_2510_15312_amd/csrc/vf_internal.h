@@ -90,7 +90,8 @@ struct vf_model {
     DrawDesc *draw;             // [VF_MAX_BATCH]
     double *draw_sums;          // [VF_MAX_BATCH, VF_STAT_CHUNKS]
     int32_t *scratch_i32;       // [64]
-    float *ss;                  // per-16-column sums of squares of h rows, [d/16][64]
+    float *ss;                  // per-16-column sums of squares of h rows, [d/16][ss_ld]
+    int ss_ld;                  // 64 (few-row kernels), float32 model: rows of the largest call
     int32_t *counters;          // split-K arrival counters, [VF_N_COUNTERS], zero between kernels
     float *topk_cand_v;         // top-k candidates per (row, vocabulary slice), [R, slices, VF_TOPK_MAX]
     int32_t *topk_cand_i;
@@ -172,14 +173,6 @@ __host__ __device__ inline size_t xfrag_index(int row, int k, int ncb) {
     int lane = (((k >> 3) & 3) << 4) | (row & 15);
     return (((size_t)kb * ncb + cb) * 64 + lane) * 8 + (k & 7);
 }
-template <typename T> __device__ inline size_t act_index(int row, int k, int K, int ncb);
-template <> __device__ inline size_t act_index<float>(int row, int k, int K, int) { return (size_t)row * K + k; }
-template <> __device__ inline size_t act_index<bf16_t>(int row, int k, int, int ncb) { return xfrag_index(row, k, ncb); }
-
-template <typename T> __device__ inline size_t w_index(int n, int k, int K);
-template <> __device__ inline size_t w_index<float>(int n, int k, int K) { return (size_t)n * K + k; }
-template <> __device__ inline size_t w_index<bf16_t>(int n, int k, int K) { return wfrag_index(n, k, K); }
-
 // KV pool: per layer and 64-token page, the K blocks of the kv heads, then their V blocks, 64 * hd
 // elements each, stored in the order the attention MFMAs read them, so that a wavefront's load of one
 // operand fragment is one contiguous kilobyte (lane l reads 16 bytes at 16 * l):
@@ -267,8 +260,6 @@ int vf_launch_accept_tree(const vf_model *m, const Batch &b, const AcceptBatch &
                           const int32_t *tokens, const float *logits, int32_t *n_accept, int32_t *out_tokens,
                           int32_t *y, int32_t *path, hipStream_t st);
 int vf_launch_swiglu(const vf_model *m, const float *part, int nparts, int rows, int ld_rows, hipStream_t st);
-int vf_launch_reduce_rows(const vf_model *m, const float *part, int nparts, int N, int row_lo, int row_hi,
-                          int ld_rows, float *out, int out_ld, hipStream_t st);
 // anc != NULL: rows of the call see, among the call's rows, only those in their ancestor mask
 int vf_launch_attention(const vf_model *m, const Batch &b, int layer, const tree_mask_t *anc, hipStream_t st);
 int vf_launch_state_set(int32_t *state, int idx, int32_t value, hipStream_t st);
@@ -288,6 +279,10 @@ int vf_accept_static_init();
 int vf_launch_attention_rows(const vf_model *m, const Batch &b, int layer, hipStream_t st);
 bool vf_fast_path_ok(const vf_model *m, int total_rows);
 int vf_run_fast(vf_model *m, const Batch &b, const int32_t *tokens, float *logits_out, hipStream_t st);
+// the float32 model's layers and output head
+int vf_f32_init(const vf_model *m);
+int vf_run_layers_f32(vf_model *m, const Batch &b, const int32_t *tokens, bool tree, hipStream_t st);
+int vf_run_head_f32(vf_model *m, int row_lo, int row_hi, float *out, hipStream_t st);
 size_t vf_fused_workspace_bytes(const vf_config &c);
 int vf_fused_init(vf_model *m, char *ws, hipStream_t st);
 bool vf_fused_ok(const vf_model *m, const Batch &b);
