@@ -139,41 +139,35 @@ int run_layers(vf_model *m, const Batch &b, const int32_t *tokens, int *tail_par
     const int rows = b.total_rows, R = rows;  // partials are laid out with ld = rows of this call
     const int d = c.d_model, F = c.d_ffn, nq = c.n_q_heads * c.head_dim, nkv = c.n_kv_heads * c.head_dim;
     int rc;
+    const GemmPlan qkv = vf_gemm_plan(m, nq + 2 * nkv, d, rows, GEMM_SPLIT), po = vf_gemm_plan(m, d, nq, rows, GEMM_SPLIT);
+    const GemmPlan gu = vf_gemm_plan(m, 2 * F, d, rows, GEMM_SWIGLU), down = vf_gemm_plan(m, d, F, rows, GEMM_SPLIT);
+    const bool act_in_gemm = gu.epi == GEMM_SWIGLU;  // the activation function is the gate/up GEMM's epilogue
     if ((rc = vf_launch_embed(m, b, tokens, st))) return rc;
     int nparts = 0;
     for (int l = 0; l < c.n_layers; ++l) {
         const LayerPacked &lp = m->layers[l];
         { ProfScope ps(m, VF_SITE_SMALL, st);
           if ((rc = vf_launch_norm(m, lp.attn_norm, m->x, m->part, nparts, rows, R, st))) return rc; }
-        GemmPlan p = vf_gemm_plan(m, nq + 2 * nkv, d, rows, 0);
         { ProfScope ps(m, VF_SITE_QKV, st);
-          if ((rc = vf_launch_gemm(m, lp.wqkv, m->x, m->part, nq + 2 * nkv, d, rows, 0, rows, R, p, st))) return rc; }
+          if ((rc = vf_launch_gemm(m, lp.wqkv, m->x, m->part, nq + 2 * nkv, d, rows, 0, rows, R, qkv, st))) return rc; }
         { ProfScope ps(m, VF_SITE_SMALL, st);
-          if ((rc = vf_launch_qkv_finish(m, b, l, m->part, p.ks, R, tree ? m->tree_depth : nullptr, st))) return rc; }
+          if ((rc = vf_launch_qkv_finish(m, b, l, m->part, qkv.ks, R, tree ? m->tree_depth : nullptr, st))) return rc; }
         { ProfScope ps(m, VF_SITE_ATTN, st);
           if ((rc = vf_launch_attention(m, b, l, tree ? m->tree_anc : nullptr, st))) return rc; }
-        p = vf_gemm_plan(m, d, nq, rows, 0);
         { ProfScope ps(m, VF_SITE_O, st);
-          if ((rc = vf_launch_gemm(m, lp.wo, m->o, m->part, d, nq, rows, 0, rows, R, p, st))) return rc; }
+          if ((rc = vf_launch_gemm(m, lp.wo, m->o, m->part, d, nq, rows, 0, rows, R, po, st))) return rc; }
         { ProfScope ps(m, VF_SITE_SMALL, st);
-          if ((rc = vf_launch_norm(m, lp.ffn_norm, m->x, m->part, p.ks, rows, R, st))) return rc; }
-        // many rows: one K range per workgroup, and the activation function is the GEMM's epilogue
-        p = vf_gemm_plan(m, 2 * F, d, rows, 0);
-        if (p.tnb) {
-            p = vf_gemm_plan(m, 2 * F, d, rows, 1);
-            p.swiglu = 1;
-        }
+          if ((rc = vf_launch_norm(m, lp.ffn_norm, m->x, m->part, po.ks, rows, R, st))) return rc; }
         { ProfScope ps(m, VF_SITE_GATEUP, st);
-          if ((rc = vf_launch_gemm(m, lp.wgu, m->x, p.swiglu ? (float *)m->a : m->part, 2 * F, d, rows, 0, rows, R, p,
+          if ((rc = vf_launch_gemm(m, lp.wgu, m->x, act_in_gemm ? (float *)m->a : m->part, 2 * F, d, rows, 0, rows, R, gu,
                                    st))) return rc; }
-        if (!p.swiglu) {
+        if (!act_in_gemm) {
             ProfScope ps(m, VF_SITE_SMALL, st);
-            if ((rc = vf_launch_swiglu(m, m->part, p.ks, rows, R, st))) return rc;
+            if ((rc = vf_launch_swiglu(m, m->part, gu.ks, rows, R, st))) return rc;
         }
-        p = vf_gemm_plan(m, d, F, rows, 0);
         { ProfScope ps(m, VF_SITE_DOWN, st);
-          if ((rc = vf_launch_gemm(m, lp.wd, m->a, m->part, d, F, rows, 0, rows, R, p, st))) return rc; }
-        nparts = p.ks;
+          if ((rc = vf_launch_gemm(m, lp.wd, m->a, m->part, d, F, rows, 0, rows, R, down, st))) return rc; }
+        nparts = down.ks;
     }
     *tail_parts = nparts;
     return VF_OK;
@@ -186,7 +180,7 @@ int run_head(vf_model *m, int rows, int tail_parts, int row_lo, int row_hi, floa
     if (c.dtype == VF_F32) return vf_run_head_f32(m, row_lo, row_hi, out, st);
     { ProfScope ps(m, VF_SITE_SMALL, st);
       if ((rc = vf_launch_norm(m, m->final_norm, m->x, m->part, tail_parts, rows, rows, st))) return rc; }
-    GemmPlan p = vf_gemm_plan(m, c.vocab, c.d_model, rows, 1);
+    const GemmPlan p = vf_gemm_plan(m, c.vocab, c.d_model, row_hi - row_lo, GEMM_PARTIAL);
     ProfScope ps(m, VF_SITE_HEAD, st);
     // with ks == 1 the "partial" [ld_rows][V] is the logits matrix itself: shift the base so
     // that row_lo lands on out[0]
@@ -246,19 +240,18 @@ int vf_model_create(const vf_config *cfg, const vf_weights *w, void *packed_dev,
     auto fail = [&](int code) { delete[] m->layers; delete m->prof; delete m->prof_pool; delete m; return code; };
 #define TRY(x) do { int rc_ = (x); if (rc_) return fail(rc_); } while (0)
 #define TRYHIP(x) do { hipError_t e_ = (x); if (e_ != hipSuccess) return fail(vf_fail(VF_ERR_HIP, "%s: %s", #x, hipGetErrorString(e_))); } while (0)
-    TRY(vf_launch_pack(m, w->embed, m->embed, c.vocab, d, 0, 1, 0, st));
-    if (!c.tie_embeddings) TRY(vf_launch_pack(m, w->lm_head, m->lm_head, c.vocab, d, 0, 1, 0, st));
+    TRY(vf_launch_pack(m, w->embed, nullptr, m->embed, c.vocab, d, 0, 0, st));
+    if (!c.tie_embeddings) TRY(vf_launch_pack(m, w->lm_head, nullptr, m->lm_head, c.vocab, d, 0, 0, st));
     TRYHIP(hipMemcpyAsync(m->final_norm, w->final_norm, (size_t)d * 4, hipMemcpyDeviceToDevice, st));
     for (int l = 0; l < c.n_layers; ++l) {
         const vf_layer_w &lw = w->layers[l];
         LayerPacked &lp = m->layers[l];
-        TRY(vf_launch_pack(m, lw.wq, lp.wqkv, nq, d, 0, 1, hd, st));
-        TRY(vf_launch_pack(m, lw.wk, lp.wqkv, nkv, d, nq / 16, 1, hd, st));
-        TRY(vf_launch_pack(m, lw.wv, lp.wqkv, nkv, d, (nq + nkv) / 16, 1, 0, st));
-        TRY(vf_launch_pack(m, lw.wo, lp.wo, d, nq, 0, 1, 0, st));
-        TRY(vf_launch_pack(m, lw.w_gate, lp.wgu, F, d, 0, 2, 0, st));
-        TRY(vf_launch_pack(m, lw.w_up, lp.wgu, F, d, 1, 2, 0, st));
-        TRY(vf_launch_pack(m, lw.w_down, lp.wd, d, F, 0, 1, 0, st));
+        TRY(vf_launch_pack(m, lw.wq, nullptr, lp.wqkv, nq, d, 0, hd, st));
+        TRY(vf_launch_pack(m, lw.wk, nullptr, lp.wqkv, nkv, d, nq / 16, hd, st));
+        TRY(vf_launch_pack(m, lw.wv, nullptr, lp.wqkv, nkv, d, (nq + nkv) / 16, 0, st));
+        TRY(vf_launch_pack(m, lw.wo, nullptr, lp.wo, d, nq, 0, 0, st));
+        TRY(vf_launch_pack(m, lw.w_gate, lw.w_up, lp.wgu, 2 * F, d, 0, 0, st));
+        TRY(vf_launch_pack(m, lw.w_down, nullptr, lp.wd, d, F, 0, 0, st));
         TRYHIP(hipMemcpyAsync(lp.attn_norm, lw.attn_norm, (size_t)d * 4, hipMemcpyDeviceToDevice, st));
         TRYHIP(hipMemcpyAsync(lp.ffn_norm, lw.ffn_norm, (size_t)d * 4, hipMemcpyDeviceToDevice, st));
         if (c.qkv_bias) {
@@ -270,8 +263,12 @@ int vf_model_create(const vf_config *cfg, const vf_weights *w, void *packed_dev,
     TRY(vf_launch_rope_table(m, st));
     // activation buffers start at zero so that padding rows of a 16-row block are finite
     TRYHIP(hipMemsetAsync(m->h, 0, (size_t)((char *)m->base + m->bytes - (char *)m->h), st));
-    if (c.dtype == VF_BF16) TRY(vf_fused_init(m, m->fz_ws, st));
-    else TRY(vf_f32_init(m));
+    if (c.dtype == VF_BF16) {
+        TRY(vf_fused_init(m, m->fz_ws, st));
+        TRY(vf_gemm_init());
+    } else {
+        TRY(vf_f32_init(m));
+    }
     TRY(vf_accept_static_init());  // device address of the static acceptance scratch on this GPU
 #undef TRY
 #undef TRYHIP
@@ -457,21 +454,23 @@ int vf_prefill_chunk_topk(vf_model *m, vf_seq *s, const int32_t *tokens_dev, int
     b.s[0] = describe(s, 0, n_tokens);
     int tail = 0, rc;
     if ((rc = run_layers(m, b, tokens_dev, &tail, st))) return rc;
-    GemmPlan p = vf_gemm_plan(m, c.vocab, c.d_model, n_tokens, 1);
     const float *last_row;
-    if (p.tnb) {
+    GemmPlan p;
+    p.epi = GEMM_PARTIAL;
+    if (c.dtype == VF_BF16) p = vf_gemm_plan(m, c.vocab, c.d_model, n_tokens, GEMM_TOPK);
+    if (p.epi == GEMM_TOPK) {
         { ProfScope ps(m, VF_SITE_SMALL, st);
           if ((rc = vf_launch_norm(m, m->final_norm, m->x, m->part, tail, n_tokens, n_tokens, st))) return rc; }
-        // many rows: the candidates leave the GEMM's epilogue, one list per (row, column tile)
-        const int n_tiles = (c.vocab / 16 + p.tnb - 1) / p.tnb;
+        // the candidates leave the GEMM's epilogue, some lists per (row, column tile)
+        const int n_lists = vf_gemm_topk_lists(p, c.vocab);
         p.topk = top_k;
         p.topk_ids = m->topk_cand_i;
         { ProfScope ps(m, VF_SITE_HEAD, st);
           if ((rc = vf_launch_gemm(m, m->lm_head, m->x, m->topk_cand_v, c.vocab, c.d_model, n_tokens, 0, n_tokens,
                                    n_tokens, p, st))) return rc; }
-        if ((rc = vf_launch_topk_merge(m, n_tokens, n_tiles, top_k, topk_logit_dev, topk_id_dev, st))) return rc;
+        if ((rc = vf_launch_topk_merge(m, n_tokens, n_lists, top_k, topk_logit_dev, topk_id_dev, st))) return rc;
         if (sample_first) {  // the last row's logits in full, for the draw of the first token
-            GemmPlan p1 = vf_gemm_plan(m, c.vocab, c.d_model, n_tokens, 1);
+            const GemmPlan p1 = vf_gemm_plan(m, c.vocab, c.d_model, 1, GEMM_PARTIAL);
             ProfScope ps(m, VF_SITE_HEAD, st);
             if ((rc = vf_launch_gemm(m, m->lm_head, m->x, m->logits - (size_t)(n_tokens - 1) * c.vocab, c.vocab,
                                      c.d_model, n_tokens, n_tokens - 1, n_tokens, n_tokens, p1, st))) return rc;

@@ -9,8 +9,9 @@ namespace {
 
 // ---- model creation -----------------------------------------------------------------------------
 
-// Row-major bf16 [n_rows, K] -> 16x32 fragments; source n-block nb lands at dst block
-// dst_nb0 + nb * dst_nb_stride (interleaving gate and up, concatenating q, k, v).
+// Row-major bf16 [n_rows, K] -> 16x32 fragments of the packed rows 16 * dst_nb0 + n.  With a second
+// source the two alternate: packed row 2 f is row f of the first, 2 f + 1 row f of the second (gate and
+// up: a lane of the GEMM then holds both factors of a SwiGLU product).
 // perm_hd > 0: within every head of perm_hd rows, packed row 2i is source row i and packed row 2i+1
 // is source row i + perm_hd/2, so that the two elements of a rotary pair are neighbours.
 __device__ inline int pack_src_row(int n, int perm_hd) {
@@ -19,8 +20,8 @@ __device__ inline int pack_src_row(int n, int perm_hd) {
     return head * perm_hd + (p >> 1) + (p & 1) * (perm_hd >> 1);
 }
 
-__global__ void pack_bf16_kernel(const uint16_t *__restrict__ src, uint4 *__restrict__ dst, int n_rows,
-                                 int K, int dst_nb0, int dst_nb_stride, int perm_hd) {
+__global__ void pack_bf16_kernel(const uint16_t *__restrict__ src, const uint16_t *__restrict__ src2, uint4 *__restrict__ dst,
+                                 int n_rows, int K, int dst_nb0, int perm_hd) {
     const int KB = K >> 5;
     size_t total = (size_t)(n_rows >> 4) * KB * 64;
     for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < total;
@@ -28,22 +29,21 @@ __global__ void pack_bf16_kernel(const uint16_t *__restrict__ src, uint4 *__rest
         int lane = (int)(i & 63);
         size_t f = i >> 6;
         int kb = (int)(f % KB), nb = (int)(f / KB);
-        int n = pack_src_row(nb * 16 + (lane & 15), perm_hd), k = kb * 32 + (lane >> 4) * 8;
-        uint4 v = *reinterpret_cast<const uint4 *>(src + (size_t)n * K + k);
-        int dnb = dst_nb0 + nb * dst_nb_stride;
-        dst[((size_t)dnb * KB + kb) * 64 + lane] = v;
+        int n = nb * 16 + (lane & 15), k = kb * 32 + (lane >> 4) * 8;
+        const uint16_t *from = src2 ? ((n & 1) ? src2 : src) + (size_t)(n >> 1) * K : src + (size_t)pack_src_row(n, perm_hd) * K;
+        dst[((size_t)(dst_nb0 + nb) * KB + kb) * 64 + lane] = *reinterpret_cast<const uint4 *>(from + k);
     }
 }
 
-// float32 model: same block re-ordering on plain row-major rows.
-__global__ void pack_f32_kernel(const float *__restrict__ src, float *__restrict__ dst, int n_rows, int K,
-                                int dst_nb0, int dst_nb_stride, int perm_hd) {
+// float32 model: the same order of rows, plain row-major.
+__global__ void pack_f32_kernel(const float *__restrict__ src, const float *__restrict__ src2, float *__restrict__ dst, int n_rows,
+                                int K, int dst_nb0, int perm_hd) {
     size_t total = (size_t)n_rows * K;
     for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < total;
          i += (size_t)gridDim.x * blockDim.x) {
         int n = (int)(i / K), k = (int)(i % K);
-        int dn = (dst_nb0 + (n >> 4) * dst_nb_stride) * 16 + (n & 15);
-        dst[(size_t)dn * K + k] = src[(size_t)pack_src_row(n, perm_hd) * K + k];
+        const float *from = src2 ? ((n & 1) ? src2 : src) + (size_t)(n >> 1) * K : src + (size_t)pack_src_row(n, perm_hd) * K;
+        dst[(size_t)(dst_nb0 * 16 + n) * K + k] = from[k];
     }
 }
 
@@ -119,11 +119,23 @@ __global__ __launch_bounds__(256) void norm_bf16_vec_kernel(float *__restrict__ 
             const float4 a = *reinterpret_cast<const float4 *>(hp), b = *reinterpret_cast<const float4 *>(hp + 4);
             v[i][0] = a.x; v[i][1] = a.y; v[i][2] = a.z; v[i][3] = a.w;
             v[i][4] = b.x; v[i][5] = b.y; v[i][6] = b.z; v[i][7] = b.w;
-            for (int p = 0; p < nparts; ++p) {
-                const float *pp = part + ((size_t)p * ld_rows + row) * d + k0;
-                const float4 c = *reinterpret_cast<const float4 *>(pp), e = *reinterpret_cast<const float4 *>(pp + 4);
-                v[i][0] += c.x; v[i][1] += c.y; v[i][2] += c.z; v[i][3] += c.w;
-                v[i][4] += e.x; v[i][5] += e.y; v[i][6] += e.z; v[i][7] += e.w;
+            // the partial sums are requested eight at a time (one after the other, each waited for the one
+            // before: 5.5 us per launch at 256 rows, 8 partials)
+            for (int p0 = 0; p0 < nparts; p0 += 8) {
+                float4 c[8], e[8];
+#pragma unroll
+                for (int p = 0; p < 8; ++p) {
+                    const float *pp = part + ((size_t)min(p0 + p, nparts - 1) * ld_rows + row) * d + k0;
+                    c[p] = *reinterpret_cast<const float4 *>(pp);
+                    e[p] = *reinterpret_cast<const float4 *>(pp + 4);
+                }
+#pragma unroll
+                for (int p = 0; p < 8; ++p) {
+                    if (p0 + p < nparts) {
+                        v[i][0] += c[p].x; v[i][1] += c[p].y; v[i][2] += c[p].z; v[i][3] += c[p].w;
+                        v[i][4] += e[p].x; v[i][5] += e[p].y; v[i][6] += e[p].z; v[i][7] += e[p].w;
+                    }
+                }
             }
             if (nparts) {
                 *reinterpret_cast<float4 *>(hp) = float4{v[i][0], v[i][1], v[i][2], v[i][3]};
@@ -159,73 +171,76 @@ __global__ __launch_bounds__(256) void norm_bf16_vec_kernel(float *__restrict__ 
     }
 }
 
-// QKV epilogue: one thread per (row, head, rotary pair).  Heads 0..Hq-1 are q, then Hkv k heads,
-// then Hkv v heads (v is not rotated).  Pair = elements (i, i + hd/2) of a head; the packed
-// q and k weight rows (and biases) hold a pair in neighbouring columns 2i, 2i+1.
-__global__ void qkv_finish_kernel(const float *__restrict__ part, int nparts, int ld_rows, Batch b, int layer,
-                                  const float *__restrict__ bias, const float *__restrict__ cosv,
-                                  const float *__restrict__ sinv, bf16_t *__restrict__ q, int hq, int hkv, int hd,
-                                  const int32_t *__restrict__ depth) {
-    const int half = hd >> 1;
-    const int heads = hq + 2 * hkv;
-    const int per_row = heads * half;
-    int idx = blockIdx.x * blockDim.x + threadIdx.x;
+// QKV epilogue: one thread per (row, four packed columns).  Heads 0..Hq-1 are q, then Hkv k heads,
+// then Hkv v heads (v is not rotated).  Packed columns 2i, 2i+1 of a q or k head are elements i and
+// i + hd/2, so four columns are the two rotary pairs i, i + 1 and every store is two elements.
+__global__ __launch_bounds__(256) void qkv_finish_kernel(const float *__restrict__ part, int nparts, int ld_rows, Batch b, int layer,
+                                                         const float *__restrict__ bias, const float *__restrict__ cosv,
+                                                         const float *__restrict__ sinv, bf16_t *__restrict__ q, int hq, int hkv,
+                                                         int hd, const int32_t *__restrict__ depth) {
+    const int half = hd >> 1, N = (hq + 2 * hkv) * hd, per_row = N >> 2;
+    const int idx = blockIdx.x * blockDim.x + threadIdx.x;
     if (idx >= b.total_rows * per_row) return;
-    const int row = idx / per_row, rem = idx % per_row;
-    const int head = rem / half, i = rem % half;
-    const int N = heads * hd;
+    const int row = idx / per_row, n0 = (idx % per_row) * 4;
+    const int head = n0 / hd, p0 = n0 % hd;
     const bool rot = head < hq + hkv;
-    const int n0 = rot ? head * hd + 2 * i : head * hd + i, n1 = rot ? n0 + 1 : n0 + half;
-    float v0 = 0.f, v1 = 0.f;
-    for (int p = 0; p < nparts; ++p) {
-        const float *pr = part + ((size_t)p * ld_rows + row) * N;
-        v0 += pr[n0];
-        v1 += pr[n1];
-    }
-    if (bias) { v0 += bias[n0]; v1 += bias[n1]; }
     const SeqDesc &s = b.s[find_seq(b, row)];
     // the rotary angle is that of the token's position; the cache row is the call's row (the two
     // differ for tree-structured drafts, where a node stands at the position of its depth)
-    const int slot = s.state[0] + (row - s.row0);
-    const int pos = depth ? s.state[0] + depth[row] : slot;
+    const int len = s.state[0], slot = len + (row - s.row0), pos = depth ? len + depth[row] : slot;
+    float4 v = {0.f, 0.f, 0.f, 0.f};
+    for (int q0 = 0; q0 < nparts; q0 += 4) {   // requested together, added in order
+        float4 t[4];
+#pragma unroll
+        for (int p = 0; p < 4; ++p)
+            t[p] = *reinterpret_cast<const float4 *>(part + ((size_t)min(q0 + p, nparts - 1) * ld_rows + row) * N + n0);
+#pragma unroll
+        for (int p = 0; p < 4; ++p)
+            if (q0 + p < nparts) { v.x += t[p].x; v.y += t[p].y; v.z += t[p].z; v.w += t[p].w; }
+    }
+    if (bias) {
+        const float4 bb = *reinterpret_cast<const float4 *>(bias + n0);
+        v.x += bb.x; v.y += bb.y; v.z += bb.z; v.w += bb.w;
+    }
     if (slot < 0 || slot >= s.capacity) return;
-    if (rot) {
-        const float c = cosv[(size_t)pos * half + i], sn = sinv[(size_t)pos * half + i];
-        const float r0 = v0 * c - v1 * sn, r1 = v1 * c + v0 * sn;
-        v0 = r0; v1 = r1;
-    }
-    if (head < hq) {
-        bf16_t *qr = q + ((size_t)row * hq + head) * hd;
-        qr[i] = (bf16_t)(v0);
-        qr[i + half] = (bf16_t)(v1);
-        return;
-    }
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
     bf16_t *kv = reinterpret_cast<bf16_t *>(s.kv);
-    const int page = kv_page(s, slot), tin = slot % VF_TILE;
-    if (head < hq + hkv) {
-        const int kh = head - hq;
-        kv[kv_k_index(layer, s.n_pages, page, hkv, kh, tin, i, hd)] = (bf16_t)(v0);
-        kv[kv_k_index(layer, s.n_pages, page, hkv, kh, tin, i + half, hd)] = (bf16_t)(v1);
+    if (rot) {
+        const int i0 = p0 >> 1;
+        const float2 c = *reinterpret_cast<const float2 *>(cosv + (size_t)pos * half + i0);
+        const float2 sn = *reinterpret_cast<const float2 *>(sinv + (size_t)pos * half + i0);
+        const bf16x2 lo = {(bf16_t)(v.x * c.x - v.y * sn.x), (bf16_t)(v.z * c.y - v.w * sn.y)};
+        const bf16x2 hi = {(bf16_t)(v.y * c.x + v.x * sn.x), (bf16_t)(v.w * c.y + v.z * sn.y)};
+        bf16_t *d0, *d1;
+        if (head < hq) {
+            d0 = q + ((size_t)row * hq + head) * hd + i0;
+            d1 = d0 + half;
+        } else {
+            const int page = kv_page(s, slot), tin = slot % VF_TILE;
+            d0 = kv + kv_k_index(layer, s.n_pages, page, hkv, head - hq, tin, i0, hd);
+            d1 = kv + kv_k_index(layer, s.n_pages, page, hkv, head - hq, tin, i0 + half, hd);
+        }
+        *reinterpret_cast<bf16x2 *>(d0) = lo;
+        *reinterpret_cast<bf16x2 *>(d1) = hi;
     } else {
-        const int vh = head - hq - hkv;
-        kv[kv_v_index(layer, s.n_pages, page, hkv, vh, tin, i, hd)] = (bf16_t)(v0);
-        kv[kv_v_index(layer, s.n_pages, page, hkv, vh, tin, i + half, hd)] = (bf16_t)(v1);
+        const int page = kv_page(s, slot), tin = slot % VF_TILE, vh = head - hq - hkv;
+        const float w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+        for (int j = 0; j < 4; ++j) kv[kv_v_index(layer, s.n_pages, page, hkv, vh, tin, p0 + j, hd)] = (bf16_t)w[j];
     }
 }
 
-// a[row, f] = bf16(silu(gate) * up); the gate/up GEMM output interleaves 16-wide blocks: block 2j is
-// gate rows 16j.., block 2j+1 the matching up rows.
+// a[row, f] = bf16(silu(gate) * up); gate and up alternate in the columns of the gate/up GEMM's output.
 __global__ void swiglu_kernel(const float *__restrict__ part, int nparts, int ld_rows, bf16_t *__restrict__ a,
                               int rows, int F, int ncb) {
     size_t idx = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
     if (idx >= (size_t)rows * F) return;
     const int row = (int)(idx / F), f = (int)(idx % F);
-    const int ng = ((f >> 4) * 2) * 16 + (f & 15), nu = ng + 16;
     float g = 0.f, u = 0.f;
     for (int p = 0; p < nparts; ++p) {
-        const float *pr = part + ((size_t)p * ld_rows + row) * (2 * (size_t)F);
-        g += pr[ng];
-        u += pr[nu];
+        const float2 gu = *reinterpret_cast<const float2 *>(part + ((size_t)p * ld_rows + row) * (2 * (size_t)F) + 2 * f);
+        g += gu.x;
+        u += gu.y;
     }
     const float sg = g / (1.0f + expf(-g));
     a[xfrag_index(row, f, ncb)] = (bf16_t)(sg * u);
@@ -323,23 +338,17 @@ int vf_launch_pack_vec(const float *src, float *dst, int n, int perm_hd, hipStre
     return VF_OK;
 }
 
-namespace {
-inline int nblocks2(size_t n, int bs) { return (int)((n + bs - 1) / bs); }
-}
-
-int vf_launch_pack(const vf_model *m, const void *src, void *dst, int n_rows, int K, int dst_nb0,
-                   int dst_nb_stride, int perm_hd, hipStream_t st) {
-    if (m->cfg.dtype == VF_BF16) {
-        size_t total = (size_t)(n_rows >> 4) * (K >> 5) * 64;
-        int grid = (int)((total + 255) / 256 < 65535 ? (total + 255) / 256 : 65535);
-        hipLaunchKernelGGL(pack_bf16_kernel, dim3(grid), dim3(256), 0, st, (const uint16_t *)src, (uint4 *)dst,
-                           n_rows, K, dst_nb0, dst_nb_stride, perm_hd);
-    } else {
-        size_t total = (size_t)n_rows * K;
-        int grid = (int)((total + 255) / 256 < 65535 ? (total + 255) / 256 : 65535);
-        hipLaunchKernelGGL(pack_f32_kernel, dim3(grid), dim3(256), 0, st, (const float *)src, (float *)dst,
-                           n_rows, K, dst_nb0, dst_nb_stride, perm_hd);
-    }
+int vf_launch_pack(const vf_model *m, const void *src, const void *src2, void *dst, int n_rows, int K, int dst_nb0,
+                   int perm_hd, hipStream_t st) {
+    const bool bf16 = m->cfg.dtype == VF_BF16;
+    const size_t total = bf16 ? (size_t)(n_rows >> 4) * (K >> 5) * 64 : (size_t)n_rows * K;
+    const int grid = (int)((total + 255) / 256 < 65535 ? (total + 255) / 256 : 65535);
+    if (bf16)
+        hipLaunchKernelGGL(pack_bf16_kernel, dim3(grid), dim3(256), 0, st, (const uint16_t *)src, (const uint16_t *)src2, (uint4 *)dst,
+                           n_rows, K, dst_nb0, perm_hd);
+    else
+        hipLaunchKernelGGL(pack_f32_kernel, dim3(grid), dim3(256), 0, st, (const float *)src, (const float *)src2, (float *)dst, n_rows,
+                           K, dst_nb0, perm_hd);
     VF_LAUNCH_CHECK("pack");
     return VF_OK;
 }
@@ -379,7 +388,7 @@ int vf_launch_norm(const vf_model *m, const float *gain, void *x_out, const floa
 int vf_launch_qkv_finish(const vf_model *m, const Batch &b, int layer, const float *part, int nparts,
                          int ld_rows, const int32_t *depth, hipStream_t st) {
     const vf_config &c = m->cfg;
-    const int total = b.total_rows * (c.n_q_heads + 2 * c.n_kv_heads) * (c.head_dim / 2);
+    const int total = b.total_rows * (c.n_q_heads + 2 * c.n_kv_heads) * (c.head_dim / 4);
     hipLaunchKernelGGL(qkv_finish_kernel, dim3(nblocks(total, 256)), dim3(256), 0, st, part, nparts, ld_rows, b, layer,
                        c.qkv_bias ? m->layers[layer].bqkv : nullptr, m->rope_cos, m->rope_sin, (bf16_t *)m->q, c.n_q_heads,
                        c.n_kv_heads, c.head_dim, depth);

@@ -44,8 +44,8 @@ template <int RB, int UB, int EPI>
 __global__ __launch_bounds__(NW * 64) VF_MFMA_KERNEL void gemm_f32_kernel(GemmF32 p, Batch b) {
     constexpr bool NORMED = EPI != F_RESID;
     constexpr int U = 4;                                  // chunks requested together
-    constexpr int TILES = EPI == F_SWIGLU ? RB : RB * UB; // epilogue tiles, one per wavefront
-    static_assert(TILES <= NW && (EPI != F_SWIGLU || UB == 2), "one epilogue tile per wavefront");
+    constexpr int TILES = RB * UB;                        // epilogue tiles, one per wavefront
+    static_assert(TILES <= NW, "one epilogue tile per wavefront");
     __shared__ floatx4 red[NW * UB * RB * 64];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), g4 = lane >> 4, l15 = lane & 15;
     const int nb0 = blockIdx.x * UB, NBt = p.N >> 4;
@@ -57,7 +57,7 @@ __global__ __launch_bounds__(NW * 64) VF_MFMA_KERNEL void gemm_f32_kernel(GemmF3
 #pragma unroll
     for (int r = 0; r < RB; ++r) xp[r] = p.X + (size_t)min(r0 + r * 16 + l15, p.rows - 1) * K + g4 * 4;
     // epilogue tile of this wavefront: row block er, weight block eu
-    const int er = wave % RB, eu = EPI == F_SWIGLU ? 0 : (wave / RB) % UB;
+    const int er = wave % RB, eu = (wave / RB) % UB;
     const int row = r0 + er * 16 + l15;
     const bool live = wave < TILES && row < p.rows && nb0 + eu < NBt;
     float ssq = 0.f;
@@ -102,18 +102,13 @@ __global__ __launch_bounds__(NW * 64) VF_MFMA_KERNEL void gemm_f32_kernel(GemmF3
     __syncthreads();
     if (wave >= TILES) return;
     // lane holds Y[row][16 nb + 4 g4 + 0..3]
-    floatx4 v = {0.f, 0.f, 0.f, 0.f}, v1 = {0.f, 0.f, 0.f, 0.f};
+    floatx4 v = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int w = 0; w < NW; ++w) {
-        v += red[((w * UB + eu) * RB + er) * 64 + lane];
-        if (EPI == F_SWIGLU) v1 += red[((w * UB + UB - 1) * RB + er) * 64 + lane];
-    }
+    for (int w = 0; w < NW; ++w) v += red[((w * UB + eu) * RB + er) * 64 + lane];
     if (NORMED) {
         ssq += __shfl_xor(ssq, 16, 64);
         ssq += __shfl_xor(ssq, 32, 64);
-        const float rstd = 1.0f / sqrtf(ssq * p.inv_d + p.eps);
-        v *= rstd;
-        v1 *= rstd;
+        v *= 1.0f / sqrtf(ssq * p.inv_d + p.eps);
     }
     const int n0 = (nb0 + eu) * 16 + g4 * 4;
     if (EPI == F_RESID) {
@@ -131,10 +126,9 @@ __global__ __launch_bounds__(NW * 64) VF_MFMA_KERNEL void gemm_f32_kernel(GemmF3
         if (live) *reinterpret_cast<floatx4 *>(p.out + (size_t)(row - p.row_lo) * p.N + n0) = v;
     } else if (EPI == F_SWIGLU) {
         if (live) {
-            floatx4 o;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) o[j] = v[j] / (1.0f + expf(-v[j])) * v1[j];
-            *reinterpret_cast<floatx4 *>(p.out + (size_t)row * (p.N >> 1) + (nb0 >> 1) * 16 + g4 * 4) = o;
+            // gate row f is packed column 2 f, up row f column 2 f + 1
+            const float2 o = {v[0] / (1.0f + expf(-v[0])) * v[1], v[2] / (1.0f + expf(-v[2])) * v[3]};
+            *reinterpret_cast<float2 *>(p.out + (size_t)row * (p.N >> 1) + (n0 >> 1)) = o;
         }
     } else if (live) {
         const int hd = p.hd, half = hd >> 1;
@@ -333,13 +327,12 @@ template <int EPI>
 int launch_gemm(const GemmF32 &p, const Batch &b, hipStream_t st) {
     const int NBt = p.N >> 4, n = p.rows - p.row_lo;
     if (n <= 0) return VF_OK;
-    constexpr int UB = EPI == F_SWIGLU ? 2 : 1;
     auto go = [&](auto kern, int rb, int ub) {
         hipLaunchKernelGGL(kern, dim3((NBt + ub - 1) / ub, (n + 16 * rb - 1) / (16 * rb)), dim3(NW * 64), 0, st, p, b);
     };
-    if ((size_t)((NBt + UB - 1) / UB) * ((n + 31) / 32) > 2048) go(gemm_f32_kernel<4, 2, EPI>, 4, 2);
-    else if (n > 16) go(gemm_f32_kernel<2, UB, EPI>, 2, UB);
-    else go(gemm_f32_kernel<1, UB, EPI>, 1, UB);
+    if ((size_t)NBt * ((n + 31) / 32) > 2048) go(gemm_f32_kernel<4, 2, EPI>, 4, 2);
+    else if (n > 16) go(gemm_f32_kernel<2, 1, EPI>, 2, 1);
+    else go(gemm_f32_kernel<1, 1, EPI>, 1, 1);
     VF_LAUNCH_CHECK("gemm_f32");
     return VF_OK;
 }

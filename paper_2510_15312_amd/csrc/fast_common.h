@@ -179,15 +179,14 @@ __device__ inline void epi_qkv(const FastGemm &g, const Batch &b, int row, int n
     }
 }
 
+// v0, v1: tiles of the weight blocks nb (even) and nb + 1; gate row f is packed column 2 f, up row f column
+// 2 f + 1, so a lane holds two (gate, up) pairs of either block
 template <bool COH>
-__device__ inline void epi_swiglu(const FastGemm &g, int row, int nb_gate, int lane, floatx4 vg, floatx4 vu) {
-    const int f0 = (nb_gate >> 1) * 16 + (lane >> 4) * 4;
-    float o[4];
-    for (int i = 0; i < 4; ++i) {
-        const float gt = vg[i], up = vu[i];
-        o[i] = gt / (1.0f + expf(-gt)) * up;
-    }
-    st_u32x2<COH>(g.a_out + (size_t)row * g.F + f0, pack4_bf16(o[0], o[1], o[2], o[3]));
+__device__ inline void epi_swiglu(const FastGemm &g, int row, int nb, int lane, floatx4 v0, floatx4 v1) {
+    bf16_t *out = g.a_out + (size_t)row * g.F + nb * 8 + (lane >> 4) * 2;
+    auto act = [](float gt, float up) { return gt / (1.0f + expf(-gt)) * up; };
+    st_u32<COH>(out, pack2_bf16(act(v0[0], v0[1]), act(v0[2], v0[3])));
+    st_u32<COH>(out + 8, pack2_bf16(act(v1[0], v1[1]), act(v1[2], v1[3])));
 }
 
 // ---- attention ----------------------------------------------------------------------------------

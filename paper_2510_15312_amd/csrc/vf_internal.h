@@ -227,21 +227,32 @@ __device__ inline int find_seq(const Batch &b, int row) {
 }
 
 // ---- launchers (defined next to their kernels) --------------------------------------------------
+enum GemmUse {
+    GEMM_PARTIAL,  // unsplit, float32 result
+    GEMM_SPLIT,    // float32 partial sums of K splits, added by the consumer
+    GEMM_SWIGLU,   // gate/up matrix: bf16(silu(gate) * up) in activation layout (VF_OPT_FAST_PATH 0: partial sums)
+    GEMM_TOPK      // output head: the top candidates of every row instead of the logits
+};
 struct GemmPlan {
     int ks;        // K splits (partials)
-    int nbw;       // n-blocks per wavefront
-    int tnb;       // > 0: many-row kernel with this many weight blocks per workgroup
-    int swiglu;    // many-row kernel only: write bf16(silu(gate) * up) in activation layout, not partials
-    int topk;      // many-row kernel only, > 0: write this many top candidates per (row, column tile), not partials
+    int nbw;       // general kernel: n-blocks per wavefront
+    int shape;     // >= 0: kernel and tile of gemm_rows.h; -1: general kernel
+    GemmUse epi;   // GEMM_PARTIAL, GEMM_SWIGLU or GEMM_TOPK
+    int topk;      // GEMM_TOPK: candidates per (row, list)
     int32_t *topk_ids;  // their ids (the values go where the partials would)
 };
-GemmPlan vf_gemm_plan(const vf_model *m, int N, int K, int rows, int force_single);
+int vf_gemm_init();
+GemmPlan vf_gemm_plan(const vf_model *m, int N, int K, int rows, GemmUse use);
+// candidate lists per row a GEMM_TOPK plan leaves
+int vf_gemm_topk_lists(const GemmPlan &p, int N);
 // Y partials [ks][R][N] (R = ld_rows) for rows [row_lo, row_hi) of X.
 int vf_launch_gemm(const vf_model *m, const void *W, const void *X, float *part, int N, int K,
-                   int rows_total, int row_lo, int row_hi, int ld_rows, GemmPlan plan, hipStream_t st);
+                   int rows_total, int row_lo, int row_hi, int ld_rows, const GemmPlan &plan, hipStream_t st);
 
-int vf_launch_pack(const vf_model *m, const void *src, void *dst, int n_rows, int K, int dst_nb0,
-                   int dst_nb_stride, int perm_hd, hipStream_t st);
+// Packs matrix rows [n_rows, K] to the packed rows 16 * dst_nb0 ..; src2: rows of the two sources alternate
+// (n_rows counts both).
+int vf_launch_pack(const vf_model *m, const void *src, const void *src2, void *dst, int n_rows, int K, int dst_nb0,
+                   int perm_hd, hipStream_t st);
 int vf_launch_pack_vec(const float *src, float *dst, int n, int perm_hd, hipStream_t st);
 int vf_launch_rope_table(const vf_model *m, hipStream_t st);
 int vf_launch_embed(const vf_model *m, const Batch &b, const int32_t *tokens, hipStream_t st);
@@ -296,7 +307,7 @@ int vf_launch_topk_merge(const vf_model *m, int rows, int n_slices, int K, float
                          hipStream_t st);
 // most (row, slice) candidate lists a row can have: slices of the slice kernel or column tiles of the GEMM
 inline int vf_topk_max_slices(const vf_config &c) {
-    const int tiles = (c.vocab / 16 + 3) / 4;  // narrow GEMM tile: four 16-column blocks
+    const int tiles = (c.vocab / 16 + 3) / 4 + 1;  // a GEMM list covers at least four 16-column blocks (an even number per tile)
     return tiles > VF_STAT_CHUNKS ? tiles : VF_STAT_CHUNKS;
 }
 int vf_launch_first_token(const vf_model *m, const SeqDesc &s, const float *logits_row, const float *u,
