@@ -1,0 +1,308 @@
+// Attention of many query items over one context (a prefill chunk of hundreds of rows, or the verify rows
+// of several sequences): a workgroup of four wavefronts takes 64 items (row, head of a key head's group)
+// of one key head over one part of the keys, a wavefront 16 of them.  The kernel for fewer items
+// (attn_rows_kernel, fast.hip) gives a workgroup 16 items and shares the keys out over its wavefronts: every
+// block of 16 then pulls all keys through the vector cache, on every die, and ends in a merge of eight states.
+// Here a page of keys (64) goes to LDS once for the four wavefronts, one page ahead by direct loads, and the
+// workgroups that share it are neighbours on one die.
+// What bounds it: a page takes a wavefront 1.05 us (2500 cycles: 768 of matrix instructions, about as many of
+// softmax arithmetic, the rest latencies of one dependent chain), and two workgroups on a compute unit read
+// their fragments at the LDS's rate (160 KB a page).  Measured and not taken: rings of three and four pages
+// (nothing, and one workgroup a compute unit: 10 to 30 % slower), eight wavefronts and 128 items (0 to 20 %
+// slower), pages of 32 keys (two softmax chains for one: 53 -> 45 us on the mix of 16 sequences), 32 items a
+// wavefront on those (slower: half the wavefronts, each 1.1 us a tile).
+#include "fast_common.h"
+#include "lds_stream.h"
+
+namespace {
+
+constexpr int ITEMS_WAVES = 4, ITEMS_GROUP = ITEMS_WAVES * 16, ITEMS_STAGES = 2;
+
+// Shape of a launch: workgroups of the sequences before sequence i (a huge number past the last one),
+// records per head before its own, pages of a part.  merge: some sequence has more than one part.
+struct ItemsGrid { int first[VF_MAX_BATCH], record[VF_MAX_BATCH], part_pages, merge; };
+
+__host__ __device__ inline int items_parts(const SeqDesc &s, int part_pages) {
+    const int keys = s.len_ub + s.nrows < s.capacity ? s.len_ub + s.nrows : s.capacity;
+    return ((keys + VF_TILE - 1) / VF_TILE + part_pages - 1) / part_pages;
+}
+
+// Largest value, or sum, over the four lanes that share an item (lane & 15).
+__device__ __forceinline__ float item_max(float x) {
+    auto a = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, x), __builtin_bit_cast(unsigned, x), false, false);
+    x = fmaxf(__builtin_bit_cast(float, a[0]), __builtin_bit_cast(float, a[1]));
+    auto c = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned, x), __builtin_bit_cast(unsigned, x), false, false);
+    return fmaxf(__builtin_bit_cast(float, c[0]), __builtin_bit_cast(float, c[1]));
+}
+__device__ __forceinline__ float item_sum(float x) {
+    x += __shfl_xor(x, 16, 64);
+    return x + __shfl_xor(x, 32, 64);
+}
+
+template <int HD>
+__global__ __launch_bounds__(ITEMS_WAVES * 64) VF_MFMA_KERNEL void attn_items_kernel(
+    Batch b, ItemsGrid grid, int layer, const bf16_t *__restrict__ q, bf16_t *__restrict__ o, int hq, int hkv, int ncb,
+    float scale_log2e, float *__restrict__ part) {
+    constexpr int KD = HD / 32, DB = HD / 16, FR = HD / 4, LPW = FR / ITEMS_WAVES, S = ITEMS_STAGES;
+    extern __shared__ __align__(1024) unsigned char smem[];   // ring of S pages: K fragments, then V^T
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), g4 = lane >> 4, l15 = lane & 15;
+    const int group = hq / hkv;
+    // The item groups that read the same keys are neighbours, so that they share a die's L2; the one that
+    // sees the most keys comes first.
+    int l = die_order(blockIdx.x, gridDim.x), seq = 0;
+#pragma unroll
+    for (int i = 1; i < VF_MAX_BATCH; ++i) seq += l >= grid.first[i];
+    seq = __builtin_amdgcn_readfirstlane(seq);
+    const SeqDesc &s = b.s[seq];
+    l -= grid.first[seq];
+    const int n_items = s.nrows * group, groups = (n_items + ITEMS_GROUP - 1) / ITEMS_GROUP;
+    const int parts = items_parts(s, grid.part_pages);
+    const int kpart = __builtin_amdgcn_readfirstlane(l / groups % parts), kvh = __builtin_amdgcn_readfirstlane(l / (groups * parts));
+    const int group0 = __builtin_amdgcn_readfirstlane(groups - 1 - l % groups) * ITEMS_GROUP, wave0 = group0 + wave * 16;
+    const int len = __builtin_amdgcn_readfirstlane(s.state[0]), kmax = min(len + s.nrows, s.capacity);
+    const int group_last = __builtin_amdgcn_readfirstlane(min(kmax - 1, len + min(n_items - 1, group0 + ITEMS_GROUP - 1) / group));   // last key any item sees
+    const int pages = group_last / VF_TILE + 1, p_begin = kpart * grid.part_pages;
+    // the last part also takes what a length beyond the host's bound adds (a call replayed from a graph)
+    const int p_end = kpart == parts - 1 ? pages : min(pages, p_begin + grid.part_pages);
+    if (p_begin >= p_end) return;
+    const bool has_items = wave0 < n_items;   // a wavefront without items still loads its share of the pages
+    const int wave_last = min(group_last, len + min(n_items - 1, wave0 + 15) / group);   // last key one of its items sees
+    const int wave_first = min(kmax - 1, len + min(n_items - 1, wave0) / group);         // last key they all see
+    const int item = min(n_items - 1, wave0 + l15);   // past the last item: the last one again, not stored
+    const int row = s.row0 + item / group, head = kvh * group + item % group, last_key = len + item / group;
+    bf16x8 qf[KD];
+#pragma unroll
+    for (int kd = 0; kd < KD; ++kd) qf[kd] = *reinterpret_cast<const bf16x8 *>(q + ((size_t)row * hq + head) * HD + kd * 32 + g4 * 8);
+    // this wavefront's share of a page: half of its K or of its V^T fragments
+    const size_t page_bytes = (size_t)2 * hkv * VF_TILE * HD * 2;
+    const char *src = s.kv + (size_t)layer * s.n_pages * page_bytes + (size_t)(wave < ITEMS_WAVES / 2 ? kvh : hkv + kvh) * (VF_TILE * HD * 2) +
+                      wave % (ITEMS_WAVES / 2) * (LPW * 1024);
+    const unsigned lds0 = lds_address(smem) + wave * (LPW * 1024), lane_off = lane * 16;
+    const int32_t *table = s.block_table;
+    int page_v = 0;   // ids of this part's pages, one per lane, read once
+    if (table) page_v = table[min(p_begin + lane, pages - 1)];
+    auto issue = [&](int i) {
+        const int t = min(p_begin + i, p_end - 1), pi = t - p_begin;   // past the end: the last page again, not used
+        const int page = !table ? t
+                         : pi < 64      ? __builtin_amdgcn_readlane(page_v, pi)
+                                        : __builtin_amdgcn_readfirstlane(table[t]);
+        const char *p = src + (size_t)page * page_bytes;
+        const unsigned dst = lds0 + (unsigned)i % S * (FR * 1024);
+        static_for<0, LPW>([&](auto f) { fragment_to_lds<(int)f * 1024>(p + (int)f * 1024, lane_off, dst); });
+    };
+    floatx4 acc[DB];
+#pragma unroll
+    for (int db = 0; db < DB; ++db) acc[db] = floatx4{0.f, 0.f, 0.f, 0.f};
+    float m_run = -1e30f, l_run = 0.f;   // l_run: this lane's own keys; the four lanes of an item are added at the end
+    auto update = [&](const unsigned char *st, int t0, auto masked) {
+        constexpr bool MASKED = decltype(masked)::value;
+        floatx4 sc[4];   // [32-key half of the page][16-key half]: lane holds keys t0 + 32 * t + 8 * g4 + 4 * h + j of item l15
+#pragma unroll
+        for (int f = 0; f < 4; ++f) sc[f] = floatx4{0.f, 0.f, 0.f, 0.f};
+        // All of a page's fragments leave LDS together, K first and V^T under the softmax: left to the
+        // compiler, each pair of them is read right in front of its products, which wait out the latency.
+        bf16x8 kf[4 * KD], vf[2 * DB];
+#pragma unroll
+        for (int kd = 0; kd < KD; ++kd)
+#pragma unroll
+            for (int f = 0; f < 4; ++f) kf[f * KD + kd] = *reinterpret_cast<const bf16x8 *>(st + (f * KD + kd) * 1024);
+        asm volatile("" ::: "memory");
+#pragma unroll
+        for (int f = 0; f < 2 * DB; ++f) vf[f] = *reinterpret_cast<const bf16x8 *>(st + (FR / 2 + f) * 1024);
+        asm volatile("" ::: "memory");
+#pragma unroll
+        for (int kd = 0; kd < KD; ++kd)
+#pragma unroll
+            for (int f = 0; f < 4; ++f) sc[f] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[f * KD + kd], qf[kd], sc[f], 0, 0, 0);
+        if constexpr (MASKED)
+#pragma unroll
+            for (int j = 0; j < 16; ++j)
+                if (t0 + (j >> 3) * 32 + g4 * 8 + (j & 7) > last_key) sc[j >> 2][j & 3] = -INFINITY;
+        float mx = fmaxf(sc[0][0], sc[0][1]);
+#pragma unroll
+        for (int j = 2; j < 16; ++j) mx = fmaxf(mx, sc[j >> 2][j & 3]);
+        const float m_new = fmaxf(m_run, item_max(mx) * scale_log2e);
+        if (__builtin_amdgcn_ballot_w64(m_new != m_run)) {
+            const float corr = __builtin_amdgcn_exp2f(m_run - m_new);
+            l_run *= corr;
+#pragma unroll
+            for (int db = 0; db < DB; ++db) acc[db] *= corr;
+            m_run = m_new;
+        }
+        // probabilities as a sum of two bfloat16 values (16 significant bits): the P V product then
+        // carries no more rounding than its bfloat16 V operand
+        bf16x8 hi[2], lo[2];
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            const float p = __builtin_amdgcn_exp2f(fmaf(sc[j >> 2][j & 3], scale_log2e, -m_new));
+            l_run += p;
+            hi[j >> 3][j & 7] = (bf16_t)p;
+            lo[j >> 3][j & 7] = (bf16_t)(p - (float)hi[j >> 3][j & 7]);
+        }
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            if constexpr (MASKED)   // rows of the cache at or past kmax may hold anything
+#pragma unroll
+                for (int j = 0; j < 8; ++j)
+                    if (t0 + t * 32 + g4 * 8 + j >= kmax)
+#pragma unroll
+                        for (int db = 0; db < DB; ++db) vf[t * DB + db][j] = (bf16_t)0.f;
+#pragma unroll
+            for (int db = 0; db < DB; ++db) acc[db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[t * DB + db], hi[t], acc[db], 0, 0, 0);
+#pragma unroll
+            for (int db = 0; db < DB; ++db) acc[db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[t * DB + db], lo[t], acc[db], 0, 0, 0);
+        }
+    };
+#pragma unroll
+    for (int i = 0; i < S - 1; ++i) issue(i);
+    // the query fragments have landed here, or the compiler would wait for every load in flight at each page
+#pragma unroll
+    for (int kd = 0; kd < KD; ++kd) asm volatile("" : "+v"(qf[kd]));
+    const int n = p_end - p_begin;
+    for (int i = 0; i < n; ++i) {
+        vm_wait<(S - 2) * LPW>();   // page i has landed; behind the barrier everyone's share of it has,
+        lds_sync();                 // and page i - 1 has been read, so its slot takes page i + S - 1
+        issue(i + S - 1);
+        const int t0 = (p_begin + i) * VF_TILE;
+        const unsigned char *st = smem + (unsigned)i % S * (FR * 1024) + lane_off;
+        if (!has_items || t0 > wave_last) continue;
+        if (t0 + VF_TILE - 1 <= wave_first) update(st, t0, std::false_type{});
+        else update(st, t0, std::true_type{});
+    }
+    vm_wait<0>();   // nothing is on its way to LDS when the workgroup ends
+    const float sum = item_sum(l_run);
+    if (wave0 + l15 >= n_items) return;
+    if (grid.merge) {   // a record [max, sum, -, -, O[hd]] for the merge kernel
+        float *rec = part + ((size_t)(grid.record[seq] + (row - s.row0) * parts + kpart) * hq + head) * (HD + ATTF_STRIDE_PAD);
+        if (g4 == 0) *reinterpret_cast<float2 *>(rec) = float2{m_run, sum};
+#pragma unroll
+        for (int db = 0; db < DB; ++db) *reinterpret_cast<floatx4 *>(rec + ATTF_STRIDE_PAD + db * 16 + g4 * 4) = acc[db];
+    } else {
+        const float inv = 1.0f / sum;
+#pragma unroll
+        for (int db = 0; db < DB; ++db) {
+            const floatx4 v = acc[db] * inv;
+            *reinterpret_cast<u32x2 *>(o + xfrag_index(row, head * HD + db * 16 + g4 * 4, ncb)) = pack4_bf16(v[0], v[1], v[2], v[3]);
+        }
+    }
+}
+
+// Merge of the key parts by log-sum-exp: HD / 4 threads per (row, head), four output values each.
+template <int HD>
+__global__ __launch_bounds__(256) void attn_items_merge_kernel(Batch b, ItemsGrid grid, const float *__restrict__ part,
+                                                               bf16_t *__restrict__ o, int hq, int ncb) {
+    constexpr int REC = HD + ATTF_STRIDE_PAD, TH = HD / 4;
+    const int idx = blockIdx.x * (256 / TH) + threadIdx.x / TH, d0 = threadIdx.x % TH * 4;
+    if (idx >= b.total_rows * hq) return;
+    const int row = idx / hq, head = idx % hq;
+    const int seq = find_seq(b, row);
+    const SeqDesc &s = b.s[seq];
+    const int parts = items_parts(s, grid.part_pages), last = min(s.state[0] + row - s.row0, s.capacity - 1);
+    const int used = min(parts, last / VF_TILE / grid.part_pages + 1);   // parts with keys of this row
+    const float *p = part + ((size_t)(grid.record[seq] + (row - s.row0) * parts) * hq + head) * REC;
+    float M = -1e30f, L = 0.f;
+    floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+    for (int i0 = 0; i0 < used; i0 += 4) {   // four records requested together
+        float2 ml[4];
+        floatx4 v[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float *r = p + (size_t)min(i0 + i, used - 1) * hq * REC;
+            ml[i] = *reinterpret_cast<const float2 *>(r);
+            v[i] = *reinterpret_cast<const floatx4 *>(r + ATTF_STRIDE_PAD + d0);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (i0 + i >= used) break;
+            const float m = fmaxf(M, ml[i].x), keep = exp2f(M - m), add = exp2f(ml[i].x - m);
+            L = L * keep + ml[i].y * add;
+            acc = acc * keep + v[i] * add;
+            M = m;
+        }
+    }
+    const float inv = 1.0f / L;
+    *reinterpret_cast<u32x2 *>(o + xfrag_index(row, head * HD + d0, ncb)) =
+        pack4_bf16(acc[0] * inv, acc[1] * inv, acc[2] * inv, acc[3] * inv);
+}
+
+template <int HD>
+int launch_items(const vf_model *m, const Batch &b, const ItemsGrid &grid, int layer, int workgroups, hipStream_t st) {
+    const vf_config &c = m->cfg;
+    const int ncb = (b.total_rows + 15) >> 4, lds = ITEMS_STAGES * (HD / 4) * 1024;
+    const float scale_log2e = 1.4426950408889634f / sqrtf((float)HD);
+    hipLaunchKernelGGL(attn_items_kernel<HD>, dim3(workgroups), dim3(ITEMS_WAVES * 64), lds, st, b, grid, layer, (const bf16_t *)m->q,
+                       (bf16_t *)m->o, c.n_q_heads, c.n_kv_heads, ncb, scale_log2e, m->attn_part);
+    VF_LAUNCH_CHECK("attn_items");
+    if (grid.merge) {
+        constexpr int PER = 256 / (HD / 4);
+        hipLaunchKernelGGL(attn_items_merge_kernel<HD>, dim3((b.total_rows * c.n_q_heads + PER - 1) / PER), dim3(256), 0, st, b,
+                           grid, m->attn_part, (bf16_t *)m->o, c.n_q_heads, ncb);
+        VF_LAUNCH_CHECK("attn_items_merge");
+    }
+    return VF_OK;
+}
+
+}  // namespace
+
+// Which kernel, and how many pages make a part.  Both are modelled (us, one launch and its merge) and this
+// file's is taken where it is a tenth cheaper:
+//   here:      8.0 + 1.27 a thousand group pages (64 items x 64 keys; 0.67 for head_dim 64) + 0.97 a page of
+//              a part (0.60) + 1.13 a chip full of workgroups + with a merge 4.2 and 0.30 a MB of records
+//              + 0.20 a MB of keys and values
+//   attn_rows: 6.3 + 0.86 a thousand block tiles (16 items x 32 keys; 0.43) + 0.12 a tile of a part (0.06)
+//              + 2.2 with a merge + 0.60 a MB of keys and values (its blocks of 16 items read them on
+//              every die)
+// The constants are least-squares fits to 18 calls (0.5B, 1.5B and 3B shapes; chunks of 128 to 1024 rows and
+// batches of 8 to 16 sequences), every part size of a power of two: mean errors 6 and 7 %.  Measured, here
+// against attn_rows with launch gaps: 16 sequences of 512 to 8192 keys at the 1.5B shape, 277 rows, 45 / 67;
+// 8 of about 2000 keys, 22 / 28; 1900 rows of 3B in two chunks, 39 / 59 a layer and chunk; 256 rows over up to
+// 2048 keys at 1.5B, 19 / 13.5; 12 sequences of about 800 keys at 0.5B, 17 / 14.
+// 1: launched, 0: left to attn_rows, < 0: an error
+int vf_launch_attention_items(const vf_model *m, const Batch &b, int layer, hipStream_t st) {
+    const vf_config &c = m->cfg;
+    const int group = c.n_q_heads / c.n_kv_heads;
+    const float w = c.head_dim / 128.f, kv_mb_key = c.n_kv_heads * c.head_dim * 4e-6f;
+    float kv_mb = 0.f, group_pages = 0.f, block_tiles = 0.f;
+    int max_keys = 0;
+    for (int i = 0; i < b.n_seqs; ++i) {
+        if ((uintptr_t)b.s[i].kv & 15) return 0;   // the direct loads move 16 bytes a lane
+        const int items = b.s[i].nrows * group, keys = b.s[i].len_ub + b.s[i].nrows;
+        const float seen = b.s[i].len_ub + 0.5f * b.s[i].nrows;   // keys an item sees on average
+        group_pages += (float)((items + ITEMS_GROUP - 1) / ITEMS_GROUP) * c.n_kv_heads * (seen / VF_TILE + 1.f);
+        block_tiles += (float)((items + 15) / 16) * c.n_kv_heads * (seen / ATT_TILE + 1.f);
+        kv_mb += kv_mb_key * keys;
+        max_keys = max(max_keys, keys);
+    }
+    const int rows_parts = vf_attention_rows_parts(m, b);
+    const float rows_cost = 6.3f + w * (0.86e-3f * block_tiles + 0.122f * max_keys / (ATT_TILE * rows_parts)) +
+                            (rows_parts > 1 ? 2.2f : 0.f) + 0.60f * kv_mb;
+    const size_t record_floats = (size_t)c.n_q_heads * (c.head_dim + ATTF_STRIDE_PAD), room = m->attn_part_floats / record_floats;
+    ItemsGrid grid, best;
+    int best_workgroups = 0;
+    float best_cost = 0.9f * rows_cost;
+    for (grid.part_pages = 4;; grid.part_pages *= 2) {
+        int records = 0, workgroups = 0;
+        grid.merge = 0;
+        for (int i = 0; i < VF_MAX_BATCH; ++i) {
+            grid.first[i] = i < b.n_seqs ? workgroups : 0x7fffffff;
+            grid.record[i] = records;
+            if (i >= b.n_seqs) continue;
+            const int parts = items_parts(b.s[i], grid.part_pages);
+            workgroups += (b.s[i].nrows * group + ITEMS_GROUP - 1) / ITEMS_GROUP * c.n_kv_heads * parts;
+            records += b.s[i].nrows * parts;
+            grid.merge |= parts > 1;
+        }
+        const int pages = min(grid.part_pages, (max_keys + VF_TILE - 1) / VF_TILE);
+        const float cost = 8.0f + 1.27e-3f * (0.35f + 0.65f * w) * group_pages + (0.23f + 0.74f * w) * pages + 1.13f / 256.f * workgroups +
+                           (grid.merge ? 4.2f + 0.30f * 4e-6f * records * record_floats : 0.f) + 0.20f * kv_mb;
+        if (cost < best_cost && (!grid.merge || (size_t)records <= room)) {
+            best_cost = cost;
+            best = grid;
+            best_workgroups = workgroups;
+        }
+        if (!grid.merge) break;
+    }
+    if (!best_workgroups) return 0;
+    const int rc = c.head_dim == 128 ? launch_items<128>(m, b, best, layer, best_workgroups, st) : launch_items<64>(m, b, best, layer, best_workgroups, st);
+    return rc ? rc : 1;
+}

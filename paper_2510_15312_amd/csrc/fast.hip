@@ -640,19 +640,23 @@ int run_fast(vf_model *m, const Batch &b, const int32_t *tokens, float *logits_o
 
 }  // namespace
 
-int vf_launch_attention_rows(const vf_model *m, const Batch &b, int layer, hipStream_t st) {
-    const vf_config &c = m->cfg;
-    const int group = c.n_q_heads / c.n_kv_heads;
-    int max_items = 0, max_keys = 0;
-    for (int i = 0; i < b.n_seqs; ++i) {
-        max_items = max(max_items, b.s[i].nrows * group);
-        max_keys = max(max_keys, b.s[i].len_ub + b.s[i].nrows);
-    }
-    // about ROWS_PART_TILES key tiles per workgroup; the record buffer has room for 16 parts per (row, head)
+// Key parts of the many-row kernel: about ROWS_PART_TILES key tiles per workgroup; the record buffer has
+// room for 16 parts per (row, head).
+int vf_attention_rows_parts(const vf_model *m, const Batch &b) {
+    int max_keys = 0;
+    for (int i = 0; i < b.n_seqs; ++i) max_keys = max(max_keys, b.s[i].len_ub + b.s[i].nrows);
     const int max_tiles = (max_keys + ATT_TILE - 1) / ATT_TILE;
     int n_parts = min(16, max(1, (max_tiles + ROWS_PART_TILES - 1) / ROWS_PART_TILES));
-    const size_t rec_floats = (size_t)b.total_rows * c.n_q_heads * (c.head_dim + ATTF_STRIDE_PAD);
+    const size_t rec_floats = (size_t)b.total_rows * m->cfg.n_q_heads * (m->cfg.head_dim + ATTF_STRIDE_PAD);
     while (n_parts > 1 && rec_floats * n_parts > m->attn_part_floats) --n_parts;
+    return n_parts;
+}
+
+int vf_launch_attention_rows(const vf_model *m, const Batch &b, int layer, hipStream_t st) {
+    const vf_config &c = m->cfg;
+    const int group = c.n_q_heads / c.n_kv_heads, n_parts = vf_attention_rows_parts(m, b);
+    int max_items = 0;
+    for (int i = 0; i < b.n_seqs; ++i) max_items = max(max_items, b.s[i].nrows * group);
     const dim3 grid((max_items + 16 * ROWS_QB - 1) / (16 * ROWS_QB), c.n_kv_heads, b.n_seqs * n_parts);
     const int ncb = (b.total_rows + 15) >> 4;
     const float scale_log2e = 1.4426950408889634f / sqrtf((float)c.head_dim);

@@ -20,14 +20,11 @@
 //   1024 x 16384 x 3072).
 #pragma once
 
-#include <type_traits>
-
-#include "vf_internal.h"
+#include "lds_stream.h"
 
 namespace {
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int ROWS_EPI_PARTIAL = 0, ROWS_EPI_SWIGLU = 1, ROWS_EPI_TOPK = 2;
 
@@ -41,43 +38,10 @@ struct RowsGemm {
     int topk;
 };
 
-template <int LO, int HI, typename F> __device__ __forceinline__ void static_for(F &&f) {
-    if constexpr (LO < HI) {
-        f(std::integral_constant<int, LO>{});
-        static_for<LO + 1, HI>(f);
-    }
-}
-
-// One fragment from memory straight to LDS (lds: its address there, the same for the whole wavefront;
-// lane_off: 16 * lane).  Inline because the compiler makes every LDS read wait for all such loads in
-// flight; the kernels count them themselves (vm_wait).  The destination goes through m0, which needs one
-// idle cycle before the load.
-template <int LDS_OFF> __device__ __forceinline__ void fragment_to_lds(const void *src, unsigned lane_off, unsigned lds) {
-    asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-                 : : "s"(lds), "v"(lane_off), "s"(src), "n"(LDS_OFF) : "memory", "scc");
-}
-// until at most N of this wavefront's vector memory operations are outstanding
-template <int N> __device__ __forceinline__ void vm_wait() { asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory"); }
-// until at most min(r, R) stages of L loads each are outstanding
-template <int R, int L> __device__ __forceinline__ void stage_wait(int r) {
-    if constexpr (R > 0) {
-        if (r >= R) vm_wait<R * L>();
-        else stage_wait<R - 1, L>(r);
-    } else {
-        vm_wait<0>();
-    }
-}
-__device__ __forceinline__ unsigned lds_address(const void *p) {
-    return (unsigned)(uintptr_t)(__attribute__((address_space(3))) const unsigned char *)p;
-}
-
 // Workgroup -> (row tile, column tile, split).  Neighbours in the order (split, column tile, row tile)
-// share a compute die (workgroup w runs on die w % 8), so that its L2 serves all but the first reader of
-// a weight tile.
+// share a compute die, so that its L2 serves all but the first reader of a weight tile.
 __device__ __forceinline__ void rows_tile(const RowsGemm &p, int &ty, int &tx, int &split) {
-    const int total = gridDim.x, pid = blockIdx.x, die = pid & 7, idx = pid >> 3;
-    const int per = (total + 7) >> 3, full = total & 7;   // dies below `full` hold `per`, the others one less
-    const int l = full == 0 || die < full ? die * per + idx : full * per + (die - full) * (per - 1) + idx;
+    const int l = die_order(blockIdx.x, gridDim.x);
     ty = l % p.ny;
     tx = (l / p.ny) % p.nx;
     split = l / (p.ny * p.nx);

@@ -287,7 +287,10 @@ int vf_launch_accept_static(const vf_model *m, const Batch &b, const AcceptBatch
                             const float *logits, int32_t *n_accept, int32_t *out_tokens, int32_t *y,
                             hipStream_t st);
 int vf_accept_static_init();
+int vf_attention_rows_parts(const vf_model *m, const Batch &b);
 int vf_launch_attention_rows(const vf_model *m, const Batch &b, int layer, hipStream_t st);
+// the same for many items over long contexts; 1: launched, 0: vf_launch_attention_rows is the faster one
+int vf_launch_attention_items(const vf_model *m, const Batch &b, int layer, hipStream_t st);
 bool vf_fast_path_ok(const vf_model *m, int total_rows);
 int vf_run_fast(vf_model *m, const Batch &b, const int32_t *tokens, float *logits_out, hipStream_t st);
 // the float32 model's layers and output head

@@ -1,0 +1,95 @@
+"""The attention kernel for many items over long contexts against the scalar one, through a model of one
+layer: random keys and values are written to it, a chunk or a batch of paged sequences runs over them, and the
+logits are compared with the general kernels' (VF_OPT_FAST_PATH 0: scalar attention, plain GEMMs).  Sizes sit
+where the kernel's shapes turn: contexts at, below and above a page of 64 and a part of pages, items that do
+not fill a wavefront or a workgroup, one part and several, both head sizes, pages in random order.  The two
+paths round the same values to bfloat16, so they differ by the order of float32 sums and the roundings that
+tips over: under 1e-2 of the largest logit (the tolerance of either against the oracle is 2e-2); a key left
+out, or one too many, moves a row whose weight is spread over few keys by far more, and the softmax here is
+peaked (keys with a spread of 3)."""
+import numpy as np
+import pytest
+import torch
+
+import workloads as wl
+import paper_2510_15312_amd as vf
+from util_gpu import DEV, Pair, i32
+from util_oracle import rel_inf
+
+pytestmark = pytest.mark.gpu
+_cache = {}
+
+
+def _pair(hd):
+    if hd not in _cache:
+        _cache.clear()
+        dims = dict(d_model=512, head_dim=hd, d_ffn=1024, vocab=2048, n_q_heads=24, n_kv_heads=8)
+        cfg = wl.scaled(wl.CONFIGS["1.5b_k16"], n_layers=1, **dims)
+        _cache[hd] = Pair(cfg, max_rows=1056, max_positions=9000)
+    return _cache[hd]
+
+
+def _fill(pair, seq, n, gen):
+    kv = torch.empty((2, n, pair.cfg.n_kv_heads, pair.cfg.head_dim), dtype=torch.float32, device=DEV)
+    kv.normal_(0.0, 3.0, generator=gen)
+    vf.vf_kv_write(pair.model, seq, 0, 0, kv[0], kv[1])
+    vf.vf_seq_set_len(seq, n)
+
+
+def _both(pair, run):
+    out = []
+    for fast in (1, 0):
+        vf.vf_set_option(pair.model, vf.VF_OPT_FAST_PATH, fast)
+        out.append(run().cpu().numpy())
+    vf.vf_set_option(pair.model, vf.VF_OPT_FAST_PATH, 1)
+    return rel_inf(out[0], out[1]).max()
+
+
+# (context, rows): 1056 rows of one page and less, contexts around a page, several parts
+@pytest.mark.parametrize("hd", [64, 128])
+@pytest.mark.parametrize("ctx,rows", [(1, 1056), (63, 1000), (64, 1055), (1900, 777), (4095, 512), (7900, 1051)])
+def test_chunk(hd, ctx, rows):
+    pair = _pair(hd)
+    gen = torch.Generator(device=DEV).manual_seed(ctx + rows)
+    seq = pair.new_seq(9000)
+    _fill(pair, seq, ctx, gen)
+    ids = i32(wl.make_context(pair.cfg.vocab, rows, np.random.default_rng(rows)))
+    logits = torch.empty((rows, pair.cfg.vocab), dtype=torch.float32, device=DEV)
+
+    def run():
+        vf.vf_seq_set_len(seq, ctx)
+        vf.vf_prefill_chunk(pair.model, seq, ids, logits_mode=2, logits_out=logits)
+        return logits
+    err = _both(pair, run)
+    print(f"hd {hd}, {ctx} + {rows}: {err:.2e}", flush=True)
+    assert err < 1e-2
+
+
+@pytest.mark.parametrize("hd", [64, 128])
+@pytest.mark.parametrize("n_seqs,lo,hi", [(32, 30, 8200), (16, 1000, 3000), (9, 3968, 4224)])
+def test_paged_batch(hd, n_seqs, lo, hi):
+    pair = _pair(hd)
+    rng = np.random.default_rng(n_seqs + lo)
+    ctx = rng.integers(lo, hi, n_seqs)
+    rows = rng.integers(6, 34, n_seqs)
+    need = [int(-(-(c + r) // 64)) for c, r in zip(ctx, rows)]
+    perm = rng.permutation(sum(need))
+    pool = torch.full((vf.vf_kv_bytes(pair.model, 64, sum(need)),), 255, dtype=torch.uint8, device=DEV)   # NaN where nothing is written
+    gen = torch.Generator(device=DEV).manual_seed(n_seqs)
+    seqs, at = [], 0
+    for c, n in zip(ctx, need):
+        seqs.append(pair.new_seq(n * 64, pool=pool, block_table=i32(perm[at:at + n])))
+        at += n
+        _fill(pair, seqs[-1], int(c), gen)
+    off = [0] + [int(x) for x in np.cumsum(rows)]
+    ids = i32(rng.integers(0, pair.cfg.vocab, off[-1]))
+    logits = torch.empty((off[-1], pair.cfg.vocab), dtype=torch.float32, device=DEV)
+
+    def run():
+        for s, c in zip(seqs, ctx):
+            vf.vf_seq_set_len(s, int(c))
+        vf.vf_verify(pair.model, seqs, ids, off, logits)
+        return logits
+    err = _both(pair, run)
+    print(f"hd {hd}, {n_seqs} sequences: {err:.2e}", flush=True)
+    assert err < 1e-2
