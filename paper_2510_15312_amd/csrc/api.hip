@@ -139,7 +139,7 @@ int run_layers(vf_model *m, const Batch &b, const int32_t *tokens, int *tail_par
     const int rows = b.total_rows, R = rows;  // partials are laid out with ld = rows of this call
     const int d = c.d_model, F = c.d_ffn, nq = c.n_q_heads * c.head_dim, nkv = c.n_kv_heads * c.head_dim;
     int rc;
-    const GemmPlan qkv = vf_gemm_plan(m, nq + 2 * nkv, d, rows, GEMM_SPLIT), po = vf_gemm_plan(m, d, nq, rows, GEMM_SPLIT);
+    const GemmPlan qkv = vf_gemm_plan(m, nq + 2 * nkv, d, rows, GEMM_QKV), po = vf_gemm_plan(m, d, nq, rows, GEMM_SPLIT);
     const GemmPlan gu = vf_gemm_plan(m, 2 * F, d, rows, GEMM_SWIGLU), down = vf_gemm_plan(m, d, F, rows, GEMM_SPLIT);
     const bool act_in_gemm = gu.epi == GEMM_SWIGLU;  // the activation function is the gate/up GEMM's epilogue
     if ((rc = vf_launch_embed(m, b, tokens, st))) return rc;
@@ -148,10 +148,15 @@ int run_layers(vf_model *m, const Batch &b, const int32_t *tokens, int *tail_par
         const LayerPacked &lp = m->layers[l];
         { ProfScope ps(m, VF_SITE_SMALL, st);
           if ((rc = vf_launch_norm(m, lp.attn_norm, m->x, m->part, nparts, rows, R, st))) return rc; }
+        const QkvEpilogue epi = vf_qkv_epilogue(m, b, l, tree ? m->tree_depth : nullptr);
         { ProfScope ps(m, VF_SITE_QKV, st);
-          if ((rc = vf_launch_gemm(m, lp.wqkv, m->x, m->part, nq + 2 * nkv, d, rows, 0, rows, R, qkv, st))) return rc; }
-        { ProfScope ps(m, VF_SITE_SMALL, st);
-          if ((rc = vf_launch_qkv_finish(m, b, l, m->part, qkv.ks, R, tree ? m->tree_depth : nullptr, st))) return rc; }
+          if (qkv.epi == GEMM_QKV) rc = vf_launch_gemm_qkv(m, lp.wqkv, m->x, nq + 2 * nkv, d, epi, qkv, st);
+          else rc = vf_launch_gemm(m, lp.wqkv, m->x, m->part, nq + 2 * nkv, d, rows, 0, rows, R, qkv, st);
+          if (rc) return rc; }
+        if (qkv.epi != GEMM_QKV) {
+            ProfScope ps(m, VF_SITE_SMALL, st);
+            if ((rc = vf_launch_qkv_finish(m, epi, m->part, qkv.ks, R, st))) return rc;
+        }
         { ProfScope ps(m, VF_SITE_ATTN, st);
           if ((rc = vf_launch_attention(m, b, l, tree ? m->tree_anc : nullptr, st))) return rc; }
         { ProfScope ps(m, VF_SITE_O, st);

@@ -171,63 +171,26 @@ __global__ __launch_bounds__(256) void norm_bf16_vec_kernel(float *__restrict__ 
     }
 }
 
-// QKV epilogue: one thread per (row, four packed columns).  Heads 0..Hq-1 are q, then Hkv k heads,
-// then Hkv v heads (v is not rotated).  Packed columns 2i, 2i+1 of a q or k head are elements i and
-// i + hd/2, so four columns are the two rotary pairs i, i + 1 and every store is two elements.
-__global__ __launch_bounds__(256) void qkv_finish_kernel(const float *__restrict__ part, int nparts, int ld_rows, Batch b, int layer,
-                                                         const float *__restrict__ bias, const float *__restrict__ cosv,
-                                                         const float *__restrict__ sinv, bf16_t *__restrict__ q, int hq, int hkv,
-                                                         int hd, const int32_t *__restrict__ depth) {
-    const int half = hd >> 1, N = (hq + 2 * hkv) * hd, per_row = N >> 2;
+// QKV epilogue of a GEMM whose K was split: one thread per (row, four packed columns).
+__global__ __launch_bounds__(256) void qkv_finish_kernel(const float *__restrict__ part, int nparts, int ld_rows, QkvEpilogue e) {
+    const int N = (e.hq + 2 * e.hkv) * e.hd, per_row = N >> 2;
     const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= b.total_rows * per_row) return;
+    if (idx >= e.b.total_rows * per_row) return;
     const int row = idx / per_row, n0 = (idx % per_row) * 4;
-    const int head = n0 / hd, p0 = n0 % hd;
-    const bool rot = head < hq + hkv;
-    const SeqDesc &s = b.s[find_seq(b, row)];
-    // the rotary angle is that of the token's position; the cache row is the call's row (the two
-    // differ for tree-structured drafts, where a node stands at the position of its depth)
-    const int len = s.state[0], slot = len + (row - s.row0), pos = depth ? len + depth[row] : slot;
-    float4 v = {0.f, 0.f, 0.f, 0.f};
+    const int nb = n0 >> 4, g4 = n0 >> 2 & 3;
+    const QkvPlace at = qkv_place(e, row, g4);
+    const QkvAngles angles = qkv_angles(e, at, nb);
+    floatx4 v = {0.f, 0.f, 0.f, 0.f};
     for (int q0 = 0; q0 < nparts; q0 += 4) {   // requested together, added in order
-        float4 t[4];
+        floatx4 t[4];
 #pragma unroll
         for (int p = 0; p < 4; ++p)
-            t[p] = *reinterpret_cast<const float4 *>(part + ((size_t)min(q0 + p, nparts - 1) * ld_rows + row) * N + n0);
+            t[p] = *reinterpret_cast<const floatx4 *>(part + ((size_t)min(q0 + p, nparts - 1) * ld_rows + row) * N + n0);
 #pragma unroll
         for (int p = 0; p < 4; ++p)
-            if (q0 + p < nparts) { v.x += t[p].x; v.y += t[p].y; v.z += t[p].z; v.w += t[p].w; }
+            if (q0 + p < nparts) v += t[p];
     }
-    if (bias) {
-        const float4 bb = *reinterpret_cast<const float4 *>(bias + n0);
-        v.x += bb.x; v.y += bb.y; v.z += bb.z; v.w += bb.w;
-    }
-    if (slot < 0 || slot >= s.capacity) return;
-    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-    bf16_t *kv = reinterpret_cast<bf16_t *>(s.kv);
-    if (rot) {
-        const int i0 = p0 >> 1;
-        const float2 c = *reinterpret_cast<const float2 *>(cosv + (size_t)pos * half + i0);
-        const float2 sn = *reinterpret_cast<const float2 *>(sinv + (size_t)pos * half + i0);
-        const bf16x2 lo = {(bf16_t)(v.x * c.x - v.y * sn.x), (bf16_t)(v.z * c.y - v.w * sn.y)};
-        const bf16x2 hi = {(bf16_t)(v.y * c.x + v.x * sn.x), (bf16_t)(v.w * c.y + v.z * sn.y)};
-        bf16_t *d0, *d1;
-        if (head < hq) {
-            d0 = q + ((size_t)row * hq + head) * hd + i0;
-            d1 = d0 + half;
-        } else {
-            const int page = kv_page(s, slot), tin = slot % VF_TILE;
-            d0 = kv + kv_k_index(layer, s.n_pages, page, hkv, head - hq, tin, i0, hd);
-            d1 = kv + kv_k_index(layer, s.n_pages, page, hkv, head - hq, tin, i0 + half, hd);
-        }
-        *reinterpret_cast<bf16x2 *>(d0) = lo;
-        *reinterpret_cast<bf16x2 *>(d1) = hi;
-    } else {
-        const int page = kv_page(s, slot), tin = slot % VF_TILE, vh = head - hq - hkv;
-        const float w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-        for (int j = 0; j < 4; ++j) kv[kv_v_index(layer, s.n_pages, page, hkv, vh, tin, p0 + j, hd)] = (bf16_t)w[j];
-    }
+    qkv_store(e, at, angles, row, nb, g4, v);
 }
 
 // a[row, f] = bf16(silu(gate) * up); gate and up alternate in the columns of the gate/up GEMM's output.
@@ -385,13 +348,15 @@ int vf_launch_norm(const vf_model *m, const float *gain, void *x_out, const floa
     return VF_OK;
 }
 
-int vf_launch_qkv_finish(const vf_model *m, const Batch &b, int layer, const float *part, int nparts,
-                         int ld_rows, const int32_t *depth, hipStream_t st) {
+QkvEpilogue vf_qkv_epilogue(const vf_model *m, const Batch &b, int layer, const int32_t *depth) {
     const vf_config &c = m->cfg;
-    const int total = b.total_rows * (c.n_q_heads + 2 * c.n_kv_heads) * (c.head_dim / 4);
-    hipLaunchKernelGGL(qkv_finish_kernel, dim3(nblocks(total, 256)), dim3(256), 0, st, part, nparts, ld_rows, b, layer,
-                       c.qkv_bias ? m->layers[layer].bqkv : nullptr, m->rope_cos, m->rope_sin, (bf16_t *)m->q, c.n_q_heads,
-                       c.n_kv_heads, c.head_dim, depth);
+    return {b, layer, c.n_q_heads, c.n_kv_heads, c.head_dim, c.qkv_bias ? m->layers[layer].bqkv : nullptr,
+            m->rope_cos, m->rope_sin, (bf16_t *)m->q, depth};
+}
+
+int vf_launch_qkv_finish(const vf_model *m, const QkvEpilogue &e, const float *part, int nparts, int ld_rows, hipStream_t st) {
+    const int total = e.b.total_rows * (e.hq + 2 * e.hkv) * (e.hd / 4);
+    hipLaunchKernelGGL(qkv_finish_kernel, dim3(nblocks(total, 256)), dim3(256), 0, st, part, nparts, ld_rows, e);
     VF_LAUNCH_CHECK("qkv_finish");
     return VF_OK;
 }

@@ -197,7 +197,7 @@ template <int EPI, typename F> int with_rows_kernel(int k, F fn) {
             default: break;
         }
     }
-    if constexpr (EPI == ROWS_EPI_PARTIAL) {
+    if constexpr (EPI == ROWS_EPI_PARTIAL || EPI == ROWS_EPI_QKV) {
         switch (k) {
             case RK_S4x2: VF_STREAM_KERNEL(4, 1, 2, 8, 4, 9);
             case RK_S8x2: VF_STREAM_KERNEL(8, 1, 2, 8, 4, 9);
@@ -222,15 +222,18 @@ template <int EPI> int allow_lds() {
     return VF_OK;
 }
 
-int launch_rows(int epi, int k, const RowsGemm &p, int workgroups, hipStream_t st) {
-    auto go = [&](auto l) -> int {
+template <int EPI> int launch_rows_as(int k, const RowsArgs<EPI> &p, int workgroups, hipStream_t st) {
+    return with_rows_kernel<EPI>(k, [&](auto l) -> int {
         hipLaunchKernelGGL(l.kern, dim3(workgroups), dim3(l.threads), l.lds, st, p);
         VF_LAUNCH_CHECK("gemm_rows");
         return VF_OK;
-    };
-    if (epi == ROWS_EPI_SWIGLU) return with_rows_kernel<ROWS_EPI_SWIGLU>(k, go);
-    if (epi == ROWS_EPI_TOPK) return with_rows_kernel<ROWS_EPI_TOPK>(k, go);
-    return with_rows_kernel<ROWS_EPI_PARTIAL>(k, go);
+    });
+}
+
+int launch_rows(int epi, int k, const RowsGemm &p, int workgroups, hipStream_t st) {
+    if (epi == ROWS_EPI_SWIGLU) return launch_rows_as<ROWS_EPI_SWIGLU>(k, p, workgroups, st);
+    if (epi == ROWS_EPI_TOPK) return launch_rows_as<ROWS_EPI_TOPK>(k, p, workgroups, st);
+    return launch_rows_as<ROWS_EPI_PARTIAL>(k, p, workgroups, st);
 }
 
 }  // namespace
@@ -239,6 +242,7 @@ int vf_gemm_init() {
     int rc = allow_lds<ROWS_EPI_PARTIAL>();
     if (!rc) rc = allow_lds<ROWS_EPI_SWIGLU>();
     if (!rc) rc = allow_lds<ROWS_EPI_TOPK>();
+    if (!rc) rc = allow_lds<ROWS_EPI_QKV>();
     return rc;
 }
 
@@ -254,12 +258,16 @@ GemmPlan vf_gemm_plan(const vf_model *m, int N, int K, int rows, GemmUse use) {
             const float mb_w = (float)N * K * 2e-6f;
             const int tiles = (NBt + s.nb - 1) / s.nb * ((cbs + s.mb - 1) / s.mb);
             for (int ks : {1, 2, 3, 4, 6, 8, 10, 12, 16}) {
-                if (ks > 1 && (use != GEMM_SPLIT || KB / ks < 4 || (size_t)ks * rows * N > m->part_floats)) break;
+                if (ks > 1 && ((use != GEMM_SPLIT && use != GEMM_QKV) || KB / ks < 4 || (size_t)ks * rows * N > m->part_floats)) break;
                 const int nk = (KB + ks - 1) / ks, splits = (KB + nk - 1) / nk, wgs = tiles * splits;
                 const float rounds = wgs <= 768 ? (float)((wgs + 255) / 256) : (float)wgs / 256.f + 0.2f;
                 const float mb_out = (use == GEMM_SWIGLU ? 1.f : use == GEMM_TOPK ? 0.5f : 4.f * splits) * rows * N * 1e-6f;
                 float t = s.start + s.step * nk * rounds + s.written * mb_out + s.hbm * mb_w;
                 if (use == GEMM_SPLIT) t += 0.2f * mb_out;   // the consumer reads the partial sums at about 5 TB/s
+                // Unsplit, the QKV epilogue runs in the GEMM, at the end of every wavefront; split, it is a launch of its own.
+                // Measured, GEMM and epilogue together, in one launch / in two: 256 rows at 1.5B 8.2 / 12.1 us, 128 at 0.5B
+                // 6.9 / 8.9, 104 in 12 sequences 8.0 / 10, 277 in 16 at 1.5B 12.2 / 15.3, 1024 at 3B 52 / 55.
+                if (use == GEMM_QKV) t += splits == 1 ? 1.0f : 4.0f + 0.2f * mb_out;
                 if (t < best) {
                     best = t;
                     p.shape = k;
@@ -267,13 +275,13 @@ GemmPlan vf_gemm_plan(const vf_model *m, int N, int K, int rows, GemmUse use) {
                 }
             }
         }
-        p.epi = use == GEMM_SPLIT ? GEMM_PARTIAL : use;
+        p.epi = use == GEMM_SPLIT || (use == GEMM_QKV && p.ks > 1) ? GEMM_PARTIAL : use;
         return p;
     }
     const int groups1 = (NBt + GEMM_WAVES - 1) / GEMM_WAVES;
     if (groups1 >= 4096) p.nbw = 4;
     else if (groups1 >= 2048) p.nbw = 2;
-    if (use != GEMM_SPLIT && use != GEMM_SWIGLU) return p;
+    if (use != GEMM_SPLIT && use != GEMM_QKV && use != GEMM_SWIGLU) return p;
     const int groups = (NBt + GEMM_WAVES * p.nbw - 1) / (GEMM_WAVES * p.nbw);
     int ks = 1;
     while (groups * ks < 256 && KB / (ks * 2) >= 4) ks *= 2;
@@ -288,6 +296,33 @@ int vf_gemm_topk_lists(const GemmPlan &p, int N) {
     return ((N >> 4) + s.nb - 1) / s.nb * s.lists;
 }
 
+static RowsGemm rows_gemm(const RowsShape &s, const void *W, const void *X, float *out, int N, int K, int ncb, int row_lo, int row_hi,
+                          int ld_rows, int ks) {
+    RowsGemm p;
+    memset(&p, 0, sizeof p);
+    p.W = (const u32x4 *)W;
+    p.X = (const u32x4 *)X;
+    p.out = out;
+    p.N = N;
+    p.KB = K >> 5;
+    p.ncb = ncb;
+    p.row_lo = row_lo;
+    p.row_hi = row_hi;
+    p.ld_rows = ld_rows;
+    p.kb_per_split = (p.KB + ks - 1) / ks;
+    p.nx = ((N >> 4) + s.nb - 1) / s.nb;
+    p.ny = (((row_hi + 15) >> 4) - (row_lo >> 4) + s.mb - 1) / s.mb;
+    return p;
+}
+
+int vf_launch_gemm_qkv(const vf_model *m, const void *W, const void *X, int N, int K, const QkvEpilogue &e, const GemmPlan &plan,
+                       hipStream_t st) {
+    const int rows = e.b.total_rows;
+    if (plan.epi != GEMM_QKV || plan.ks != 1 || N != (e.hq + 2 * e.hkv) * e.hd) return vf_fail(VF_ERR_ARG, "QKV GEMM: not its plan");
+    RowsGemmQkv p{rows_gemm(ROWS_SHAPES[plan.shape], W, X, nullptr, N, K, (rows + 15) >> 4, 0, rows, rows, 1), e};
+    return launch_rows_as<ROWS_EPI_QKV>(plan.shape, p, p.nx * p.ny, st);
+}
+
 int vf_launch_gemm(const vf_model *m, const void *W, const void *X, float *out, int N, int K,
                    int rows_total, int row_lo, int row_hi, int ld_rows, const GemmPlan &plan, hipStream_t st) {
     if (row_hi <= row_lo) return VF_OK;
@@ -297,19 +332,7 @@ int vf_launch_gemm(const vf_model *m, const void *W, const void *X, float *out, 
         const RowsShape &s = ROWS_SHAPES[plan.shape];
         if (plan.epi == GEMM_TOPK && (plan.topk < 1 || plan.topk > VF_TOPK_MAX || !plan.topk_ids))
             return vf_fail(VF_ERR_ARG, "top-k epilogue: k %d", plan.topk);
-        RowsGemm p;
-        p.W = (const u32x4 *)W;
-        p.X = (const u32x4 *)X;
-        p.out = out;
-        p.N = N;
-        p.KB = K >> 5;
-        p.ncb = ncb;
-        p.row_lo = row_lo;
-        p.row_hi = row_hi;
-        p.ld_rows = ld_rows;
-        p.kb_per_split = (p.KB + plan.ks - 1) / plan.ks;
-        p.nx = ((N >> 4) + s.nb - 1) / s.nb;
-        p.ny = (cbs + s.mb - 1) / s.mb;
+        RowsGemm p = rows_gemm(s, W, X, out, N, K, ncb, row_lo, row_hi, ld_rows, plan.ks);
         p.cand_i = plan.topk_ids;
         p.topk = plan.topk;
         const int epi = plan.epi == GEMM_SWIGLU ? ROWS_EPI_SWIGLU : plan.epi == GEMM_TOPK ? ROWS_EPI_TOPK : ROWS_EPI_PARTIAL;

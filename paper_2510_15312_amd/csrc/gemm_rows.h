@@ -26,7 +26,7 @@ namespace {
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int ROWS_EPI_PARTIAL = 0, ROWS_EPI_SWIGLU = 1, ROWS_EPI_TOPK = 2;
+constexpr int ROWS_EPI_PARTIAL = 0, ROWS_EPI_SWIGLU = 1, ROWS_EPI_TOPK = 2, ROWS_EPI_QKV = 3;
 
 struct RowsGemm {
     const u32x4 *W, *X;
@@ -37,6 +37,19 @@ struct RowsGemm {
     int32_t *cand_i;
     int topk;
 };
+struct RowsGemmQkv : RowsGemm { QkvEpilogue e; };
+// QKV: where a wavefront's rows go, looked up ahead of the products
+template <int EPI, int WMB> struct RowsQkv {
+    __device__ __forceinline__ void request(const RowsGemm &, int, int) {}
+};
+template <int WMB> struct RowsQkv<ROWS_EPI_QKV, WMB> {
+    QkvPlace at[WMB];
+    __device__ __forceinline__ void request(const RowsGemmQkv &p, int cb0, int lane) {
+#pragma unroll
+        for (int c = 0; c < WMB; ++c) at[c] = qkv_place(p.e, min((cb0 + c) * 16 + (lane & 15), p.row_hi - 1), lane >> 4);
+    }
+};
+template <int EPI> using RowsArgs = std::conditional_t<EPI == ROWS_EPI_QKV, RowsGemmQkv, RowsGemm>;
 
 // Workgroup -> (row tile, column tile, split).  Neighbours in the order (split, column tile, row tile)
 // share a compute die, so that its L2 serves all but the first reader of a weight tile.
@@ -66,12 +79,14 @@ __device__ __forceinline__ float silu_mul(float g, float u) {
 //   PARTIAL: float32 sums of this K split.
 //   SWIGLU : gate row f is column 2 f and up row f column 2 f + 1 of the packed matrix, so a lane holds
 //            two (gate, up) pairs: a = bf16(silu(gate) * up), columns 8 nb + 2 (lane >> 4) + 0..1.
+//   QKV    : bias, rotary embedding, q rows and the cache's keys and values (qkv_store): a lane's four
+//            columns are its unit.
 //   TOPK   : per row, the topk largest of the wavefront's 16 WNB columns with their ids, in falling order,
 //            equal values by rising id, as list `list` of n_lists.  The four lanes that share a row run one
 //            round per result: every lane offers its best remaining value, two shuffles pick the row's.
 template <int EPI, int WNB, int WMB>
-__device__ __forceinline__ void rows_epilogue(const RowsGemm &p, const floatx4 (&acc)[WNB][WMB], int nb0, int cb0, int split,
-                                              int list, int n_lists, int lane) {
+__device__ __forceinline__ void rows_epilogue(const RowsArgs<EPI> &p, const RowsQkv<EPI, WMB> &qkv, const floatx4 (&acc)[WNB][WMB], int nb0,
+                                              int cb0, int split, int list, int n_lists, int lane) {
     const int NBt = p.N >> 4, g4 = lane >> 4;
     if constexpr (EPI == ROWS_EPI_SWIGLU) {
         unsigned *a_out = reinterpret_cast<unsigned *>(p.out);
@@ -87,6 +102,25 @@ __device__ __forceinline__ void rows_epilogue(const RowsGemm &p, const floatx4 (
                 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
                 const bf16x2 o = {(bf16_t)silu_mul(v[0], v[1]), (bf16_t)silu_mul(v[2], v[3])};
                 a_out[(((size_t)(nb >> 2) * p.ncb + cb) * 64 + ((nb & 3) << 4) + (lane & 15)) * 4 + g4] = __builtin_bit_cast(unsigned, o);
+            }
+        }
+    } else if constexpr (EPI == ROWS_EPI_QKV) {
+        // the next row block's angles are on their way while one is stored
+        QkvAngles an[2][WNB];
+        auto request = [&](int c) {
+#pragma unroll
+            for (int n = 0; n < WNB; ++n) an[c & 1][n] = qkv_angles(p.e, qkv.at[c], min(nb0 + n, NBt - 1));
+        };
+        request(0);
+#pragma unroll
+        for (int c = 0; c < WMB; ++c) {
+            if (c + 1 < WMB) request(c + 1);
+            const int row = (cb0 + c) * 16 + (lane & 15);
+            if (row < p.row_lo || row >= p.row_hi) continue;
+#pragma unroll
+            for (int n = 0; n < WNB; ++n) {
+                if (nb0 + n >= NBt) break;
+                qkv_store(p.e, qkv.at[c], an[c & 1][n], row, nb0 + n, g4, acc[n][c]);
             }
         }
     } else if constexpr (EPI == ROWS_EPI_TOPK) {
@@ -145,7 +179,7 @@ __device__ __forceinline__ void rows_epilogue(const RowsGemm &p, const floatx4 (
 // CW compute wavefronts of WMB row blocks each and one producer; NB weight blocks per tile; activation
 // fragments D k-blocks ahead; weight ring of SW slots of KS k-blocks (one barrier per slot).
 template <int CW, int WMB, int NB, int D, int KS, int SW, int EPI>
-__global__ __launch_bounds__((CW + 1) * 64) VF_MFMA_KERNEL void gemm_stream_kernel(RowsGemm p) {
+__global__ __launch_bounds__((CW + 1) * 64) VF_MFMA_KERNEL void gemm_stream_kernel(RowsArgs<EPI> p) {
     static_assert(D % 2 == 0 && D % KS == 0, "register sets and LDS slots line up with the unrolled loop");
     static_assert((SW - 2) * NB * KS < 64, "the wait counter counts to 63");
     extern __shared__ __align__(1024) unsigned char smem[];
@@ -219,6 +253,8 @@ __global__ __launch_bounds__((CW + 1) * 64) VF_MFMA_KERNEL void gemm_stream_kern
             for (int c = 0; c < WMB; ++c)
                 acc[n][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[n], __builtin_bit_cast(bf16x8, r[c]), acc[n][c], 0, 0, 0);
     };
+    RowsQkv<EPI, WMB> qkv;
+    qkv.request(p, cb0 + wave * WMB, lane);
 #pragma unroll
     for (int d = 0; d < D; ++d) fetch(x[d]);
     read(w[0], 0);
@@ -243,12 +279,12 @@ __global__ __launch_bounds__((CW + 1) * 64) VF_MFMA_KERNEL void gemm_stream_kern
             mma(w[d & 1], x[d]);
         }
     }
-    rows_epilogue<EPI, NB, WMB>(p, acc, nb0, cb0 + wave * WMB, split, tx, p.nx, lane);
+    rows_epilogue<EPI, NB, WMB>(p, qkv, acc, nb0, cb0 + wave * WMB, split, tx, p.nx, lane);
 }
 
 // Tile of MB row blocks x NB weight blocks, WM x WN wavefronts, ring of S stages of one k-block.
 template <int MB, int NB, int WM, int WN, int S, int EPI>
-__global__ __launch_bounds__(WM *WN * 64) VF_MFMA_KERNEL void gemm_tile_kernel(RowsGemm p) {
+__global__ __launch_bounds__(WM *WN * 64) VF_MFMA_KERNEL void gemm_tile_kernel(RowsArgs<EPI> p) {
     constexpr int NW = WM * WN, WMB = MB / WM, WNB = NB / WN, FR = MB + NB, LPW = FR / NW, NR = WMB + WNB, NM = WMB * WNB;
     static_assert(FR % NW == 0 && MB % WM == 0 && NB % WN == 0 && (S & (S - 1)) == 0, "tile shape");
     extern __shared__ __align__(1024) unsigned char smem[];
@@ -317,6 +353,8 @@ __global__ __launch_bounds__(WM *WN * 64) VF_MFMA_KERNEL void gemm_tile_kernel(R
         static_for<0, LPW>([&](auto i) { issue1((unsigned)(s * FR) * 1024u, i); });
         --left;
     }
+    RowsQkv<EPI, WMB> qkv;
+    qkv.request(p, cb0 + wm * WMB, lane);
     Frags f0, f1;
     vm_wait<(S - 1) * LPW>();
     lds_sync();
@@ -328,7 +366,7 @@ __global__ __launch_bounds__(WM *WN * 64) VF_MFMA_KERNEL void gemm_tile_kernel(R
     }
     if (s < nk) static_for<0, NM>([&](auto i) { mma1(f0, i); });
     vm_wait<0>();   // nothing is on its way to LDS when the workgroup ends
-    rows_epilogue<EPI, WNB, WMB>(p, acc, nb0 + wn * WNB, cb0 + wm * WMB, split, tx * WN + wn, p.nx * WN, lane);
+    rows_epilogue<EPI, WNB, WMB>(p, qkv, acc, nb0 + wn * WNB, cb0 + wm * WMB, split, tx * WN + wn, p.nx * WN, lane);
 }
 
 }  // namespace

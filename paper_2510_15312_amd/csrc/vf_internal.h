@@ -231,10 +231,71 @@ __device__ inline int find_seq(const Batch &b, int row) {
 }
 static_assert(VF_MAX_BATCH % 8 == 0, "find_seq reads descriptors in eights");
 
+// ---- QKV epilogue ---------------------------------------------------------------------------------
+// Columns of the packed QKV matrix: heads 0..hq-1 are q, then hkv k heads, then hkv v heads (v is not
+// rotated).  Packed columns 2i, 2i+1 of a q or k head are elements i and i + hd/2, so four columns are the
+// two rotary pairs i, i + 1 and every store is two elements.
+struct QkvEpilogue {
+    Batch b;
+    int32_t layer, hq, hkv, hd;
+    const float *bias, *cosv, *sinv;   // bias: NULL without one
+    bf16_t *q;
+    const int32_t *depth;              // tree verify: depth of every row; NULL: row r of a sequence has depth r
+};
+// Where a row goes: offsets (elements) of lane group g4's share, columns 16 nb + 4 g4 .. + 3 of any block
+// nb.  What depends on nb alone is added per block, by the scalar unit where nb is the same for the wavefront.
+struct QkvPlace { unsigned rope, k, v; bf16_t *page; };   // page: NULL for a row that is not stored
+struct QkvAngles { float2 c, s; };
+// The rotary angle is that of the token's position; the cache row is the call's row (the two differ for
+// tree-structured drafts, where a node stands at the position of its depth).
+__device__ __forceinline__ QkvPlace qkv_place_in(const QkvEpilogue &e, const SeqDesc &s, int row, int g4) {
+    const int len = s.state[0], r = row - s.row0, slot = len + r, tin = slot % VF_TILE, hd = e.hd;
+    if (slot < 0 || slot >= s.capacity) return {0, 0, 0, nullptr};
+    return {(unsigned)((len + (e.depth ? e.depth[row] : r)) * (hd >> 1) + g4 * 2),
+            (unsigned)kv_k_index(0, 0, 0, 0, 0, tin, 0, hd) + g4 * 2, (unsigned)kv_v_index(0, 0, 0, 0, 0, tin, 0, hd) + g4 * 32,
+            reinterpret_cast<bf16_t *>(s.kv) + ((size_t)e.layer * s.n_pages + kv_page(s, slot)) * 2 * e.hkv * VF_TILE * hd};
+}
+// One sequence (a prefill chunk): its descriptor is read by the scalar unit.  Several: per lane, a wavefront's
+// rows may belong to more than one (a loop over all sequences with scalar reads: 8.2 -> 10.8 us the QKV GEMM of
+// 104 rows in 12 sequences).
+__device__ __forceinline__ QkvPlace qkv_place(const QkvEpilogue &e, int row, int g4) {
+    if (e.b.n_seqs == 1) return qkv_place_in(e, e.b.s[0], row, g4);
+    return qkv_place_in(e, e.b.s[find_seq(e.b, row)], row, g4);
+}
+// the angles of the lane's columns of block nb (any, for a v head)
+__device__ __forceinline__ QkvAngles qkv_angles(const QkvEpilogue &e, const QkvPlace &p, int nb) {
+    const unsigned at = p.rope + ((nb * 16 & (e.hd - 1)) >> 1);
+    return {*reinterpret_cast<const float2 *>(e.cosv + at), *reinterpret_cast<const float2 *>(e.sinv + at)};
+}
+__device__ __forceinline__ void qkv_store(const QkvEpilogue &e, const QkvPlace &p, const QkvAngles &a, int row, int nb, int g4, floatx4 v) {
+    if (!p.page) return;
+    const int hd = e.hd, half = hd >> 1, head = nb * 16 >> (hd == 128 ? 7 : 6), p0 = nb * 16 & (hd - 1), i0 = p0 >> 1;
+    if (e.bias) v += *reinterpret_cast<const floatx4 *>(e.bias + nb * 16 + g4 * 4);
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    if (head < e.hq + e.hkv) {
+        const bf16x2 lo = {(bf16_t)(v[0] * a.c.x - v[1] * a.s.x), (bf16_t)(v[2] * a.c.y - v[3] * a.s.y)};
+        const bf16x2 hi = {(bf16_t)(v[1] * a.c.x + v[0] * a.s.x), (bf16_t)(v[3] * a.c.y + v[2] * a.s.y)};
+        if (head < e.hq) {
+            bf16_t *d = e.q + (unsigned)((row * e.hq + head) * hd + i0 + g4 * 2);
+            *reinterpret_cast<bf16x2 *>(d) = lo;
+            *reinterpret_cast<bf16x2 *>(d + half) = hi;
+        } else {   // tin 0 of the index map: what element i0 adds
+            bf16_t *d = p.page + (p.k + (unsigned)((head - e.hq) * VF_TILE * hd));
+            *reinterpret_cast<bf16x2 *>(d + (unsigned)kv_k_index(0, 0, 0, 0, 0, 0, i0, hd)) = lo;
+            *reinterpret_cast<bf16x2 *>(d + (unsigned)kv_k_index(0, 0, 0, 0, 0, 0, i0 + half, hd)) = hi;
+        }
+    } else {
+        bf16_t *d = p.page + (p.v + (unsigned)((head - e.hq) * VF_TILE * hd + p0 / 16 * 512));
+#pragma unroll
+        for (int j = 0; j < 4; ++j) d[j * 8] = (bf16_t)v[j];
+    }
+}
+
 // ---- launchers (defined next to their kernels) --------------------------------------------------
 enum GemmUse {
     GEMM_PARTIAL,  // unsplit, float32 result
     GEMM_SPLIT,    // float32 partial sums of K splits, added by the consumer
+    GEMM_QKV,      // QKV matrix: unsplit, with the QKV epilogue, or as GEMM_SPLIT, whichever is cheaper
     GEMM_SWIGLU,   // gate/up matrix: bf16(silu(gate) * up) in activation layout (VF_OPT_FAST_PATH 0: partial sums)
     GEMM_TOPK      // output head: the top candidates of every row instead of the logits
 };
@@ -242,7 +303,7 @@ struct GemmPlan {
     int ks;        // K splits (partials)
     int nbw;       // general kernel: n-blocks per wavefront
     int shape;     // >= 0: kernel and tile of gemm_rows.h; -1: general kernel
-    GemmUse epi;   // GEMM_PARTIAL, GEMM_SWIGLU or GEMM_TOPK
+    GemmUse epi;   // GEMM_PARTIAL, GEMM_QKV (unsplit), GEMM_SWIGLU or GEMM_TOPK
     int topk;      // GEMM_TOPK: candidates per (row, list)
     int32_t *topk_ids;  // their ids (the values go where the partials would)
 };
@@ -263,9 +324,12 @@ int vf_launch_rope_table(const vf_model *m, hipStream_t st);
 int vf_launch_embed(const vf_model *m, const Batch &b, const int32_t *tokens, hipStream_t st);
 int vf_launch_norm(const vf_model *m, const float *gain, void *x_out, const float *part, int nparts,
                    int rows, int ld_rows, hipStream_t st);
+// the QKV GEMM of a GEMM_QKV plan
+int vf_launch_gemm_qkv(const vf_model *m, const void *W, const void *X, int N, int K, const QkvEpilogue &e, const GemmPlan &plan,
+                       hipStream_t st);
 // depth != NULL (tree verify): row r stands at position len + depth[row], not len + r
-int vf_launch_qkv_finish(const vf_model *m, const Batch &b, int layer, const float *part, int nparts,
-                         int ld_rows, const int32_t *depth, hipStream_t st);
+QkvEpilogue vf_qkv_epilogue(const vf_model *m, const Batch &b, int layer, const int32_t *depth);
+int vf_launch_qkv_finish(const vf_model *m, const QkvEpilogue &e, const float *part, int nparts, int ld_rows, hipStream_t st);
 // ancestor masks and depths of every row of the call from the parent table, into the model workspace
 int vf_launch_tree_prep(const vf_model *m, const Batch &b, const TreeDesc &tree, hipStream_t st);
 // moves the K/V rows of the accepted path (path[row0 + j], j = 1..n_accept) to the positions right
