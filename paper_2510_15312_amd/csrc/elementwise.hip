@@ -102,8 +102,11 @@ __global__ __launch_bounds__(256) void norm_kernel(float *__restrict__ h, const 
 
 // The same for d up to 4096: a thread owns runs of eight consecutive
 // elements (one 16-byte piece of an activation fragment), keeps them in registers between the
-// sum of squares and the scaling, and stores the piece whole.
-template <int VPT>
+// sum of squares and the scaling, and stores the piece whole.  NP: partial sums requested together (one after
+// the other, each waited for the one before: 5.5 us per launch at 256 rows, 8 partials); the smallest of 1, 2,
+// 4, 8 that holds them, as the loads past the last one repeat it: with 8 for one
+// partial 1024 rows of 3072 took 12.9 us instead of 11.6, 876 rows 12.1 instead of 10.2.
+template <int VPT, int NP>
 __global__ __launch_bounds__(256) void norm_bf16_vec_kernel(float *__restrict__ h, const float *__restrict__ part,
                                                             int nparts, int ld_rows, const float *__restrict__ gain,
                                                             u32x4_t *__restrict__ x, int d, int ncb, float eps) {
@@ -119,18 +122,16 @@ __global__ __launch_bounds__(256) void norm_bf16_vec_kernel(float *__restrict__ 
             const float4 a = *reinterpret_cast<const float4 *>(hp), b = *reinterpret_cast<const float4 *>(hp + 4);
             v[i][0] = a.x; v[i][1] = a.y; v[i][2] = a.z; v[i][3] = a.w;
             v[i][4] = b.x; v[i][5] = b.y; v[i][6] = b.z; v[i][7] = b.w;
-            // the partial sums are requested eight at a time (one after the other, each waited for the one
-            // before: 5.5 us per launch at 256 rows, 8 partials)
-            for (int p0 = 0; p0 < nparts; p0 += 8) {
-                float4 c[8], e[8];
+            for (int p0 = 0; p0 < nparts; p0 += NP) {
+                float4 c[NP], e[NP];
 #pragma unroll
-                for (int p = 0; p < 8; ++p) {
+                for (int p = 0; p < NP; ++p) {
                     const float *pp = part + ((size_t)min(p0 + p, nparts - 1) * ld_rows + row) * d + k0;
                     c[p] = *reinterpret_cast<const float4 *>(pp);
                     e[p] = *reinterpret_cast<const float4 *>(pp + 4);
                 }
 #pragma unroll
-                for (int p = 0; p < 8; ++p) {
+                for (int p = 0; p < NP; ++p) {
                     if (p0 + p < nparts) {
                         v[i][0] += c[p].x; v[i][1] += c[p].y; v[i][2] += c[p].z; v[i][3] += c[p].w;
                         v[i][4] += e[p].x; v[i][5] += e[p].y; v[i][6] += e[p].z; v[i][7] += e[p].w;
@@ -335,15 +336,24 @@ int vf_launch_norm(const vf_model *m, const float *gain, void *x_out, const floa
                    int ld_rows, hipStream_t st) {
     const int ncb = (rows + 15) >> 4;
     const int d = m->cfg.d_model;
-    if (d <= 2048)
-        hipLaunchKernelGGL(norm_bf16_vec_kernel<1>, dim3(rows), dim3(256), 0, st, m->h, part, nparts, ld_rows, gain,
-                           (u32x4_t *)x_out, d, ncb, m->cfg.rms_eps);
-    else if (d <= 4096)
-        hipLaunchKernelGGL(norm_bf16_vec_kernel<2>, dim3(rows), dim3(256), 0, st, m->h, part, nparts, ld_rows, gain,
-                           (u32x4_t *)x_out, d, ncb, m->cfg.rms_eps);
-    else
+    auto vec = [&](auto kern) {
+        hipLaunchKernelGGL(kern, dim3(rows), dim3(256), 0, st, m->h, part, nparts, ld_rows, gain, (u32x4_t *)x_out, d, ncb,
+                           m->cfg.rms_eps);
+    };
+    if (d <= 2048) {
+        if (nparts <= 1) vec(norm_bf16_vec_kernel<1, 1>);
+        else if (nparts <= 2) vec(norm_bf16_vec_kernel<1, 2>);
+        else if (nparts <= 4) vec(norm_bf16_vec_kernel<1, 4>);
+        else vec(norm_bf16_vec_kernel<1, 8>);
+    } else if (d <= 4096) {
+        if (nparts <= 1) vec(norm_bf16_vec_kernel<2, 1>);
+        else if (nparts <= 2) vec(norm_bf16_vec_kernel<2, 2>);
+        else if (nparts <= 4) vec(norm_bf16_vec_kernel<2, 4>);
+        else vec(norm_bf16_vec_kernel<2, 8>);
+    } else {
         hipLaunchKernelGGL(norm_kernel, dim3(rows), dim3(256), 0, st, m->h, part, nparts, ld_rows, gain, (bf16_t *)x_out, d, ncb,
                            m->cfg.rms_eps);
+    }
     VF_LAUNCH_CHECK("norm");
     return VF_OK;
 }
