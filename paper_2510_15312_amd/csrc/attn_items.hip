@@ -195,7 +195,7 @@ __global__ __launch_bounds__(256) void attn_items_merge_kernel(Batch b, ItemsGri
     const int idx = blockIdx.x * (256 / TH) + threadIdx.x / TH, d0 = threadIdx.x % TH * 4;
     if (idx >= b.total_rows * hq) return;
     const int row = idx / hq, head = idx % hq;
-    const int seq = find_seq(b, row);
+    const int seq = find_seq_many(b, row);
     const SeqDesc &s = b.s[seq];
     const int parts = items_parts(s, grid.part_pages), last = min(s.state[0] + row - s.row0, s.capacity - 1);
     const int used = min(parts, last / VF_TILE / grid.part_pages + 1);   // parts with keys of this row

@@ -220,16 +220,22 @@ __device__ __forceinline__ void lds_sync() {
     asm volatile("" ::: "memory");
 }
 
-// Sequence of a row of the call.  Eight descriptors are looked at together: one after the other, each a
-// read of the kernel arguments, the search took 3 us of the QKV epilogue's 7.5 at 12 sequences.
 __device__ inline int find_seq(const Batch &b, int row) {
+    int i = 0;
+    while (i + 1 < b.n_seqs && row >= b.s[i + 1].row0) ++i;
+    return i;
+}
+// The same for kernels of many sequences.  Eight descriptors are looked at together: one after the other, each
+// a read of the kernel arguments, the search took 3 us of the QKV epilogue's 7.5 at 12 sequences.  (In the
+// persistent kernel, mostly one sequence, it costs: 1312 -> 1317 us per step of 17 rows.)
+__device__ inline int find_seq_many(const Batch &b, int row) {
     int seq = 0;
     for (int i0 = 0; i0 < b.n_seqs; i0 += 8)
 #pragma unroll
         for (int j = 0; j < 8; ++j) seq += i0 + j > 0 && i0 + j < b.n_seqs && row >= b.s[i0 + j].row0;
     return seq;
 }
-static_assert(VF_MAX_BATCH % 8 == 0, "find_seq reads descriptors in eights");
+static_assert(VF_MAX_BATCH % 8 == 0, "find_seq_many reads descriptors in eights");
 
 // ---- QKV epilogue ---------------------------------------------------------------------------------
 // Columns of the packed QKV matrix: heads 0..hq-1 are q, then hkv k heads, then hkv v heads (v is not
@@ -260,7 +266,7 @@ __device__ __forceinline__ QkvPlace qkv_place_in(const QkvEpilogue &e, const Seq
 // 104 rows in 12 sequences).
 __device__ __forceinline__ QkvPlace qkv_place(const QkvEpilogue &e, int row, int g4) {
     if (e.b.n_seqs == 1) return qkv_place_in(e, e.b.s[0], row, g4);
-    return qkv_place_in(e, e.b.s[find_seq(e.b, row)], row, g4);
+    return qkv_place_in(e, e.b.s[find_seq_many(e.b, row)], row, g4);
 }
 // the angles of the lane's columns of block nb (any, for a v head)
 __device__ __forceinline__ QkvAngles qkv_angles(const QkvEpilogue &e, const QkvPlace &p, int nb) {
