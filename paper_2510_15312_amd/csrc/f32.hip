@@ -14,7 +14,7 @@
 // workgroup's eight wavefronts split K so that most of a tile's operands are requested at once, and
 // operands go from memory straight to registers.  Measured on a 512-token prompt in chunks of 128 plus
 // a verify of 5 rows: 8607 us with one wavefront per output column on the vector units and scalar
-// attention (180 and 80 us per launch), 382 us like this.
+// attention (180 and 80 us per launch), 400 us like this.
 #include "vf_internal.h"
 
 namespace {
@@ -182,14 +182,18 @@ __global__ __launch_bounds__(256) void embed_f32_kernel(const float *__restrict_
     }
 }
 
+// What exponents are taken against where the largest score is m: m, or 0 where no key has been seen yet.
+__device__ __forceinline__ float f32_reference(float m) { return m == -INFINITY ? 0.f : m; }
+
 // Attention: one workgroup per (16 query items, kv head, sequence, part of the keys); a query item is a
 // (row, head of the group) pair.  The wavefronts take the 32-key tiles in turn, operands straight from
 // the cache: its fragment order gives lane (g, i) eight consecutive features of key 8 (i >> 2) + (i & 3)
 // + 4 half, so the scores S^T[key, item] leave the matrix unit with keys 8 g .. 8 g + 7 in one lane,
-// which is how the P V product takes them.
+// which is how the P V product takes them.  An item takes nothing from a key it does not see, whatever that
+// key's value is (0 * infinity is not 0): tiles with such keys look at their values first.
 template <int HD>
 __global__ __launch_bounds__(NW * 64) VF_MFMA_KERNEL void attn_f32_kernel(
-    Batch b, int layer, const float *__restrict__ q, float *__restrict__ o, int hq, int hkv, float scale_log2e,
+    Batch b, int layer, const float *__restrict__ q, float *__restrict__ o, int hq, int hkv, float scale,
     int n_parts, float *__restrict__ part, const tree_mask_t *__restrict__ anc) {
     constexpr int KD = HD / 32, DB = HD / 16, REC = HD + 4;
     extern __shared__ __align__(16) unsigned char smem[];
@@ -207,15 +211,16 @@ __global__ __launch_bounds__(NW * 64) VF_MFMA_KERNEL void attn_f32_kernel(
     const int last_key = valid ? len + r : -1;
     const int blk_last = min(kmax - 1, len + min(s.nrows - 1, (item0 + 15) / group));
     const tree_mask_t mask = anc && valid ? anc[row] : ~(tree_mask_t)0;
+    auto visible = [&](int key) { return key <= last_key && (!anc || key < len || ((mask >> ((unsigned)(key - len) & 63u)) & 1)); };
     floatx4 qf[KD][2], oacc[DB];
 #pragma unroll
     for (int kd = 0; kd < KD; ++kd)
 #pragma unroll
         for (int i = 0; i < 2; ++i)
-            qf[kd][i] = *reinterpret_cast<const floatx4 *>(q + ((size_t)row * hq + head) * HD + kd * 32 + g4 * 8 + i * 4);
+            qf[kd][i] = *reinterpret_cast<const floatx4 *>(q + ((size_t)row * hq + head) * HD + kd * 32 + g4 * 8 + i * 4) * scale;
 #pragma unroll
     for (int db = 0; db < DB; ++db) oacc[db] = floatx4{0.f, 0.f, 0.f, 0.f};
-    float m_run = -1e30f, l_run = 0.f;
+    float m_run = -INFINITY, l_run = 0.f;
     const int tiles = blk_last / 32 + 1, tpp = (tiles + n_parts - 1) / n_parts;
     const int t_begin = kpart * tpp, t_end = min(tiles, t_begin + tpp);
     const float *kv = reinterpret_cast<const float *>(s.kv);
@@ -243,37 +248,62 @@ __global__ __launch_bounds__(NW * 64) VF_MFMA_KERNEL void attn_f32_kernel(
                 for (int h = 0; h < 2; ++h)
                     sc[h] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[h][kd][j >> 2][j & 3], qf[kd][j >> 2][j & 3], sc[h], 0, 0, 0);
         // lane holds keys t0 + 8 g4 + j of item l15
-        float pr[8], tmax = -1e30f;
+        float pr[8], tmax = -INFINITY;
         bool vis[8];
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
-            const int key = t0 + g4 * 8 + j;
-            vis[j] = key <= last_key && (!anc || key < len || ((mask >> ((unsigned)(key - len) & 63u)) & 1));
-            pr[j] = vis[j] ? sc[j >> 2][j & 3] * scale_log2e : -1e30f;
+            vis[j] = visible(t0 + g4 * 8 + j);
+            pr[j] = vis[j] ? sc[j >> 2][j & 3] : -INFINITY;
             tmax = fmaxf(tmax, pr[j]);
         }
         tmax = fmaxf(tmax, __shfl_xor(tmax, 16, 64));
         tmax = fmaxf(tmax, __shfl_xor(tmax, 32, 64));
-        const float m_new = fmaxf(m_run, tmax), corr = exp2f(m_run - m_new);
+        const float m_old = m_run;
+        m_run = fmaxf(m_run, tmax);
+        const float m_new = f32_reference(m_run), corr = expf(m_old - m_new);
         float psum = 0.f;
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
-            pr[j] = vis[j] ? exp2f(pr[j] - m_new) : 0.f;
+            pr[j] = vis[j] ? expf(pr[j] - m_new) : 0.f;
             psum += pr[j];
         }
         psum += __shfl_xor(psum, 16, 64);
         psum += __shfl_xor(psum, 32, 64);
         l_run = l_run * corr + psum;
-        m_run = m_new;
 #pragma unroll
-        for (int db = 0; db < DB; ++db) {
-            oacc[db] *= corr;
+        for (int db = 0; db < DB; ++db) oacc[db] *= corr;
+        float odd = 0.f;   // 0, or NaN where a value that some item may not see is not finite
+        if (t0 + 31 > len) {
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                // rows of the cache at or past kmax may hold anything: kept out of the product
-                const float vv = t0 + g4 * 8 + j < kmax ? vf[db][j >> 2][j & 3] : 0.f;
-                oacc[db] = __builtin_amdgcn_mfma_f32_16x16x4f32(vv, pr[j], oacc[db], 0, 0, 0);
-            }
+            for (int db = 0; db < DB; ++db)
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    // rows of the cache at or past kmax may hold anything
+                    if (t0 + g4 * 8 + j >= kmax) vf[db][j >> 2][j & 3] = 0.f;
+                    odd = fmaf(vf[db][j >> 2][j & 3], 0.f, odd);
+                }
+        }
+        if (__builtin_amdgcn_ballot_w64(odd != 0.f)) {   // key by key, what the item sees
+#pragma unroll
+            for (int db = 0; db < DB; ++db)
+#pragma unroll
+                for (int j = 0; j < 8; ++j)
+#pragma unroll 1
+                    for (int g = 0; g < 4; ++g) {
+                        const float p = __shfl(pr[j], g * 16 + l15, 64);
+                        const bool seen = visible(t0 + g * 8 + j);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            const float v = __shfl(vf[db][j >> 2][j & 3], g * 16 + g4 * 4 + e, 64);
+                            if (seen) oacc[db][e] = fmaf(p, v, oacc[db][e]);
+                        }
+                    }
+        } else {
+#pragma unroll
+            for (int db = 0; db < DB; ++db)
+#pragma unroll
+                for (int j = 0; j < 8; ++j)
+                    oacc[db] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[db][j >> 2][j & 3], pr[j], oacc[db], 0, 0, 0);
         }
     }
 #pragma unroll
@@ -285,13 +315,13 @@ __global__ __launch_bounds__(NW * 64) VF_MFMA_KERNEL void attn_f32_kernel(
     __syncthreads();
     if (wave >= DB) return;
     // wavefront = 16-wide block of the head dimension
-    float M = -1e30f, L = 0.f;
+    float M = -INFINITY, L = 0.f;
     floatx4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int w = 0; w < NW; ++w) M = fmaxf(M, ml_s[(w * 2) * 16 + l15]);
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
-        const float wt = exp2f(ml_s[(w * 2) * 16 + l15] - M);
+        const float wt = expf(ml_s[(w * 2) * 16 + l15] - f32_reference(M));
         L += ml_s[(w * 2 + 1) * 16 + l15] * wt;
         acc += o_s[(w * DB + wave) * 64 + lane] * wt;
     }
@@ -311,10 +341,10 @@ __global__ __launch_bounds__(HD) void attn_f32_combine_kernel(const float *__res
     constexpr int REC = HD + 4;
     const int d = threadIdx.x;
     const float *p = part + (size_t)blockIdx.x * n_parts * REC;
-    float M = -1e30f, L = 0.f, acc = 0.f;
+    float M = -INFINITY, L = 0.f, acc = 0.f;
     for (int i = 0; i < n_parts; ++i) M = fmaxf(M, p[i * REC]);
     for (int i = 0; i < n_parts; ++i) {
-        const float w = exp2f(p[i * REC] - M);
+        const float w = expf(p[i * REC] - f32_reference(M));
         L += p[i * REC + 1] * w;
         acc += p[i * REC + 4 + d] * w;
     }
@@ -352,7 +382,7 @@ int launch_attn(const vf_model *m, const Batch &b, int layer, const tree_mask_t 
     const int lds = NW * (HD / 16) * 1024 + NW * 2 * 16 * 4;
     hipLaunchKernelGGL(attn_f32_kernel<HD>, dim3((max_items + 15) / 16, c.n_kv_heads, b.n_seqs * n_parts), dim3(NW * 64), lds, st,
                        b, layer, (const float *)m->q, (float *)m->o, c.n_q_heads, c.n_kv_heads,
-                       1.4426950408889634f / sqrtf((float)HD), n_parts, m->attn_part, anc);
+                       1.0f / sqrtf((float)HD), n_parts, m->attn_part, anc);
     VF_LAUNCH_CHECK("attn_f32");
     if (n_parts > 1) {
         hipLaunchKernelGGL(attn_f32_combine_kernel<HD>, dim3(b.total_rows * c.n_q_heads), dim3(HD), 0, st, m->attn_part,
