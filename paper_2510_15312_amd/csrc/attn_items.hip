@@ -141,6 +141,7 @@ __global__ __launch_bounds__(ITEMS_WAVES * 64) VF_MFMA_KERNEL void attn_items_ke
         }
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
+            if (MASKED && t0 + t * 32 > wave_last) continue;   // no item sees a key of this half: nor does 0 times its values
             if constexpr (MASKED)   // rows of the cache at or past kmax may hold anything
 #pragma unroll
                 for (int j = 0; j < 8; ++j)

@@ -93,3 +93,32 @@ def test_paged_batch(hd, n_seqs, lo, hi):
     err = _both(pair, run)
     print(f"hd {hd}, {n_seqs} sequences: {err:.2e}", flush=True)
     assert err < 1e-2
+
+
+# A value that is not finite may reach the rows of its own 32 keys and of the items (16 to a wavefront, 3 to a
+# row here) that share them, as in the kernel for few items, and no row further up.
+@pytest.mark.parametrize("at", [44, 70, 703])   # second half of the chunk's first page, first half, a later page
+def test_value_that_is_not_finite(at):
+    pair = _pair(128)
+    rows, ctx, V, d = 777, 1920, pair.cfg.vocab, pair.cfg.d_model
+    seq = pair.new_seq(9000)
+    ids = wl.make_context(V, rows, np.random.default_rng(at))
+    ids[at] = np.setdiff1d(np.arange(V), ids)[0]   # a token of its own
+    _fill(pair, seq, ctx, torch.Generator(device=DEV).manual_seed(at))
+    logits = torch.empty((rows, V), dtype=torch.float32, device=DEV)
+
+    def run(value):
+        w = {**pair.dw, "lm_head": pair.dw["embed"], "embed": pair.dw["embed"].clone()}
+        w["embed"][int(ids[at])] = value
+        cfg = vf.make_config(1, d, pair.cfg.n_q_heads, pair.cfg.n_kv_heads, 128, pair.cfg.d_ffn, V, "bf16", pair.cfg.rope_theta,
+                             pair.cfg.rms_eps, rows, 9000, tie_embeddings=False)
+        model = vf.vf_model_create(cfg, w, DEV)
+        own = vf.vf_seq_create(model, 9000)
+        own.kv.copy_(seq.kv)
+        vf.vf_seq_set_len(own, ctx)
+        vf.vf_prefill_chunk(model, own, i32(ids), logits_mode=2, logits_out=logits)
+        return logits.cpu().numpy()
+    want, got = run(0.02), run(float("inf"))
+    clear = [r for r in range(at) if r + 6 < at - at % 32]
+    assert len(clear) > 20 and np.isnan(got[at:]).any(axis=1).all()
+    assert np.array_equal(got[clear], want[clear])
