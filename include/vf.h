@@ -243,10 +243,11 @@ int vf_accept_static(vf_model *m, vf_seq *const *seqs, int n_seqs, const int32_t
  *   topk_logit_dev[n_tokens, top_k] float32, topk_id_dev[n_tokens, top_k] int32,
  * in falling order of the logit, equal logits by rising id (entry 0 is the arg-max of the row).
  * 1 <= top_k <= VF_TOPK_MAX.  sample_first / u_dev / temperature as in vf_prefill_chunk.  On a
- * bfloat16 model with more than 64 rows the candidates come out of the output-head GEMM's
- * epilogue and the logits are never written; otherwise they are computed into the model
- * workspace first.  Both give the top_k of the same float32 logits vf_prefill_chunk with
- * logits_mode 2 would return. */
+ * bfloat16 model with more than 64 rows, and about 30 to 40 rows or more per candidate, the
+ * candidates come out of the output-head GEMM's epilogue and the logits are never written;
+ * otherwise the logits are computed into the model workspace first.  Both give the top_k of the same float32 logits
+ * vf_prefill_chunk with logits_mode 2 would return (out of the epilogue, an id of -1 stands for a
+ * logit of -infinity). */
 int vf_prefill_chunk_topk(vf_model *m, vf_seq *s, const int32_t *tokens_dev, int n_tokens, int top_k,
                           float *topk_logit_dev, int32_t *topk_id_dev, int sample_first,
                           const float *u_dev, float temperature, void *stream);

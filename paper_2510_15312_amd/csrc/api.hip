@@ -178,6 +178,15 @@ int run_layers(vf_model *m, const Batch &b, const int32_t *tokens, int *tail_par
     return VF_OK;
 }
 
+// Top successors out of the output head's epilogue, or from the logits?  The epilogue's rounds run once per candidate
+// while the matrix units wait, whatever the rows of a tile; the way over the logits costs a write and top_k reads of
+// them.  Measured, epilogue / logits (us, one layer and the head): top 8 at 0.5B, 128 rows 417 / 275, 256 645 / 466, 384
+// 667 / 719; at 1.5B 256 721 / 559, 384 773 / 828; top 5 at 0.5B 192 329 / 297, 256 338 / 369; top 3 96 171 / 170, 128
+// 176 / 192; top 1 at 1.5B 65 191 / 193, 256 243 / 313.  At 3B, where a tile's products take twice as long, top 8 192
+// 518 / 530, 256 537 / 619, top 5 128 397 / 379, 192 417 / 459.  Up to 64 rows always from the logits: top 8 of 16 rows
+// 395 / 199 at 1.5B, top 1 172 / 184 of 33.
+bool topk_in_gemm(const vf_config &c, int rows, int top_k) { return rows > 64 && rows >= (c.d_model >= 2048 ? 28 : 40) * top_k; }
+
 // Final norm + output head for rows [row_lo, row_hi) -> out[(row - row_lo), vocab].
 int run_head(vf_model *m, int rows, int tail_parts, int row_lo, int row_hi, float *out, hipStream_t st) {
     const vf_config &c = m->cfg;
@@ -462,7 +471,7 @@ int vf_prefill_chunk_topk(vf_model *m, vf_seq *s, const int32_t *tokens_dev, int
     const float *last_row;
     GemmPlan p;
     p.epi = GEMM_PARTIAL;
-    if (c.dtype == VF_BF16) p = vf_gemm_plan(m, c.vocab, c.d_model, n_tokens, GEMM_TOPK);
+    if (c.dtype == VF_BF16 && topk_in_gemm(c, n_tokens, top_k)) p = vf_gemm_plan(m, c.vocab, c.d_model, n_tokens, GEMM_TOPK);
     if (p.epi == GEMM_TOPK) {
         { ProfScope ps(m, VF_SITE_SMALL, st);
           if ((rc = vf_launch_norm(m, m->final_norm, m->x, m->part, tail, n_tokens, n_tokens, st))) return rc; }

@@ -1,6 +1,6 @@
 """Top successors of every prefill position through the C ABI: bit-exact against the top-k (oracle
-rule) of the library's own all-row logits, on both routes (candidates from the GEMM epilogue for
-many rows, from the logits for few rows and float32 models), and against the oracle's logits
+rule) of the library's own all-row logits, on both routes (candidates from the GEMM epilogue from 65
+rows and 28 to 40 rows a candidate on, from the logits for fewer rows and float32 models), and against the oracle's logits
 wherever the gap to the next value exceeds the logit error."""
 import numpy as np
 import pytest
@@ -18,7 +18,8 @@ CASES = {
     # name: (config, rows of the chunk, context before it, k)
     "tiny_f32_rows100": (C["tiny_f32"], 100, 37, 8),
     "tiny_f32_rows5": (C["tiny_f32"], 5, 0, 3),
-    "1.5b_shape_rows256_epilogue": (wl.scaled(C["1.5b_k16"], n_layers=1, vocab=20000), 256, 64, 8),
+    "1.5b_shape_rows330_epilogue": (wl.scaled(C["1.5b_k16"], n_layers=1, vocab=20000), 330, 64, 8),
+    "1.5b_shape_rows256_from_logits": (wl.scaled(C["1.5b_k16"], n_layers=1, vocab=20000), 256, 64, 8),
     "1.5b_shape_rows200_epilogue": (wl.scaled(C["1.5b_k16"], n_layers=1, vocab=20000), 200, 0, 5),
     "0.5b_shape_rows130_narrow_tile": (wl.scaled(C["0.5b_k8"], n_layers=1, vocab=4096), 130, 10, 1),
     "1.5b_shape_rows40_from_logits": (wl.scaled(C["1.5b_k16"], n_layers=1, vocab=20000), 40, 30, 8),
@@ -29,7 +30,7 @@ CASES = {
 def test_prefill_topk(name):
     cfg, rows, before, k = CASES[name]
     print(f"case {name}: rows {rows}, context {before}, k {k}", flush=True)
-    pair = Pair(cfg, max_rows=256, max_positions=before + rows + 8)
+    pair = Pair(cfg, max_rows=max(256, rows), max_positions=before + rows + 8)
     rng = np.random.default_rng(3)
     ctx = wl.make_context(cfg.vocab, before + rows, rng)
     toks = i32(ctx)
@@ -90,3 +91,31 @@ def test_topk_argument_errors():
     with pytest.raises(vf.VfError):
         vf.vf_prefill_chunk_topk(pair.model, seq, toks, 4, None, ti)
     assert vf.vf_seq_get_state(seq)[0] == 0
+
+
+# Fewer finite logits than candidates: the rest are ids with a logit of -infinity, by rising id, as the definition
+# has it (equal logits by rising id).  Few rows, where the candidates come from the logits.
+@pytest.mark.parametrize("rows", [40, 64])
+def test_topk_of_infinite_logits(rows):
+    k, V = 8, 4096
+    cfg = wl.scaled(C["1.5b_k16"], n_layers=1, d_model=256, n_q_heads=2, n_kv_heads=1, d_ffn=512, vocab=V)
+    wd = wl.make_weights(cfg, wl.streams(cfg).weights)
+    wd["embed"][:, 0] = 1.0     # the residual's first element, and with it that of every normalised row, is above zero
+    wd["layers"][0]["wo"][0] = wd["layers"][0]["w_down"][0] = 0.0
+    finite = [5, 700, 701, 4000]
+    wd["lm_head"] = wd["embed"].copy()
+    wd["lm_head"][np.setdiff1d(np.arange(V), finite), 0] = -np.inf
+    mc = vf.make_config(1, 256, 2, 1, cfg.head_dim, 512, V, "bf16", cfg.rope_theta, cfg.rms_eps, rows, 128, tie_embeddings=False)
+    model = vf.vf_model_create(mc, vf.upload_weights(wd, "bf16", DEV), DEV)
+    ids = i32(wl.make_context(V, rows, np.random.default_rng(rows)))
+    seq = vf.vf_seq_create(model, 128)
+    z = torch.empty((rows, V), dtype=torch.float32, device=DEV)
+    vf.vf_prefill_chunk(model, seq, ids, logits_mode=2, logits_out=z)
+    tv = torch.empty((rows, k), dtype=torch.float32, device=DEV)
+    ti = torch.empty((rows, k), dtype=torch.int32, device=DEV)
+    vf.vf_seq_set_len(seq, 0)
+    vf.vf_prefill_chunk_topk(model, seq, ids, k, tv, ti)
+    z = z.cpu().numpy()
+    assert np.isfinite(z).sum() == rows * len(finite) and not np.isnan(z).any()
+    want_v, want_i = topk_rows(z, k)
+    assert np.array_equal(ti.cpu().numpy(), want_i) and np.array_equal(tv.cpu().numpy(), want_v)
