@@ -143,67 +143,57 @@ int launch_bf16(const vf_model *m, const void *W, const void *X, float *part, in
 // is 1.2 % slower on average than the best of all timed, 16 % at worst.  What decides is visible in them: a
 // shape of few weight blocks per tile (stream) wins while its column tiles fill the chip once, the square tiles
 // once there are several rounds of them anyway (their step covers more products).
-enum RowsKernel { RK_T16x16, RK_T16x8, RK_T8x8, RK_S4x2, RK_S4x4, RK_S4x5, RK_S8x2, RK_S8x4, RK_S8x5, RK_S16x4, RK_S16x5, RK_S24x5, RK_COUNT };
+enum RowsKernel { RK_T16x16, RK_T16x8, RK_T8x8, RK_S4x2, RK_S4x4, RK_S4x5, RK_S8x4, RK_S8x5, RK_S16x5, RK_S24x5, RK_COUNT };
 struct RowsShape {
     int mb, nb;                        // 16-row blocks x weight blocks of a tile
     float start, step, written, hbm;
-    bool swiglu, topk, partial;        // epilogues it is built with
+    bool partial, qkv, swiglu, topk;   // epilogues it is built with: those that rows of the three full-size shapes take
     int lists;                         // top-k candidate lists per tile and row
 };
 constexpr RowsShape ROWS_SHAPES[RK_COUNT] = {
-    {16, 16, 4.93f, 0.5881f, 0.192f, 0.0463f, true, true, true, 2},     // RK_T16x16: square tile, 8 wavefronts of 64 x 128
-    {16, 8, 3.70f, 0.3476f, 0.220f, 0.0478f, true, true, true, 2},      // RK_T16x8 : square tile, 8 wavefronts of 64 x 64
-    {8, 8, 3.06f, 0.2053f, 0.210f, 0.0841f, true, true, true, 2},       // RK_T8x8  : square tile, 4 wavefronts of 64 x 64
-    {4, 2, 2.00f, 0.0566f, 0.311f, 0.1253f, false, false, true, 0},     // RK_S4x2  : stream, 4 wavefronts of 16 rows
-    {4, 4, 2.20f, 0.0826f, 0.239f, 0.1143f, true, false, true, 0},      // RK_S4x4
-    {4, 5, 2.88f, 0.1332f, 0.368f, 0.0598f, true, true, true, 1},       // RK_S4x5
-    {8, 2, 2.06f, 0.0875f, 0.275f, 0.1119f, false, false, true, 0},     // RK_S8x2  : stream, 8 wavefronts of 16 rows
-    {8, 4, 2.42f, 0.1244f, 0.264f, 0.0947f, true, false, true, 0},      // RK_S8x4
-    {8, 5, 2.79f, 0.1839f, 0.331f, 0.0406f, true, true, true, 1},       // RK_S8x5
-    {16, 4, 2.70f, 0.2240f, 0.262f, 0.0755f, true, false, true, 0},     // RK_S16x4 : stream, 8 wavefronts of 32 rows
-    {16, 5, 2.77f, 0.3189f, 0.281f, 0.0091f, true, false, false, 0},    // RK_S16x5
-    {24, 5, 1.17f, 0.3889f, 0.803f, 0.0203f, true, false, false, 0},    // RK_S24x5 : stream, 8 wavefronts of 48 rows
+    {16, 16, 4.93f, 0.5881f, 0.192f, 0.0463f, true, true, true, true, 2},     // RK_T16x16: square tile, 8 wavefronts of 64 x 128
+    {16, 8, 3.70f, 0.3476f, 0.220f, 0.0478f, true, true, true, true, 2},      // RK_T16x8 : square tile, 8 wavefronts of 64 x 64
+    {8, 8, 3.06f, 0.2053f, 0.210f, 0.0841f, true, true, true, true, 2},       // RK_T8x8  : square tile, 4 wavefronts of 64 x 64
+    {4, 2, 2.00f, 0.0566f, 0.311f, 0.1253f, true, true, false, false, 0},     // RK_S4x2  : stream, 4 wavefronts of 16 rows
+    {4, 4, 2.20f, 0.0826f, 0.239f, 0.1143f, true, true, true, false, 0},      // RK_S4x4
+    {4, 5, 2.88f, 0.1332f, 0.368f, 0.0598f, true, false, true, false, 0},     // RK_S4x5
+    {8, 4, 2.42f, 0.1244f, 0.264f, 0.0947f, true, true, true, false, 0},      // RK_S8x4  : stream, 8 wavefronts of 16 rows
+    {8, 5, 2.79f, 0.1839f, 0.331f, 0.0406f, true, true, true, true, 1},       // RK_S8x5
+    {16, 5, 2.77f, 0.3189f, 0.281f, 0.0091f, false, false, true, false, 0},   // RK_S16x5 : stream, 8 wavefronts of 32 rows
+    {24, 5, 1.17f, 0.3889f, 0.803f, 0.0203f, false, false, true, false, 0},   // RK_S24x5 : stream, 8 wavefronts of 48 rows
 };
+// ROWS_EPI_*
+constexpr bool rows_built(const RowsShape &s, int epi) {
+    return epi == ROWS_EPI_PARTIAL ? s.partial : epi == ROWS_EPI_QKV ? s.qkv : epi == ROWS_EPI_SWIGLU ? s.swiglu : s.topk;
+}
 
 template <typename Kern> struct Launch { Kern kern; int threads, lds; };
 template <typename Kern> Launch(Kern, int, int) -> Launch<Kern>;
 
 // calls fn(Launch) for the kernel of shape `k` with epilogue EPI (only combinations that are built)
 template <int EPI, typename F> int with_rows_kernel(int k, F fn) {
-#define VF_TILE_KERNEL(MB, NB, WM, WN) \
-    return fn(Launch{gemm_tile_kernel<MB, NB, WM, WN, 4, EPI>, WM * WN * 64, 4 * (MB + NB) * 1024})
-#define VF_STREAM_KERNEL(CW, WMB, NB, D, KS, SW) \
-    return fn(Launch{gemm_stream_kernel<CW, WMB, NB, D, KS, SW, EPI>, (CW + 1) * 64, SW * KS * NB * 1024})
+#define VF_ROWS_CASE(RK, KERN, THREADS, LDS) \
+    case RK:                                 \
+        if constexpr (rows_built(ROWS_SHAPES[RK], EPI)) return fn(Launch{KERN, THREADS, LDS}); \
+        break;
+#define VF_TILE_KERNEL(RK, MB, NB, WM, WN) \
+    VF_ROWS_CASE(RK, (gemm_tile_kernel<MB, NB, WM, WN, 4, EPI>), WM * WN * 64, 4 * (MB + NB) * 1024)
+#define VF_STREAM_KERNEL(RK, CW, WMB, NB, D, KS, SW) \
+    VF_ROWS_CASE(RK, (gemm_stream_kernel<CW, WMB, NB, D, KS, SW, EPI>), (CW + 1) * 64, SW * KS * NB * 1024)
     switch (k) {
-        case RK_T16x16: VF_TILE_KERNEL(16, 16, 4, 2);
-        case RK_T16x8: VF_TILE_KERNEL(16, 8, 4, 2);
-        case RK_T8x8: VF_TILE_KERNEL(8, 8, 2, 2);
-        case RK_S4x5: VF_STREAM_KERNEL(4, 1, 5, 8, 4, 5);
-        case RK_S8x5: VF_STREAM_KERNEL(8, 1, 5, 8, 4, 5);
+        VF_TILE_KERNEL(RK_T16x16, 16, 16, 4, 2)
+        VF_TILE_KERNEL(RK_T16x8, 16, 8, 4, 2)
+        VF_TILE_KERNEL(RK_T8x8, 8, 8, 2, 2)
+        VF_STREAM_KERNEL(RK_S4x2, 4, 1, 2, 8, 4, 9)
+        VF_STREAM_KERNEL(RK_S4x4, 4, 1, 4, 8, 4, 5)
+        VF_STREAM_KERNEL(RK_S4x5, 4, 1, 5, 8, 4, 5)
+        VF_STREAM_KERNEL(RK_S8x4, 8, 1, 4, 8, 4, 5)
+        VF_STREAM_KERNEL(RK_S8x5, 8, 1, 5, 8, 4, 5)
+        VF_STREAM_KERNEL(RK_S16x5, 8, 2, 5, 8, 4, 5)
+        VF_STREAM_KERNEL(RK_S24x5, 8, 3, 5, 4, 4, 5)
         default: break;
     }
-    if constexpr (EPI != ROWS_EPI_TOPK) {
-        switch (k) {
-            case RK_S4x4: VF_STREAM_KERNEL(4, 1, 4, 8, 4, 5);
-            case RK_S8x4: VF_STREAM_KERNEL(8, 1, 4, 8, 4, 5);
-            case RK_S16x4: VF_STREAM_KERNEL(8, 2, 4, 8, 4, 5);
-            default: break;
-        }
-    }
-    if constexpr (EPI == ROWS_EPI_SWIGLU) {
-        switch (k) {
-            case RK_S16x5: VF_STREAM_KERNEL(8, 2, 5, 8, 4, 5);
-            case RK_S24x5: VF_STREAM_KERNEL(8, 3, 5, 4, 4, 5);
-            default: break;
-        }
-    }
-    if constexpr (EPI == ROWS_EPI_PARTIAL || EPI == ROWS_EPI_QKV) {
-        switch (k) {
-            case RK_S4x2: VF_STREAM_KERNEL(4, 1, 2, 8, 4, 9);
-            case RK_S8x2: VF_STREAM_KERNEL(8, 1, 2, 8, 4, 9);
-            default: break;
-        }
-    }
+#undef VF_ROWS_CASE
 #undef VF_TILE_KERNEL
 #undef VF_STREAM_KERNEL
     return vf_fail(VF_ERR_ARG, "many-row GEMM: shape %d is not built with this epilogue", k);
@@ -211,8 +201,7 @@ template <int EPI, typename F> int with_rows_kernel(int k, F fn) {
 
 template <int EPI> int allow_lds() {
     for (int k = 0; k < RK_COUNT; ++k) {
-        const RowsShape &s = ROWS_SHAPES[k];
-        if (!(EPI == ROWS_EPI_SWIGLU ? s.swiglu : EPI == ROWS_EPI_TOPK ? s.topk : s.partial)) continue;
+        if (!rows_built(ROWS_SHAPES[k], EPI)) continue;
         const int rc = with_rows_kernel<EPI>(k, [&](auto l) -> int {
             VF_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(l.kern), hipFuncAttributeMaxDynamicSharedMemorySize, l.lds));
             return VF_OK;
@@ -254,12 +243,13 @@ GemmPlan vf_gemm_plan(const vf_model *m, int N, int K, int rows, GemmUse use) {
         float best = 1e30f;
         for (int k = 0; k < RK_COUNT; ++k) {
             const RowsShape &s = ROWS_SHAPES[k];
-            if (use == GEMM_SWIGLU ? !s.swiglu : use == GEMM_TOPK ? !s.topk : !s.partial) continue;
+            const int whole = use == GEMM_SWIGLU ? ROWS_EPI_SWIGLU : use == GEMM_TOPK ? ROWS_EPI_TOPK : use == GEMM_QKV ? ROWS_EPI_QKV : ROWS_EPI_PARTIAL;
             const float mb_w = (float)N * K * 2e-6f;
             const int tiles = (NBt + s.nb - 1) / s.nb * ((cbs + s.mb - 1) / s.mb);
             for (int ks : {1, 2, 3, 4, 6, 8, 10, 12, 16}) {
                 if (ks > 1 && ((use != GEMM_SPLIT && use != GEMM_QKV) || KB / ks < 4 || (size_t)ks * rows * N > m->part_floats)) break;
                 const int nk = (KB + ks - 1) / ks, splits = (KB + nk - 1) / nk, wgs = tiles * splits;
+                if (!rows_built(s, splits > 1 ? ROWS_EPI_PARTIAL : whole)) continue;
                 const float rounds = wgs <= 768 ? (float)((wgs + 255) / 256) : (float)wgs / 256.f + 0.2f;
                 const float mb_out = (use == GEMM_SWIGLU ? 1.f : use == GEMM_TOPK ? 0.5f : 4.f * splits) * rows * N * 1e-6f;
                 float t = s.start + s.step * nk * rounds + s.written * mb_out + s.hbm * mb_w;
