@@ -671,6 +671,57 @@ int vf_stream_read(vf_model *m, size_t *bytes_host, void *stream) {
     return vf_launch_stream_read(m, bytes_host, (hipStream_t)stream);
 }
 
+// Which kernels a many-row call takes: not part of the interface, exported so that the tests can state what they
+// run and check that nothing chosen goes untested.  Host only.
+//   use: a GemmUse-like number: 0 QKV, 1 O, 2 gate/up, 3 down, 4 output head, 5 output head with the top-k epilogue
+//   out: kernel of gemm_rows.h (index into the shapes of gemm.hip), K splits, epilogue (GemmUse)
+int vf_debug_gemm_plan(const vf_config *cfg, int use, int rows, int32_t *out) {
+    vf_model m;
+    memset(&m, 0, sizeof m);
+    const int rc = check_config(cfg);
+    if (rc) return rc;
+    if (cfg->dtype != VF_BF16 || rows < 1 || rows > cfg->max_rows || use < 0 || use > 5) return vf_fail(VF_ERR_ARG, "vf_debug_gemm_plan");
+    m.cfg = *cfg;
+    m.es = 2;
+    m.fast_path = 1;
+    carve_model(&m, nullptr);
+    const int d = cfg->d_model, nq = cfg->n_q_heads * cfg->head_dim, nkv = cfg->n_kv_heads * cfg->head_dim, F = cfg->d_ffn;
+    const int N[] = {nq + 2 * nkv, d, 2 * F, d, cfg->vocab, cfg->vocab}, K[] = {d, nq, d, F, d, d};
+    const GemmUse as[] = {GEMM_QKV, GEMM_SPLIT, GEMM_SWIGLU, GEMM_SPLIT, GEMM_PARTIAL, GEMM_TOPK};
+    const GemmPlan p = vf_gemm_plan(&m, N[use], K[use], rows, as[use]);
+    out[0] = p.shape;
+    out[1] = p.ks;
+    out[2] = p.epi;
+    return VF_OK;
+}
+
+// Sequences of the given lengths and rows, caches aligned.  out: pages of a part (0: the kernel for few items),
+// whether parts are merged.
+int vf_debug_attention_plan(const vf_config *cfg, int n_seqs, const int32_t *len, const int32_t *rows, int32_t *out) {
+    vf_model m;
+    memset(&m, 0, sizeof m);
+    const int rc = check_config(cfg);
+    if (rc) return rc;
+    if (cfg->dtype != VF_BF16 || n_seqs < 1 || n_seqs > VF_MAX_BATCH) return vf_fail(VF_ERR_ARG, "vf_debug_attention_plan");
+    m.cfg = *cfg;
+    m.es = 2;
+    m.fast_path = 1;
+    carve_model(&m, nullptr);
+    Batch b;
+    memset(&b, 0, sizeof b);
+    b.n_seqs = n_seqs;
+    for (int i = 0; i < n_seqs; ++i) {
+        b.s[i].row0 = b.total_rows;
+        b.s[i].nrows = rows[i];
+        b.s[i].len_ub = len[i];
+        b.s[i].capacity = cfg->max_positions;
+        b.total_rows += rows[i];
+    }
+    out[1] = 0;
+    out[0] = vf_attention_items_plan(&m, b, &out[1]);
+    return VF_OK;
+}
+
 int vf_profile(vf_model *m, int enable) {
     if (!m) return vf_fail(VF_ERR_ARG, "vf_profile: NULL");
     m->prof_on = enable != 0;

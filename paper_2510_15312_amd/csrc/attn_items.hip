@@ -258,8 +258,8 @@ int launch_items(const vf_model *m, const Batch &b, const ItemsGrid &grid, int l
 // against attn_rows with launch gaps: 16 sequences of 512 to 8192 keys at the 1.5B shape, 277 rows, 45 / 67;
 // 8 of about 2000 keys, 22 / 28; 1900 rows of 3B in two chunks, 39 / 59 a layer and chunk; 256 rows over up to
 // 2048 keys at 1.5B, 19 / 13.5; 12 sequences of about 800 keys at 0.5B, 17 / 14.
-// 1: launched, 0: left to attn_rows, < 0: an error
-int vf_launch_attention_items(const vf_model *m, const Batch &b, int layer, hipStream_t st) {
+// Workgroups of the launch; 0: left to attn_rows.
+static int plan_items(const vf_model *m, const Batch &b, ItemsGrid &best) {
     const vf_config &c = m->cfg;
     const int group = c.n_q_heads / c.n_kv_heads;
     const float w = c.head_dim / 128.f, kv_mb_key = c.n_kv_heads * c.head_dim * 4e-6f;
@@ -278,7 +278,7 @@ int vf_launch_attention_items(const vf_model *m, const Batch &b, int layer, hipS
     const float rows_cost = 6.3f + w * (0.86e-3f * block_tiles + 0.122f * max_keys / (ATT_TILE * rows_parts)) +
                             (rows_parts > 1 ? 2.2f : 0.f) + 0.60f * kv_mb;
     const size_t record_floats = (size_t)c.n_q_heads * (c.head_dim + ATTF_STRIDE_PAD), room = m->attn_part_floats / record_floats;
-    ItemsGrid grid, best;
+    ItemsGrid grid;
     int best_workgroups = 0;
     float best_cost = 0.9f * rows_cost;
     for (grid.part_pages = 4;; grid.part_pages *= 2) {
@@ -303,7 +303,21 @@ int vf_launch_attention_items(const vf_model *m, const Batch &b, int layer, hipS
         }
         if (!grid.merge) break;
     }
-    if (!best_workgroups) return 0;
-    const int rc = c.head_dim == 128 ? launch_items<128>(m, b, best, layer, best_workgroups, st) : launch_items<64>(m, b, best, layer, best_workgroups, st);
+    return best_workgroups;
+}
+
+int vf_attention_items_plan(const vf_model *m, const Batch &b, int *merge) {
+    ItemsGrid grid;
+    if (!plan_items(m, b, grid)) return 0;
+    *merge = grid.merge;
+    return grid.part_pages;
+}
+
+// 1: launched, 0: left to attn_rows, < 0: an error
+int vf_launch_attention_items(const vf_model *m, const Batch &b, int layer, hipStream_t st) {
+    ItemsGrid grid;
+    const int workgroups = plan_items(m, b, grid);
+    if (!workgroups) return 0;
+    const int rc = m->cfg.head_dim == 128 ? launch_items<128>(m, b, grid, layer, workgroups, st) : launch_items<64>(m, b, grid, layer, workgroups, st);
     return rc ? rc : 1;
 }

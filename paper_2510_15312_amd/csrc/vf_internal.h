@@ -366,6 +366,8 @@ int vf_attention_rows_parts(const vf_model *m, const Batch &b);
 int vf_launch_attention_rows(const vf_model *m, const Batch &b, int layer, hipStream_t st);
 // the same for many items over long contexts; 1: launched, 0: vf_launch_attention_rows is the faster one
 int vf_launch_attention_items(const vf_model *m, const Batch &b, int layer, hipStream_t st);
+// its choice: pages of a part (merge: whether a sequence has several), 0: vf_launch_attention_rows
+int vf_attention_items_plan(const vf_model *m, const Batch &b, int *merge);
 bool vf_fast_path_ok(const vf_model *m, int total_rows);
 int vf_run_fast(vf_model *m, const Batch &b, const int32_t *tokens, float *logits_out, hipStream_t st);
 // the float32 model's layers and output head

@@ -2,7 +2,8 @@
 layer: random keys and values are written to it, a chunk or a batch of paged sequences runs over them, and the
 logits are compared with the general kernels' (VF_OPT_FAST_PATH 0: scalar attention, plain GEMMs).  Sizes sit
 where the kernel's shapes turn: contexts at, below and above a page of 64 and a part of pages, items that do
-not fill a wavefront or a workgroup, one part and several, both head sizes, pages in random order.  The two
+not fill a wavefront or a workgroup, one part and several, both head sizes, pages in random order; each case
+asserts that the cost model gives it to this kernel (test_plans.py, that some have one part and some several).  The two
 paths round the same values to bfloat16, so they differ by the order of float32 sums and the roundings that
 tips over: under 1e-2 of the largest logit (the tolerance of either against the oracle is 2e-2); a key left
 out, or one too many, moves a row whose weight is spread over few keys by far more, and the softmax here is
@@ -14,18 +15,32 @@ import torch
 import workloads as wl
 import paper_2510_15312_amd as vf
 from util_gpu import DEV, Pair, i32
+from util_plan import attention_plan
 from util_oracle import rel_inf
 
 pytestmark = pytest.mark.gpu
 _cache = {}
 
 
+CHUNKS = [(1, 1056), (63, 1000), (64, 1055), (1900, 777), (4095, 512), (7900, 1051)]   # (context, rows)
+BATCHES = [(32, 30, 8200), (16, 1000, 3000), (9, 3968, 4224), (16, 400, 700)]          # (sequences, contexts from .. to)
+
+
+def config_of(hd):
+    # heads enough that the model gives short contexts to this kernel for either head size
+    heads = dict(n_q_heads=24, n_kv_heads=8) if hd == 128 else dict(n_q_heads=48, n_kv_heads=16)
+    return wl.scaled(wl.CONFIGS["1.5b_k16"], n_layers=1, d_model=512, head_dim=hd, d_ffn=1024, vocab=2048, **heads)
+
+
+def batch_of(n_seqs, lo, hi):
+    rng = np.random.default_rng(n_seqs + lo)
+    return rng.integers(lo, hi, n_seqs), rng.integers(6, 34, n_seqs), rng
+
+
 def _pair(hd):
     if hd not in _cache:
         _cache.clear()
-        dims = dict(d_model=512, head_dim=hd, d_ffn=1024, vocab=2048, n_q_heads=24, n_kv_heads=8)
-        cfg = wl.scaled(wl.CONFIGS["1.5b_k16"], n_layers=1, **dims)
-        _cache[hd] = Pair(cfg, max_rows=1056, max_positions=9000)
+        _cache[hd] = Pair(config_of(hd), max_rows=1056, max_positions=9000)
     return _cache[hd]
 
 
@@ -45,11 +60,12 @@ def _both(pair, run):
     return rel_inf(out[0], out[1]).max()
 
 
-# (context, rows): 1056 rows of one page and less, contexts around a page, several parts
+# 1056 rows of one page and less, contexts around a page, several parts
 @pytest.mark.parametrize("hd", [64, 128])
-@pytest.mark.parametrize("ctx,rows", [(1, 1056), (63, 1000), (64, 1055), (1900, 777), (4095, 512), (7900, 1051)])
+@pytest.mark.parametrize("ctx,rows", CHUNKS)
 def test_chunk(hd, ctx, rows):
     pair = _pair(hd)
+    assert attention_plan(pair.vcfg, [ctx], [rows])[0]
     gen = torch.Generator(device=DEV).manual_seed(ctx + rows)
     seq = pair.new_seq(9000)
     _fill(pair, seq, ctx, gen)
@@ -66,12 +82,11 @@ def test_chunk(hd, ctx, rows):
 
 
 @pytest.mark.parametrize("hd", [64, 128])
-@pytest.mark.parametrize("n_seqs,lo,hi", [(32, 30, 8200), (16, 1000, 3000), (9, 3968, 4224)])
+@pytest.mark.parametrize("n_seqs,lo,hi", BATCHES)
 def test_paged_batch(hd, n_seqs, lo, hi):
     pair = _pair(hd)
-    rng = np.random.default_rng(n_seqs + lo)
-    ctx = rng.integers(lo, hi, n_seqs)
-    rows = rng.integers(6, 34, n_seqs)
+    ctx, rows, rng = batch_of(n_seqs, lo, hi)
+    assert attention_plan(pair.vcfg, ctx, rows)[0]
     need = [int(-(-(c + r) // 64)) for c, r in zip(ctx, rows)]
     perm = rng.permutation(sum(need))
     pool = torch.full((vf.vf_kv_bytes(pair.model, 64, sum(need)),), 255, dtype=torch.uint8, device=DEV)   # NaN where nothing is written
@@ -104,6 +119,7 @@ def test_value_that_is_not_finite(at):
     seq = pair.new_seq(9000)
     ids = wl.make_context(V, rows, np.random.default_rng(at))
     ids[at] = np.setdiff1d(np.arange(V), ids)[0]   # a token of its own
+    assert attention_plan(pair.vcfg, [ctx], [rows])[0]
     _fill(pair, seq, ctx, torch.Generator(device=DEV).manual_seed(at))
     logits = torch.empty((rows, V), dtype=torch.float32, device=DEV)
 

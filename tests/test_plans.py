@@ -1,0 +1,69 @@
+"""What the cost models choose (no GPU): every kernel and epilogue that some row count of the three full-size shapes
+takes is run by test_gpu_rows.py against the oracle, and the attention kernel for many items by test_gpu_attn_items.py
+with and without a merge for either head size, so that constants fitted anew cannot bring one into use that no
+test reaches."""
+import pytest
+
+import paper_2510_15312_amd as vf
+import workloads as wl
+import test_gpu_attn_items as items
+from test_gpu_rows import MODELS, candidates, config_of
+from util_plan import GEMMS, attention_plan, gemm_plan
+
+FULL = ["0.5b_k8", "1.5b_k16", "3b_k32"]
+
+
+def _taken(cfg, rows, top_k):
+    """(kernel, epilogue, K split or not) of every GEMM of a call of so many rows."""
+    out = set()
+    for g in GEMMS:
+        if g == "topk" and (rows <= 64 or rows < (28 if cfg.d_model >= 2048 else 40) * top_k):
+            continue   # the candidates come from the logits
+        kernel, splits, epilogue = gemm_plan(cfg, g, rows)
+        out.add((kernel, epilogue, splits > 1))
+    return out
+
+
+def _of_full_shapes():
+    out = {}
+    for name in FULL:
+        cfg = vf.config_from(wl.CONFIGS[name], 4096, 8192)
+        for rows in range(1, 4097):
+            for what in _taken(cfg, rows, 1):
+                out.setdefault(what, (name, rows))
+    return out
+
+
+def test_every_kernel_that_is_taken_is_tested():
+    tested = set()
+    for name, (_, _, rows) in MODELS.items():
+        for r in rows:
+            tested |= _taken(config_of(name)[1], r, candidates(r))
+    missed = {what: where for what, where in _of_full_shapes().items() if what not in tested}
+    assert not missed, missed
+
+
+def test_splits_leave_no_part_empty():
+    # part p takes k-blocks p * ceil(KB / splits) on: the last one has to have some
+    for name in FULL:
+        cfg = vf.config_from(wl.CONFIGS[name], 4096, 8192)
+        for gemm, K in (("o", cfg.n_q_heads * cfg.head_dim), ("down", cfg.d_ffn), ("qkv", cfg.d_model)):
+            for rows in range(1, 4097):
+                _, splits, _ = gemm_plan(cfg, gemm, rows)
+                assert (splits - 1) * -(-(K // 32) // splits) < K // 32
+
+
+@pytest.mark.parametrize("hd", [64, 128])
+def test_attention_cases_take_the_kernel_they_are_for(hd):
+    cfg = vf.config_from(items.config_of(hd), 1056, 9000)
+    calls = [([ctx], [rows]) for ctx, rows in items.CHUNKS] + [items.batch_of(*b)[:2] for b in items.BATCHES]
+    plans = [attention_plan(cfg, lens, rows) for lens, rows in calls]
+    assert all(pages for pages, _ in plans)
+    assert {merged for _, merged in plans[:len(items.CHUNKS)]} == {merged for _, merged in plans[len(items.CHUNKS):]} == {False, True}
+
+
+@pytest.mark.parametrize("name", FULL)
+def test_attention_of_few_items_stays_with_their_kernel(name):
+    cfg = vf.config_from(wl.CONFIGS[name], 4096, 8192)
+    assert attention_plan(cfg, [1000], [64]) == (0, False)
+    assert attention_plan(cfg, [7000] * 16, [33] * 16)[0] > 0
