@@ -14,7 +14,7 @@
 // workgroup's eight wavefronts split K so that most of a tile's operands are requested at once, and
 // operands go from memory straight to registers.  Measured on a 512-token prompt in chunks of 128 plus
 // a verify of 5 rows: 8607 us with one wavefront per output column on the vector units and scalar
-// attention (180 and 80 us per launch), 400 us like this.
+// attention (180 and 80 us per launch), 391 us like this.
 #include "vf_internal.h"
 
 namespace {
@@ -37,13 +37,25 @@ struct GemmF32 {
     const int32_t *depth;
 };
 
+// sum of N partial sums, in pairs
+template <int N> __device__ __forceinline__ floatx4 pairwise(const floatx4 *p) {
+    if constexpr (N == 1) return p[0];
+    else return pairwise<N / 2>(p) + pairwise<N - N / 2>(p + N / 2);
+}
+
 // One workgroup: 16 * RB rows x 16 * UB columns.  A 16-wide K chunk is one 16-byte load per lane and
 // operand block: lane (g, i) holds columns 4 g .. 4 g + 3 of row i, and matrix instruction j of the
 // chunk takes column 4 g + j from every lane, of both operands.
 template <int RB, int UB, int EPI>
 __global__ __launch_bounds__(NW * 64) VF_MFMA_KERNEL void gemm_f32_kernel(GemmF32 p, Batch b) {
     constexpr bool NORMED = EPI != F_RESID;
-    constexpr int U = 4;                                  // chunks requested together
+    constexpr int U = RB * UB > 2 ? 2 : 4;                // chunks requested together
+    // Eight partial sums of a wavefront: matrix instruction j of a chunk adds to sum j, and the four are put aside half
+    // way through the wavefront's chunks.  A sum is a chain of K / 64 products, as with one product a lane, and sums are
+    // added in pairs: with one sum a wavefront the logits' error was a third to two thirds larger (1.41e-7 for 1.07e-7 at
+    // d 256, 2.37e-7 for 1.43e-7 at d 512), and its instructions waited for one another (512 tokens and 5 rows: 400 us
+    // for 391; eight sums kept to the end: 412).
+    constexpr int A = 4;
     constexpr int TILES = RB * UB;                        // epilogue tiles, one per wavefront
     static_assert(TILES <= NW, "one epilogue tile per wavefront");
     __shared__ floatx4 red[NW * UB * RB * 64];
@@ -64,11 +76,24 @@ __global__ __launch_bounds__(NW * 64) VF_MFMA_KERNEL void gemm_f32_kernel(GemmF3
     if (NORMED && wave < TILES)
         _Pragma("unroll 4") for (int j = g4; j < p.n_ss; j += 4) ssq += p.ss_in[(size_t)j * p.ss_ld + min(row, p.rows - 1)];
 
-    floatx4 acc[UB][RB];
+    floatx4 acc[A][UB][RB], first[UB][RB];
+    auto clear = [&] {
 #pragma unroll
-    for (int u = 0; u < UB; ++u)
+        for (int a = 0; a < A; ++a)
 #pragma unroll
-        for (int r = 0; r < RB; ++r) acc[u][r] = floatx4{0.f, 0.f, 0.f, 0.f};
+            for (int u = 0; u < UB; ++u)
+#pragma unroll
+                for (int r = 0; r < RB; ++r) acc[a][u][r] = floatx4{0.f, 0.f, 0.f, 0.f};
+    };
+    auto total = [&](int u, int r) {
+        floatx4 part[A];
+#pragma unroll
+        for (int a = 0; a < A; ++a) part[a] = acc[a][u][r];
+        return pairwise<A>(part);
+    };
+    clear();
+    // first chunk of the second half of this wavefront's chunks; at or past KC where it has one or none
+    const int half = wave + ((KC - wave + NW - 1) / NW + 1) / 2 * NW;
     for (int c0 = wave; c0 < KC; c0 += NW * U) {
         floatx4 w[U][UB], x[U][RB], gn[U];
 #pragma unroll
@@ -82,6 +107,13 @@ __global__ __launch_bounds__(NW * 64) VF_MFMA_KERNEL void gemm_f32_kernel(GemmF3
         }
 #pragma unroll
         for (int i = 0; i < U; ++i) {
+            if (c0 + i * NW == half && half < KC) {
+#pragma unroll
+                for (int u = 0; u < UB; ++u)
+#pragma unroll
+                    for (int r = 0; r < RB; ++r) first[u][r] = total(u, r);
+                clear();
+            }
             if (c0 + i * NW < KC) {  // the same for the whole wavefront
 #pragma unroll
                 for (int r = 0; r < RB; ++r) {
@@ -90,7 +122,7 @@ __global__ __launch_bounds__(NW * 64) VF_MFMA_KERNEL void gemm_f32_kernel(GemmF3
                     for (int j = 0; j < 4; ++j)
 #pragma unroll
                         for (int u = 0; u < UB; ++u)
-                            acc[u][r] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[i][u][j], xv[j], acc[u][r], 0, 0, 0);
+                            acc[(i * 4 + j) % A][u][r] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[i][u][j], xv[j], acc[(i * 4 + j) % A][u][r], 0, 0, 0);
                 }
             }
         }
@@ -98,13 +130,14 @@ __global__ __launch_bounds__(NW * 64) VF_MFMA_KERNEL void gemm_f32_kernel(GemmF3
 #pragma unroll
     for (int u = 0; u < UB; ++u)
 #pragma unroll
-        for (int r = 0; r < RB; ++r) red[((wave * UB + u) * RB + r) * 64 + lane] = acc[u][r];
+        for (int r = 0; r < RB; ++r) red[((wave * UB + u) * RB + r) * 64 + lane] = half < KC ? first[u][r] + total(u, r) : total(u, r);
     __syncthreads();
     if (wave >= TILES) return;
     // lane holds Y[row][16 nb + 4 g4 + 0..3]
-    floatx4 v = {0.f, 0.f, 0.f, 0.f};
+    floatx4 part[NW];
 #pragma unroll
-    for (int w = 0; w < NW; ++w) v += red[((w * UB + eu) * RB + er) * 64 + lane];
+    for (int w = 0; w < NW; ++w) part[w] = red[((w * UB + eu) * RB + er) * 64 + lane];
+    floatx4 v = pairwise<NW>(part);
     if (NORMED) {
         ssq += __shfl_xor(ssq, 16, 64);
         ssq += __shfl_xor(ssq, 32, 64);

@@ -49,3 +49,23 @@ def test_f32_prefill_and_verify_against_oracle(d, hq, hkv, hd, ffn, vocab, n, ch
     vf.vf_verify(pair.model, [seq], i32(drafts), [0, rows], logits)
     z = oracle.verify(pair.spec, pair.ow, cache, int(drafts[0]), drafts[1:])
     assert rel_inf(logits.cpu().numpy(), z).max() < 1e-5
+
+
+# Precision: the 2-norm of the logits' error against float64, at a row count of every tile.  A plain kernel whose
+# lanes each sum K / 64 products has 4.37e-7 and 7.58e-7 here, sums of K / 8 products 5.62e-7 and 9.79e-7; the bounds lie
+# 5 % above the first (the same seeds: what varies is the order within a chain).
+@pytest.mark.parametrize("d,ffn,vocab,bound", [(256, 1024, 4096, 4.6e-7), (512, 2048, 8192, 8.0e-7)])
+def test_f32_error_of_the_sums(d, ffn, vocab, bound):
+    cfg = wl.scaled(BASE, d_model=d, d_ffn=ffn, vocab=vocab)
+    pair = Pair(cfg, max_rows=320, max_positions=320, std=0.05)
+    ids = wl.make_context(vocab, 320, pair.s.context)
+    z = forward(pair.spec, pair.ow, oracle.KVCache(pair.spec, 320), ids)
+    for chunk in (16, 64, 320):
+        seq, got = pair.new_seq(320), []
+        for a in range(0, 320, chunk):
+            out = torch.empty((chunk, vocab), dtype=torch.float32, device=DEV)
+            vf.vf_prefill_chunk(pair.model, seq, i32(ids[a:a + chunk]), logits_mode=2, logits_out=out)
+            got.append(out.cpu().numpy().astype(np.float64))
+        err = np.linalg.norm(np.concatenate(got) - z) / np.linalg.norm(z)
+        print(f"d {d}, chunks of {chunk}: {err:.3e}", flush=True)
+        assert err < bound
