@@ -219,7 +219,7 @@ def bench_mix(args, cfg, torch, wl, vf):
         k_bytes = float(cfg.weight_bytes() + int(mix.ctx.sum() + total) * kvb + total * kvb + total * V * 4)
         avg_us = prof["step"][0] / prof["step"][1] * 1e3
     else:
-        kern = "gemm_rows_kernel (gate/up GEMM + SwiGLU, many-row tile), one launch per layer"
+        kern = "gemm_stream_kernel (gate/up GEMM + SwiGLU, many rows), one launch per layer"
         k_bytes = float(2 * cfg.d_ffn * cfg.d_model * 2 + total * cfg.d_model * 2 + total * cfg.d_ffn * 2)
         avg_us = prof["gateup"][0] / prof["gateup"][1] * 1e3
     achieved = k_bytes / (avg_us * 1e-6) / 1e9

@@ -10,8 +10,8 @@
 //   few weight blocks, so that the column tiles fill the chip once.  A producer wavefront keeps a deep
 //   ring of weight fragments filled with direct loads to LDS; the compute wavefronts stack up over the
 //   rows, keep their own activation fragments in registers several k-blocks ahead, and all take the
-//   weights from the ring.  256 x 17920 x 1536: 27.9 -> 21.6 us, 128 rows: 26.2 -> 15.9 us (before: a
-//   256 x 128 tile, two k-blocks of weights ahead in registers).
+//   weights from the ring.  Gate/up of the 1.5B shape in a prefill (17920 x 1536, SwiGLU): 256 rows 27 -> 21.5
+//   us, 128 rows 27 -> 16.7 (before: a 256 x 128 tile, two k-blocks of weights ahead in registers).
 //
 //   gemm_tile_kernel (square tiles, K splits): both operands go through an LDS ring of S stages of one
 //   k-block, filled by direct loads S - 1 k-blocks ahead; fragments leave LDS one k-block ahead of their
