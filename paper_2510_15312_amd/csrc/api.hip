@@ -81,10 +81,10 @@ size_t carve_model(vf_model *m, char *base) {
     m->q = cv.take(R * nq * es);
     m->o = cv.take(R * nq * es);
     m->a = cv.take(R * F * es);
-    size_t widest = 2 * F;
-    if (nq + 2 * nkv > widest) widest = nq + 2 * nkv;
+    const size_t widest = std::max(std::max(2 * F, nq + 2 * nkv), d);
     m->part_floats = R * widest * 2;  // room for two partials of the widest layer GEMM
-    m->part_floats = std::max(m->part_floats, vf_fused_part_floats(c));  // and for the persistent kernel's K splits
+    // and for the K splits of the few-row kernels
+    m->part_floats = std::max(m->part_floats, std::max(vf_fused_part_floats(c), vf_fast_part_floats(c)));
     m->part = (float *)cv.take(m->part_floats * 4);
     {
         // general path: 16 slices per row of max_rows; few-row path: up to 48 rows, one slice per 128 keys
@@ -674,7 +674,8 @@ int vf_stream_read(vf_model *m, size_t *bytes_host, void *stream) {
 // Which kernels a many-row call takes: not part of the interface, exported so that the tests can state what they
 // run and check that nothing chosen goes untested.  Host only.
 //   use: a GemmUse-like number: 0 QKV, 1 O, 2 gate/up, 3 down, 4 output head, 5 output head with the top-k epilogue
-//   out: kernel of gemm_rows.h (index into the shapes of gemm.hip), K splits, epilogue (GemmUse)
+//   out: kernel of gemm_rows.h (index into the shapes of gemm.hip), K splits, epilogue (GemmUse), and whether the
+//   partial sums, where it leaves some, fit their workspace
 int vf_debug_gemm_plan(const vf_config *cfg, int use, int rows, int32_t *out) {
     vf_model m;
     memset(&m, 0, sizeof m);
@@ -692,6 +693,7 @@ int vf_debug_gemm_plan(const vf_config *cfg, int use, int rows, int32_t *out) {
     out[0] = p.shape;
     out[1] = p.ks;
     out[2] = p.epi;
+    out[3] = use > 3 || p.epi != GEMM_PARTIAL || (size_t)p.ks * rows * N[use] <= m.part_floats;
     return VF_OK;
 }
 

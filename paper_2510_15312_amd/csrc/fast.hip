@@ -518,14 +518,18 @@ constexpr size_t LDS_X_BUDGET = 53 * 1024;
 #define HEAD_NW 4
 #endif
 
-// want_wgs: workgroups to aim for by splitting K across workgroups (0: never split).
+// K splits across workgroups, aiming for want_wgs of them (0: never split)
+int fast_splits(int units, int want_wgs, int KB, int nw) {
+    int ks = 1;
+    while (units * ks < want_wgs && KB / (ks * 2) >= nw) ks *= 2;
+    const int kbps = (KB + ks - 1) / ks;
+    return (KB + kbps - 1) / kbps;
+}
+
 template <int NB, int UB, int PD, int EPI, int NW>
 int launch_gemm(FastGemm g, const Batch &b, int units, int want_wgs, hipStream_t st) {
     const int m = g.m;
-    int ks = 1;
-    while (units * ks < want_wgs && g.KB / (ks * 2) >= NW) ks *= 2;
-    int kbps = (g.KB + ks - 1) / ks;
-    ks = (g.KB + kbps - 1) / kbps;
+    const int ks = fast_splits(units, want_wgs, g.KB, NW), kbps = (g.KB + ks - 1) / ks;
     int kch = kbps;
     while ((size_t)kch * m * 64 > LDS_X_BUDGET) kch = (kch + 1) / 2;
     g.ks = ks;
@@ -684,6 +688,14 @@ int vf_launch_attention_rows(const vf_model *m, const Batch &b, int layer, hipSt
         VF_LAUNCH_CHECK("attn_rows_combine");
     }
     return VF_OK;
+}
+
+// Partial tiles of the one GEMM that splits K: 16 x 16 floats per unit, split and 16 rows.
+size_t vf_fast_part_floats(const vf_config &c) {
+    if (c.dtype != VF_BF16) return 0;
+    const int units = c.d_model / 16, ks = fast_splits(units, DOWN_WGS, c.d_ffn / 32, DOWN_NW);
+    const int rows = c.max_rows < 48 ? c.max_rows : 48;
+    return ks > 1 ? (size_t)units * ks * ((rows + 15) / 16) * 256 : 0;
 }
 
 bool vf_fast_path_ok(const vf_model *m, int total_rows) {

@@ -369,6 +369,7 @@ int vf_launch_attention_items(const vf_model *m, const Batch &b, int layer, hipS
 // its choice: pages of a part (merge: whether a sequence has several), 0: vf_launch_attention_rows
 int vf_attention_items_plan(const vf_model *m, const Batch &b, int *merge);
 bool vf_fast_path_ok(const vf_model *m, int total_rows);
+size_t vf_fast_part_floats(const vf_config &c);
 int vf_run_fast(vf_model *m, const Batch &b, const int32_t *tokens, float *logits_out, hipStream_t st);
 // the float32 model's layers and output head
 int vf_f32_init(const vf_model *m);

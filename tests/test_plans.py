@@ -53,6 +53,16 @@ def test_splits_leave_no_part_empty():
                 assert (splits - 1) * -(-(K // 32) // splits) < K // 32
 
 
+# also of models far wider than their heads and ffn, whose one partial of O and down is the widest there is
+@pytest.mark.parametrize("d,heads,ffn", [(4096, 1, 64), (8192, 2, 32), (2048, 4, 544), (256, 32, 64)])
+def test_partial_sums_fit_their_workspace(d, heads, ffn):
+    for max_rows in (16, 100, 1024):
+        cfg = vf.make_config(1, d, heads, heads, 64, ffn, 160, "bf16", 1e4, 1e-6, max_rows, 2048)
+        for rows in {1, max_rows // 2, max_rows}:
+            for gemm in GEMMS:
+                gemm_plan(cfg, gemm, rows)   # asserts it
+
+
 @pytest.mark.parametrize("hd", [64, 128])
 def test_attention_cases_take_the_kernel_they_are_for(hd):
     cfg = vf.config_from(items.config_of(hd), 1056, 9000)

@@ -10,8 +10,9 @@ EPILOGUES = ["partial", "split", "qkv", "swiglu", "topk"]
 
 def gemm_plan(cfg, gemm, rows):
     """(kernel, K splits, epilogue) of a GEMM of a vf_config at a number of rows."""
-    out = (C.c_int32 * 3)()
+    out = (C.c_int32 * 4)()
     vf.binding._check(vf.lib.vf_debug_gemm_plan(C.byref(cfg), GEMMS.index(gemm), rows, out))
+    assert out[3], f"{gemm} of {rows} rows: the partial sums do not fit"
     return SHAPES[out[0]], out[1], EPILOGUES[out[2]]
 
 
