@@ -43,17 +43,11 @@ constexpr long long SPIN_LIMIT = 4000000;  // polls before a barrier gives up (s
 #ifndef FUSED_PREFETCH_EARLY
 #define FUSED_PREFETCH_EARLY 1   // first weight loads of a phase go out before the barrier wait
 #endif
-#ifndef FUSED_PD_DOWN
-#define FUSED_PD_DOWN 5            // ring depth of the down projection (nine fragments per wavefront at the 1.5B shape)
-#endif
 #ifndef FUSED_AHEAD
 #define FUSED_AHEAD 3          // gate/up, down and head phases: this many steps of the item after next are held in registers too (0: off)
 #endif
 #ifndef FUSED_LAST_MERGES
 #define FUSED_LAST_MERGES 1     // attention: the last part to arrive merges the block (0: all parts wait and merge a slice each)
-#endif
-#ifndef FUSED_FREE_SPLIT
-#define FUSED_FREE_SPLIT 1     // a phase of at most one item per workgroup may use a K split that does not divide the grid
 #endif
 #ifndef FUSED_MAXP
 #define FUSED_MAXP 6              // most key parts per attention block (8 parts: 1280 us per launch, 6 1261, 5 1258, 4 1254, 3 1274, 2 1318;
@@ -114,7 +108,7 @@ struct FusedArgs {
     short att_first[FUSED_G];
     float inv_d, eps, scale_log2e;
     unsigned root0;   // value of the barrier's root counter when this launch starts
-    int ks_qkv, ks_o, ks_gu, ks_down, ks_head;
+    int ks_qkv, ks_gu, ks_down, ks_head;
     int gu_light;            // gate/up: the first gu_light workgroups (busy in the O projection) take one unit each (0: even shares)
     int wave_gu, wave_head;  // gate/up, output head: one weight block per wavefront (K unsplit and the staged rows fit)
     int lds_total;    // dynamic LDS bytes of this launch
@@ -248,9 +242,6 @@ __device__ __forceinline__ void embed_phase(const FusedArgs &a, const Batch &b) 
 #ifndef FUSED_XP
 #define FUSED_XP 16                // activation staging: loads in flight per thread (a multiple of FUSED_STAGE_GROUP)
 #endif
-#ifndef FUSED_SHORT_COPY
-#define FUSED_SHORT_COPY 1          // plain activation staging: a copy of half the depth for calls whose pieces it covers
-#endif
 #ifndef FUSED_STAGE_GROUP
 #define FUSED_STAGE_GROUP 4       // staging of a normalising phase: pieces whose LDS reads (1/rms, gain) are issued together
 #endif
@@ -268,9 +259,7 @@ __device__ __forceinline__ EpiPre epi_prefetch(const FastGemm &g, const FusedSha
     p.bias = floatx4{0.f, 0.f, 0.f, 0.f};
     const int n0 = nb * 16 + (lane >> 4) * 4;
     if (EPI == EPI_QKV && g.bias) p.bias = load_global_f4(g.bias + n0);
-    if (EPI == EPI_RESID) {
-        p.v = ssa_load_f4(g.h_in + (size_t)row * g.N + n0);
-    } else if (EPI == EPI_QKV) {
+    if (EPI == EPI_QKV) {
         const int half = g.hd >> 1, i0 = (n0 % g.hd) >> 1;
         const size_t at = (size_t)sh.rows[row].pos * half + i0;   // past the K heads: loaded, not used
         const float2 c = *reinterpret_cast<const float2 *>(g.cosv + at), sn = *reinterpret_cast<const float2 *>(g.sinv + at);
@@ -323,6 +312,16 @@ __device__ __forceinline__ void epi_qkv_pre(const FastGemm &g, const FusedShared
     }
 }
 
+// SwiGLU product in MFMA operand order (fragment (K block, row block), see xfrag_index).  v0, v1: tiles of the weight
+// blocks nb (even) and nb + 1: a lane holds ffn columns f, f + 1 and f + 8, f + 9 of its row.
+template <int NB>
+__device__ __forceinline__ void epi_swiglu_frag(const FastGemm &g, int row, int nb, int lane, floatx4 v0, floatx4 v1) {
+    bf16_t *out = g.a_out + xfrag_index(row, nb * 8, NB) + (lane >> 4) * 2;
+    auto act = [](float gt, float up) { return gt / (1.0f + expf(-gt)) * up; };
+    st_u32<true>(out, pack2_bf16(act(v0[0], v0[1]), act(v0[2], v0[3])));
+    st_u32<true>(out + 128, pack2_bf16(act(v1[0], v1[1]), act(v1[2], v1[3])));
+}
+
 // Second half of the staging of a normalising phase: x = bf16(h * rstd * gain) for the XP pieces
 // (four columns of one row each) this thread loaded, written to the staged activations.  The three
 // LDS arrays are distinct (restrict), which lets the reads of later pieces pass the writes of
@@ -370,7 +369,7 @@ __device__ __forceinline__ void scale_and_stage(const floatx4 (&v)[XP], const fl
 template <int NB, int UB, int PD, int EPI>
 __device__ __forceinline__ void gemm_phase(const FastGemm &g, const Batch &b, GridBar &bar, unsigned char *smem,
                                   int lds_total, FusedShared &sh TRACE_ARG) {
-    constexpr bool NORMED = EPI != EPI_RESID;
+    static_assert(EPI != EPI_RESID, "resid_phase");
     constexpr bool COH = EPI != EPI_LOGITS;  // logits are read by the next kernel only
     constexpr int RW = FW / 2;               // wavefronts whose partial sums sit in LDS at a time
     constexpr int RED_BYTES = RW * 2 * NB * 1024;
@@ -441,7 +440,7 @@ __device__ __forceinline__ void gemm_phase(const FastGemm &g, const Batch &b, Gr
     if (n_my == 0) return;
 
     // ---- stage the activations of this K slice: every global load goes out before the first use ----
-    if (NORMED) {
+    {
         // x = bf16(h * rstd * gain) with rstd = 1/rms from the per-16-column sums of squares
         // (lane = row, wavefront = every FW-th block of columns); pieces of four columns
         const int chunks = nk * 8, pieces = m * chunks;
@@ -499,40 +498,6 @@ __device__ __forceinline__ void gemm_phase(const FastGemm &g, const Batch &b, Gr
             }
             scale_and_stage<XP>(v, sh.rs_s, gain_s, reinterpret_cast<u32x2 *>(xs), row0, c0, qstep, rstep, chunks, m);
         }
-    } else {
-        const int chunks = nk * 4, pieces = m * chunks;
-        const int qstep = FT / chunks, rstep = FT % chunks;
-        const bf16_t *x_slice = g.X + (size_t)kb0 * 32;
-        // passes of `depth` loads in flight per thread; few pieces (a K slice of a call of few rows)
-        // take the short copy, which issues half as many loads that only repeat the last row
-        auto stage_copy = [&](auto depth_tag) {
-            constexpr int D = decltype(depth_tag)::value;
-            for (int base = 0; base < pieces; base += FT * D) {
-                u32x4 v[D];
-                int row = (base + tid) / chunks, c = (base + tid) % chunks;
-                const int row0 = row, c0 = c;
-#pragma unroll
-                for (int i = 0; i < D; ++i) {
-                    v[i] = ssa_load_16(x_slice + (unsigned)(min(row, m - 1) * KB * 32 + c * 8));  // uniform base + 32-bit offset
-                    row += qstep;
-                    c += rstep;
-                    if (c >= chunks) { c -= chunks; ++row; }
-                }
-                if (!FUSED_PREFETCH_EARLY && base == 0) first_fragments();
-                row = row0;
-                c = c0;
-#pragma unroll
-                for (int i = 0; i < D; ++i) {
-                    const int rr = min(row, m - 1);  // a piece past the last row: the last row's, written again
-                    xs[((c >> 2) * m + rr) * 4 + (c & 3)] = v[i];
-                    row += qstep;
-                    c += rstep;
-                    if (c >= chunks) { c -= chunks; ++row; }
-                }
-            }
-        };
-        if (FUSED_SHORT_COPY && pieces <= FT * (XP / 2)) stage_copy(std::integral_constant<int, XP / 2>{});
-        else stage_copy(std::integral_constant<int, XP>{});
     }
     lds_sync();
     TRACE(3);
@@ -561,7 +526,7 @@ __device__ __forceinline__ void gemm_phase(const FastGemm &g, const Batch &b, Gr
         EpiPre pre;
         pre.v = floatx4{0.f, 0.f, 0.f, 0.f};
         pre.bias = floatx4{0.f, 0.f, 0.f, 0.f};
-        if (FUSED_EPI_PREFETCH && (EPI == EPI_RESID || EPI == EPI_QKV) && tid < NTH_) {
+        if (FUSED_EPI_PREFETCH && EPI == EPI_QKV && tid < NTH_) {
             const int eu = tid / (NB * 64), ec = (tid >> 6) % NB;
             pre = epi_prefetch<EPI>(g, sh, min(ec * 16 + (lane & 15), m - 1), min(nb0 + eu, NBt - 1), lane);
         }
@@ -731,13 +696,10 @@ __device__ __forceinline__ void gemm_phase(const FastGemm &g, const Batch &b, Gr
             const int nb = nb0 + u;
             const int row = c * 16 + (lane & 15);
             const bool live = row < m && nb < NBt;
-            if (EPI == EPI_RESID) {
-                if (FUSED_EPI_PREFETCH) epi_resid_pre(g, row, live, nb, lane, v0, pre);
-                else epi_resid<COH>(g, row, live, nb, lane, v0);
-            } else if (live) {
+            if (live) {
                 if (EPI == EPI_QKV && FUSED_EPI_PREFETCH) epi_qkv_pre(g, sh, row, nb, lane, v0, pre);
                 else if (EPI == EPI_QKV) epi_qkv<COH>(g, b, row, nb, lane, v0);
-                else if (EPI == EPI_SWIGLU) epi_swiglu<COH>(g, row, nb, lane, v0, v1);
+                else if (EPI == EPI_SWIGLU) epi_swiglu_frag<NB>(g, row, nb, lane, v0, v1);
                 else __builtin_nontemporal_store(v0, reinterpret_cast<floatx4 *>(g.logits + (size_t)row * g.N + nb * 16 + (lane >> 4) * 4));
             }
         }
@@ -747,6 +709,157 @@ __device__ __forceinline__ void gemm_phase(const FastGemm &g, const Batch &b, Gr
 #pragma unroll
             for (int u = 0; u < UB; ++u) wp[u] = wpn[u];
         }
+    }
+}
+
+// ---- residual phases: O and down projection -----------------------------------------------------------
+// h_out = h_in + X W^T with X bfloat16 in MFMA operand order (the attention and SwiGLU epilogues write it that
+// way).  Every fragment of X has one reader in a workgroup, the wavefront that owns its k-blocks, so X goes from
+// memory into registers: no staging in LDS, no barrier between the loads and the products, no index arithmetic,
+// and no limit on the K slice.  Behind the grid barrier a wavefront issues one load per fragment, its products,
+// and the sum over the wavefronts; everything else (weights, addresses, the residual tile) comes before it.
+// Items: (unit of UB weight blocks) x (K split), as in gemm_phase.  A split unit meets tile by tile: the
+// wavefront that finishes a 16x16 tile stores its partial sums, counts itself in, and the last one to come adds
+// them in split order; no workgroup barrier is in that chain.
+// Depth: all k-blocks of a wavefront at once where the shape allows (weights requested before the barrier, X in one
+// round trip behind it).  Release to last arrival, staged through LDS / so: O of 0.5B, 1 row 2.9 / 1.7 us, of 1.5B,
+// 17 rows 3.1 / 2.5; down of 1.5B, 17 rows 8.3 / 7.0 (in two rounds of five k-blocks instead of one of seven 8.4).
+struct ResidGemm {
+    global_w_ptr W;
+    const bf16_t *X;   // [K / 32][NB] fragments
+    const float *h_in;
+    float *h, *ss_out, *part;
+    int *counters;     // one per tile of a unit, zero between uses
+    int N, KB, m, ks, kbps;
+    int unit0, ustep, split, n_my;   // this workgroup's items: units unit0 + i * ustep of K split `split`
+};
+template <int NB, int UB, int PD>
+__device__ __forceinline__ void resid_phase(const ResidGemm &g, GridBar &bar, unsigned char *smem TRACE_ARG) {
+    constexpr int NTILE = UB * NB;
+    static_assert(NTILE <= FW, "a tile of the unit per wavefront");
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int KB = g.KB, NBt = g.N >> 4;
+    const int kb0 = g.split * g.kbps, kb1 = min(KB, kb0 + g.kbps);
+    const int cnt = (kb1 - kb0 + FW - 1) / FW, rounds = (cnt + PD - 1) / PD;
+    const int wk0 = kb0 + wave * cnt, mine = min(cnt, kb1 - wk0);   // k-blocks wk0 .. wk0 + mine - 1 (none: mine <= 0)
+    floatx4 *red = reinterpret_cast<floatx4 *>(smem);
+    const int tu = wave / NB, tc = wave % NB;   // this wavefront's tile of a unit (wave < NTILE)
+    const int row = tc * 16 + (lane & 15), crow = min(row, g.m - 1);
+
+    u32x4 w[PD][UB], x[PD][NB];
+#pragma unroll
+    for (int d = 0; d < PD; ++d)
+#pragma unroll
+        for (int u = 0; u < UB; ++u) w[d][u] = u32x4{0u, 0u, 0u, 0u};
+    // never predicated: a step past the end of the run loads the run's last fragment again and is skipped
+    auto load_w = [&](int unit, int d, int kbl) {
+        const int kb = min(wk0 + min(kbl, cnt - 1), kb1 - 1);
+#pragma unroll
+        for (int u = 0; u < UB; ++u)
+            w[d][u] = __builtin_nontemporal_load(g.W + ((size_t)min(unit * UB + u, NBt - 1) * KB + kb) * 64 + lane);
+    };
+    auto load_x = [&](int d, int kbl) {
+        const int kb = min(wk0 + min(kbl, cnt - 1), kb1 - 1);
+#pragma unroll
+        for (int c = 0; c < NB; ++c) x[d][c] = ssa_load_16(g.X + ((size_t)(kb * NB + c) * 64 + lane) * 8);
+    };
+    auto load_h = [&](int unit) {
+        const int nb = min(unit * UB + tu, NBt - 1);
+        return ssa_load_f4(g.h_in + (size_t)crow * g.N + nb * 16 + (lane >> 4) * 4);
+    };
+    EpiPre pre;
+    pre.v = pre.bias = floatx4{0.f, 0.f, 0.f, 0.f};
+    if (g.n_my > 0) {
+#pragma unroll
+        for (int d = 0; d < PD; ++d) load_w(g.unit0, d, d);
+        pre.v = load_h(g.unit0);   // written two or more barriers ago
+    }
+    TRACE(1);
+    bar.wait();
+    TRACE(2);
+    if (g.n_my <= 0) return;
+#pragma unroll
+    for (int d = 0; d < PD; ++d) load_x(d, d);
+    for (int it = 0; it < g.n_my; ++it) {
+        const int unit = g.unit0 + it * g.ustep;
+        const bool has_next = it + 1 < g.n_my;
+        floatx4 acc[UB][NB];
+#pragma unroll
+        for (int u = 0; u < UB; ++u)
+#pragma unroll
+            for (int c = 0; c < NB; ++c) acc[u][c] = floatx4{0.f, 0.f, 0.f, 0.f};
+        auto round_body = [&](auto refill_tag, int r) {
+            constexpr bool REFILL = decltype(refill_tag)::value;
+            const bool last_round = r + 1 == rounds;
+            const int nunit = last_round ? unit + g.ustep : unit, nk = last_round ? 0 : (r + 1) * PD;
+#pragma unroll
+            for (int d = 0; d < PD; ++d) {
+                if (r * PD + d < mine) {
+#pragma unroll
+                    for (int c = 0; c < NB; ++c)
+#pragma unroll
+                        for (int u = 0; u < UB; ++u)
+                            acc[u][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[d][u]),
+                                                                                __builtin_bit_cast(bf16x8, x[d][c]), acc[u][c], 0, 0, 0);
+                }
+                if (REFILL) {
+                    load_w(nunit, d, nk + d);
+                    load_x(d, nk + d);
+                }
+            }
+        };
+#pragma unroll 1
+        for (int r = 0; r + 1 < rounds; ++r) round_body(std::true_type{}, r);
+        if (has_next) round_body(std::true_type{}, rounds - 1);
+        else round_body(std::false_type{}, rounds - 1);
+        TRACE(4);
+        // sum over the wavefronts: pairs (w, w + 4), then the four pairs in order
+        if (it) lds_sync();   // the previous item's sums have been read
+#pragma unroll
+        for (int u = 0; u < UB; ++u)
+#pragma unroll
+            for (int c = 0; c < NB; ++c) red[((u * NB + c) * FW + wave) * 64 + lane] = acc[u][c];
+        lds_sync();
+        if (wave < NTILE) {
+            floatx4 p[FW], v = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int i = 0; i < FW; ++i) p[i] = red[(wave * FW + i) * 64 + lane];
+            asm volatile("" ::: "memory");   // all reads are issued before the first sum
+#pragma unroll
+            for (int i = 0; i < FW / 2; ++i) v += p[i] + p[i + FW / 2];
+            bool last = true;
+            if (g.ks > 1) {
+                float *tile = g.part + ((size_t)unit * g.ks * NTILE + wave) * 256 + lane * 4;   // of split 0
+                store_coherent(tile + (size_t)g.split * NTILE * 256, v);
+                stores_done();
+                int old = 0;
+                int *cnt_p = g.counters + unit * NTILE + wave;
+                if (lane == 0) old = __hip_atomic_fetch_add(cnt_p, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                last = __builtin_amdgcn_readfirstlane(old) == g.ks - 1;
+                if (last) {
+                    if (lane == 0) __hip_atomic_store(cnt_p, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    v = floatx4{0.f, 0.f, 0.f, 0.f};
+                    for (int sp0 = 0; sp0 < g.ks; sp0 += 8) {
+                        floatx4 t[8];
+#pragma unroll
+                        for (int i = 0; i < 8; ++i) t[i] = load_coherent(tile + (size_t)min(sp0 + i, g.ks - 1) * NTILE * 256);
+#pragma unroll
+                        for (int i = 0; i < 8; ++i)
+                            if (sp0 + i < g.ks) v += t[i];
+                    }
+                }
+            }
+            const int nb = unit * UB + tu;
+            if (last) {
+                FastGemm e;
+                e.N = g.N; e.h = g.h; e.ss_out = g.ss_out;
+                epi_resid_pre(e, row, row < g.m && nb < NBt, nb, lane, v, pre);
+            }
+            if (has_next) pre.v = load_h(unit + g.ustep);
+        }
+        TRACE(5);
     }
 }
 
@@ -1005,7 +1118,7 @@ __device__ __forceinline__ void wave_phase(const FastGemm &g, int n_light, GridB
                 for (int i = 0; i < 4; ++i) t4[i] = exch[((w0 + i) * NB + q) * 64 + lane];
                 asm volatile("" ::: "memory");
                 const int row = q * 16 + (lane & 15);
-                if (row < m) epi_swiglu<true>(g, row, nb & ~1, lane, t4[0] + t4[1], t4[2] + t4[3]);
+                if (row < m) epi_swiglu_frag<NB>(g, row, nb & ~1, lane, t4[0] + t4[1], t4[2] + t4[3]);
             }
 #pragma unroll
             for (int c = 0; c < NB; ++c) acc[c] = floatx4{0.f, 0.f, 0.f, 0.f};
@@ -1050,7 +1163,7 @@ __device__ __forceinline__ AttItem att_item(const FusedArgs &a, const Batch &b, 
 
 // len0: length of the sequence of this workgroup's first item, read once per launch (lengths do
 // not change during a launch).
-template <int HD>
+template <int NB, int HD>
 __device__ __forceinline__ void attn_phase(const FusedArgs &a, const Batch &b, int layer, const bf16_t *q, bf16_t *o,
                                   int len0, GridBar &bar, unsigned char *smem, FusedShared &sh TRACE_ARG) {
     constexpr int KD = HD / 32, DB = HD / 16, REC = HD + ATTF_STRIDE_PAD, MAXP = FUSED_MAXP;
@@ -1227,13 +1340,13 @@ __device__ __forceinline__ void attn_phase(const FusedArgs &a, const Batch &b, i
                 }
                 if (valid) {
                     const float inv = 1.0f / Lg;
-                    st_u32x2<true>(o + (size_t)row * hq * HD + head * HD + db * 16 + g4 * 4,
+                    st_u32x2<true>(o + xfrag_index(row, head * HD + db * 16 + g4 * 4, NB),
                                    pack4_bf16(og[0] * inv, og[1] * inv, og[2] * inv, og[3] * inv));
                 }
             }
         } else if (wave < DB && valid) {
             const float inv = 1.0f / L;
-            st_u32x2<true>(o + (size_t)row * hq * HD + head * HD + wave * 16 + g4 * 4,
+            st_u32x2<true>(o + xfrag_index(row, head * HD + wave * 16 + g4 * 4, NB),
                            pack4_bf16(acc[0] * inv, acc[1] * inv, acc[2] * inv, acc[3] * inv));
         }
     }
@@ -1298,6 +1411,13 @@ __global__ __launch_bounds__(FT, FUSED_MINW) void verify_fused_kernel(FusedArgs 
     base.h = nullptr; base.ss_out = nullptr; base.a_out = nullptr; base.logits = nullptr; base.bias = nullptr;
     base.q = nullptr; base.layer = 0;
 
+    const int G = gridDim.x, wg = blockIdx.x;
+    // items of the down projection: (unit of two weight blocks) x (K split), w, w + G, ...; the splits divide G or
+    // leave at most one item per workgroup
+    const int down_items = (d / 16 + 1) / 2 * a.ks_down, kbps_down = (F / 32 + a.ks_down - 1) / a.ks_down;
+    const int down_unit0 = wg / a.ks_down, down_split = wg % a.ks_down, down_ustep = G / a.ks_down;
+    const int down_n = wg < down_items ? (down_items - wg + G - 1) / G : 0;
+
 #pragma unroll 1
     for (int l = 0; l < a.n_layers; ++l) {
         const FusedLayer lp = a.layers[l];
@@ -1314,14 +1434,14 @@ __global__ __launch_bounds__(FT, FUSED_MINW) void verify_fused_kernel(FusedArgs 
         }
         bar.arrive();
         TRACE(10);
-        attn_phase<HD>(a, b, l, q, o, len0, bar, smem, sh TRACE_PASS);
+        attn_phase<NB, HD>(a, b, l, q, o, len0, bar, smem, sh TRACE_PASS);
         bar.arrive();
         TRACE(13);
         {
-            FastGemm g = base;
-            g.W = lp.wo; g.N = d; g.KB = nq / 32; g.X = o; g.h_in = h0; g.h = h1; g.ss_out = ss1;
-            g.ks = a.ks_o; g.kbps = (g.KB + g.ks - 1) / g.ks;
-            gemm_phase<NB, 1, 6, EPI_RESID>(g, b, bar, smem, a.lds_total, sh TRACE_PASS);
+            const ResidGemm g{(global_w_ptr)lp.wo, o, h0, h1, ss1, a.part, a.counters, d, nq / 32, a.m, 1, nq / 32,
+                              wg, G, 0, wg < d / 16 ? (d / 16 - wg + G - 1) / G : 0};
+            if (nq <= 4 * FW * 32) resid_phase<NB, 1, 4>(g, bar, smem TRACE_PASS);   // four k-blocks a wavefront
+            else resid_phase<NB, 1, 6>(g, bar, smem TRACE_PASS);
         }
         bar.arrive();
         TRACE(14);
@@ -1335,10 +1455,10 @@ __global__ __launch_bounds__(FT, FUSED_MINW) void verify_fused_kernel(FusedArgs 
         bar.arrive();
         TRACE(15);
         {
-            FastGemm g = base;
-            g.W = lp.wd; g.N = d; g.KB = F / 32; g.X = act; g.h_in = h1; g.h = h2; g.ss_out = ss2;
-            g.ks = a.ks_down; g.kbps = (g.KB + g.ks - 1) / g.ks;
-            gemm_phase<NB, 2, FUSED_PD_DOWN, EPI_RESID>(g, b, bar, smem, a.lds_total, sh TRACE_PASS);
+            const ResidGemm g{(global_w_ptr)lp.wd, act, h1, h2, ss2, a.part, a.counters, d, F / 32, a.m, a.ks_down, kbps_down,
+                              down_unit0, down_ustep, down_split, down_n};
+            if (kbps_down <= 4 * FW) resid_phase<NB, 2, 4>(g, bar, smem TRACE_PASS);
+            else resid_phase<NB, 2, NB <= 2 ? 7 : 5>(g, bar, smem TRACE_PASS);
         }
         bar.arrive();
         TRACE(16);
@@ -1366,21 +1486,23 @@ int slice_limit(int lds_total, int rows, int nb) {
     return x_bytes / (rows * 64);
 }
 
-// K split for a phase: a divisor of G, at least what LDS demands; with allow_fill as many more
-// splits as keep the item count within one item per workgroup.  0: nothing fits.
-int pick_split(int G, int lds_total, int units, int KB, int rows, int nb, bool allow_fill) {
+// K split of a phase that stages its activations: the smallest divisor of G whose slice fits LDS (workgroup w takes
+// items w, w + G, ...: they share a K slice if ks divides G).  0: nothing fits.
+int pick_split(int G, int lds_total, int KB, int rows, int nb) {
     const int lim = slice_limit(lds_total, rows, nb);
-    int best = 0;
     for (int ks = 1; ks <= G && ks <= KB; ++ks) {
-        // workgroup w takes items w, w + G, ...: they share a K slice if ks divides G, or if there is
-        // at most one item per workgroup
-        if (G % ks && !(FUSED_FREE_SPLIT && allow_fill && units * ks <= G)) continue;
         const int kbps = (KB + ks - 1) / ks;
-        if ((KB + kbps - 1) / kbps != ks) continue;  // every split must own k-blocks
-        if (kbps > lim) continue;
-        if (!best) best = ks;
-        if (!allow_fill) break;
-        if (units * ks <= G && kbps >= FW) best = ks;
+        if (G % ks == 0 && (KB + kbps - 1) / kbps == ks && kbps <= lim) return ks;   // every split owns k-blocks
+    }
+    return 0;
+}
+// K split of the down projection, whose slices are not staged: as many splits as leave one item per workgroup and a
+// k-block per wavefront.
+int fill_split(int G, int units, int KB) {
+    int best = 1;
+    for (int ks = 2; units * ks <= G && ks <= KB; ++ks) {
+        const int kbps = (KB + ks - 1) / ks;
+        if ((KB + kbps - 1) / kbps == ks && kbps >= FW) best = ks;
     }
     return best;
 }
@@ -1452,27 +1574,26 @@ int vf_fused_init(vf_model *m, char *ws, hipStream_t st) {
 // Whether the persistent kernel can run this call; fills the grid size, LDS size and K splits.
 // K splits of the six GEMM phases for a call of `rows` rows (nb blocks of 16), and the floats of
 // partial-sum workspace they need.  false: some phase does not fit.
-struct Splits { int qkv, o, gu, down, head; };
+struct Splits { int qkv, gu, down, head; };
 static bool plan_splits(const vf_config &c, int rows, int nb, Splits *sp, size_t *part_floats) {
     const int d = c.d_model, F = c.d_ffn, hd = c.head_dim, nq = c.n_q_heads * hd, nkv = c.n_kv_heads * hd;
     if (c.dtype != VF_BF16 || rows > FROWS || d % 64) return false;
     if (std::max(std::max((nq + 2 * nkv) / 16, F / 16), (c.vocab / 16 + 1) / 2) > VF_N_COUNTERS) return false;
     const int G = FUSED_G, lds = LDS_BYTES;
     if (G % BAR_COUNTERS) return false;
-    sp->qkv = pick_split(G, lds, (nq + 2 * nkv) / 16, d / 32, rows, nb, false);
-    sp->o = pick_split(G, lds, d / 16, nq / 32, rows, nb, false);
-    sp->gu = pick_split(G, lds, F / 16, d / 32, rows, nb, false);
-    sp->down = pick_split(G, lds, (d / 16 + 1) / 2, F / 32, rows, nb, true);
-    sp->head = pick_split(G, lds, (c.vocab / 16 + 1) / 2, d / 32, rows, nb, false);
-    if (!sp->qkv || !sp->o || !sp->gu || !sp->down || !sp->head) return false;
+    sp->qkv = pick_split(G, lds, d / 32, rows, nb);
+    sp->gu = pick_split(G, lds, d / 32, rows, nb);
+    sp->down = fill_split(G, (d / 16 + 1) / 2, F / 32);
+    sp->head = pick_split(G, lds, d / 32, rows, nb);
+    if (!sp->qkv || !sp->gu || !sp->head) return false;
+    if ((d / 16 + 1) / 2 * 2 * nb > VF_N_COUNTERS) return false;   // a counter per tile of the down projection
     // the gain slice of a normalising phase is staged where the partial sums go later
     const int red_bytes = (FW / 2) * 2 * nb * 1024;
     auto slice_bytes = [&](int ks) { return (d / 32 + ks - 1) / ks * 128; };
     if (slice_bytes(sp->gu) > red_bytes || slice_bytes(sp->qkv) > red_bytes || slice_bytes(sp->head) > red_bytes)
         return false;
     // partial tiles of the split phases: units * ks tiles of UB * NB * 256 floats
-    size_t tiles = std::max(std::max((nq + 2 * nkv) / 16 * sp->qkv, d / 16 * sp->o),
-                            std::max(F / 16 * sp->gu, (d / 16 + 1) / 2 * sp->down));
+    size_t tiles = std::max((nq + 2 * nkv) / 16 * sp->qkv, std::max(F / 16 * sp->gu, (d / 16 + 1) / 2 * sp->down));
     if (sp->head > 1) tiles = std::max(tiles, (size_t)((c.vocab / 16 + 1) / 2) * sp->head);
     *part_floats = tiles * 2 * nb * 256;
     return true;
@@ -1498,7 +1619,6 @@ static bool plan_fused(const vf_model *m, const Batch &b, FusedArgs &a, int *G_o
     size_t pf = 0;
     if (!plan_splits(m->cfg, rows, nb, &sp, &pf) || pf > m->part_floats) return false;
     a.ks_qkv = sp.qkv;
-    a.ks_o = sp.o;
     a.ks_gu = sp.gu;
     a.ks_down = sp.down;
     a.ks_head = sp.head;
@@ -1601,7 +1721,7 @@ int vf_run_fused(vf_model *m, const Batch &b, const int32_t *tokens, float *logi
         {
             // one unit for each workgroup of the O projection, if the others can take the rest in at most
             // three units each (two passes)
-            const int n_o = (c.d_model / 16) * a.ks_o, units = c.d_ffn / 16, H = G - n_o;
+            const int n_o = c.d_model / 16, units = c.d_ffn / 16, H = G - n_o;
             a.gu_light = (FUSED_GU_LIGHT && n_o > 0 && H > 0 && n_o < units && units - n_o <= 3 * H && units - n_o > H) ? n_o : 0;
         }
         a.wave_head = fits && a.ks_head == 1;
