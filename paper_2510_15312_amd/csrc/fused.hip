@@ -40,9 +40,6 @@ constexpr int ATT_COUNTERS = 4096;  // arrival counters of the attention blocks 
 constexpr int LDS_BYTES = 152 * 1024;  // dynamic LDS of the one workgroup a CU holds (160 KB less the static part)
 constexpr long long SPIN_LIMIT = 4000000;  // polls before a barrier gives up (seconds, not microseconds)
 
-#ifndef FUSED_PREFETCH_EARLY
-#define FUSED_PREFETCH_EARLY 1   // first weight loads of a phase go out before the barrier wait
-#endif
 #ifndef FUSED_AHEAD
 #define FUSED_AHEAD 3          // gate/up, down and head phases: this many steps of the item after next are held in registers too (0: off)
 #endif
@@ -85,7 +82,8 @@ struct FusedLayer {
 };
 
 struct FusedArgs {
-    const FusedLayer *layers;
+    FusedLayer layer0;              // the first layer's parameters; the others follow at equal distances
+    unsigned long long layer_bytes;
     const bf16_t *embed;
     const u32x4 *lm_head;
     const float *final_norm, *cosv, *sinv;
@@ -233,38 +231,24 @@ __device__ __forceinline__ void embed_phase(const FusedArgs &a, const Batch &b) 
 #ifndef FUSED_BB_AHEAD
 #define FUSED_BB_AHEAD 1          // GEMM phases: activation fragments are read from LDS this many steps ahead of their MFMAs (0: right before)
 #endif
-#ifndef FUSED_EPI_PREFETCH
-#define FUSED_EPI_PREFETCH 1      // what an epilogue reads from memory is requested before the item's MFMA loop
-#endif
 #ifndef FUSED_SGB
 #define FUSED_SGB 1               // GEMM phases: LDS reads are scheduled this many steps ahead of their MFMAs (0: left to the compiler)
 #endif
-#ifndef FUSED_XP
-#define FUSED_XP 16                // activation staging: loads in flight per thread (a multiple of FUSED_STAGE_GROUP)
-#endif
-#ifndef FUSED_STAGE_GROUP
-#define FUSED_STAGE_GROUP 4       // staging of a normalising phase: pieces whose LDS reads (1/rms, gain) are issued together
-#endif
 
-// Epilogues of the persistent kernel.  What they read from memory is requested before the item's
-// MFMA loop (epi_prefetch) and only used after it, so that no round trip is left between the last
-// MFMA and the stores.
+// Epilogues of the persistent kernel.  What they read from memory is requested ahead of the products, for a phase's
+// first item before the grid barrier, so that no round trip is left between the last product and the stores.
 //   QKV: bias, rotary embedding, q to its buffer, K and V rows into the cache (row table in LDS)
 //   residual: h = h_in + y, and the tile's sums of squares for the next RMSNorm
 struct EpiPre { floatx4 v, bias; };
-template <int EPI>
-__device__ __forceinline__ EpiPre epi_prefetch(const FastGemm &g, const FusedShared &sh, int row, int nb, int lane) {
+// nb: the same for all lanes
+template <int HD>
+__device__ __forceinline__ EpiPre epi_qkv_ask(const FastGemm &g, const FusedShared &sh, int row, int nb, int lane) {
     EpiPre p;
-    p.v = floatx4{0.f, 0.f, 0.f, 0.f};
     p.bias = floatx4{0.f, 0.f, 0.f, 0.f};
-    const int n0 = nb * 16 + (lane >> 4) * 4;
-    if (EPI == EPI_QKV && g.bias) p.bias = load_global_f4(g.bias + n0);
-    if (EPI == EPI_QKV) {
-        const int half = g.hd >> 1, i0 = (n0 % g.hd) >> 1;
-        const size_t at = (size_t)sh.rows[row].pos * half + i0;   // past the K heads: loaded, not used
-        const float2 c = *reinterpret_cast<const float2 *>(g.cosv + at), sn = *reinterpret_cast<const float2 *>(g.sinv + at);
-        p.v = floatx4{c.x, sn.x, c.y, sn.y};
-    }
+    if (g.bias) p.bias = load_global_f4(g.bias + nb * 16 + (lane >> 4) * 4);
+    const unsigned at = sh.rows[row].pos * (HD / 2) + (((nb * 16) % HD + (lane >> 4) * 4) >> 1);   // past the K heads: loaded, not used
+    const float2 c = *reinterpret_cast<const float2 *>(g.cosv + at), sn = *reinterpret_cast<const float2 *>(g.sinv + at);
+    p.v = floatx4{c.x, sn.x, c.y, sn.y};
     return p;
 }
 __device__ __forceinline__ void epi_resid_pre(const FastGemm &g, int row, bool live, int nb, int lane, floatx4 v, const EpiPre &pre) {
@@ -279,35 +263,34 @@ __device__ __forceinline__ void epi_resid_pre(const FastGemm &g, int row, bool l
     ssq += __shfl_xor(ssq, 32, 64);
     if (live && (lane >> 4) == 0) st_f32<true>(g.ss_out + nb * 64 + row, ssq);
 }
-__device__ __forceinline__ void epi_qkv_pre(const FastGemm &g, const FusedShared &sh, int row, int nb, int lane, floatx4 v, const EpiPre &pre) {
-    const int n0 = nb * 16 + (lane >> 4) * 4;
-    const int hd = g.hd, half = hd >> 1;
+template <int HD>
+__device__ __forceinline__ void epi_qkv_store(const FastGemm &g, const FusedShared &sh, int row, int nb, int lane, floatx4 v, const EpiPre &pre) {
+    const int head = nb * 16 / HD, p0 = nb * 16 % HD + (lane >> 4) * 4;   // the head is the same for all lanes
     v += pre.bias;
     const RowMeta rm = sh.rows[row];
     if (!rm.live) return;
-    const int head = n0 / hd, p0 = n0 % hd;
     if (head < g.hq + g.hkv) {
-        const int i0 = p0 >> 1;  // packed columns 2i, 2i+1 are elements i and i + hd/2
+        const int i0 = p0 >> 1;  // packed columns 2i, 2i+1 are elements i and i + HD/2
         const float c0 = pre.v[0], s0 = pre.v[1], c1 = pre.v[2], s1 = pre.v[3];
         const float a0 = v[0] * c0 - v[1] * s0, b0 = v[1] * c0 + v[0] * s0;
         const float a1 = v[2] * c1 - v[3] * s1, b1 = v[3] * c1 + v[2] * s1;
         // i0 is even: elements i0, i0 + 1 are neighbours in either layout, 4-byte aligned
         bf16_t *d0, *d1;
         if (head < g.hq) {
-            d0 = g.q + ((size_t)row * g.hq + head) * hd + i0;
-            d1 = d0 + half;
+            d0 = g.q + ((size_t)row * g.hq + head) * HD + i0;
+            d1 = d0 + HD / 2;
         } else {
-            d0 = rm.kv + kv_k_index(g.layer, rm.n_pages, rm.page, g.hkv, head - g.hq, rm.tin, i0, hd);
-            d1 = rm.kv + kv_k_index(g.layer, rm.n_pages, rm.page, g.hkv, head - g.hq, rm.tin, i0 + half, hd);
+            d0 = rm.kv + kv_k_index(g.layer, rm.n_pages, rm.page, g.hkv, head - g.hq, rm.tin, i0, HD);
+            d1 = rm.kv + kv_k_index(g.layer, rm.n_pages, rm.page, g.hkv, head - g.hq, rm.tin, i0 + HD / 2, HD);
         }
         st_u32<true>(d0, pack2_bf16(a0, a1));
         st_u32<true>(d1, pack2_bf16(b0, b1));
     } else {
-        const int vh = head - g.hq - g.hkv;
-        for (int i = 0; i < 4; ++i) {
+        bf16_t *d = rm.kv + kv_v_index(g.layer, rm.n_pages, rm.page, g.hkv, head - g.hq - g.hkv, rm.tin, p0, HD);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {   // four dimensions of a key: 16 bytes apart
             const bf16_t x = (bf16_t)v[i];
-            st_u16<true>(rm.kv + kv_v_index(g.layer, rm.n_pages, rm.page, g.hkv, vh, rm.tin, p0 + i, hd),
-                         __builtin_bit_cast(unsigned short, x));
+            st_u16<true>(d + i * 8, __builtin_bit_cast(unsigned short, x));
         }
     }
 }
@@ -322,41 +305,152 @@ __device__ __forceinline__ void epi_swiglu_frag(const FastGemm &g, int row, int 
     st_u32<true>(out + 128, pack2_bf16(act(v1[0], v1[1]), act(v1[2], v1[3])));
 }
 
-// Second half of the staging of a normalising phase: x = bf16(h * rstd * gain) for the XP pieces
-// (four columns of one row each) this thread loaded, written to the staged activations.  The three
-// LDS arrays are distinct (restrict), which lets the reads of later pieces pass the writes of
-// earlier ones.  No branch: a piece past the last row was loaded from the last row (clamped) and is
-// written there again, the same value its owner writes.
-template <int XP>
-__device__ __forceinline__ void scale_and_stage(const floatx4 (&v)[XP], const float *__restrict__ rs, const float *__restrict__ gain,
-                                                u32x2 *__restrict__ out, int row, int c, int qstep, int rstep, int chunks, int m) {
-    constexpr int GRP = FUSED_STAGE_GROUP;  // pieces whose LDS reads are issued together
+// Staging of a normalising phase: x = bf16(h * rstd * gain) of nk k-blocks of all rows, to LDS as [k-block][row][32].
+// What bounds it is instruction issue: two wavefronts a SIMD, every instruction of a piece (four columns of a row per
+// lane) at four to five cycles.  So a wavefront takes whole rows, w, w + 8, ...: its columns are the same in every row,
+// and gain, load and LDS offsets stay in registers, worked out before the grid barrier; what is left of a piece is
+// its load, eight products, two conversions, an addition and its write.  Two rows are in flight per wavefront, and
+// none is loaded that is not needed: with few rows the loads themselves (16 cycles each in the vector cache) were
+// most of it.  Release to staged, 1 row of 0.5B: 3.0 us with pieces dealt to threads in turn and 16 loads a thread,
+// 1.7 with pieces dealt to wavefronts and as many loads as a call needs, 1.1 so; 17 rows of 1.5B 3.2, 3.0, 2.2 us.
+// 1/rms from the producer's sums of squares per 16 columns: wavefront w adds blocks w, w + 8, ... of row `lane`
+// (one contiguous load a block), the eight sums meet in LDS, and every wavefront adds them up for itself.
+// pieces of a row in one pass: rows of up to 1024 columns with heads of 64, 1536 with heads of 128
+constexpr int JP_OF(int hd) { return hd == 64 ? 4 : 6; }
+template <int JP> struct NormStage {
+    static constexpr int TS = 12;   // sums of squares requested ahead of the rows
+    floatx4 gain[JP];
+    unsigned off[JP], out[JP];      // bytes: of the lane's piece j in a row's slice, and in the staged k-blocks (row 0)
+    const float *h, *gain_p, *ss;
+    int K, n_ss, m, chunks;
+    float inv_d, eps;
+
+    // columns of pieces seg * 64 JP ..: a slice of more than 64 JP pieces takes several passes over the rows
+    __device__ __forceinline__ void columns(int seg, int lane) {
 #pragma unroll
-    for (int i0 = 0; i0 < XP; i0 += GRP) {
-        float r[GRP];
-        floatx4 gv[GRP];
-        int at[GRP];
-#pragma unroll
-        for (int j = 0; j < GRP; ++j) {
-            const int rr = min(row, m - 1);
-            r[j] = rs[rr];
-            gv[j] = *reinterpret_cast<const floatx4 *>(gain + c * 4);
-            at[j] = ((c >> 3) * m + rr) * 8 + (c & 7);
-            row += qstep;
-            c += rstep;
-            if (c >= chunks) { c -= chunks; ++row; }
+        for (int j = 0; j < JP; ++j) {
+            const int c = min((seg * JP + j) * 64 + lane, chunks - 1);   // past the end: the last piece, written again
+            off[j] = c * 16;
+            out[j] = (c >> 3) * m * 64 + (c & 7) * 8;
+            gain[j] = load_global_f4(gain_p + c * 4);
         }
-        asm volatile("" ::: "memory");  // the group's reads are issued before its first product
+    }
+    // before the barrier.  h, gain: first column of the slice; K: stride of h; nk: k-blocks of the slice
+    __device__ __forceinline__ void init(const FastGemm &g, int kb0, int nk, int lane) {
+        h = g.Xh + (size_t)kb0 * 32;
+        gain_p = g.gain + (size_t)kb0 * 32;
+        ss = g.ss_in;
+        K = g.KB * 32;
+        n_ss = g.n_ss;
+        m = g.m;
+        chunks = nk * 8;
+        inv_d = g.inv_d;
+        eps = g.eps;
+        columns(0, lane);
+    }
+    __device__ __forceinline__ void load(floatx4 (&v)[JP], int row) const {
+        const char *src = reinterpret_cast<const char *>(h + (size_t)row * K);   // the same for all lanes
 #pragma unroll
-        for (int j = 0; j < GRP; ++j) {
-            if (i0 + j < XP) {
-                const floatx4 x = v[i0 + j < XP ? i0 + j : 0];
-                out[at[j]] = pack4_bf16(x[0] * r[j] * gv[j][0], x[1] * r[j] * gv[j][1], x[2] * r[j] * gv[j][2], x[3] * r[j] * gv[j][3]);
+        for (int j = 0; j < JP; ++j) v[j] = ssa_load_f4(reinterpret_cast<const float *>(src + off[j]));
+        asm volatile("" ::: "memory");
+    }
+    __device__ __forceinline__ void put(const floatx4 (&v)[JP], int row, float rs, unsigned char *xs) const {
+        const float r = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, rs), row));
+#pragma unroll
+        for (int j = 0; j < JP; ++j) {
+            const floatx4 x = v[j], gv = gain[j];
+            *reinterpret_cast<u32x2 *>(xs + (out[j] + row * 64)) = pack4_bf16(x[0] * r * gv[0], x[1] * r * gv[1], x[2] * r * gv[2], x[3] * r * gv[3]);
+        }
+    }
+    __device__ __forceinline__ void ask(float (&t)[TS], int lane, int wave) const {
+        const float *p = ss + min(lane, m - 1);
+#pragma unroll
+        for (int i = 0; i < TS; ++i) t[i] = ssa_load_f1(p + min(wave + i * FW, n_ss - 1) * 64);   // the block is the same for all lanes
+        asm volatile("" ::: "memory");   // all of them before the first is used
+    }
+    // 1/rms of row `lane`; a workgroup barrier inside
+    __device__ __forceinline__ float rms(const float (&t)[TS], FusedShared &sh, int lane, int wave) const {
+        float sum = 0.f;
+#pragma unroll
+        for (int i = 0; i < TS; ++i) sum += t[i] * (wave + i * FW < n_ss ? 1.f : 0.f);
+        for (int b = wave + TS * FW; b < n_ss; b += 4 * FW) {
+            float r[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) r[i] = ssa_load_f1(ss + min(b + i * FW, n_ss - 1) * 64 + min(lane, m - 1)) * (b + i * FW < n_ss ? 1.f : 0.f);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) sum += r[i];
+        }
+        sh.rs_tmp[wave][lane] = sum;
+        lds_sync();
+        float part[FW], tot = 0.f;
+#pragma unroll
+        for (int i = 0; i < FW; ++i) part[i] = sh.rs_tmp[i][lane];
+        asm volatile("" ::: "memory");  // the eight reads are issued together
+#pragma unroll
+        for (int i = 0; i < FW; ++i) tot += part[i];
+        return 1.0f / sqrtf(tot * inv_d + eps);
+    }
+    // Rows wave, wave + 8, ... from the k-th on, n of them, rows k and k + 1 in flight in a and b.  The branches are
+    // the same for all lanes, and every path waits only for what it uses next.
+    __device__ __forceinline__ void rows(floatx4 (&a)[JP], floatx4 (&b)[JP], int n, float rs, unsigned char *xs, int wave) const {
+        for (int k = 0;; k += 2) {
+            put(a, wave + k * FW, rs, xs);
+            if (k + 2 >= n) {
+                put(b, wave + (k + 1) * FW, rs, xs);
+                return;
+            }
+            load(a, wave + (k + 2) * FW);
+            put(b, wave + (k + 1) * FW, rs, xs);
+            if (k + 3 >= n) {
+                put(a, wave + (k + 2) * FW, rs, xs);
+                return;
+            }
+            load(b, wave + (k + 3) * FW);
+        }
+    }
+    // behind the barrier
+    __device__ __forceinline__ void run(unsigned char *xs, FusedShared &sh, int lane, int wave TRACE_ARG) {
+        const int n = m > wave ? (m - wave + FW - 1) / FW : 0;   // this wavefront's rows
+        float t[TS], rs;
+        ask(t, lane, wave);
+        if (n == 0) {
+            rs = rms(t, sh, lane, wave);
+        } else if (n == 1) {
+            floatx4 a[JP];
+            load(a, wave);
+            rs = rms(t, sh, lane, wave);
+            TRACE(7);
+            put(a, wave, rs, xs);
+        } else {
+            floatx4 a[JP], b[JP];
+            load(a, wave);
+            load(b, wave + FW);
+            rs = rms(t, sh, lane, wave);
+            TRACE(7);
+            rows(a, b, n, rs, xs, wave);
+        }
+        for (int seg = 1; seg * 64 * JP < chunks; ++seg) {
+            columns(seg, lane);
+            floatx4 a[JP], b[JP];
+            if (n == 1) {
+                load(a, wave);
+                put(a, wave, rs, xs);
+            } else if (n > 1) {
+                load(a, wave);
+                load(b, wave + FW);
+                rows(a, b, n, rs, xs, wave);
             }
         }
     }
-}
+};
 
+// A workgroup's items in a GEMM phase: units unit0 + i * ustep, i < n_my, of K split `split`; worked out once per launch.
+// Workgroup w takes items w, w + G, ... of (unit, split): the splits divide G, or there is one item per workgroup at most.
+struct Items { int unit0, ustep, split, n_my; };
+__device__ __forceinline__ Items items_of(int units, int ks) {
+    const int w = blockIdx.x, G = gridDim.x, n = units * ks;
+    return Items{w / ks, G / ks, w % ks, w < n ? (n - w + G - 1) / G : 0};
+}
 // ---- GEMM phase -------------------------------------------------------------------------------------
 // Work items = (unit of UB weight blocks) x (K split); workgroup w takes items w, w + G, ...  G is
 // a multiple of ks, so all items of a workgroup share one K slice and its activations are staged
@@ -366,30 +460,23 @@ __device__ __forceinline__ void scale_and_stage(const floatx4 (&v)[XP], const fl
 // next item's fragments in the last round.  Trip counts are the same for every wavefront, so the
 // loop has no divergent branches.  The caller has arrived at the grid barrier; this function
 // waits on it after issuing the first loads.
-template <int NB, int UB, int PD, int EPI>
-__device__ __forceinline__ void gemm_phase(const FastGemm &g, const Batch &b, GridBar &bar, unsigned char *smem,
+template <int NB, int HD, int UB, int PD, int EPI>
+__device__ __forceinline__ void gemm_phase(const FastGemm &g, const Items &im, GridBar &bar, unsigned char *smem,
                                   int lds_total, FusedShared &sh TRACE_ARG) {
-    static_assert(EPI != EPI_RESID, "resid_phase");
-    constexpr bool COH = EPI != EPI_LOGITS;  // logits are read by the next kernel only
+    static_assert(EPI == EPI_SWIGLU || EPI == EPI_LOGITS, "gate/up and output head");
     constexpr int RW = FW / 2;               // wavefronts whose partial sums sit in LDS at a time
     constexpr int RED_BYTES = RW * 2 * NB * 1024;
-    constexpr int XP = FUSED_XP;
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));  // per-thread index math is redone per phase instead of living across all of them
-    const int lane = tid & 63, wave = tid >> 6;
-    const int G = gridDim.x, wg = blockIdx.x;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int m = g.m, KB = g.KB, NBt = g.N >> 4;
-    const int n_units = (NBt + UB - 1) / UB;
-    const int items = n_units * g.ks;
-    const int n_my = wg < items ? (items - wg + G - 1) / G : 0;
-    const int split = wg % g.ks;
+    const int n_my = im.n_my, split = im.split;
     const int kb0 = split * g.kbps, kb1 = min(KB, kb0 + g.kbps), nk = kb1 - kb0;
     const int cnt = (nk + FW - 1) / FW;          // k-blocks per wavefront, the same for all
     const int rounds = (cnt + PD - 1) / PD;
     const int wk0 = kb0 + wave * cnt;            // this wavefront's run: wk0 .. wk0 + cnt - 1, valid below kb1
     u32x4 *xs = reinterpret_cast<u32x4 *>(smem);
     floatx4 *red = reinterpret_cast<floatx4 *>(smem + lds_total - RED_BYTES);
-    float *gain_s = reinterpret_cast<float *>(smem + lds_total - RED_BYTES);  // staging only: red is idle then
 
     global_w_ptr wp[UB], wpn[UB];
     u32x4 w[PD][UB];
@@ -409,7 +496,7 @@ __device__ __forceinline__ void gemm_phase(const FastGemm &g, const Batch &b, Gr
 #pragma unroll
         for (int u = 0; u < UB; ++u) w2[d][u] = u32x4{0u, 0u, 0u, 0u};
     auto unit_ptrs = [&](int it, global_w_ptr (&dst)[UB]) {
-        const int unit = (wg + it * G) / g.ks;
+        const int unit = im.unit0 + it * im.ustep;
 #pragma unroll
         for (int u = 0; u < UB; ++u) dst[u] = (global_w_ptr)g.W + (size_t)min(unit * UB + u, NBt - 1) * KB * 64 + lane;
     };
@@ -433,72 +520,17 @@ __device__ __forceinline__ void gemm_phase(const FastGemm &g, const Batch &b, Gr
                 for (int u = 0; u < UB; ++u) w2[d][u] = frag(wpa[u], min(d, cnt - 1));
         }
     };
-    if (FUSED_PREFETCH_EARLY && n_my > 0) first_fragments();
+    NormStage<JP_OF(HD)> ns;
+    if (n_my > 0) {
+        ns.init(g, kb0, nk, lane);
+        first_fragments();
+    }
     TRACE(1);
     bar.wait();
     TRACE(2);
     if (n_my == 0) return;
 
-    // ---- stage the activations of this K slice: every global load goes out before the first use ----
-    {
-        // x = bf16(h * rstd * gain) with rstd = 1/rms from the per-16-column sums of squares
-        // (lane = row, wavefront = every FW-th block of columns); pieces of four columns
-        const int chunks = nk * 8, pieces = m * chunks;
-        const int qstep = FT / chunks, rstep = FT % chunks;
-        // sums of squares of the column blocks wave, wave + FW, ... of row `lane`: the block index is
-        // the same for the whole wavefront, so the scalar unit forms each address (uniform base +
-        // per-lane offset) and the 0/1 factor of a block past the last.  Lanes past the last row
-        // read the last row's sums; their 1/rms is never used.
-        float t[16];
-        const int wave_s = __builtin_amdgcn_readfirstlane(wave);
-        const unsigned ss_lane = (unsigned)min(lane, m - 1);
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const int j = wave_s + i * FW;
-            t[i] = ssa_load_f1(g.ss_in + min(j, g.n_ss - 1) * 64 + ss_lane) * (j < g.n_ss ? 1.f : 0.f);
-        }
-        floatx4 gn = load_global_f4(g.gain + (size_t)kb0 * 32 + min(tid, chunks - 1) * 4);
-        const float *xh_slice = g.Xh + (size_t)kb0 * 32;
-        for (int base = 0; base < pieces; base += FT * XP) {
-            floatx4 v[XP];
-            int row = (base + tid) / chunks, c = (base + tid) % chunks;
-            const int row0 = row, c0 = c;
-#pragma unroll
-            for (int i = 0; i < XP; ++i) {
-                v[i] = ssa_load_f4(xh_slice + (unsigned)(min(row, m - 1) * KB * 32 + c * 4));  // uniform base + 32-bit offset
-                row += qstep;
-                c += rstep;
-                if (c >= chunks) { c -= chunks; ++row; }
-            }
-            if (base == 0) {
-                if (!FUSED_PREFETCH_EARLY) first_fragments();
-                float sum = 0.f;
-#pragma unroll
-                for (int i = 0; i < 16; ++i) sum += t[i];
-                if (lane < m)
-                    for (int j = wave + 16 * FW; j < g.n_ss; j += FW) sum += ssa_load_f1(g.ss_in + j * 64 + lane);
-                sh.rs_tmp[wave][lane] = sum;
-                for (int cc = tid; cc < chunks; cc += FT) {
-                    if (cc != tid) gn = load_global_f4(g.gain + (size_t)kb0 * 32 + cc * 4);
-                    *reinterpret_cast<floatx4 *>(gain_s + cc * 4) = gn;
-                }
-                lds_sync();
-                TRACE(6);
-                if (tid < 64) {
-                    float part[FW], tot = 0.f;
-#pragma unroll
-                    for (int j = 0; j < FW; ++j) part[j] = sh.rs_tmp[j][tid];
-                    asm volatile("" ::: "memory");  // the eight reads are issued together
-#pragma unroll
-                    for (int j = 0; j < FW; ++j) tot += part[j];
-                    sh.rs_s[tid] = 1.0f / sqrtf(tot * g.inv_d + g.eps);
-                }
-                lds_sync();
-                TRACE(7);
-            }
-            scale_and_stage<XP>(v, sh.rs_s, gain_s, reinterpret_cast<u32x2 *>(xs), row0, c0, qstep, rstep, chunks, m);
-        }
-    }
+    ns.run(smem, sh, lane, wave TRACE_PASS);
     lds_sync();
     TRACE(3);
 
@@ -514,22 +546,13 @@ __device__ __forceinline__ void gemm_phase(const FastGemm &g, const Batch &b, Gr
         const bool has_ahead = AHEAD && it + 2 < n_my;
         unit_ptrs(has_next ? it + 1 : it, wpn);
         if (AHEAD) unit_ptrs(has_ahead ? it + 2 : it, wpa);
-        const int unit = (wg + it * G) / g.ks;
+        const int unit = im.unit0 + it * im.ustep;
         const int nb0 = unit * UB;
         floatx4 acc[UB][NB];
 #pragma unroll
         for (int u = 0; u < UB; ++u)
 #pragma unroll
             for (int c = 0; c < NB; ++c) acc[u][c] = floatx4{0.f, 0.f, 0.f, 0.f};
-        // this thread's epilogue tile (whole wavefronts: NTH is a multiple of 64) and what its epilogue reads
-        constexpr int NTH_ = EPI == EPI_SWIGLU ? NB * 64 : UB * NB * 64;
-        EpiPre pre;
-        pre.v = floatx4{0.f, 0.f, 0.f, 0.f};
-        pre.bias = floatx4{0.f, 0.f, 0.f, 0.f};
-        if (FUSED_EPI_PREFETCH && EPI == EPI_QKV && tid < NTH_) {
-            const int eu = tid / (NB * 64), ec = (tid >> 6) % NB;
-            pre = epi_prefetch<EPI>(g, sh, min(ec * 16 + (lane & 15), m - 1), min(nb0 + eu, NBt - 1), lane);
-        }
         // One round = PD steps of straight-line code.  REFILL: after its use every slot is loaded
         // again, with the same item's next round or, in the last round, the next item's first; the
         // final round of the final item has nothing left to load and runs without.
@@ -697,9 +720,7 @@ __device__ __forceinline__ void gemm_phase(const FastGemm &g, const Batch &b, Gr
             const int row = c * 16 + (lane & 15);
             const bool live = row < m && nb < NBt;
             if (live) {
-                if (EPI == EPI_QKV && FUSED_EPI_PREFETCH) epi_qkv_pre(g, sh, row, nb, lane, v0, pre);
-                else if (EPI == EPI_QKV) epi_qkv<COH>(g, b, row, nb, lane, v0);
-                else if (EPI == EPI_SWIGLU) epi_swiglu_frag<NB>(g, row, nb, lane, v0, v1);
+                if (EPI == EPI_SWIGLU) epi_swiglu_frag<NB>(g, row, nb, lane, v0, v1);
                 else __builtin_nontemporal_store(v0, reinterpret_cast<floatx4 *>(g.logits + (size_t)row * g.N + nb * 16 + (lane >> 4) * 4));
             }
         }
@@ -709,6 +730,129 @@ __device__ __forceinline__ void gemm_phase(const FastGemm &g, const Batch &b, Gr
 #pragma unroll
             for (int u = 0; u < UB; ++u) wp[u] = wpn[u];
         }
+    }
+}
+
+// ---- sums over wavefronts and K splits -------------------------------------------------------------------
+// red: partial tiles [tile][wavefront][lane].  Pairs (w, w + 4), then the four pairs in order.
+__device__ __forceinline__ floatx4 sum_waves(const floatx4 *red, int tile, int lane) {
+    floatx4 p[FW], v = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < FW; ++i) p[i] = red[(tile * FW + i) * 64 + lane];
+    asm volatile("" ::: "memory");   // all reads are issued before the first sum
+#pragma unroll
+    for (int i = 0; i < FW / 2; ++i) v += p[i] + p[i + FW / 2];
+    return v;
+}
+// K splits of a tile meet: this split's sums go to part (of split 0; the next splits' at `stride` floats each), the
+// last to count itself in adds all of them in split order.  True: v is the whole sum.
+__device__ __forceinline__ bool meet_splits(floatx4 &v, float *part, int *counter, int split, int ks, int stride, int lane) {
+    part += lane * 4;
+    store_coherent(part + (size_t)split * stride, v);
+    stores_done();
+    int old = 0;
+    if (lane == 0) old = __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (__builtin_amdgcn_readfirstlane(old) != ks - 1) return false;
+    if (lane == 0) __hip_atomic_store(counter, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    v = floatx4{0.f, 0.f, 0.f, 0.f};
+    for (int sp0 = 0; sp0 < ks; sp0 += 8) {
+        floatx4 t[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) t[i] = load_coherent(part + (size_t)min(sp0 + i, ks - 1) * stride);
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            if (sp0 + i < ks) v += t[i];
+    }
+    return true;
+}
+
+// ---- QKV phase --------------------------------------------------------------------------------------------
+// One 16-row weight block per item; the wavefronts share its K slice.  Few items a workgroup (one at the 0.5B and
+// 1.5B shapes, whose weights are then all requested before the barrier), so what counts is the chain behind the
+// barrier: staging, one read of the wavefront's activation fragments, products, the sum over the wavefronts.
+template <int NB, int HD, int JP>
+__device__ __forceinline__ void qkv_phase(const FastGemm &g, const Items &im, GridBar &bar, unsigned char *smem, int lds_total,
+                                          FusedShared &sh TRACE_ARG) {
+    constexpr int PD = JP;   // k-blocks of a wavefront: an eighth of a pass's columns
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int m = g.m, KB = g.KB;
+    const int kb0 = im.split * g.kbps, kb1 = min(KB, kb0 + g.kbps), nk = kb1 - kb0;
+    const int cnt = (nk + FW - 1) / FW, rounds = (cnt + PD - 1) / PD;
+    const int wk0 = kb0 + wave * cnt, mine = min(cnt, kb1 - wk0);   // k-blocks wk0 .. wk0 + mine - 1 (none: mine <= 0)
+    floatx4 *red = reinterpret_cast<floatx4 *>(smem + lds_total - FW * NB * 1024);
+    const int row = wave * 16 + (lane & 15);   // wavefront c < NB finishes the tile of row block c
+    global_w_ptr W = (global_w_ptr)g.W;
+
+    u32x4 w[PD];
+#pragma unroll
+    for (int d = 0; d < PD; ++d) w[d] = u32x4{0u, 0u, 0u, 0u};
+    auto load_w = [&](int unit, int d, int kbl) {   // never predicated: see resid_phase
+        w[d] = __builtin_nontemporal_load(W + ((size_t)unit * KB + min(wk0 + min(kbl, cnt - 1), kb1 - 1)) * 64 + lane);
+    };
+    NormStage<JP> ns;
+    EpiPre pre;
+    pre.v = pre.bias = floatx4{0.f, 0.f, 0.f, 0.f};
+    if (im.n_my > 0) {
+        ns.init(g, kb0, nk, lane);
+#pragma unroll
+        for (int d = 0; d < PD; ++d) load_w(im.unit0, d, d);
+        if (wave < NB) pre = epi_qkv_ask<HD>(g, sh, min(row, m - 1), im.unit0, lane);
+    }
+    TRACE(1);
+    bar.wait();
+    TRACE(2);
+    if (im.n_my <= 0) return;
+    ns.run(smem, sh, lane, wave TRACE_PASS);
+    lds_sync();
+    TRACE(3);
+    // lane's 16 bytes of row block 0 in a k-block; rows past the last read what lies behind (their columns of the
+    // product are not stored)
+    const unsigned char *xl = smem + (lane & 15) * 64 + (lane >> 4) * 16;
+    for (int it = 0; it < im.n_my; ++it) {
+        const int unit = im.unit0 + it * im.ustep;
+        const bool has_next = it + 1 < im.n_my;
+        floatx4 acc[NB];
+#pragma unroll
+        for (int c = 0; c < NB; ++c) acc[c] = floatx4{0.f, 0.f, 0.f, 0.f};
+        auto round_body = [&](auto refill_tag, int r) {
+            constexpr bool REFILL = decltype(refill_tag)::value;
+            const bool last_round = r + 1 == rounds;
+            bf16x8 x[PD][NB];
+#pragma unroll
+            for (int d = 0; d < PD; ++d) {
+                const int kx = min(wk0 + min(r * PD + d, cnt - 1), kb1 - 1) - kb0;
+#pragma unroll
+                for (int c = 0; c < NB; ++c) x[d][c] = *reinterpret_cast<const bf16x8 *>(xl + kx * m * 64 + c * 1024);
+            }
+#pragma unroll
+            for (int d = 0; d < PD; ++d) {
+                if (r * PD + d < mine) {
+#pragma unroll
+                    for (int c = 0; c < NB; ++c)
+                        acc[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[d]), x[d][c], acc[c], 0, 0, 0);
+                }
+                if (REFILL) load_w(last_round ? unit + im.ustep : unit, d, last_round ? d : (r + 1) * PD + d);
+            }
+        };
+#pragma unroll 1
+        for (int r = 0; r + 1 < rounds; ++r) round_body(std::true_type{}, r);
+        if (has_next) round_body(std::true_type{}, rounds - 1);
+        else round_body(std::false_type{}, rounds - 1);
+        TRACE(4);
+        if (it) lds_sync();   // the previous item's sums have been read
+#pragma unroll
+        for (int c = 0; c < NB; ++c) red[(c * FW + wave) * 64 + lane] = acc[c];
+        lds_sync();
+        if (wave < NB) {
+            floatx4 v = sum_waves(red, wave, lane);
+            bool whole = true;
+            if (g.ks > 1) whole = meet_splits(v, g.part + ((size_t)unit * g.ks * NB + wave) * 256, g.counters + unit * NB + wave, im.split, g.ks, NB * 256, lane);
+            if (whole && row < m) epi_qkv_store<HD>(g, sh, row, unit, lane, v, pre);
+            if (has_next) pre = epi_qkv_ask<HD>(g, sh, min(row, m - 1), unit + im.ustep, lane);
+        }
+        TRACE(5);
     }
 }
 
@@ -731,7 +875,7 @@ struct ResidGemm {
     float *h, *ss_out, *part;
     int *counters;     // one per tile of a unit, zero between uses
     int N, KB, m, ks, kbps;
-    int unit0, ustep, split, n_my;   // this workgroup's items: units unit0 + i * ustep of K split `split`
+    Items im;
 };
 template <int NB, int UB, int PD>
 __device__ __forceinline__ void resid_phase(const ResidGemm &g, GridBar &bar, unsigned char *smem TRACE_ARG) {
@@ -741,7 +885,7 @@ __device__ __forceinline__ void resid_phase(const ResidGemm &g, GridBar &bar, un
     asm volatile("" : "+v"(tid));
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int KB = g.KB, NBt = g.N >> 4;
-    const int kb0 = g.split * g.kbps, kb1 = min(KB, kb0 + g.kbps);
+    const int kb0 = g.im.split * g.kbps, kb1 = min(KB, kb0 + g.kbps);
     const int cnt = (kb1 - kb0 + FW - 1) / FW, rounds = (cnt + PD - 1) / PD;
     const int wk0 = kb0 + wave * cnt, mine = min(cnt, kb1 - wk0);   // k-blocks wk0 .. wk0 + mine - 1 (none: mine <= 0)
     floatx4 *red = reinterpret_cast<floatx4 *>(smem);
@@ -771,20 +915,20 @@ __device__ __forceinline__ void resid_phase(const ResidGemm &g, GridBar &bar, un
     };
     EpiPre pre;
     pre.v = pre.bias = floatx4{0.f, 0.f, 0.f, 0.f};
-    if (g.n_my > 0) {
+    if (g.im.n_my > 0) {
 #pragma unroll
-        for (int d = 0; d < PD; ++d) load_w(g.unit0, d, d);
-        pre.v = load_h(g.unit0);   // written two or more barriers ago
+        for (int d = 0; d < PD; ++d) load_w(g.im.unit0, d, d);
+        pre.v = load_h(g.im.unit0);   // written two or more barriers ago
     }
     TRACE(1);
     bar.wait();
     TRACE(2);
-    if (g.n_my <= 0) return;
+    if (g.im.n_my <= 0) return;
 #pragma unroll
     for (int d = 0; d < PD; ++d) load_x(d, d);
-    for (int it = 0; it < g.n_my; ++it) {
-        const int unit = g.unit0 + it * g.ustep;
-        const bool has_next = it + 1 < g.n_my;
+    for (int it = 0; it < g.im.n_my; ++it) {
+        const int unit = g.im.unit0 + it * g.im.ustep;
+        const bool has_next = it + 1 < g.im.n_my;
         floatx4 acc[UB][NB];
 #pragma unroll
         for (int u = 0; u < UB; ++u)
@@ -793,7 +937,7 @@ __device__ __forceinline__ void resid_phase(const ResidGemm &g, GridBar &bar, un
         auto round_body = [&](auto refill_tag, int r) {
             constexpr bool REFILL = decltype(refill_tag)::value;
             const bool last_round = r + 1 == rounds;
-            const int nunit = last_round ? unit + g.ustep : unit, nk = last_round ? 0 : (r + 1) * PD;
+            const int nunit = last_round ? unit + g.im.ustep : unit, nk = last_round ? 0 : (r + 1) * PD;
 #pragma unroll
             for (int d = 0; d < PD; ++d) {
                 if (r * PD + d < mine) {
@@ -823,41 +967,16 @@ __device__ __forceinline__ void resid_phase(const ResidGemm &g, GridBar &bar, un
             for (int c = 0; c < NB; ++c) red[((u * NB + c) * FW + wave) * 64 + lane] = acc[u][c];
         lds_sync();
         if (wave < NTILE) {
-            floatx4 p[FW], v = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int i = 0; i < FW; ++i) p[i] = red[(wave * FW + i) * 64 + lane];
-            asm volatile("" ::: "memory");   // all reads are issued before the first sum
-#pragma unroll
-            for (int i = 0; i < FW / 2; ++i) v += p[i] + p[i + FW / 2];
-            bool last = true;
-            if (g.ks > 1) {
-                float *tile = g.part + ((size_t)unit * g.ks * NTILE + wave) * 256 + lane * 4;   // of split 0
-                store_coherent(tile + (size_t)g.split * NTILE * 256, v);
-                stores_done();
-                int old = 0;
-                int *cnt_p = g.counters + unit * NTILE + wave;
-                if (lane == 0) old = __hip_atomic_fetch_add(cnt_p, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                last = __builtin_amdgcn_readfirstlane(old) == g.ks - 1;
-                if (last) {
-                    if (lane == 0) __hip_atomic_store(cnt_p, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    v = floatx4{0.f, 0.f, 0.f, 0.f};
-                    for (int sp0 = 0; sp0 < g.ks; sp0 += 8) {
-                        floatx4 t[8];
-#pragma unroll
-                        for (int i = 0; i < 8; ++i) t[i] = load_coherent(tile + (size_t)min(sp0 + i, g.ks - 1) * NTILE * 256);
-#pragma unroll
-                        for (int i = 0; i < 8; ++i)
-                            if (sp0 + i < g.ks) v += t[i];
-                    }
-                }
-            }
+            floatx4 v = sum_waves(red, wave, lane);
+            bool whole = true;
+            if (g.ks > 1) whole = meet_splits(v, g.part + ((size_t)unit * g.ks * NTILE + wave) * 256, g.counters + unit * NTILE + wave, g.im.split, g.ks, NTILE * 256, lane);
             const int nb = unit * UB + tu;
-            if (last) {
+            if (whole) {
                 FastGemm e;
                 e.N = g.N; e.h = g.h; e.ss_out = g.ss_out;
                 epi_resid_pre(e, row, row < g.m && nb < NBt, nb, lane, v, pre);
             }
-            if (has_next) pre.v = load_h(unit + g.ustep);
+            if (has_next) pre.v = load_h(unit + g.im.ustep);
         }
         TRACE(5);
     }
@@ -876,9 +995,6 @@ __device__ __forceinline__ void resid_phase(const ResidGemm &g, GridBar &bar, un
 //            wavefront q of the unit adds the halves of row block q and applies SwiGLU.
 //   head:    blocks w, w + W, ... (W = wavefronts of the grid) per wavefront, full K, one after
 //            the other through the same ring; logits are stored from the accumulators.
-#ifndef FUSED_WRING
-#define FUSED_WRING 24
-#endif
 #ifndef FUSED_ATT_TOP
 #define FUSED_ATT_TOP 1         // attention items go to the workgroups at the top of the grid
 #endif
@@ -888,28 +1004,23 @@ __device__ __forceinline__ void resid_phase(const ResidGemm &g, GridBar &bar, un
 #ifndef FUSED_GU_REV
 #define FUSED_GU_REV 1          // gate/up: the units of a partial last range go to the workgroups at the top of the grid
 #endif
-#ifndef FUSED_WXP
-#define FUSED_WXP 8             // activation staging of these phases: loads in flight per thread (the ring is live meanwhile)
-#endif
 #ifndef FUSED_WAVE_PHASES
 #define FUSED_WAVE_PHASES 1     // 1: gate/up and the output head run this way when K is not split across workgroups
 #endif
-constexpr int WAVE_TAIL_BYTES = 24 * 1024;  // LDS kept free behind the staged activations: the gain vector (up to
-                                            // 6144 columns) while staging, then the tiles of a pass (FW * NB KB)
-template <int NB, int EPI>
+constexpr int wave_tail_bytes(int nb) { return FW * nb * 1024; }   // LDS behind the staged activations: the tiles of a pass
+template <int NB, int HD, int EPI>
 __device__ __forceinline__ void wave_phase(const FastGemm &g, int n_light, GridBar &bar, unsigned char *smem, int lds_total,
                                            FusedShared &sh TRACE_ARG) {
     static_assert(EPI == EPI_SWIGLU || EPI == EPI_LOGITS, "gate/up and output head");
-    static_assert(FW * NB * 1024 <= WAVE_TAIL_BYTES && NB <= 4, "a pass's tiles fit the tail; one row block per wavefront of a unit");
-    constexpr int RING = FUSED_WRING, XP = FUSED_WXP;
+    static_assert(NB <= 4, "one row block per wavefront of a unit");
+    constexpr int RING = HD == 64 ? 16 : 24;   // half a row of the narrow models' K, of 1536 columns
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int G = gridDim.x, wg = blockIdx.x;
     const int m = g.m, KB = g.KB, NBt = g.N >> 4;
     u32x4 *xs = reinterpret_cast<u32x4 *>(smem);
-    floatx4 *exch = reinterpret_cast<floatx4 *>(smem + lds_total - WAVE_TAIL_BYTES);
-    float *gain_s = reinterpret_cast<float *>(smem + lds_total - WAVE_TAIL_BYTES);  // staging only
+    floatx4 *exch = reinterpret_cast<floatx4 *>(smem + lds_total - wave_tail_bytes(NB));
 
     // this wavefront's tasks: block of task j = blk0 + j * bstride, all over the K range [kb_lo, kb_hi)
     // (gate/up: pass j, slot s covers units (2j + s) G .. + G; a range that the units fill only in part is
@@ -976,6 +1087,8 @@ __device__ __forceinline__ void wave_phase(const FastGemm &g, int n_light, GridB
         const size_t blk = (size_t)min(task_block(j), NBt - 1);
         return __builtin_nontemporal_load(wbase + (blk * KB + kb) * 64);
     };
+    NormStage<JP_OF(HD)> ns;
+    ns.init(g, 0, KB, lane);
     if (n_task > 0) {
 #pragma unroll
         for (int d = 0; d < RING; ++d) w[d] = frag(0, d);
@@ -984,57 +1097,7 @@ __device__ __forceinline__ void wave_phase(const FastGemm &g, int n_light, GridB
     bar.wait();
     TRACE(2);
 
-    // ---- stage x = bf16(h * rstd * gain) for the whole K (as in gemm_phase, one slice) ----
-    {
-        const int nk = KB, chunks = nk * 8, pieces = m * chunks;
-        const int qstep = FT / chunks, rstep = FT % chunks;
-        float t[16];
-        const unsigned ss_lane = (unsigned)min(lane, m - 1);
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const int j = wave + i * FW;
-            t[i] = ssa_load_f1(g.ss_in + min(j, g.n_ss - 1) * 64 + ss_lane) * (j < g.n_ss ? 1.f : 0.f);
-        }
-        floatx4 gn = load_global_f4(g.gain + min(tid, chunks - 1) * 4);
-        for (int base = 0; base < pieces; base += FT * XP) {
-            floatx4 v[XP];
-            int row = (base + tid) / chunks, c = (base + tid) % chunks;
-            const int row0 = row, c0 = c;
-#pragma unroll
-            for (int i = 0; i < XP; ++i) {
-                v[i] = ssa_load_f4(g.Xh + (unsigned)(min(row, m - 1) * KB * 32 + c * 4));
-                row += qstep;
-                c += rstep;
-                if (c >= chunks) { c -= chunks; ++row; }
-            }
-            if (base == 0) {
-                float sum = 0.f;
-#pragma unroll
-                for (int i = 0; i < 16; ++i) sum += t[i];
-                if (lane < m)
-                    for (int j = wave + 16 * FW; j < g.n_ss; j += FW) sum += ssa_load_f1(g.ss_in + j * 64 + lane);
-                sh.rs_tmp[wave][lane] = sum;
-                for (int cc = tid; cc < chunks; cc += FT) {
-                    if (cc != tid) gn = load_global_f4(g.gain + cc * 4);
-                    *reinterpret_cast<floatx4 *>(gain_s + cc * 4) = gn;
-                }
-                lds_sync();
-                TRACE(6);
-                if (tid < 64) {
-                    float part[FW], tot = 0.f;
-#pragma unroll
-                    for (int j = 0; j < FW; ++j) part[j] = sh.rs_tmp[j][tid];
-                    asm volatile("" ::: "memory");
-#pragma unroll
-                    for (int j = 0; j < FW; ++j) tot += part[j];
-                    sh.rs_s[tid] = 1.0f / sqrtf(tot * g.inv_d + g.eps);
-                }
-                lds_sync();
-                TRACE(7);
-            }
-            scale_and_stage<XP>(v, sh.rs_s, gain_s, reinterpret_cast<u32x2 *>(xs), row0, c0, qstep, rstep, chunks, m);
-        }
-    }
+    ns.run(smem, sh, lane, wave TRACE_PASS);
     lds_sync();
     TRACE(3);
 
@@ -1411,16 +1474,18 @@ __global__ __launch_bounds__(FT, FUSED_MINW) void verify_fused_kernel(FusedArgs 
     base.h = nullptr; base.ss_out = nullptr; base.a_out = nullptr; base.logits = nullptr; base.bias = nullptr;
     base.q = nullptr; base.layer = 0;
 
-    const int G = gridDim.x, wg = blockIdx.x;
-    // items of the down projection: (unit of two weight blocks) x (K split), w, w + G, ...; the splits divide G or
-    // leave at most one item per workgroup
-    const int down_items = (d / 16 + 1) / 2 * a.ks_down, kbps_down = (F / 32 + a.ks_down - 1) / a.ks_down;
-    const int down_unit0 = wg / a.ks_down, down_split = wg % a.ks_down, down_ustep = G / a.ks_down;
-    const int down_n = wg < down_items ? (down_items - wg + G - 1) / G : 0;
+    const Items it_qkv = items_of((nq + 2 * nkv) / 16, a.ks_qkv), it_o = items_of(d / 16, 1);
+    const Items it_gu = items_of(F / 16, a.ks_gu), it_down = items_of((d / 16 + 1) / 2, a.ks_down);
+    const int kbps_down = (F / 32 + a.ks_down - 1) / a.ks_down;
 
 #pragma unroll 1
     for (int l = 0; l < a.n_layers; ++l) {
-        const FusedLayer lp = a.layers[l];
+        // kernel arguments and a multiple of the layer's number: addresses that the scalar unit forms, no load
+        FusedLayer lp = a.layer0;
+        const size_t lo = (size_t)l * a.layer_bytes;
+        auto at_layer = [&](auto &p) { p = reinterpret_cast<std::remove_reference_t<decltype(p)>>(reinterpret_cast<uintptr_t>(p) + lo); };
+        at_layer(lp.wqkv); at_layer(lp.wo); at_layer(lp.wgu); at_layer(lp.wd);
+        at_layer(lp.attn_norm); at_layer(lp.ffn_norm); at_layer(lp.bqkv);
         float *h0 = a.hv + (size_t)(2 * l) * hstride, *h1 = h0 + hstride, *h2 = h1 + hstride;
         float *ss0 = a.ssv + (size_t)(2 * l) * sstride, *ss1 = ss0 + sstride, *ss2 = ss1 + sstride;
         bf16_t *q = a.qv + (size_t)l * FROWS * nq, *o = a.ov + (size_t)l * FROWS * nq;
@@ -1430,7 +1495,7 @@ __global__ __launch_bounds__(FT, FUSED_MINW) void verify_fused_kernel(FusedArgs 
             g.W = lp.wqkv; g.N = nq + 2 * nkv; g.KB = d / 32; g.Xh = h0; g.gain = lp.attn_norm; g.ss_in = ss0;
             g.bias = a.has_bias ? lp.bqkv : nullptr; g.layer = l; g.q = q;
             g.ks = a.ks_qkv; g.kbps = (g.KB + g.ks - 1) / g.ks;
-            gemm_phase<NB, 1, 6, EPI_QKV>(g, b, bar, smem, a.lds_total, sh TRACE_PASS);
+            qkv_phase<NB, HD, JP_OF(HD)>(g, it_qkv, bar, smem, a.lds_total, sh TRACE_PASS);
         }
         bar.arrive();
         TRACE(10);
@@ -1438,8 +1503,7 @@ __global__ __launch_bounds__(FT, FUSED_MINW) void verify_fused_kernel(FusedArgs 
         bar.arrive();
         TRACE(13);
         {
-            const ResidGemm g{(global_w_ptr)lp.wo, o, h0, h1, ss1, a.part, a.counters, d, nq / 32, a.m, 1, nq / 32,
-                              wg, G, 0, wg < d / 16 ? (d / 16 - wg + G - 1) / G : 0};
+            const ResidGemm g{(global_w_ptr)lp.wo, o, h0, h1, ss1, a.part, a.counters, d, nq / 32, a.m, 1, nq / 32, it_o};
             if (nq <= 4 * FW * 32) resid_phase<NB, 1, 4>(g, bar, smem TRACE_PASS);   // four k-blocks a wavefront
             else resid_phase<NB, 1, 6>(g, bar, smem TRACE_PASS);
         }
@@ -1449,14 +1513,13 @@ __global__ __launch_bounds__(FT, FUSED_MINW) void verify_fused_kernel(FusedArgs 
             FastGemm g = base;
             g.W = lp.wgu; g.N = 2 * F; g.KB = d / 32; g.Xh = h1; g.gain = lp.ffn_norm; g.ss_in = ss1; g.a_out = act;
             g.ks = a.ks_gu; g.kbps = (g.KB + g.ks - 1) / g.ks;
-            if (a.wave_gu) wave_phase<NB, EPI_SWIGLU>(g, a.gu_light, bar, smem, a.lds_total, sh TRACE_PASS);
-            else gemm_phase<NB, 2, 6, EPI_SWIGLU>(g, b, bar, smem, a.lds_total, sh TRACE_PASS);
+            if (a.wave_gu) wave_phase<NB, HD, EPI_SWIGLU>(g, a.gu_light, bar, smem, a.lds_total, sh TRACE_PASS);
+            else gemm_phase<NB, HD, 2, 6, EPI_SWIGLU>(g, it_gu, bar, smem, a.lds_total, sh TRACE_PASS);
         }
         bar.arrive();
         TRACE(15);
         {
-            const ResidGemm g{(global_w_ptr)lp.wd, act, h1, h2, ss2, a.part, a.counters, d, F / 32, a.m, a.ks_down, kbps_down,
-                              down_unit0, down_ustep, down_split, down_n};
+            const ResidGemm g{(global_w_ptr)lp.wd, act, h1, h2, ss2, a.part, a.counters, d, F / 32, a.m, a.ks_down, kbps_down, it_down};
             if (kbps_down <= 4 * FW) resid_phase<NB, 2, 4>(g, bar, smem TRACE_PASS);
             else resid_phase<NB, 2, NB <= 2 ? 7 : 5>(g, bar, smem TRACE_PASS);
         }
@@ -1469,8 +1532,8 @@ __global__ __launch_bounds__(FT, FUSED_MINW) void verify_fused_kernel(FusedArgs 
         g.Xh = a.hv + (size_t)(2 * a.n_layers) * hstride; g.gain = a.final_norm;
         g.ss_in = a.ssv + (size_t)(2 * a.n_layers) * sstride; g.logits = a.logits;
         g.ks = a.ks_head; g.kbps = (g.KB + g.ks - 1) / g.ks;
-        if (a.wave_head) wave_phase<NB, EPI_LOGITS>(g, 0, bar, smem, a.lds_total, sh TRACE_PASS);
-        else gemm_phase<NB, 2, 6, EPI_LOGITS>(g, b, bar, smem, a.lds_total, sh TRACE_PASS);
+        if (a.wave_head) wave_phase<NB, HD, EPI_LOGITS>(g, 0, bar, smem, a.lds_total, sh TRACE_PASS);
+        else gemm_phase<NB, HD, 2, 6, EPI_LOGITS>(g, items_of((a.vocab / 16 + 1) / 2, a.ks_head), bar, smem, a.lds_total, sh TRACE_PASS);
     }
     TRACE(99);
 #ifdef FUSED_ARRIVALS
@@ -1542,11 +1605,10 @@ size_t vf_fused_workspace_bytes(const vf_config &c) {
     add(L * FROWS * F * 2);
     add(L * FUSED_G * 16 * ((size_t)c.head_dim + ATTF_STRIDE_PAD) * 4);
     add(65536);
-    add(L * sizeof(FusedLayer));
     return n;
 }
 
-int vf_fused_init(vf_model *m, char *ws, hipStream_t st) {
+int vf_fused_init(vf_model *m, char *ws) {
     const vf_config &c = m->cfg;
     const size_t L = c.n_layers, d = c.d_model, nq = (size_t)c.n_q_heads * c.head_dim, F = c.d_ffn;
     size_t off = 0;
@@ -1558,15 +1620,15 @@ int vf_fused_init(vf_model *m, char *ws, hipStream_t st) {
     m->fz_a = take(L * FROWS * F * 2);
     m->fz_att = (float *)take(L * FUSED_G * 16 * ((size_t)c.head_dim + ATTF_STRIDE_PAD) * 4);
     m->fz_bar = (unsigned *)take(65536);
-    m->fz_layers = take(L * sizeof(FusedLayer));
-    std::vector<FusedLayer> host(L);
-    for (size_t l = 0; l < L; ++l) {
-        const LayerPacked &lp = m->layers[l];
-        host[l] = FusedLayer{(const u32x4 *)lp.wqkv, (const u32x4 *)lp.wo, (const u32x4 *)lp.wgu, (const u32x4 *)lp.wd,
-                             lp.attn_norm, lp.ffn_norm, lp.bqkv};
+    // the kernel addresses the parameters of layer l as those of layer 0 plus l times one distance
+    for (size_t l = 1; l < L; ++l) {
+        const LayerPacked &x = m->layers[l - 1], &y = m->layers[l], &z = m->layers[0], &o = m->layers[1];
+        auto same = [](const void *a, const void *b, const void *c, const void *d) { return (const char *)b - (const char *)a == (const char *)d - (const char *)c; };
+        if (!same(x.wqkv, y.wqkv, z.wqkv, o.wqkv) || !same(x.wo, y.wo, z.wqkv, o.wqkv) || !same(x.wgu, y.wgu, z.wqkv, o.wqkv) ||
+            !same(x.wd, y.wd, z.wqkv, o.wqkv) || !same(x.attn_norm, y.attn_norm, z.wqkv, o.wqkv) ||
+            !same(x.ffn_norm, y.ffn_norm, z.wqkv, o.wqkv) || !same(x.bqkv, y.bqkv, z.wqkv, o.wqkv))
+            return vf_fail(VF_ERR_ARG, "persistent kernel: layers at unequal distances");
     }
-    VF_HIP(hipMemcpyAsync(m->fz_layers, host.data(), L * sizeof(FusedLayer), hipMemcpyHostToDevice, st));
-    VF_HIP(hipStreamSynchronize(st));  // the host array goes away
     m->fz_epoch = 0;
     return VF_OK;
 }
@@ -1586,12 +1648,8 @@ static bool plan_splits(const vf_config &c, int rows, int nb, Splits *sp, size_t
     sp->down = fill_split(G, (d / 16 + 1) / 2, F / 32);
     sp->head = pick_split(G, lds, d / 32, rows, nb);
     if (!sp->qkv || !sp->gu || !sp->head) return false;
-    if ((d / 16 + 1) / 2 * 2 * nb > VF_N_COUNTERS) return false;   // a counter per tile of the down projection
-    // the gain slice of a normalising phase is staged where the partial sums go later
-    const int red_bytes = (FW / 2) * 2 * nb * 1024;
-    auto slice_bytes = [&](int ks) { return (d / 32 + ks - 1) / ks * 128; };
-    if (slice_bytes(sp->gu) > red_bytes || slice_bytes(sp->qkv) > red_bytes || slice_bytes(sp->head) > red_bytes)
-        return false;
+    // a counter per tile of a split unit
+    if (std::max((d / 16 + 1) / 2 * 2, (nq + 2 * nkv) / 16) * nb > VF_N_COUNTERS) return false;
     // partial tiles of the split phases: units * ks tiles of UB * NB * 256 floats
     size_t tiles = std::max((nq + 2 * nkv) / 16 * sp->qkv, std::max(F / 16 * sp->gu, (d / 16 + 1) / 2 * sp->down));
     if (sp->head > 1) tiles = std::max(tiles, (size_t)((c.vocab / 16 + 1) / 2) * sp->head);
@@ -1650,7 +1708,9 @@ int vf_run_fused(vf_model *m, const Batch &b, const int32_t *tokens, float *logi
     parts = std::min(parts, FUSED_MAXP);
     if (blocks > VF_N_COUNTERS) return vf_fail(VF_ERR_UNSUPPORTED, "%d attention blocks", blocks);
     if (blocks * parts > FUSED_G) parts = 1;  // records have room for one per workgroup
-    a.layers = (const FusedLayer *)m->fz_layers;
+    const LayerPacked &l0 = m->layers[0];
+    a.layer0 = FusedLayer{(const u32x4 *)l0.wqkv, (const u32x4 *)l0.wo, (const u32x4 *)l0.wgu, (const u32x4 *)l0.wd, l0.attn_norm, l0.ffn_norm, l0.bqkv};
+    a.layer_bytes = c.n_layers > 1 ? (unsigned long long)((char *)m->layers[1].wqkv - (char *)l0.wqkv) : 0;
     a.embed = (const bf16_t *)m->embed;
     a.lm_head = (const u32x4 *)m->lm_head;
     a.final_norm = m->final_norm;
@@ -1715,8 +1775,7 @@ int vf_run_fused(vf_model *m, const Batch &b, const int32_t *tokens, float *logi
     m->fz_epoch += (1u + 5u * (unsigned)c.n_layers) * (unsigned)(G / BAR_COUNTERS);  // barriers per launch x arrivals per counter
     const int rows = b.total_rows;
     {
-        const bool fits = FUSED_WAVE_PHASES && (size_t)(c.d_model / 32) * rows * 64 + WAVE_TAIL_BYTES <= (size_t)LDS_BYTES &&
-                          (size_t)c.d_model * 4 <= (size_t)WAVE_TAIL_BYTES;
+        const bool fits = FUSED_WAVE_PHASES && (size_t)(c.d_model / 32) * rows * 64 + wave_tail_bytes((rows + 15) / 16) <= (size_t)LDS_BYTES;
         a.wave_gu = fits && a.ks_gu == 1;
         {
             // one unit for each workgroup of the O projection, if the others can take the rest in at most
