@@ -278,7 +278,7 @@ int vf_model_create(const vf_config *cfg, const vf_weights *w, void *packed_dev,
     // activation buffers start at zero so that padding rows of a 16-row block are finite
     TRYHIP(hipMemsetAsync(m->h, 0, (size_t)((char *)m->base + m->bytes - (char *)m->h), st));
     if (c.dtype == VF_BF16) {
-        TRY(vf_fused_init(m, m->fz_ws));
+        TRY(vf_fused_init(m, m->fz_ws, st));
         TRY(vf_gemm_init());
     } else {
         TRY(vf_f32_init(m));

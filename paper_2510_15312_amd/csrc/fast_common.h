@@ -91,7 +91,14 @@ __device__ inline void store_coherent(float *p, floatx4 v) { st_f32x4<true>(p, v
 // release fence does not: within a workgroup the memory pipeline keeps stores in order, so the
 // compiler emits no wait for it, and a signal to ANOTHER workgroup (a counter increment) could
 // then overtake the write-through stores it is meant to publish.
-__device__ inline void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+// The wait is the builtin, not inline assembly, so that the compiler knows that nothing is in flight behind it: it would
+// go on to wait for loads of earlier phases, and with them for stores issued since (loads and stores return in order),
+// before it writes a register anew.
+__device__ inline void stores_done() {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0)
+    asm volatile("" ::: "memory");
+}
 #ifndef VF_COH_LOAD_SCOPE
 #define VF_COH_LOAD_SCOPE __HIP_MEMORY_SCOPE_AGENT
 #endif

@@ -33,18 +33,15 @@ namespace {
 constexpr int FW = 8;            // wavefronts per workgroup
 constexpr int FT = FW * 64;      // threads per workgroup
 constexpr int FROWS = 48;        // most rows of a call
+constexpr int MAX_DOWN_SPLITS = 9;   // K splits of the down projection
 #ifndef BAR_COUNTERS
 #define BAR_COUNTERS 64           // counters a barrier's arrivals are spread over
 #endif
-constexpr int ATT_COUNTERS = 4096;  // arrival counters of the attention blocks inside the barrier block (uints)
 constexpr int LDS_BYTES = 152 * 1024;  // dynamic LDS of the one workgroup a CU holds (160 KB less the static part)
 constexpr long long SPIN_LIMIT = 4000000;  // polls before a barrier gives up (seconds, not microseconds)
 
 #ifndef FUSED_AHEAD
 #define FUSED_AHEAD 3          // gate/up, down and head phases: this many steps of the item after next are held in registers too (0: off)
-#endif
-#ifndef FUSED_LAST_MERGES
-#define FUSED_LAST_MERGES 1     // attention: the last part to arrive merges the block (0: all parts wait and merge a slice each)
 #endif
 #ifndef FUSED_MAXP
 #define FUSED_MAXP 6              // most key parts per attention block (8 parts: 1280 us per launch, 6 1261, 5 1258, 4 1254, 3 1274, 2 1318;
@@ -93,7 +90,7 @@ struct FusedArgs {
     float *hv;        // residual stream, [2L+1][FROWS][d]
     float *ssv;       // sums of squares of its rows per 16 columns, [2L+1][d/16][64]
     bf16_t *qv, *ov, *av;  // per layer: q [FROWS][Hq*hd], attention output, SwiGLU product [FROWS][F]
-    float *att_rec;   // attention records of the key parts, [L][FUSED_G][16][hd + 4]
+    float *xch;       // partial tiles of the down projection's K splits, then of the attention's key parts; marks between uses
     float *part;
     int *counters;
     unsigned *bar, *fail;
@@ -107,6 +104,7 @@ struct FusedArgs {
     float inv_d, eps, scale_log2e;
     unsigned root0;   // value of the barrier's root counter when this launch starts
     int ks_qkv, ks_gu, ks_down, ks_head;
+    int down_ub;              // weight blocks of a down projection item
     int gu_light;            // gate/up: the first gu_light workgroups (busy in the O projection) take one unit each (0: even shares)
     int wave_gu, wave_head;  // gate/up, output head: one weight block per wavefront (K unsplit and the staged rows fit)
     int lds_total;    // dynamic LDS bytes of this launch
@@ -205,8 +203,6 @@ struct FusedShared {
 // ---- embedding: row r by workgroup r ---------------------------------------------------------------
 __device__ __forceinline__ void embed_phase(const FusedArgs &a, const Batch &b) {
     const int d = a.d;
-    if (blockIdx.x == gridDim.x - 1)  // arrival counters of the attention blocks start at zero in every launch
-        for (int i = threadIdx.x; i < a.att_blocks; i += FT) st_u32<true>(a.bar + ATT_COUNTERS + i, 0u);
     for (int row = blockIdx.x; row < a.m; row += gridDim.x) {
         int tok = a.tokens[row];
         if (tok == VF_PENDING) tok = b.s[find_seq(b, row)].state[1];
@@ -766,6 +762,84 @@ __device__ __forceinline__ bool meet_splits(floatx4 &v, float *part, int *counte
     return true;
 }
 
+// ---- exchange of partial tiles ------------------------------------------------------------------------------
+// K splits of a down projection tile, and key parts of an attention block, meet through memory that holds a mark
+// (all bits set, which no sent value has) wherever nothing has been sent.  Each tile has an owner among the
+// workgroups that share it; the others send theirs and go on, the owner reads until no mark is left, puts the marks
+// back and goes on with the sum.  Against a counter that the last to arrive reads (store, wait for the store,
+// increment with its round trip, read): the wait and the increment are gone from the chain, and the owners of
+// different tiles work at the same time.
+// Everyone who sends is resident and sends without waiting for anybody, so the wait ends; it is bounded like the
+// grid barrier's all the same.  Attention and down projection together: 1.5B, 17 rows 1252 -> 1154 us a pass, 0.5B, 9
+// rows 714 -> 674.
+constexpr unsigned XCH_MARK = 0xffffffffu;
+__device__ __forceinline__ void xch_send(float *slot, floatx4 v) {
+    u32x4 r = __builtin_bit_cast(u32x4, v);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) r[i] = r[i] == XCH_MARK ? 0x7fc00000u : r[i];   // a NaN like any other
+    st_f32x4<true>(slot, __builtin_bit_cast(floatx4, r));
+}
+// What parts 0 .. n - 1 (n >= 2) but `self` have sent: NV values a lane and part, value k of part i `at` + i * stride +
+// k * 1024 bytes into the exchange.  t[i] of part `self` and of parts past the last is undefined.  A round of the wait
+// is one round trip to memory and what its code costs: 16-byte loads past the caches (two of 8 bytes each before),
+// and a maximum over the words instead of a comparison of each.
+template <int MAXN, int NV>
+__device__ __forceinline__ void xch_receive(floatx4 (&t)[MAXN][NV], float *xch, unsigned at, unsigned stride, int n, int self, int lane,
+                                            unsigned *fail) {
+    constexpr int AGENT = 16;   // cache policy of an agent-scope load
+    const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(xch, 0, 0x7fffffff, 0x00027000);
+    const int other = self == 0 ? 1 : 0;
+    for (int spins = 0;;) {
+        asm volatile("" ::: "memory");   // read again in every round
+#pragma unroll
+        for (int i = 0; i < MAXN; ++i)
+#pragma unroll
+            for (int k = 0; k < NV; ++k)
+                t[i][k] = __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(
+                                                          rsrc, lane * 16, at + (i < n && i != self ? i : other) * stride + k * 1024, AGENT));
+        unsigned most = 0;
+#pragma unroll
+        for (int i = 0; i < MAXN; ++i)
+#pragma unroll
+            for (int k = 0; k < NV; ++k) {
+                const u32x4 r = __builtin_bit_cast(u32x4, t[i][k]);
+                most = max(max(most, r[0]), max(r[1], max(r[2], r[3])));
+            }
+        if (!__any(most == XCH_MARK)) break;
+        ++spins;
+        if (spins > SPIN_LIMIT || ((spins & 1023) == 0 && __hip_atomic_load(fail, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))) {
+            __hip_atomic_store(fail, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            break;
+        }
+    }
+}
+// Puts the marks back where this workgroup has received: tiles self, self + n, ... of `tiles`, NV values a lane.  Called
+// behind the arrival at the grid barrier, when all wavefronts are done with the values; the next arrival waits for
+// these stores, the next use is a phase or more behind that.  Not by the wavefront that polls the barrier: its polls
+// would wait for the stores (1.5B, 17 rows: 1178 us a pass; marks put back at the end of the phase 1162; so 1154).
+struct XchUsed { unsigned at, stride; int n, self, tiles; };   // at: of tile 0; n = 0: nothing received
+template <int NV>
+__device__ __forceinline__ void xch_clear(float *xch, const XchUsed &u) {
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), t = u.self + (FW - 1 - wave) * u.n;
+    if (u.n < 2 || wave < 2 || t >= u.tiles) return;
+    const floatx4 mark = __builtin_bit_cast(floatx4, u32x4{XCH_MARK, XCH_MARK, XCH_MARK, XCH_MARK});
+    float *p = xch + (u.at + t * NV * 1024) / 4 + (threadIdx.x & 63) * 4;
+    for (int i = 0; i < u.n; ++i)
+        if (i != u.self)
+#pragma unroll
+            for (int k = 0; k < NV; ++k) st_f32x4<true>(p + (i * u.stride + k * 1024) / 4, mark);
+}
+// Sum of a tile over its K splits, in split order.
+template <int MAXN>
+__device__ __forceinline__ floatx4 xch_sum(floatx4 v, float *xch, unsigned at, unsigned stride, int n, int self, int lane, unsigned *fail) {
+    floatx4 t[MAXN][1], sum = {0.f, 0.f, 0.f, 0.f};
+    xch_receive<MAXN, 1>(t, xch, at, stride, n, self, lane, fail);
+#pragma unroll
+    for (int i = 0; i < MAXN; ++i)
+        if (i < n) sum += i == self ? v : t[i][0];
+    return sum;
+}
+
 // ---- QKV phase --------------------------------------------------------------------------------------------
 // One 16-row weight block per item; the wavefronts share its K slice.  Few items a workgroup (one at the 0.5B and
 // 1.5B shapes, whose weights are then all requested before the barrier), so what counts is the chain behind the
@@ -862,9 +936,8 @@ __device__ __forceinline__ void qkv_phase(const FastGemm &g, const Items &im, Gr
 // memory into registers: no staging in LDS, no barrier between the loads and the products, no index arithmetic,
 // and no limit on the K slice.  Behind the grid barrier a wavefront issues one load per fragment, its products,
 // and the sum over the wavefronts; everything else (weights, addresses, the residual tile) comes before it.
-// Items: (unit of UB weight blocks) x (K split), as in gemm_phase.  A split unit meets tile by tile: the
-// wavefront that finishes a 16x16 tile stores its partial sums, counts itself in, and the last one to come adds
-// them in split order; no workgroup barrier is in that chain.
+// Items: (unit of UB weight blocks) x (K split), as in gemm_phase.  The splits of a unit exchange their sums tile by
+// tile, wavefront to wavefront; no workgroup barrier is in that chain.
 // Depth: all k-blocks of a wavefront at once where the shape allows (weights requested before the barrier, X in one
 // round trip behind it).  Release to last arrival, staged through LDS / so: O of 0.5B, 1 row 2.9 / 1.7 us, of 1.5B,
 // 17 rows 3.1 / 2.5; down of 1.5B, 17 rows 8.3 / 7.0 (in two rounds of five k-blocks instead of one of seven 8.4).
@@ -872,13 +945,15 @@ struct ResidGemm {
     global_w_ptr W;
     const bf16_t *X;   // [K / 32][NB] fragments
     const float *h_in;
-    float *h, *ss_out, *part;
-    int *counters;     // one per tile of a unit, zero between uses
+    float *h, *ss_out;
+    float *xch;        // partial tiles of the K splits
+    unsigned *fail;
     int N, KB, m, ks, kbps;
     Items im;
 };
 template <int NB, int UB, int PD>
-__device__ __forceinline__ void resid_phase(const ResidGemm &g, GridBar &bar, unsigned char *smem TRACE_ARG) {
+__device__ __forceinline__ XchUsed resid_phase(const ResidGemm &g, GridBar &bar, unsigned char *smem TRACE_ARG) {
+    const XchUsed used{(unsigned)(g.im.unit0 * g.ks * UB * NB) * 1024, UB * NB * 1024, g.im.n_my > 0 && g.ks > 1 ? g.ks : 0, g.im.split, UB * NB};
     constexpr int NTILE = UB * NB;
     static_assert(NTILE <= FW, "a tile of the unit per wavefront");
     int tid = threadIdx.x;
@@ -890,6 +965,7 @@ __device__ __forceinline__ void resid_phase(const ResidGemm &g, GridBar &bar, un
     const int wk0 = kb0 + wave * cnt, mine = min(cnt, kb1 - wk0);   // k-blocks wk0 .. wk0 + mine - 1 (none: mine <= 0)
     floatx4 *red = reinterpret_cast<floatx4 *>(smem);
     const int tu = wave / NB, tc = wave % NB;   // this wavefront's tile of a unit (wave < NTILE)
+    const int owner = wave % g.ks;              // the K split that puts it together
     const int row = tc * 16 + (lane & 15), crow = min(row, g.m - 1);
 
     u32x4 w[PD][UB], x[PD][NB];
@@ -923,7 +999,7 @@ __device__ __forceinline__ void resid_phase(const ResidGemm &g, GridBar &bar, un
     TRACE(1);
     bar.wait();
     TRACE(2);
-    if (g.im.n_my <= 0) return;
+    if (g.im.n_my <= 0) return used;
 #pragma unroll
     for (int d = 0; d < PD; ++d) load_x(d, d);
     for (int it = 0; it < g.im.n_my; ++it) {
@@ -968,10 +1044,15 @@ __device__ __forceinline__ void resid_phase(const ResidGemm &g, GridBar &bar, un
         lds_sync();
         if (wave < NTILE) {
             floatx4 v = sum_waves(red, wave, lane);
-            bool whole = true;
-            if (g.ks > 1) whole = meet_splits(v, g.part + ((size_t)unit * g.ks * NTILE + wave) * 256, g.counters + unit * NTILE + wave, g.im.split, g.ks, NTILE * 256, lane);
-            const int nb = unit * UB + tu;
-            if (whole) {
+            TRACE(8);
+            const unsigned at = (unsigned)(unit * g.ks * NTILE + wave) * 1024, stride = NTILE * 1024;
+            if (g.ks > 1 && owner != g.im.split) {
+                xch_send(g.xch + (at + g.im.split * stride) / 4 + lane * 4, v);
+            } else {
+                if (g.ks > 5) v = xch_sum<MAX_DOWN_SPLITS>(v, g.xch, at, stride, g.ks, g.im.split, lane, g.fail);
+                else if (g.ks > 1) v = xch_sum<5>(v, g.xch, at, stride, g.ks, g.im.split, lane, g.fail);
+                TRACE(9);
+                const int nb = unit * UB + tu;
                 FastGemm e;
                 e.N = g.N; e.h = g.h; e.ss_out = g.ss_out;
                 epi_resid_pre(e, row, row < g.m && nb < NBt, nb, lane, v, pre);
@@ -980,6 +1061,7 @@ __device__ __forceinline__ void resid_phase(const ResidGemm &g, GridBar &bar, un
         }
         TRACE(5);
     }
+    return used;
 }
 
 // ---- GEMM phase with whole weight blocks per wavefront ---------------------------------------------------
@@ -1227,9 +1309,10 @@ __device__ __forceinline__ AttItem att_item(const FusedArgs &a, const Batch &b, 
 // len0: length of the sequence of this workgroup's first item, read once per launch (lengths do
 // not change during a launch).
 template <int NB, int HD>
-__device__ __forceinline__ void attn_phase(const FusedArgs &a, const Batch &b, int layer, const bf16_t *q, bf16_t *o,
+__device__ __forceinline__ XchUsed attn_phase(const FusedArgs &a, const Batch &b, int layer, const bf16_t *q, bf16_t *o,
                                   int len0, GridBar &bar, unsigned char *smem, FusedShared &sh TRACE_ARG) {
-    constexpr int KD = HD / 32, DB = HD / 16, REC = HD + ATTF_STRIDE_PAD, MAXP = FUSED_MAXP;
+    XchUsed used{0, 0, 0, 0, 0};
+    constexpr int KD = HD / 32, DB = HD / 16, MAXP = FUSED_MAXP;
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));
     // the wavefront's number as a scalar: which tile it takes, and whether that tile holds keys of
@@ -1335,75 +1418,34 @@ __device__ __forceinline__ void attn_phase(const FusedArgs &a, const Batch &b, i
         }
         TRACE(21);
         if (P > 1) {
-            // Merge across the parts of the block without a second grid-wide phase: every part
-            // leaves its record in memory and counts itself in; once all P have (all of them are
-            // resident and none has other work left, so the wait ends), part p merges the d-blocks
-            // p, p + P, ... of all records -- wavefront w takes d-block p + w * P -- and writes
-            // that slice of the output.
-            float *base = a.att_rec + ((size_t)layer * FUSED_G + (size_t)it.blk * P) * 16 * REC;
-            float *mine = base + (size_t)part * 16 * REC;
-            if (wave < DB) {
-                if (wave == 0 && g4 == 0) st_u32x2<true>(mine + l15 * REC, __builtin_bit_cast(u32x2, float2{M, L}));
-                st_f32x4<true>(mine + l15 * REC + ATTF_STRIDE_PAD + wave * 16 + g4 * 4, acc);
-            }
-            stores_done();
-            __syncthreads();
-#if FUSED_LAST_MERGES
-            // the part that counts itself in last merges the whole block (wavefront w takes d-block w);
-            // the others are done: nobody waits, nothing is polled
-            if (tid == 0) {
-                unsigned *cnt = a.bar + ATT_COUNTERS + it.blk;
-                const unsigned old = __hip_atomic_fetch_add(cnt, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                sh.s_last = old + 1u == (unsigned)P * (unsigned)(layer + 1);
-            }
-            __syncthreads();
-            TRACE(22);
-            const int db = sh.s_last ? wave : DB;
-#else
-            if (tid == 0) {
-                unsigned *cnt = a.bar + ATT_COUNTERS + it.blk;
-                __hip_atomic_fetch_add(cnt, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                const unsigned want = (unsigned)P * (unsigned)(layer + 1);
-                long long spins = 0;
-                while (!bar.dead && __hip_atomic_load(cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < want) {
-                    __builtin_amdgcn_s_sleep(1);
-                    if (++spins > SPIN_LIMIT) {
-                        __hip_atomic_store(a.fail, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                        bar.dead = true;
-                    }
-                }
-            }
-            lds_sync();
-            TRACE(22);
-            const int db = part + wave * P;
-#endif
-            if (db < DB) {
-                // all records in flight at once (slots past P repeat the last part and weigh nothing);
-                // the records of a layer have a buffer of their own, so ordinary loads see them
-                float mp[MAXP], lp[MAXP];
-                floatx4 op[MAXP];
+            // The parts of a block exchange their results: d-block db is put together by part db % P, whose wavefront
+            // db has the other parts' O tiles and (max, sum) pairs sent to it.
+            const unsigned at = (unsigned)(it.blk * P * DB + wave) * 2048, stride = DB * 2048;
+            used = XchUsed{at - wave * 2048, stride, P, part, DB};
+            if (wave < DB && wave % P != part) {
+                float *slot = a.xch + (at + part * stride) / 4 + lane * 4;
+                xch_send(slot, acc);
+                xch_send(slot + 256, floatx4{M, L, 0.f, 0.f});
+            } else if (wave < DB) {
+                floatx4 t[MAXP][2];
+                xch_receive<MAXP, 2>(t, a.xch, at, stride, P, part, lane, a.fail);
+                TRACE(22);
+                float Mg = M;
 #pragma unroll
-                for (int pp = 0; pp < MAXP; ++pp) {
-                    const float *rec = base + ((size_t)min(pp, P - 1) * 16 + l15) * REC;
-                    const floatx4 hd4 = ssa_load_f4(rec);  // [max, sum, -, -]
-                    mp[pp] = hd4[0];
-                    lp[pp] = hd4[1];
-                    op[pp] = ssa_load_f4(rec + ATTF_STRIDE_PAD + db * 16 + g4 * 4);
-                }
-                float Mg = -1e30f;
-#pragma unroll
-                for (int pp = 0; pp < MAXP; ++pp) Mg = fmaxf(Mg, mp[pp]);
+                for (int pp = 0; pp < MAXP; ++pp) Mg = pp < P && pp != part ? fmaxf(Mg, t[pp][1][0]) : Mg;
                 float Lg = 0.f;
                 floatx4 og = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                 for (int pp = 0; pp < MAXP; ++pp) {
-                    const float wt = pp < P ? exp2f(mp[pp] - Mg) : 0.f;
-                    Lg += lp[pp] * wt;
-                    og += op[pp] * wt;
+                    if (pp < P) {
+                        const float wt = exp2f((pp == part ? M : t[pp][1][0]) - Mg);
+                        Lg += (pp == part ? L : t[pp][1][1]) * wt;
+                        og += (pp == part ? acc : t[pp][0]) * wt;
+                    }
                 }
                 if (valid) {
                     const float inv = 1.0f / Lg;
-                    st_u32x2<true>(o + xfrag_index(row, head * HD + db * 16 + g4 * 4, NB),
+                    st_u32x2<true>(o + xfrag_index(row, head * HD + wave * 16 + g4 * 4, NB),
                                    pack4_bf16(og[0] * inv, og[1] * inv, og[2] * inv, og[3] * inv));
                 }
             }
@@ -1413,6 +1455,7 @@ __device__ __forceinline__ void attn_phase(const FusedArgs &a, const Batch &b, i
                            pack4_bf16(acc[0] * inv, acc[1] * inv, acc[2] * inv, acc[3] * inv));
         }
     }
+    return used;
 }
 
 #ifndef FUSED_MINW
@@ -1475,7 +1518,7 @@ __global__ __launch_bounds__(FT, FUSED_MINW) void verify_fused_kernel(FusedArgs 
     base.q = nullptr; base.layer = 0;
 
     const Items it_qkv = items_of((nq + 2 * nkv) / 16, a.ks_qkv), it_o = items_of(d / 16, 1);
-    const Items it_gu = items_of(F / 16, a.ks_gu), it_down = items_of((d / 16 + 1) / 2, a.ks_down);
+    const Items it_gu = items_of(F / 16, a.ks_gu), it_down = items_of((d / 16 + a.down_ub - 1) / a.down_ub, a.ks_down);
     const int kbps_down = (F / 32 + a.ks_down - 1) / a.ks_down;
 
 #pragma unroll 1
@@ -1499,11 +1542,12 @@ __global__ __launch_bounds__(FT, FUSED_MINW) void verify_fused_kernel(FusedArgs 
         }
         bar.arrive();
         TRACE(10);
-        attn_phase<NB, HD>(a, b, l, q, o, len0, bar, smem, sh TRACE_PASS);
+        const XchUsed att_used = attn_phase<NB, HD>(a, b, l, q, o, len0, bar, smem, sh TRACE_PASS);
         bar.arrive();
+        xch_clear<2>(a.xch, att_used);
         TRACE(13);
         {
-            const ResidGemm g{(global_w_ptr)lp.wo, o, h0, h1, ss1, a.part, a.counters, d, nq / 32, a.m, 1, nq / 32, it_o};
+            const ResidGemm g{(global_w_ptr)lp.wo, o, h0, h1, ss1, a.xch, a.fail, d, nq / 32, a.m, 1, nq / 32, it_o};
             if (nq <= 4 * FW * 32) resid_phase<NB, 1, 4>(g, bar, smem TRACE_PASS);   // four k-blocks a wavefront
             else resid_phase<NB, 1, 6>(g, bar, smem TRACE_PASS);
         }
@@ -1518,12 +1562,14 @@ __global__ __launch_bounds__(FT, FUSED_MINW) void verify_fused_kernel(FusedArgs 
         }
         bar.arrive();
         TRACE(15);
+        XchUsed down_used;
         {
-            const ResidGemm g{(global_w_ptr)lp.wd, act, h1, h2, ss2, a.part, a.counters, d, F / 32, a.m, a.ks_down, kbps_down, it_down};
-            if (kbps_down <= 4 * FW) resid_phase<NB, 2, 4>(g, bar, smem TRACE_PASS);
-            else resid_phase<NB, 2, NB <= 2 ? 7 : 5>(g, bar, smem TRACE_PASS);
+            const ResidGemm g{(global_w_ptr)lp.wd, act, h1, h2, ss2, a.xch, a.fail, d, F / 32, a.m, a.ks_down, kbps_down, it_down};
+            if (a.down_ub == 1) down_used = resid_phase<NB, 1, 5>(g, bar, smem TRACE_PASS);
+            else down_used = resid_phase<NB, 2, NB <= 2 ? 7 : 5>(g, bar, smem TRACE_PASS);
         }
         bar.arrive();
+        xch_clear<1>(a.xch, down_used);
         TRACE(16);
     }
     {
@@ -1563,7 +1609,7 @@ int pick_split(int G, int lds_total, int KB, int rows, int nb) {
 // k-block per wavefront.
 int fill_split(int G, int units, int KB) {
     int best = 1;
-    for (int ks = 2; units * ks <= G && ks <= KB; ++ks) {
+    for (int ks = 2; units * ks <= G && ks <= std::min(KB, MAX_DOWN_SPLITS); ++ks) {
         const int kbps = (KB + ks - 1) / ks;
         if ((KB + kbps - 1) / kbps == ks && kbps >= FW) best = ks;
     }
@@ -1593,6 +1639,10 @@ int launch_fused(vf_model *m, FusedArgs &a, const Batch &b, int G, hipStream_t s
 
 }  // namespace
 
+// One work item per workgroup sends: the tiles of a down projection item, or the d-blocks of an attention part with
+// their (max, sum) pairs.
+static size_t xch_bytes(const vf_config &c) { return (size_t)FUSED_G * std::max(2 * (FROWS / 16), c.head_dim / 16 * 2) * 1024; }
+
 size_t vf_fused_workspace_bytes(const vf_config &c) {
     if (c.dtype != VF_BF16) return 0;
     const size_t L = c.n_layers, d = c.d_model, nq = (size_t)c.n_q_heads * c.head_dim, F = c.d_ffn;
@@ -1603,12 +1653,12 @@ size_t vf_fused_workspace_bytes(const vf_config &c) {
     add(L * FROWS * nq * 2);
     add(L * FROWS * nq * 2);
     add(L * FROWS * F * 2);
-    add(L * FUSED_G * 16 * ((size_t)c.head_dim + ATTF_STRIDE_PAD) * 4);
+    add(xch_bytes(c));
     add(65536);
     return n;
 }
 
-int vf_fused_init(vf_model *m, char *ws) {
+int vf_fused_init(vf_model *m, char *ws, hipStream_t st) {
     const vf_config &c = m->cfg;
     const size_t L = c.n_layers, d = c.d_model, nq = (size_t)c.n_q_heads * c.head_dim, F = c.d_ffn;
     size_t off = 0;
@@ -1618,7 +1668,8 @@ int vf_fused_init(vf_model *m, char *ws) {
     m->fz_q = take(L * FROWS * nq * 2);
     m->fz_o = take(L * FROWS * nq * 2);
     m->fz_a = take(L * FROWS * F * 2);
-    m->fz_att = (float *)take(L * FUSED_G * 16 * ((size_t)c.head_dim + ATTF_STRIDE_PAD) * 4);
+    m->fz_xch = (float *)take(xch_bytes(c));
+    VF_HIP(hipMemsetAsync(m->fz_xch, 0xff, xch_bytes(c), st));   // marks everywhere
     m->fz_bar = (unsigned *)take(65536);
     // the kernel addresses the parameters of layer l as those of layer 0 plus l times one distance
     for (size_t l = 1; l < L; ++l) {
@@ -1629,6 +1680,7 @@ int vf_fused_init(vf_model *m, char *ws) {
             !same(x.ffn_norm, y.ffn_norm, z.wqkv, o.wqkv) || !same(x.bqkv, y.bqkv, z.wqkv, o.wqkv))
             return vf_fail(VF_ERR_ARG, "persistent kernel: layers at unequal distances");
     }
+    VF_HIP(hipStreamSynchronize(st));   // a model is ready for any stream once it is created
     m->fz_epoch = 0;
     return VF_OK;
 }
@@ -1636,7 +1688,7 @@ int vf_fused_init(vf_model *m, char *ws) {
 // Whether the persistent kernel can run this call; fills the grid size, LDS size and K splits.
 // K splits of the six GEMM phases for a call of `rows` rows (nb blocks of 16), and the floats of
 // partial-sum workspace they need.  false: some phase does not fit.
-struct Splits { int qkv, gu, down, head; };
+struct Splits { int qkv, gu, down, down_ub, head; };
 static bool plan_splits(const vf_config &c, int rows, int nb, Splits *sp, size_t *part_floats) {
     const int d = c.d_model, F = c.d_ffn, hd = c.head_dim, nq = c.n_q_heads * hd, nkv = c.n_kv_heads * hd;
     if (c.dtype != VF_BF16 || rows > FROWS || d % 64) return false;
@@ -1645,13 +1697,16 @@ static bool plan_splits(const vf_config &c, int rows, int nb, Splits *sp, size_t
     if (G % BAR_COUNTERS) return false;
     sp->qkv = pick_split(G, lds, d / 32, rows, nb);
     sp->gu = pick_split(G, lds, d / 32, rows, nb);
-    sp->down = fill_split(G, (d / 16 + 1) / 2, F / 32);
+    // one weight block an item where that still gives three splits or more: a narrow model's items of two blocks need
+    // nine splits to fill the chip, and an owner waits for all of them (0.5B, 1 row: 632 us a pass, with four 601)
+    sp->down_ub = d / 16 * 3 <= G ? 1 : 2;
+    sp->down = fill_split(G, (d / 16 + sp->down_ub - 1) / sp->down_ub, F / 32);
     sp->head = pick_split(G, lds, d / 32, rows, nb);
     if (!sp->qkv || !sp->gu || !sp->head) return false;
     // a counter per tile of a split unit
-    if (std::max((d / 16 + 1) / 2 * 2, (nq + 2 * nkv) / 16) * nb > VF_N_COUNTERS) return false;
+    if ((nq + 2 * nkv) / 16 * nb > VF_N_COUNTERS) return false;
     // partial tiles of the split phases: units * ks tiles of UB * NB * 256 floats
-    size_t tiles = std::max((nq + 2 * nkv) / 16 * sp->qkv, std::max(F / 16 * sp->gu, (d / 16 + 1) / 2 * sp->down));
+    size_t tiles = std::max((nq + 2 * nkv) / 16 * sp->qkv, F / 16 * sp->gu);
     if (sp->head > 1) tiles = std::max(tiles, (size_t)((c.vocab / 16 + 1) / 2) * sp->head);
     *part_floats = tiles * 2 * nb * 256;
     return true;
@@ -1679,6 +1734,7 @@ static bool plan_fused(const vf_model *m, const Batch &b, FusedArgs &a, int *G_o
     a.ks_qkv = sp.qkv;
     a.ks_gu = sp.gu;
     a.ks_down = sp.down;
+    a.down_ub = sp.down_ub;
     a.ks_head = sp.head;
     a.lds_total = LDS_BYTES;
     *G_out = FUSED_G;
@@ -1706,8 +1762,7 @@ int vf_run_fused(vf_model *m, const Batch &b, const int32_t *tokens, float *logi
     for (int i = 0; i < b.n_seqs; ++i) blocks += c.n_kv_heads * ((b.s[i].nrows * group + 15) / 16);
     int parts = std::max(1, std::min(G / std::max(1, blocks), ((max_keys + FKT - 1) / FKT + FW - 1) / FW));
     parts = std::min(parts, FUSED_MAXP);
-    if (blocks > VF_N_COUNTERS) return vf_fail(VF_ERR_UNSUPPORTED, "%d attention blocks", blocks);
-    if (blocks * parts > FUSED_G) parts = 1;  // records have room for one per workgroup
+    if (blocks * parts > FUSED_G) parts = 1;  // the exchange has room for one item per workgroup
     const LayerPacked &l0 = m->layers[0];
     a.layer0 = FusedLayer{(const u32x4 *)l0.wqkv, (const u32x4 *)l0.wo, (const u32x4 *)l0.wgu, (const u32x4 *)l0.wd, l0.attn_norm, l0.ffn_norm, l0.bqkv};
     a.layer_bytes = c.n_layers > 1 ? (unsigned long long)((char *)m->layers[1].wqkv - (char *)l0.wqkv) : 0;
@@ -1724,7 +1779,7 @@ int vf_run_fused(vf_model *m, const Batch &b, const int32_t *tokens, float *logi
     a.qv = (bf16_t *)m->fz_q;
     a.ov = (bf16_t *)m->fz_o;
     a.av = (bf16_t *)m->fz_a;
-    a.att_rec = m->fz_att;
+    a.xch = m->fz_xch;
     a.part = m->part;
     a.counters = m->counters;
     a.bar = m->fz_bar;
@@ -1805,6 +1860,7 @@ int vf_fused_check(vf_model *m) {
         // counters are out of step now: start over from zero
         VF_HIP(hipMemset(m->fz_bar, 0, 65536));
         VF_HIP(hipMemset(m->counters, 0, VF_N_COUNTERS * 4));
+        VF_HIP(hipMemset(m->fz_xch, 0xff, xch_bytes(m->cfg)));
         m->fz_epoch = 0;
         return vf_fail(VF_ERR_HIP, "persistent verify kernel: a grid barrier timed out; results of that call are invalid");
     }

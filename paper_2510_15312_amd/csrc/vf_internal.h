@@ -100,7 +100,7 @@ struct vf_model {
     int fast_path;              // option: use the few-row kernels when they apply
     int persistent;             // option: use the persistent whole-pass kernel when it applies
     // persistent kernel: single-assignment activation buffers, barrier counters
-    float *fz_h, *fz_ss, *fz_att;
+    float *fz_h, *fz_ss, *fz_xch;
     void *fz_q, *fz_o, *fz_a;
     unsigned *fz_bar;
     char *fz_ws;                // their workspace
@@ -376,7 +376,7 @@ int vf_f32_init(const vf_model *m);
 int vf_run_layers_f32(vf_model *m, const Batch &b, const int32_t *tokens, bool tree, hipStream_t st);
 int vf_run_head_f32(vf_model *m, int row_lo, int row_hi, float *out, hipStream_t st);
 size_t vf_fused_workspace_bytes(const vf_config &c);
-int vf_fused_init(vf_model *m, char *ws);
+int vf_fused_init(vf_model *m, char *ws, hipStream_t st);
 bool vf_fused_ok(const vf_model *m, const Batch &b);
 // tree: rows take position and visibility from the model's tree_depth / tree_anc tables
 int vf_run_fused(vf_model *m, const Batch &b, const int32_t *tokens, float *logits_out, bool tree, hipStream_t st);
