@@ -84,7 +84,7 @@ size_t carve_model(vf_model *m, char *base) {
     const size_t widest = std::max(std::max(2 * F, nq + 2 * nkv), d);
     m->part_floats = R * widest * 2;  // room for two partials of the widest layer GEMM
     // and for the K splits of the few-row kernels
-    m->part_floats = std::max(m->part_floats, std::max(vf_fused_part_floats(c), vf_fast_part_floats(c)));
+    m->part_floats = std::max(m->part_floats, vf_fast_part_floats(c));
     m->part = (float *)cv.take(m->part_floats * 4);
     {
         // general path: 16 slices per row of max_rows; few-row path: up to 48 rows, one slice per 128 keys
@@ -135,6 +135,10 @@ int run_layers(vf_model *m, const Batch &b, const int32_t *tokens, int *tail_par
     if (c.dtype == VF_F32) {
         *tail_parts = 0;
         return vf_run_layers_f32(m, b, tokens, tree, st);
+    }
+    if (m->fast_path && m->persistent && vf_direct_ok(m, b)) {
+        *tail_parts = 0;
+        return vf_run_direct(m, b, tokens, tree, st);
     }
     const int rows = b.total_rows, R = rows;  // partials are laid out with ld = rows of this call
     const int d = c.d_model, F = c.d_ffn, nq = c.n_q_heads * c.head_dim, nkv = c.n_kv_heads * c.head_dim;
@@ -562,7 +566,7 @@ static int verify_impl(vf_model *m, vf_seq *const *seqs, int n_seqs, const int32
     float *dst = logits_out_dev ? logits_out_dev : m->logits;
     if (m->fast_path && m->persistent && vf_fused_ok(m, b)) {
         if ((rc = vf_run_fused(m, b, tokens_dev, dst, tree, st))) return rc;
-    } else if (!tree && m->fast_path && vf_fast_path_ok(m, b.total_rows)) {
+    } else if (!tree && m->fast_path && vf_fast_path_ok(m, b.total_rows) && !(m->persistent && vf_direct_ok(m, b))) {
         if ((rc = vf_run_fast(m, b, tokens_dev, dst, st))) return rc;
     } else {
         int tail = 0;

@@ -101,7 +101,7 @@ struct vf_model {
     int persistent;             // option: use the persistent whole-pass kernel when it applies
     // persistent kernel: single-assignment activation buffers, barrier counters
     float *fz_h, *fz_ss, *fz_xch;
-    void *fz_q, *fz_o, *fz_a;
+    void *fz_q, *fz_o, *fz_a, *fz_x;
     unsigned *fz_bar;
     char *fz_ws;                // their workspace
     unsigned fz_epoch;          // value the barrier's root counter has after all launches so far
@@ -381,7 +381,9 @@ bool vf_fused_ok(const vf_model *m, const Batch &b);
 // tree: rows take position and visibility from the model's tree_depth / tree_anc tables
 int vf_run_fused(vf_model *m, const Batch &b, const int32_t *tokens, float *logits_out, bool tree, hipStream_t st);
 int vf_fused_check(vf_model *m);
-size_t vf_fused_part_floats(const vf_config &c);
+// the decoder layers alone, for more rows (fused_direct.hip); leaves the residual stream in m->h
+bool vf_direct_ok(const vf_model *m, const Batch &b);
+int vf_run_direct(vf_model *m, const Batch &b, const int32_t *tokens, bool tree, hipStream_t st);
 // per-row top-k of logits: candidates per vocabulary slice into the model's candidate buffers, then the merge
 int vf_launch_topk_slices(const vf_model *m, const float *logits, int rows, int K, hipStream_t st);
 int vf_launch_topk_merge(const vf_model *m, int rows, int n_slices, int K, float *out_v, int32_t *out_i,
