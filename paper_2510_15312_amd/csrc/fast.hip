@@ -404,7 +404,8 @@ __global__ __launch_bounds__(ROWS_WAVES * 64) void attn_rows_kernel(Batch b, int
         tile.mask_values(t0, kmax, lane);
 #pragma unroll
         for (int c = 0; c < ROWS_QB; ++c)
-            if (t0 <= blk_last[c]) att_tile_update<HD>(st[c], qf[c], tile, t0, last_key[c], ATT_NO_TREE, 0, scale_log2e, lane);
+            if (t0 <= blk_last[c])
+                att_tile_update<HD>(st[c], qf[c], tile, t0, last_key[c], ATT_NO_TREE, 0, t0 + ATT_TILE <= len, scale_log2e, lane);
     };
     AttTile<HD> tile;
 #pragma unroll 1

@@ -407,12 +407,15 @@ template <int HD> struct AttTile {
     // page: the cache page of tile t, for a caller that has looked it up already
     template <bool coh>
     __device__ __forceinline__ void load_page(const SeqDesc &s, int layer, int hkv, int kvh, int t, int page, int lane) {
-        // the cache keeps a tile's fragments in operand order: fragment f of the tile is the kilobyte at
-        // 512 * f elements, a lane's share the 16 bytes at 8 * lane
-        const bf16_t *kv = reinterpret_cast<const bf16_t *>(s.kv);
-        const int t0 = t * ATT_TILE, tin = t0 % VF_TILE;
-        const bf16_t *kb = kv + kv_k_index(layer, s.n_pages, page, hkv, kvh, tin, 0, HD) + lane * 8;
-        const bf16_t *vb = kv + kv_v_index(layer, s.n_pages, page, hkv, kvh, tin, 0, HD) + lane * 8;
+        load_keys<coh>(s, layer, hkv, kvh, t, page, lane);
+        load_values<coh>(s, layer, hkv, kvh, t, page, lane);
+    }
+    // the cache keeps a tile's fragments in operand order: fragment f of the tile is the kilobyte at
+    // 512 * f elements, a lane's share the 16 bytes at 8 * lane
+    template <bool coh>
+    __device__ __forceinline__ void load_keys(const SeqDesc &s, int layer, int hkv, int kvh, int t, int page, int lane) {
+        const bf16_t *kb = reinterpret_cast<const bf16_t *>(s.kv) +
+                           kv_k_index(layer, s.n_pages, page, hkv, kvh, t * ATT_TILE % VF_TILE, 0, HD) + lane * 8;
 #pragma unroll
         for (int h = 0; h < 2; ++h)
 #pragma unroll
@@ -420,6 +423,11 @@ template <int HD> struct AttTile {
                 const bf16_t *kp = kb + (h * (HD / 32) + kd) * 512;
                 kf[h][kd] = coh ? __builtin_bit_cast(bf16x8, load_coherent16(kp)) : *reinterpret_cast<const bf16x8 *>(kp);
             }
+    }
+    template <bool coh>
+    __device__ __forceinline__ void load_values(const SeqDesc &s, int layer, int hkv, int kvh, int t, int page, int lane) {
+        const bf16_t *vb = reinterpret_cast<const bf16_t *>(s.kv) +
+                           kv_v_index(layer, s.n_pages, page, hkv, kvh, t * ATT_TILE % VF_TILE, 0, HD) + lane * 8;
 #pragma unroll
         for (int db = 0; db < HD / 16; ++db) {
             const bf16_t *vp = vb + db * 512;
@@ -439,15 +447,37 @@ template <int HD> struct AttTile {
     }
 };
 
+// Maximum and sum over the four lanes of an item (l, l + 16, l + 32, l + 48): a register exchange between rows of 16 lanes and
+// between halves instead of a trip through LDS.
+// (Inline: of the builtins' two results this compiler takes the first for both.  Two idle cycles stand between the
+// writes of the operands and the exchange.)
+template <typename F> __device__ __forceinline__ float over_item(float x, F f) {
+    float y = x;
+    asm("s_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(x), "+v"(y));
+    x = f(x, y);
+    y = x;
+    asm("s_nop 1\n\tv_permlane32_swap_b32 %0, %1" : "+v"(x), "+v"(y));
+    return f(x, y);
+}
+// 2^x for x <= 0.  The instruction alone: what the library function adds to it are results below 2^-126, which weigh nothing
+// next to the item's largest key, whose weight is 1.
+__device__ __forceinline__ float exp2_weight(float x) { return __builtin_amdgcn_exp2f(x); }
+
 // One tile for one block of 16 query items: masked online softmax update of st.
 // last_key: last visible key of this lane's item (-1: none).  Tree-structured drafts: of the keys
 // from own_base on (the rows of the same call) only those whose bit is set in own_mask are
-// visible; a plain causal call passes ATT_NO_TREE as own_base.
+// visible; a plain causal call passes ATT_NO_TREE as own_base.  whole (the same for all lanes): every key of the tile
+// is visible to every valid item.
+// Few wavefronts a SIMD, so its instructions count: tiles of old keys skip the masks, the accumulators are only rescaled
+// when some item's maximum has moved (attention phase of the persistent kernel, release to the last tile: 17 rows over
+// 2048 keys at 1.5B 3.0 -> 2.7 us, 33 over 4096 at 3B 9.1 -> 8.4).
 constexpr int ATT_NO_TREE = 0x7fffffff;
-template <int HD>
+// keys_used(): called when the tile's keys have been multiplied (their registers may take the next tile's).
+struct AttNothing { __device__ __forceinline__ void operator()() const {} };
+template <int HD, typename F = AttNothing>
 __device__ __forceinline__ void att_tile_update(AttState<HD> &st, const bf16x8 (&qf)[HD / 32], const AttTile<HD> &T, int t0,
-                                                int last_key, int own_base, tree_mask_t own_mask,
-                                                float scale_log2e, int lane) {
+                                                int last_key, int own_base, tree_mask_t own_mask, bool whole,
+                                                float scale_log2e, int lane, F keys_used = F()) {
     constexpr int KD = HD / 32, DB = HD / 16;
     const int g4 = lane >> 4;
     floatx4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
@@ -456,39 +486,53 @@ __device__ __forceinline__ void att_tile_update(AttState<HD> &st, const bf16x8 (
         s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(T.kf[0][kd], qf[kd], s0, 0, 0, 0);
         s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(T.kf[1][kd], qf[kd], s1, 0, 0, 0);
     }
+    keys_used();
     // lane holds keys t0 + 8*g4 + j (s0) and t0 + 8*g4 + 4 + j (s1) of item (lane & 15)
     float p[8], tmax = -1e30f;
-    bool vis[8];
-    if (own_base == ATT_NO_TREE) {  // the same for every lane: a scalar branch, the causal test alone
+    unsigned vis = 0xff;
+    if (!whole) {
+        if (own_base == ATT_NO_TREE) {  // the same for every lane: a scalar branch, the causal test alone
+            vis = last_key < t0 + g4 * 8 ? 0u : 0xffu >> (7 - min(last_key - t0 - g4 * 8, 7));
+        } else {
+            vis = 0;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) vis[j] = t0 + g4 * 8 + j <= last_key;
-    } else {
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int key = t0 + g4 * 8 + j;
-            vis[j] = key <= last_key && (key < own_base || ((own_mask >> ((unsigned)(key - own_base) & 63u)) & 1));
+            for (int j = 0; j < 8; ++j) {
+                const int key = t0 + g4 * 8 + j;
+                vis |= (unsigned)(key <= last_key && (key < own_base || ((own_mask >> ((unsigned)(key - own_base) & 63u)) & 1))) << j;
+            }
         }
     }
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-        p[j] = vis[j] ? s0[j] * scale_log2e : -1e30f;
-        p[4 + j] = vis[4 + j] ? s1[j] * scale_log2e : -1e30f;
-        tmax = fmaxf(tmax, fmaxf(p[j], p[4 + j]));
+        p[j] = s0[j] * scale_log2e;
+        p[4 + j] = s1[j] * scale_log2e;
     }
-    tmax = fmaxf(tmax, __shfl_xor(tmax, 16, 64));
-    tmax = fmaxf(tmax, __shfl_xor(tmax, 32, 64));
+    if (!whole) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) p[j] = vis >> j & 1 ? p[j] : -1e30f;
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) tmax = fmaxf(tmax, fmaxf(p[j], p[4 + j]));
+    tmax = over_item(tmax, [](float x, float y) { return fmaxf(x, y); });
     const float m_new = fmaxf(st.m_run, tmax);
-    const float corr = exp2f(st.m_run - m_new);
+    const float corr = exp2_weight(st.m_run - m_new);
+    const bool rescale = __any(st.m_run != m_new);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) p[j] = exp2_weight(p[j] - m_new);
+    if (!whole) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) p[j] = vis >> j & 1 ? p[j] : 0.f;
+    }
     float psum = 0.f;
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        p[j] = vis[j] ? exp2f(p[j] - m_new) : 0.f;
-        psum += p[j];
-    }
-    psum += __shfl_xor(psum, 16, 64);
-    psum += __shfl_xor(psum, 32, 64);
+    for (int j = 0; j < 8; ++j) psum += p[j];
+    psum = over_item(psum, [](float x, float y) { return x + y; });
     st.l_run = st.l_run * corr + psum;
     st.m_run = m_new;
+    if (rescale) {
+#pragma unroll
+        for (int db = 0; db < DB; ++db) st.o[db] = st.o[db] * corr;
+    }
     // probabilities as a sum of two bfloat16 values (16 significant bits): the P * V product
     // then carries no more rounding than its bfloat16 V operand
     bf16x8 pf, pl;
@@ -499,7 +543,6 @@ __device__ __forceinline__ void att_tile_update(AttState<HD> &st, const bf16x8 (
     }
 #pragma unroll
     for (int db = 0; db < DB; ++db) {
-        st.o[db] = st.o[db] * corr;
         st.o[db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(T.vf[db], pf, st.o[db], 0, 0, 0);
         st.o[db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(T.vf[db], pl, st.o[db], 0, 0, 0);
     }

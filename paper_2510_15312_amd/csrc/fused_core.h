@@ -495,15 +495,27 @@ __device__ __forceinline__ XchUsed attn_phase(const FusedArgs &a, const Batch &b
         for (int db = 0; db < DB; ++db) st.o[db] = floatx4{0.f, 0.f, 0.f, 0.f};
         st.m_run = -1e30f;
         st.l_run = 0.f;
-#pragma unroll 1
-        for (int t = t_begin + wave; t < t_end; t += FW) {
-            const int t0 = t * FKT;
-            if (!preloaded) tile.load(s, layer, hkv, kvh, t, (t + 1) * FKT > len, lane);
-            preloaded = false;
-            tile.mask_values(t0, kmax, lane);
-            att_tile_update<HD>(st, qf, tile, t0, last_key, own_base, own_mask, a.scale_log2e, lane);
-        }
+        // The next tile's keys are requested when this one's have been multiplied, its values when these have: no
+        // registers for a second tile (with whole tiles in two register sets 400 of them were spilled), and a round trip
+        // a tile less than one tile after the other.
+        int t = t_begin + wave;
+        if (t < t_end && !preloaded) tile.load(s, layer, hkv, kvh, t, (t + 1) * FKT > len, lane);
         preloaded = false;
+#pragma unroll 1
+        for (; t + FW < t_end; t += FW) {
+            const int n = t + FW, page = kv_page(s, n * FKT);
+            const bool coh = (n + 1) * FKT > len;   // (a tile with keys past the last is the part's last: none here)
+            att_tile_update<HD>(st, qf, tile, t * FKT, last_key, own_base, own_mask, (t + 1) * FKT <= len, a.scale_log2e, lane, [&] {
+                if (coh) tile.template load_keys<true>(s, layer, hkv, kvh, n, page, lane);
+                else tile.template load_keys<false>(s, layer, hkv, kvh, n, page, lane);
+            });
+            if (coh) tile.template load_values<true>(s, layer, hkv, kvh, n, page, lane);
+            else tile.template load_values<false>(s, layer, hkv, kvh, n, page, lane);
+        }
+        if (t < t_end) {
+            tile.mask_values(t * FKT, kmax, lane);
+            att_tile_update<HD>(st, qf, tile, t * FKT, last_key, own_base, own_mask, (t + 1) * FKT <= len, a.scale_log2e, lane);
+        }
         TRACE(20);
         // ---- merge of the eight wavefronts through LDS ----
         if (i != i_first) lds_sync();  // the previous item's merge has been read
