@@ -136,10 +136,6 @@ int run_layers(vf_model *m, const Batch &b, const int32_t *tokens, int *tail_par
         *tail_parts = 0;
         return vf_run_layers_f32(m, b, tokens, tree, st);
     }
-    if (m->fast_path && m->persistent && vf_direct_ok(m, b)) {
-        *tail_parts = 0;
-        return vf_run_direct(m, b, tokens, tree, st);
-    }
     const int rows = b.total_rows, R = rows;  // partials are laid out with ld = rows of this call
     const int d = c.d_model, F = c.d_ffn, nq = c.n_q_heads * c.head_dim, nkv = c.n_kv_heads * c.head_dim;
     int rc;
@@ -566,7 +562,10 @@ static int verify_impl(vf_model *m, vf_seq *const *seqs, int n_seqs, const int32
     float *dst = logits_out_dev ? logits_out_dev : m->logits;
     if (m->fast_path && m->persistent && vf_fused_ok(m, b)) {
         if ((rc = vf_run_fused(m, b, tokens_dev, dst, tree, st))) return rc;
-    } else if (!tree && m->fast_path && vf_fast_path_ok(m, b.total_rows) && !(m->persistent && vf_direct_ok(m, b))) {
+    } else if (m->fast_path && m->persistent && vf_direct_ok(m, b)) {
+        if ((rc = vf_run_direct(m, b, tokens_dev, tree, st))) return rc;
+        if ((rc = run_head(m, b.total_rows, 0, 0, b.total_rows, dst, st))) return rc;
+    } else if (!tree && m->fast_path && vf_fast_path_ok(m, b.total_rows)) {
         if ((rc = vf_run_fast(m, b, tokens_dev, dst, st))) return rc;
     } else {
         int tail = 0;

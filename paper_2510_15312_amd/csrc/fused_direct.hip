@@ -342,6 +342,8 @@ static void plan_down(const vf_config &c, int nbw, int groups, FusedArgs &a) {
 //   0.5B  9 rows 730 / 945, 33 819 / 946, 64 892 / 974, 80 1030 / 1026, 128 1113 / 1054
 //   1.5B  9 rows 1234 / 1486, 33 1468 / 1509, 64 1483 / 1568, 80 1919 / 1647, 128 1930 / 1734
 //   3B    9 rows 1605 / 2119, 33 1936 / 2123, 64 2093 / 2224, 80 2977 / 2426, 128 3294 / 2671
+// Of vf_verify's calls alone: a chunk of a prompt keeps a launch per operation, which shares the GPU with whatever runs
+// on other streams; this kernel needs all of it.
 // (more rows: tiles as large as the accumulators take cost more in the sum over the wavefronts than the launches do)
 bool vf_direct_ok(const vf_model *m, const Batch &b) {
     const vf_config &c = m->cfg;

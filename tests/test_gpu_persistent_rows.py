@@ -23,7 +23,7 @@ MODELS = {
     "two_passes_128": (dict(d_model=2048, n_q_heads=12, n_kv_heads=4, head_dim=128, d_ffn=4128, vocab=2064), 300),
 }
 VERIFY = (1, 7, 8, 9, 16, 17, 24, 25, 32, 33)   # two_passes_128: 32 rows are the most that LDS takes
-CHUNK = (1, 15, 33, 47, 49, 63, 64, 65)         # 65: a launch per operation
+BATCH = (34, 47, 48, 49, 63, 64, 65, 66)        # two sequences; from 65 rows on a launch per operation
 
 
 def _model(name):
@@ -34,21 +34,22 @@ def _model(name):
         wd = wl.make_weights(cfg, wl.streams(cfg).weights)
         model = vf.vf_model_create(vf.config_from(cfg, 128, 1024), vf.upload_weights(wd, cfg.dtype, DEV), DEV)
         spec, w32 = spec_of(cfg), weights_of(wd, np.float32)
-        seq = vf.vf_seq_create(model, 1024)
+        seqs = [vf.vf_seq_create(model, 1024) for _ in range(2)]
         ids = wl.make_context(cfg.vocab, ctx, np.random.default_rng(7))
         cache = oracle.KVCache(spec, 1024, np.float32)
         forward(spec, w32, cache, ids, np.float32)
         # the same keys and values on both sides
         for layer in range(cfg.n_layers):
             k, v = (np.ascontiguousarray(c[layer, :, :ctx].transpose(1, 0, 2)) for c in (cache.k, cache.v))
-            vf.vf_kv_write(model, seq, layer, 0, torch.as_tensor(k, device=DEV), torch.as_tensor(v, device=DEV))
-        _cache[name] = cfg, model, spec, w32, seq, cache, ctx
+            for seq in seqs:
+                vf.vf_kv_write(model, seq, layer, 0, torch.as_tensor(k, device=DEV), torch.as_tensor(v, device=DEV))
+        _cache[name] = cfg, model, spec, w32, seqs, cache, ctx
     return _cache[name]
 
 
-def _want(name, rows):
+def _want(name, rows, seed=0):
     cfg, _, spec, w32, _, cache, ctx = _model(name)
-    ids = wl.make_context(cfg.vocab, rows, np.random.default_rng(rows))
+    ids = wl.make_context(cfg.vocab, rows, np.random.default_rng((rows, seed)))
     cache.len = ctx
     z = forward(spec, w32, cache, ids, np.float32)
     cache.len = ctx
@@ -57,7 +58,7 @@ def _want(name, rows):
 
 @pytest.mark.parametrize("name,rows", [(n, r) for n in MODELS for r in VERIFY])
 def test_verify_logits_against_oracle(name, rows):
-    cfg, model, _, _, seq, _, ctx = _model(name)
+    cfg, model, _, _, (seq, _), _, ctx = _model(name)
     ids, z = _want(name, rows)
     out = torch.empty((rows, cfg.vocab), dtype=torch.float32, device=DEV)
     again = torch.empty_like(out)
@@ -72,17 +73,19 @@ def test_verify_logits_against_oracle(name, rows):
 
 
 @pytest.mark.parametrize("persistent", [1, 0])
-@pytest.mark.parametrize("name,rows", [(n, r) for n in MODELS for r in CHUNK])
-def test_chunk_logits_against_oracle(name, rows, persistent):
-    cfg, model, _, _, seq, _, ctx = _model(name)
-    ids, z = _want(name, rows)
+@pytest.mark.parametrize("name,rows", [(n, r) for n in MODELS for r in BATCH])
+def test_batch_logits_against_oracle(name, rows, persistent):
+    cfg, model, _, _, seqs, _, ctx = _model(name)
+    first = rows // 2
+    (ids_a, z_a), (ids_b, z_b) = _want(name, first, 1), _want(name, rows - first, 2)
     out = torch.empty((rows, cfg.vocab), dtype=torch.float32, device=DEV)
-    vf.vf_seq_set_len(seq, ctx)
+    for seq in seqs:
+        vf.vf_seq_set_len(seq, ctx)
     vf.vf_set_option(model, vf.VF_OPT_PERSISTENT, persistent)
     try:
-        vf.vf_prefill_chunk(model, seq, i32(ids), logits_mode=2, logits_out=out)
+        vf.vf_verify(model, seqs, i32(np.concatenate([ids_a, ids_b])), [0, first, rows], out)
     finally:
         vf.vf_set_option(model, vf.VF_OPT_PERSISTENT, 1)
-    err = rel_inf(out.cpu().numpy(), z).max()
+    err = rel_inf(out.cpu().numpy(), np.concatenate([z_a, z_b])).max()
     print(f"{name}, {rows} rows: {err:.2e}", flush=True)
     assert err < 2e-2
