@@ -113,11 +113,14 @@ __global__ __launch_bounds__(256) void norm_bf16_vec_kernel(float *__restrict__ 
     __shared__ float red[4];
     const int row = blockIdx.x;
     float v[VPT][8];
+    floatx4 g[VPT][2];   // the gain is requested with the row, not behind its sum
     float ss = 0.f;
 #pragma unroll
     for (int i = 0; i < VPT; ++i) {
         const int k0 = (threadIdx.x + i * 256) * 8;
         if (k0 < d) {
+            g[i][0] = *reinterpret_cast<const floatx4 *>(gain + k0);
+            g[i][1] = *reinterpret_cast<const floatx4 *>(gain + k0 + 4);
             float *hp = h + (size_t)row * d + k0;
             const float4 a = *reinterpret_cast<const float4 *>(hp), b = *reinterpret_cast<const float4 *>(hp + 4);
             v[i][0] = a.x; v[i][1] = a.y; v[i][2] = a.z; v[i][3] = a.w;
@@ -159,8 +162,7 @@ __global__ __launch_bounds__(256) void norm_bf16_vec_kernel(float *__restrict__ 
     for (int i = 0; i < VPT; ++i) {
         const int k0 = (threadIdx.x + i * 256) * 8;
         if (k0 >= d) continue;
-        const float4 ga = *reinterpret_cast<const float4 *>(gain + k0), gb = *reinterpret_cast<const float4 *>(gain + k0 + 4);
-        const float gv[8] = {ga.x, ga.y, ga.z, ga.w, gb.x, gb.y, gb.z, gb.w};
+        const float gv[8] = {g[i][0][0], g[i][0][1], g[i][0][2], g[i][0][3], g[i][1][0], g[i][1][1], g[i][1][2], g[i][1][3]};
         u32x4_t out;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {

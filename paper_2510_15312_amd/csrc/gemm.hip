@@ -19,7 +19,6 @@ constexpr int PREFETCH = 4;   // weight fragments in flight per stream and wavef
 
 template <int NB> struct Chunk { static constexpr int KC = (NB <= 2) ? 16 : 8; };
 
-__device__ inline u32x4 load_stream(const u32x4 *p) { return __builtin_nontemporal_load(p); }
 
 // NB: 16-row activation blocks handled per pass; NBW: weight n-blocks per wavefront.
 template <int NB, int NBW>

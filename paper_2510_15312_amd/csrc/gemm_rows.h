@@ -20,11 +20,10 @@
 //   1024 x 16384 x 3072).
 #pragma once
 
+#include "fast_common.h"
 #include "lds_stream.h"
 
 namespace {
-
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int ROWS_EPI_PARTIAL = 0, ROWS_EPI_SWIGLU = 1, ROWS_EPI_TOPK = 2, ROWS_EPI_QKV = 3;
 
@@ -69,7 +68,10 @@ __device__ __forceinline__ float silu_mul(float g, float u) { return g / (1.0f +
 // holds Y[row = 16 cb + (lane & 15)][16 nb + 4 (lane >> 4) + 0..3].
 //   PARTIAL: float32 sums of this K split.
 //   SWIGLU : gate row f is column 2 f and up row f column 2 f + 1 of the packed matrix, so a lane holds
-//            two (gate, up) pairs: a = bf16(silu(gate) * up), columns 8 nb + 2 (lane >> 4) + 0..1.
+//            two (gate, up) pairs: a = bf16(silu(gate) * up), columns 8 nb + 2 (lane >> 4) + 0..1.  Written through:
+//            workgroups of all dies write four bytes of the same lines, and what is left in a die's L2 has to be
+//            written back before the next kernel starts (down behind it, 256 rows of 1.5B, 17.6 -> 17.4 us).  Partial sums,
+//            whose lines have one writer, and norms lose by it what the kernel behind them gains.
 //   QKV    : bias, rotary embedding, q rows and the cache's keys and values (qkv_store): a lane's four
 //            columns are its unit.
 //   TOPK   : per row, the topk largest of the wavefront's 16 WNB columns with their ids, in falling order,
@@ -92,7 +94,7 @@ __device__ __forceinline__ void rows_epilogue(const RowsArgs<EPI> &p, const Rows
                 const floatx4 v = acc[n][c];
                 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
                 const bf16x2 o = {(bf16_t)silu_mul(v[0], v[1]), (bf16_t)silu_mul(v[2], v[3])};
-                a_out[(((size_t)(nb >> 2) * p.ncb + cb) * 64 + ((nb & 3) << 4) + (lane & 15)) * 4 + g4] = __builtin_bit_cast(unsigned, o);
+                st_u32<true>(a_out + (((size_t)(nb >> 2) * p.ncb + cb) * 64 + ((nb & 3) << 4) + (lane & 15)) * 4 + g4, __builtin_bit_cast(unsigned, o));
             }
         }
     } else if constexpr (EPI == ROWS_EPI_QKV) {
