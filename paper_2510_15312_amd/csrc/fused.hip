@@ -19,7 +19,7 @@
 //     the residual stream per half layer, one q / attention output / SwiGLU buffer and one set
 //     of attention records per layer -- so no cache can hold a stale line of it: a line is never
 //     read before its only write in a launch, and caches start clean at every launch;
-//   * data in reused buffers (split-K partial tiles, counters) is read with agent-scope loads.
+//   * data in reused buffers (the exchange of partial tiles, counters) is read with agent-scope loads.
 // The KV cache is written (new rows) and read (all rows) once per layer and launch, in that
 // order; tiles that hold new rows are read with agent-scope loads.
 //
@@ -274,7 +274,7 @@ __device__ __forceinline__ void qkv_phase(const FastGemm &g, const Items &im, Gr
 // memory into registers: no staging in LDS, no barrier between the loads and the products, no index arithmetic,
 // and no limit on the K slice.  Behind the grid barrier a wavefront issues one load per fragment, its products,
 // and the sum over the wavefronts; everything else (weights, addresses, the residual tile) comes before it.
-// Items: (unit of UB weight blocks) x (K split), as in gemm_phase.  The splits of a unit exchange their sums tile by
+// Items: (unit of UB weight blocks) x (K split).  The splits of a unit exchange their sums tile by
 // tile, wavefront to wavefront; no workgroup barrier is in that chain.
 // Depth: all k-blocks of a wavefront at once where the shape allows (weights requested before the barrier, X in one
 // round trip behind it).  Release to last arrival, staged through LDS / so: O of 0.5B, 1 row 2.9 / 1.7 us, of 1.5B,
