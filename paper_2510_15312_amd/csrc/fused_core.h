@@ -21,9 +21,10 @@ constexpr int LDS_BYTES = 152 * 1024;  // dynamic LDS of the one workgroup a CU 
 constexpr long long SPIN_LIMIT = 4000000;  // polls before a barrier gives up (seconds, not microseconds)
 
 #ifndef FUSED_MAXP
-#define FUSED_MAXP 6              // most key parts per attention block (8 parts: 1280 us per launch, 6 1261, 5 1258, 4 1254, 3 1274, 2 1318;
-                                  // every setting gives the same mean logit error at the full 1.5B size, 1.3e-2, but with 4 and 5 parts one row
-                                  // of 136 lands at 2.12e-2 and 2.005e-2, past the stated 2e-2: 6 is the fastest setting inside it)
+#define FUSED_MAXP 6              // most key parts per attention block (verify step of 1.5B, 17 rows, 2048 keys: 9 parts 1135 us, 6 1126, 5 1143,
+                                  // 4 1157; the 0.5B shape at 1024 keys takes five: 4 577 for 582; every setting gives the same mean logit
+                                  // error at the full 1.5B size, 1.3e-2, but with 4 and 5 parts one row of 136 landed at 2.12e-2 and 2.005e-2,
+                                  // past the stated 2e-2)
 #endif
 // One workgroup of 8 wavefronts per CU: two wavefronts per SIMD, so each may use up to 256 vector
 // registers (weight ring + staging loads in flight) without spilling.
@@ -420,8 +421,8 @@ __device__ __forceinline__ floatx4 xch_sum(floatx4 v, float *xch, unsigned at, u
 // order 8*(rho >> 2) + (rho & 3) (+ 4 for the second 16-key block): that is the B-operand layout
 // of O^T[d, item] += V^T[d, key] P[key, item], and the matching V^T fragment is one 16-byte load.
 // Wavefront results (running max, sum, O^T) are merged through LDS; with several parts the
-// merged partials go to memory and the last workgroup to arrive merges the parts.  No second
-// grid-wide phase is needed for the merge.
+// parts exchange their d-blocks (above), one owner each.  No second grid-wide phase is needed
+// for the merge.
 constexpr int FKT = ATT_TILE;  // keys per tile
 
 // len0: length of the sequence of this workgroup's first item, read once per launch (lengths do
