@@ -27,13 +27,7 @@ __host__ __device__ inline int items_parts(const SeqDesc &s, int part_pages) {
     return ((keys + VF_TILE - 1) / VF_TILE + part_pages - 1) / part_pages;
 }
 
-// Largest value, or sum, over the four lanes that share an item (lane & 15).
-__device__ __forceinline__ float item_max(float x) {
-    auto a = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, x), __builtin_bit_cast(unsigned, x), false, false);
-    x = fmaxf(__builtin_bit_cast(float, a[0]), __builtin_bit_cast(float, a[1]));
-    auto c = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned, x), __builtin_bit_cast(unsigned, x), false, false);
-    return fmaxf(__builtin_bit_cast(float, c[0]), __builtin_bit_cast(float, c[1]));
-}
+// Sum over the four lanes that share an item (lane & 15).
 __device__ __forceinline__ float item_sum(float x) {
     x += __shfl_xor(x, 16, 64);
     return x + __shfl_xor(x, 32, 64);
@@ -121,7 +115,8 @@ __global__ __launch_bounds__(ITEMS_WAVES * 64) VF_MFMA_KERNEL void attn_items_ke
         float mx = fmaxf(sc[0][0], sc[0][1]);
 #pragma unroll
         for (int j = 2; j < 16; ++j) mx = fmaxf(mx, sc[j >> 2][j & 3]);
-        const float m_new = fmaxf(m_run, item_max(mx) * scale_log2e);
+        mx = over_item(mx, [](float x, float y) { return fmaxf(x, y); });
+        const float m_new = fmaxf(m_run, mx * scale_log2e);
         if (__builtin_amdgcn_ballot_w64(m_new != m_run)) {
             const float corr = __builtin_amdgcn_exp2f(m_run - m_new);
             l_run *= corr;

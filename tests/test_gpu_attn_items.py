@@ -8,6 +8,8 @@ paths round the same values to bfloat16, so they differ by the order of float32 
 tips over: under 1e-2 of the largest logit (the tolerance of either against the oracle is 2e-2); a key left
 out, or one too many, moves a row whose weight is spread over few keys by far more, and the softmax here is
 peaked (keys with a spread of 3)."""
+from types import SimpleNamespace
+
 import numpy as np
 import pytest
 import torch
@@ -138,3 +140,39 @@ def test_value_that_is_not_finite(at):
     clear = [r for r in range(at) if r + 6 < at - at % 32]
     assert len(clear) > 20 and np.isnan(got[at:]).any(axis=1).all()
     assert np.array_equal(got[clear], want[clear])
+
+
+# One key that all rows see scores some 270 above every other (natural logarithm): its weight is 1, and a running maximum
+# that is not the largest of all keys of a page lets its exponential overflow.  Every lane of an item holds eight keys of 32.
+# The queries are a bias that the rotary embedding hardly turns (theta so large that only the first quarter of the
+# frequencies counts, where the bias is zero).
+@pytest.mark.parametrize("hd", [64, 128])
+def test_one_key_far_above_the_others(hd):
+    pair = _pair(hd)
+    ctx, rows, half = 1900, 777, hd // 2
+    assert attention_plan(pair.vcfg, [ctx], [rows])[0]
+    turned = torch.arange(hd, device=DEV) % half < half // 4
+    direction = torch.where(turned, 0.0, 1.0).to(DEV)
+    nq, nkv = pair.cfg.n_q_heads, pair.cfg.n_kv_heads
+    layer = {**pair.dw["layers"][0], "bq": 2.0 * direction.repeat(nq), "bk": torch.zeros(nkv * hd, device=DEV),
+             "bv": torch.zeros(nkv * hd, device=DEV)}
+    cfg = vf.make_config(1, pair.cfg.d_model, nq, nkv, hd, pair.cfg.d_ffn, pair.cfg.vocab, "bf16", 1e38, pair.cfg.rms_eps, rows, 9000,
+                         qkv_bias=True)
+    own = SimpleNamespace(cfg=pair.cfg, model=vf.vf_model_create(cfg, {**pair.dw, "layers": [layer]}, DEV))
+    seq = vf.vf_seq_create(own.model, 9000, device=DEV)
+    ids = i32(wl.make_context(pair.cfg.vocab, rows, np.random.default_rng(hd)))
+    logits = torch.empty((rows, pair.cfg.vocab), dtype=torch.float32, device=DEV)
+    scale = 270.0 / (2.0 * float(direction.sum()) / hd ** 0.5)
+
+    def run():
+        vf.vf_seq_set_len(seq, ctx)
+        vf.vf_prefill_chunk(own.model, seq, ids, logits_mode=2, logits_out=logits)
+        return logits
+    for key in (192 + 3, 192 + 9, 192 + 20, 192 + 31, 192 + 36, 192 + 46, 192 + 55, 192 + 56, ctx - 1):
+        gen = torch.Generator(device=DEV).manual_seed(key)
+        kv = torch.empty((2, ctx, nkv, hd), dtype=torch.float32, device=DEV).normal_(0.0, 1.0, generator=gen)
+        kv[0, key] = scale * direction
+        vf.vf_kv_write(own.model, seq, 0, 0, kv[0], kv[1])
+        err = _both(own, run)
+        print(f"hd {hd}, key {key}: {err:.2e}", flush=True)
+        assert err < 1e-2
