@@ -345,7 +345,8 @@ int vf_draft_suffix_match(const int32_t *history_host, int n, int max_suffix, in
  * on-chip memory, vf_verify runs the whole forward pass as one persistent kernel whose phases are
  * separated by grid-wide barriers; 0 keeps one kernel per GEMM.  Same function, same rounding
  * points; sums are taken in a different (fixed) order.  Where they do not fit, and for 49 to 64 rows in total,
- * the layers alone run that way, and the output head behind them.  The persistent kernel occupies the whole
+ * the layers alone run that way, and the output head behind them.  Either may be captured into a graph
+ * and replayed (the call reads the sequences' lengths on the device).  The persistent kernel occupies the whole
  * GPU: two vf_verify calls on the same model must not overlap (they share its workspace anyway),
  * and a barrier that cannot complete within seconds (the GPU shared with another process that
  * keeps workgroups from becoming resident) gives up; vf_seq_get_state and vf_profile_read then

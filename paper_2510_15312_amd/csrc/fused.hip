@@ -611,13 +611,7 @@ template <int NB, int HD>
 __global__ __launch_bounds__(FT, FUSED_MINW) void verify_fused_kernel(FusedArgs a, Batch b) {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ FusedShared sh;
-#ifdef FUSED_ARRIVALS
-    // debug build: stamps go behind the first 64 rows of the logits buffer (the model workspace's, when the caller passes none)
-    GridBar bar{a.bar, a.fail, a.root0, gridDim.x / BAR_COUNTERS, false,
-                reinterpret_cast<unsigned long long *>(a.logits + (size_t)64 * a.vocab), 0, 0};
-#else
-    GridBar bar{a.bar, a.fail, a.root0, gridDim.x / BAR_COUNTERS, false};
-#endif
+    const unsigned start = barrier_start(a.bar_start);
     const int d = a.d, F = a.F, hd = a.hd, nq = a.hq * hd, nkv = a.hkv * hd;
     const size_t hstride = (size_t)a.frows * d, sstride = (size_t)(d / 16) * 64;
 
@@ -627,6 +621,13 @@ __global__ __launch_bounds__(FT, FUSED_MINW) void verify_fused_kernel(FusedArgs 
     const int len0 = launch_tables(a, b, sh);
     TRACE(0);
     embed_phase(a, b);
+#ifdef FUSED_ARRIVALS
+    // debug build: stamps go behind the first 64 rows of the logits buffer (the model workspace's, when the caller passes none)
+    GridBar bar{a.bar, a.fail, (unsigned)__builtin_amdgcn_readfirstlane(start), gridDim.x / BAR_COUNTERS, false,
+                reinterpret_cast<unsigned long long *>(a.logits + (size_t)64 * a.vocab), 0, 0};
+#else
+    GridBar bar{a.bar, a.fail, (unsigned)__builtin_amdgcn_readfirstlane(start), gridDim.x / BAR_COUNTERS, false};
+#endif
     bar.arrive();   // (a workgroup barrier inside: the row table is visible to every wavefront from here on)
 
     FastGemm base;
@@ -700,6 +701,7 @@ __global__ __launch_bounds__(FT, FUSED_MINW) void verify_fused_kernel(FusedArgs 
         g.ss_in = a.ssv + (size_t)(2 * a.n_layers) * sstride; g.logits = a.logits;
         wave_phase<NB, HD, EPI_LOGITS>(g, 0, bar, smem, a.lds_total, sh TRACE_PASS);
     }
+    barrier_advance(a.bar_start, bar);
     TRACE(99);
 #ifdef FUSED_ARRIVALS
     if (threadIdx.x == 0) bar.stamps[((size_t)bar.n_arr * 2) * gridDim.x + blockIdx.x] = wall_clock64();  // end of the head phase
@@ -767,7 +769,6 @@ int vf_fused_init(vf_model *m, char *ws, hipStream_t st) {
             return vf_fail(VF_ERR_ARG, "persistent kernel: layers at unequal distances");
     }
     VF_HIP(hipStreamSynchronize(st));   // a model is ready for any stream once it is created
-    m->fz_epoch = 0;
     return VF_OK;
 }
 
@@ -797,27 +798,26 @@ int vf_run_fused(vf_model *m, const Batch &b, const int32_t *tokens, float *logi
         a.gu_light = (FUSED_GU_LIGHT && H > 0 && n_o < units && units - n_o <= 3 * H && units - n_o > H) ? n_o : 0;
     }
     ProfScope ps(m, VF_SITE_STEP, st);
-    const int nb = (b.total_rows + 15) / 16, barriers = 1 + 5 * c.n_layers;
+    const int nb = (b.total_rows + 15) / 16;
     if (c.head_dim == 128) {
-        if (nb == 1) return fused_launch<&verify_fused_kernel<1, 128>>(m, a, b, barriers, st);
-        if (nb == 2) return fused_launch<&verify_fused_kernel<2, 128>>(m, a, b, barriers, st);
-        return fused_launch<&verify_fused_kernel<3, 128>>(m, a, b, barriers, st);
+        if (nb == 1) return fused_launch<&verify_fused_kernel<1, 128>>(a, b, st);
+        if (nb == 2) return fused_launch<&verify_fused_kernel<2, 128>>(a, b, st);
+        return fused_launch<&verify_fused_kernel<3, 128>>(a, b, st);
     }
-    if (nb == 1) return fused_launch<&verify_fused_kernel<1, 64>>(m, a, b, barriers, st);
-    if (nb == 2) return fused_launch<&verify_fused_kernel<2, 64>>(m, a, b, barriers, st);
-    return fused_launch<&verify_fused_kernel<3, 64>>(m, a, b, barriers, st);
+    if (nb == 1) return fused_launch<&verify_fused_kernel<1, 64>>(a, b, st);
+    if (nb == 2) return fused_launch<&verify_fused_kernel<2, 64>>(a, b, st);
+    return fused_launch<&verify_fused_kernel<3, 64>>(a, b, st);
 }
 
 // Whether any barrier of an earlier launch gave up (the stream must be idle).
 int vf_fused_check(vf_model *m) {
     if (!m->fz_bar) return VF_OK;
     unsigned flag = 0;
-    VF_HIP(hipMemcpy(&flag, m->fz_bar + 8000, 4, hipMemcpyDeviceToHost));
+    VF_HIP(hipMemcpy(&flag, m->fz_bar + BAR_FAIL, 4, hipMemcpyDeviceToHost));
     if (flag) {
-        // counters are out of step now: start over from zero
+        // counters and their start value are out of step now: start over from zero
         VF_HIP(hipMemset(m->fz_bar, 0, 65536));
         VF_HIP(hipMemset(m->fz_xch, 0xff, xch_bytes(m->cfg)));
-        m->fz_epoch = 0;
         return vf_fail(VF_ERR_HIP, "persistent verify kernel: a grid barrier timed out; results of that call are invalid");
     }
     return VF_OK;

@@ -17,6 +17,9 @@ constexpr int MAX_DOWN_SPLITS = 9;   // K splits of the down projection
 #ifndef BAR_COUNTERS
 #define BAR_COUNTERS 64           // counters a barrier's arrivals are spread over
 #endif
+// words of the barrier block behind the counters, in memory lines of their own (from word 8192 on: phase timelines)
+constexpr int BAR_START = 7936, BAR_FAIL = 8000;
+static_assert(BAR_COUNTERS * 64 <= BAR_START, "counters end below");
 constexpr int LDS_BYTES = 152 * 1024;  // dynamic LDS of the one workgroup a CU holds (160 KB less the static part)
 constexpr long long SPIN_LIMIT = 4000000;  // polls before a barrier gives up (seconds, not microseconds)
 
@@ -72,7 +75,7 @@ struct FusedArgs {
     bf16_t *xv;       // fused_direct.hip: normalised rows, [2L][frows][d]
     float *h_last;    // fused_direct.hip: the residual stream behind the last layer
     float *xch;       // partial tiles of the down projection's K splits, then of the attention's key parts; marks between uses
-    unsigned *bar, *fail;
+    unsigned *bar, *fail, *bar_start;   // barrier counters, whether one gave up, the counters' value at launch start
     float *logits;
     int n_layers, d, F, hq, hkv, hd, vocab, m, has_bias;
     int att_blocks, att_parts;  // (query block, kv head, sequence) blocks of the call; key parts per block
@@ -81,7 +84,6 @@ struct FusedArgs {
     // die, so that its L2 serves all but the first of those reads.
     short att_first[FUSED_G];
     float inv_d, eps, scale_log2e;
-    unsigned root0;   // value of the barrier's root counter when this launch starts
     int ks_down;              // K splits of the down projection
     int down_ub;              // weight blocks of a down projection item
     int gu_light;            // gate/up: the first gu_light workgroups (busy in the O projection) take one unit each (0: even shares)
@@ -93,10 +95,12 @@ struct FusedArgs {
 // at one address); an arrival is one increment that returns nothing, and a barrier is complete when
 // every counter has grown by the number of workgroups mapped to it.  Counters only ever grow:
 // barrier number e of a launch waits for the counters' value at launch start + e * (G / BAR_COUNTERS).
+// That start value is in device memory, not an argument: every workgroup reads it before its first arrival, and the
+// launch leaves it advanced (barrier_advance), so that a launch replayed from a graph finds its own.
 // Lanes 0..BAR_COUNTERS-1 of the first wavefront poll one counter each.
 struct GridBar {
     unsigned *mem, *fail;
-    unsigned target, per;  // per: workgroups per counter
+    unsigned target, per;  // target: at first the counters' value at launch start; per: workgroups per counter
     bool dead;
 #ifdef FUSED_ARRIVALS
     unsigned long long *stamps;  // [barrier][2][workgroup]: clock at the arrival and at the end of the wait
@@ -138,6 +142,14 @@ struct GridBar {
 #endif
     }
 };
+
+// The counters' value at launch start: requested first thing in a kernel, used when its first phase is done.
+__device__ __forceinline__ unsigned barrier_start(const unsigned *start) { return __hip_atomic_load(start, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+// For the next launch: what the counters have grown to when all arrivals of this one are in.  Anywhere behind this
+// workgroup's first wait, when every workgroup has read the old value, and its last arrival.
+__device__ __forceinline__ void barrier_advance(unsigned *start, const GridBar &bar) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) __hip_atomic_store(start, bar.target, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 
 // Optional phase timeline of one workgroup (build with -DFUSED_TRACE=<workgroup>): thread 0 stamps the
 // constant-rate clock at the marked points into the second half of the barrier block.
@@ -631,7 +643,8 @@ inline void fused_args(const vf_model *m, const Batch &b, const int32_t *tokens,
     a.av = (bf16_t *)m->fz_a;
     a.xch = m->fz_xch;
     a.bar = m->fz_bar;
-    a.fail = m->fz_bar + 8000;
+    a.fail = m->fz_bar + BAR_FAIL;
+    a.bar_start = m->fz_bar + BAR_START;
     a.n_layers = c.n_layers;
     a.d = c.d_model;
     a.F = c.d_ffn;
@@ -675,8 +688,7 @@ inline void fused_args(const vf_model *m, const Batch &b, const int32_t *tokens,
     a.scale_log2e = 1.4426950408889634f / sqrtf((float)c.head_dim);
 }
 
-// barriers: arrivals of a launch
-template <auto KERN> int fused_launch(vf_model *m, FusedArgs &a, const Batch &b, int barriers, hipStream_t st) {
+template <auto KERN> int fused_launch(const FusedArgs &a, const Batch &b, hipStream_t st) {
     static int max_wgs = -1;  // workgroups that can be resident at once
     const void *kern = reinterpret_cast<const void *>(KERN);
     if (max_wgs < 0) {
@@ -690,8 +702,6 @@ template <auto KERN> int fused_launch(vf_model *m, FusedArgs &a, const Batch &b,
     }
     if (FUSED_G > max_wgs)
         return vf_fail(VF_ERR_UNSUPPORTED, "persistent kernel: %d workgroups wanted, %d can be resident", FUSED_G, max_wgs);
-    a.root0 = m->fz_epoch;
-    m->fz_epoch += (unsigned)barriers * (unsigned)(FUSED_G / BAR_COUNTERS);  // barriers per launch x arrivals per counter
     hipLaunchKernelGGL(KERN, dim3(FUSED_G), dim3(FT), a.lds_total, st, a, b);
     VF_LAUNCH_CHECK("persistent kernel");
     return VF_OK;

@@ -235,7 +235,7 @@ template <int NBW, int HD>
 __global__ __launch_bounds__(FT, 2) void layers_direct_kernel(FusedArgs a, Batch b) {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ FusedShared sh;
-    GridBar bar{a.bar, a.fail, a.root0, gridDim.x / BAR_COUNTERS, false};
+    const unsigned start = barrier_start(a.bar_start);
 #ifdef FUSED_TRACE
     Trace trace{reinterpret_cast<unsigned long long *>(a.bar + 8192), 0};
 #endif
@@ -243,6 +243,7 @@ __global__ __launch_bounds__(FT, 2) void layers_direct_kernel(FusedArgs a, Batch
     const size_t hstride = (size_t)a.frows * d;
     const int len0 = launch_tables(a, b, sh);
     embed_phase(a, b);
+    GridBar bar{a.bar, a.fail, (unsigned)__builtin_amdgcn_readfirstlane(start), gridDim.x / BAR_COUNTERS, false};
     bar.arrive();
     FastGemm base;
     base.m = a.m;
@@ -317,6 +318,7 @@ __global__ __launch_bounds__(FT, 2) void layers_direct_kernel(FusedArgs a, Batch
         TRACE(16);
         xch_clear<1>(a.xch, down_used);
     }
+    barrier_advance(a.bar_start, bar);
 }
 
 }  // namespace
@@ -366,13 +368,12 @@ int vf_run_direct(vf_model *m, const Batch &b, const int32_t *tokens, bool tree,
     if (ncb == 1) nbw = 2;
     plan_down(c, nbw, (ncb + nbw - 1) / nbw, a);
     ProfScope ps(m, VF_SITE_STEP, st);
-    const int barriers = 1 + 7 * c.n_layers;
     if (c.head_dim == 128) {
-        if (nbw == 2) return fused_launch<&layers_direct_kernel<2, 128>>(m, a, b, barriers, st);
-        if (nbw == 3) return fused_launch<&layers_direct_kernel<3, 128>>(m, a, b, barriers, st);
-        return fused_launch<&layers_direct_kernel<4, 128>>(m, a, b, barriers, st);
+        if (nbw == 2) return fused_launch<&layers_direct_kernel<2, 128>>(a, b, st);
+        if (nbw == 3) return fused_launch<&layers_direct_kernel<3, 128>>(a, b, st);
+        return fused_launch<&layers_direct_kernel<4, 128>>(a, b, st);
     }
-    if (nbw == 2) return fused_launch<&layers_direct_kernel<2, 64>>(m, a, b, barriers, st);
-    if (nbw == 3) return fused_launch<&layers_direct_kernel<3, 64>>(m, a, b, barriers, st);
-    return fused_launch<&layers_direct_kernel<4, 64>>(m, a, b, barriers, st);
+    if (nbw == 2) return fused_launch<&layers_direct_kernel<2, 64>>(a, b, st);
+    if (nbw == 3) return fused_launch<&layers_direct_kernel<3, 64>>(a, b, st);
+    return fused_launch<&layers_direct_kernel<4, 64>>(a, b, st);
 }

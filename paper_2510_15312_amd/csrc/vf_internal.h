@@ -104,7 +104,6 @@ struct vf_model {
     void *fz_q, *fz_o, *fz_a, *fz_x;
     unsigned *fz_bar;
     char *fz_ws;                // their workspace
-    unsigned fz_epoch;          // value the barrier's root counter has after all launches so far
     const float *last_logits;   // where the last verify left its logits
     int last_rows;
     // measurement hook
