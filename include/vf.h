@@ -343,14 +343,15 @@ int vf_draft_suffix_match(const int32_t *history_host, int n, int max_suffix, in
 #define VF_OPT_FAST_PATH 1
 /* VF_OPT_PERSISTENT (default 1): when the few-row kernels apply and the activations of the call fit
  * on-chip memory, vf_verify runs the whole forward pass as one persistent kernel whose phases are
- * separated by grid-wide barriers; 0 keeps one kernel per GEMM.  Same function, same rounding
- * points; sums are taken in a different (fixed) order.  Where they do not fit, and for 49 to 64 rows in total,
- * the layers alone run that way, and the output head behind them.  Either may be captured into a graph
- * and replayed (the call reads the sequences' lengths on the device).  The persistent kernel occupies the whole
- * GPU: two vf_verify calls on the same model must not overlap (they share its workspace anyway),
- * and a barrier that cannot complete within seconds (the GPU shared with another process that
- * keeps workgroups from becoming resident) gives up; vf_seq_get_state and vf_profile_read then
- * report VF_ERR_HIP. */
+ * separated by grid-wide barriers; where they do not fit, the decoder layers alone run that way and
+ * the output head behind them; 0 keeps one kernel per GEMM.  Same function, same rounding points; sums
+ * are taken in a different (fixed) order.  Either may be captured into a graph and replayed (a call
+ * reads the sequences' lengths on the device).  A persistent kernel occupies the whole GPU: two calls
+ * that take one must not run on a GPU at the same time, of one model (whose workspace they share) or
+ * of several; order them by one stream or by events, or set 0.  Calls of more than 48 rows, prefill
+ * chunks and float32 models never take one.  A barrier that cannot complete within seconds (two such
+ * calls at once, the GPU shared with another process that keeps workgroups from becoming resident)
+ * gives up; vf_seq_get_state and vf_profile_read then report VF_ERR_HIP. */
 #define VF_OPT_PERSISTENT 2
 int vf_set_option(vf_model *m, int option, int value);
 

@@ -560,9 +560,9 @@ static int verify_impl(vf_model *m, vf_seq *const *seqs, int n_seqs, const int32
         if ((rc = vf_launch_tree_prep(m, b, td, st))) return rc;
     }
     float *dst = logits_out_dev ? logits_out_dev : m->logits;
-    if (m->fast_path && m->persistent && vf_fused_ok(m, b)) {
+    if (m->fast_path && m->persistent && vf_fused_ok(m->cfg, b.total_rows)) {
         if ((rc = vf_run_fused(m, b, tokens_dev, dst, tree, st))) return rc;
-    } else if (m->fast_path && m->persistent && vf_direct_ok(m, b)) {
+    } else if (m->fast_path && m->persistent && vf_direct_ok(m->cfg, b.total_rows)) {
         if ((rc = vf_run_direct(m, b, tokens_dev, tree, st))) return rc;
         if ((rc = run_head(m, b.total_rows, 0, 0, b.total_rows, dst, st))) return rc;
     } else if (!tree && m->fast_path && vf_fast_path_ok(m, b.total_rows)) {
@@ -697,6 +697,17 @@ int vf_debug_gemm_plan(const vf_config *cfg, int use, int rows, int32_t *out) {
     out[1] = p.ks;
     out[2] = p.epi;
     out[3] = use > 3 || p.epi != GEMM_PARTIAL || (size_t)p.ks * rows * N[use] <= m.part_floats;
+    return VF_OK;
+}
+
+// Which persistent kernel a call of vf_verify takes (options at their defaults).  out: 0 none, 1 the whole pass, 2 the
+// layers; grid barriers of its launch.
+int vf_debug_persistent_plan(const vf_config *cfg, int rows, int32_t *out) {
+    const int rc = check_config(cfg);
+    if (rc) return rc;
+    if (rows < 1 || rows > cfg->max_rows) return vf_fail(VF_ERR_ARG, "vf_debug_persistent_plan");
+    out[0] = vf_fused_ok(*cfg, rows) ? 1 : vf_direct_ok(*cfg, rows) ? 2 : 0;
+    out[1] = out[0] ? 1 + cfg->n_layers * (out[0] == 1 ? 5 : 7) : 0;
     return VF_OK;
 }
 

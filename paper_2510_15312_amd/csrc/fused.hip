@@ -723,9 +723,9 @@ int fill_split(int G, int units, int KB) {
 
 }  // namespace
 
-// What a work item sends through the exchange at most: 4 x 4 tiles of a down projection (fused_direct.hip), the d-blocks of
+// What a work item sends through the exchange at most: 4 x 3 tiles of a down projection (fused_direct.hip), the d-blocks of
 // an attention part with their (max, sum) pairs.  One item per workgroup.
-static size_t xch_bytes(const vf_config &c) { return (size_t)FUSED_G * std::max(16, c.head_dim / 16 * 2) * 1024; }
+static size_t xch_bytes(const vf_config &c) { return (size_t)FUSED_G * std::max(4 * 3, c.head_dim / 16 * 2) * 1024; }
 
 struct FusedBuffers { size_t h, ss, q, o, a, x, xch, bar, total; };
 static FusedBuffers fused_buffers(const vf_config &c) {
@@ -773,16 +773,14 @@ int vf_fused_init(vf_model *m, char *ws, hipStream_t st) {
 }
 
 // Whether a call's rows fit LDS next to the tiles of a pass.
-bool vf_fused_ok(const vf_model *m, const Batch &b) {
-    const vf_config &c = m->cfg;
-    const int rows = b.total_rows;
-    return m->fz_h && fused_shape_ok(c) && rows <= STAGED_ROWS &&
+bool vf_fused_ok(const vf_config &c, int rows) {
+    return fused_shape_ok(c) && rows <= FROWS &&
            (size_t)(c.d_model / 32) * rows * 64 + wave_tail_bytes((rows + 15) / 16) <= (size_t)LDS_BYTES;
 }
 
 int vf_run_fused(vf_model *m, const Batch &b, const int32_t *tokens, float *logits_out, bool tree, hipStream_t st) {
     const vf_config &c = m->cfg;
-    if (!vf_fused_ok(m, b)) return vf_fail(VF_ERR_UNSUPPORTED, "persistent kernel does not apply to this call");
+    if (!vf_fused_ok(c, b.total_rows)) return vf_fail(VF_ERR_UNSUPPORTED, "persistent kernel does not apply to this call");
     FusedArgs a;
     memset(&a, 0, sizeof a);
     fused_args(m, b, tokens, tree, a);

@@ -11,8 +11,7 @@ namespace {
 
 constexpr int FW = 8;            // wavefronts per workgroup
 constexpr int FT = FW * 64;      // threads per workgroup
-constexpr int FROWS = 64;        // most rows of a call (fused_direct.hip)
-constexpr int STAGED_ROWS = 48;  // most rows of a call of fused.hip
+constexpr int FROWS = 48;        // most rows of a call
 constexpr int MAX_DOWN_SPLITS = 9;   // K splits of the down projection
 #ifndef BAR_COUNTERS
 #define BAR_COUNTERS 64           // counters a barrier's arrivals are spread over
@@ -184,7 +183,6 @@ struct RowMeta {
     int live;        // 0: the slot lies outside the sequence's capacity, nothing is written
 };
 struct FusedShared {
-    float rs_s[64];
     float rs_tmp[FW][64];
     RowMeta rows[FROWS];
 };
@@ -259,7 +257,7 @@ __device__ __forceinline__ void embed_phase(const FusedArgs &a, const Batch &b) 
             sq += __shfl_xor(sq, 4, 64);
             sq += __shfl_xor(sq, 2, 64);
             sq += __shfl_xor(sq, 1, 64);
-            if (k < d && (threadIdx.x & 15) == 0 && row < STAGED_ROWS) st_f32<true>(a.ssv + (k >> 4) * 64 + row, sq);
+            if (k < d && (threadIdx.x & 15) == 0) st_f32<true>(a.ssv + (k >> 4) * 64 + row, sq);
         }
     }
 }

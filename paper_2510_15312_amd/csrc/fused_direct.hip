@@ -1,31 +1,30 @@
-// The decoder layers of a call as one persistent kernel whose activations are too many for the staging of fused.hip:
-// more rows than it takes, or rows that do not fit LDS whole.  Same structure and memory protocol; the phases are
+// The decoder layers of a call whose rows do not fit LDS whole, as the staging of fused.hip needs them, as one persistent
+// kernel.  Same structure and memory protocol; the phases are
 //   embed | per layer: norm, QKV, attention, O, norm, gate/up, down
 // The normalised rows go through memory as MFMA fragments, written once by the norm phases, and every GEMM phase
 // reads both operands in operand order straight into registers: no staging in LDS, no limit on the rows from it, no
 // K split for its sake.  A norm phase costs a barrier and a round trip (about 2.5 us); staging costs every workgroup
 // the loads and conversions of all its rows (at 33 rows of 3072 columns 8 us twice a layer, and K splits that meet in
 // memory on top).
-// The output head is the many-row path's, on the rows whose logits are wanted.
+// The output head is the many-row path's.
 #include "fused_core.h"
 
 namespace {
 
-// A GEMM phase's items: (unit of UB weight blocks) x (group of NBW row blocks) x (K split), dealt to the workgroups in
-// turn; a unit's row groups lie units apart, so that they read its weights through the same L2 where units are a
-// multiple of the eight dies.
+// A GEMM phase's items: (unit of UB weight blocks) x (K split), all rows of the call, dealt to the workgroups in turn.
 struct DirectGemm {
     global_w_ptr W;
-    const bf16_t *X;     // [K / 32][ncb] fragments
-    int N, KB, m, ncb;
-    int units, groups, ks, kbps;
+    const bf16_t *X;     // [K / 32][NBW] fragments
+    int N, KB, m;
+    int units, ks, kbps;
     // epilogues
     FastGemm e;          // QKV: bias, angles, q, layer; SwiGLU: a_out; residual: h_in, h
     float *xch;
     unsigned *fail;
 };
 
-// What bounds a phase of some 30 to 64 rows is the operand fragments through the vector cache (64 bytes a cycle and
+// NBW: row blocks of the call.
+// What bounds a phase of some 30 to 48 rows is the operand fragments through the vector cache (64 bytes a cycle and
 // compute unit), then HBM: per k-block a wavefront loads UB + NBW fragments for UB * NBW products, so tiles are as
 // square as the accumulators allow.  The eight wavefronts of a workgroup share the K slice and nothing else; weights
 // are requested PW k-blocks ahead, the first of them before the grid barrier, activations PX ahead (from the L2).
@@ -38,8 +37,8 @@ __device__ __forceinline__ XchUsed direct_phase(const DirectGemm &g, GridBar &ba
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int G = gridDim.x, wg = blockIdx.x, KB = g.KB, NBt = g.N >> 4, ncb = g.ncb;
-    const int items = g.units * g.groups * g.ks;
+    const int G = gridDim.x, wg = blockIdx.x, KB = g.KB, NBt = g.N >> 4;
+    const int items = g.units * g.ks;
     // K splits only where every workgroup has one item at most
     const int split = g.ks > 1 ? wg % g.ks : 0, first = g.ks > 1 ? wg / g.ks : wg;
     const int n_my = wg < items ? (g.ks > 1 ? 1 : (items - wg + G - 1) / G) : 0;
@@ -54,8 +53,6 @@ __device__ __forceinline__ XchUsed direct_phase(const DirectGemm &g, GridBar &ba
     for (int d = 0; d < PW; ++d)
 #pragma unroll
         for (int u = 0; u < UB; ++u) w[d][u] = u32x4{0u, 0u, 0u, 0u};
-    auto unit_of = [&](int it) { return (first + it * G) % g.units; };
-    auto group_of = [&](int it) { return (first + it * G) / g.units; };
     // never predicated: a step past the end of the run loads the run's last fragment again and is skipped
     auto load_w = [&](int unit, int d, int kbl) {
         const int kb = min(wk0 + min(kbl, cnt - 1), kb1 - 1);
@@ -63,42 +60,43 @@ __device__ __forceinline__ XchUsed direct_phase(const DirectGemm &g, GridBar &ba
         for (int u = 0; u < UB; ++u)
             w[d][u] = __builtin_nontemporal_load(g.W + ((size_t)min(unit * UB + u, NBt - 1) * KB + kb) * 64 + lane);
     };
-    auto load_x = [&](int cb0, int d, int kbl) {
+    auto load_x = [&](int r0, int d, int kbl) {
         const int kb = min(wk0 + min(kbl, cnt - 1), kb1 - 1);
 #pragma unroll
-        for (int c = 0; c < NBW; ++c) x[d][c] = ssa_load_16(g.X + ((size_t)(kb * ncb + min(cb0 + c, ncb - 1)) * 64 + lane) * 8);
+        for (int c = 0; c < NBW; ++c) x[d][c] = ssa_load_16(g.X + ((size_t)(kb * NBW + r0 + c) * 64 + lane) * 8);
     };
     // this wavefront's tiles of an item: t = wave + 8 i; weight block t / NBW of the unit (SwiGLU: pair), row block t % NBW
     EpiPre pre[TPW];
 #pragma unroll
     for (int i = 0; i < TPW; ++i) pre[i].v = pre[i].bias = floatx4{0.f, 0.f, 0.f, 0.f};
-    auto ask = [&](int unit, int cb0) {
+    auto ask = [&](int unit, int row0) {
         if (EPI == EPI_SWIGLU) return;
 #pragma unroll
         for (int i = 0; i < TPW; ++i) {
             const int t = min(wave + i * FW, NOUT - 1), nb = min(unit * UB + t / NBW, NBt - 1);
-            const int row = min((cb0 + t % NBW) * 16 + (lane & 15), g.m - 1);
+            const int row = min(row0 + t % NBW * 16 + (lane & 15), g.m - 1);
             if (EPI == EPI_QKV) pre[i] = epi_qkv_ask<HD>(g.e, sh, row, nb, lane);
             else pre[i].v = ssa_load_f4(g.e.h_in + (size_t)row * g.N + nb * 16 + (lane >> 4) * 4);
         }
     };
-    int unit = 0, cb0 = 0;
     if (n_my > 0) {
-        unit = unit_of(0);
-        cb0 = group_of(0) * NBW;
 #pragma unroll
-        for (int d = 0; d < PW; ++d) load_w(unit, d, d);
-        ask(unit, cb0);
+        for (int d = 0; d < PW; ++d) load_w(first, d, d);
+        ask(first, 0);
     }
     TRACE(1);
     bar.wait();
     TRACE(2);
     if (n_my <= 0) return used;
 #pragma unroll
-    for (int d = 0; d < PX; ++d) load_x(cb0, d, d);
+    for (int d = 0; d < PX; ++d) load_x(0, d, d);
     for (int it = 0; it < n_my; ++it) {
         const bool has_next = it + 1 < n_my;
-        const int nunit = has_next ? unit_of(it + 1) : unit, ncb0 = has_next ? group_of(it + 1) * NBW : cb0;
+        const int unit = first + it * G;
+        // 0, which the compiler doesn't know: addresses that depend on it are formed anew for every item.  Held in registers
+        // from item to item they spill 43 others (33 rows of 3B 2251 -> 2396 us).
+        int row0 = 0;
+        asm volatile("" : "+s"(row0));
         floatx4 acc[UB][NBW];
 #pragma unroll
         for (int u = 0; u < UB; ++u)
@@ -118,9 +116,9 @@ __device__ __forceinline__ XchUsed direct_phase(const DirectGemm &g, GridBar &ba
                                                                                 __builtin_bit_cast(bf16x8, x[d % PX][c]), acc[u][c], 0, 0, 0);
                 }
                 // the slot's next k-block: of this round, the next one, or the next item's first
-                if (d + PX < PW) load_x(cb0, d % PX, r * PW + d + PX);
-                else if (REFILL) load_x(last_round ? ncb0 : cb0, d % PX, last_round ? d + PX - PW : r * PW + d + PX);
-                if (REFILL) load_w(last_round ? nunit : unit, d, last_round ? d : (r + 1) * PW + d);
+                if (d + PX < PW) load_x(row0, d % PX, r * PW + d + PX);
+                else if (REFILL) load_x(row0, d % PX, last_round ? d + PX - PW : r * PW + d + PX);
+                if (REFILL) load_w(last_round ? unit + G : unit, d, last_round ? d : (r + 1) * PW + d);
             }
         };
 #pragma unroll 1
@@ -160,10 +158,10 @@ __device__ __forceinline__ XchUsed direct_phase(const DirectGemm &g, GridBar &ba
         for (int i = 0; i < TPW; ++i) {
             const int t = wave + i * FW;
             if (t >= NOUT) continue;
-            const int row = (cb0 + t % NBW) * 16 + (lane & 15);
+            const int row = row0 + t % NBW * 16 + (lane & 15);
             if (EPI == EPI_SWIGLU) {
                 const int nb = unit * UB + t / NBW * 2;
-                if (row < g.m && nb < NBt) epi_swiglu_frag(g.e, row, nb, lane, v[i], v1[i], ncb);
+                if (row < g.m && nb < NBt) epi_swiglu_frag(g.e, row, nb, lane, v[i], v1[i], NBW);
             } else if (EPI == EPI_QKV) {
                 const int nb = unit * UB + t / NBW;
                 if (row < g.m && nb < NBt) epi_qkv_store<HD>(g.e, sh, row, nb, lane, v[i], pre[i]);
@@ -175,9 +173,7 @@ __device__ __forceinline__ XchUsed direct_phase(const DirectGemm &g, GridBar &ba
             }
         }
         TRACE(5);
-        if (has_next) ask(nunit, ncb0);
-        unit = nunit;
-        cb0 = ncb0;
+        if (has_next) ask(unit + G, row0);
     }
     return used;
 }
@@ -239,7 +235,7 @@ __global__ __launch_bounds__(FT, 2) void layers_direct_kernel(FusedArgs a, Batch
 #ifdef FUSED_TRACE
     Trace trace{reinterpret_cast<unsigned long long *>(a.bar + 8192), 0};
 #endif
-    const int d = a.d, F = a.F, nq = a.hq * HD, nkv = a.hkv * HD, ncb = (a.m + 15) >> 4, groups = (ncb + NBW - 1) / NBW;
+    const int d = a.d, F = a.F, nq = a.hq * HD, nkv = a.hkv * HD;
     const size_t hstride = (size_t)a.frows * d;
     const int len0 = launch_tables(a, b, sh);
     embed_phase(a, b);
@@ -260,17 +256,17 @@ __global__ __launch_bounds__(FT, 2) void layers_direct_kernel(FusedArgs a, Batch
         float *h0 = a.hv + (size_t)(2 * l) * hstride, *h1 = h0 + hstride, *h2 = l + 1 < a.n_layers ? h1 + hstride : a.h_last;
         bf16_t *q = a.qv + (size_t)l * a.frows * nq, *o = a.ov + (size_t)l * a.frows * nq, *act = a.av + (size_t)l * a.frows * F;
         bf16_t *x0 = a.xv + (size_t)(2 * l) * hstride, *x1 = x0 + hstride;
-        norm_phase(h0, lp.attn_norm, x0, a.m, ncb, d, a.inv_d, a.eps, bar, sh TRACE_PASS);
+        norm_phase(h0, lp.attn_norm, x0, a.m, NBW, d, a.inv_d, a.eps, bar, sh TRACE_PASS);
         bar.arrive();
         TRACE(17);
         {
             const int units = (nq + 2 * nkv) / 16;
-            DirectGemm g{(global_w_ptr)lp.wqkv, x0, nq + 2 * nkv, d / 32, a.m, ncb, units, groups, 1, d / 32, base, a.xch, a.fail};
+            DirectGemm g{(global_w_ptr)lp.wqkv, x0, nq + 2 * nkv, d / 32, a.m, units, 1, d / 32, base, a.xch, a.fail};
             g.e.bias = a.has_bias ? lp.bqkv : nullptr;
             g.e.q = q;
             g.e.layer = l;
-            if (units * groups <= FUSED_G) {
-                direct_phase<HD, NBW, 1, 6, NBW <= 3 ? 6 : 3, EPI_QKV>(g, bar, smem, sh TRACE_PASS);
+            if (units <= FUSED_G) {
+                direct_phase<HD, NBW, 1, 6, 6, EPI_QKV>(g, bar, smem, sh TRACE_PASS);
             } else {
                 g.units = (units + 1) / 2;
                 direct_phase<HD, NBW, 2, 6, 3, EPI_QKV>(g, bar, smem, sh TRACE_PASS);
@@ -278,16 +274,16 @@ __global__ __launch_bounds__(FT, 2) void layers_direct_kernel(FusedArgs a, Batch
         }
         bar.arrive();
         TRACE(10);
-        const XchUsed att_used = attn_phase<HD>(a, b, l, q, o, ncb, len0, bar, smem, sh TRACE_PASS);
+        const XchUsed att_used = attn_phase<HD>(a, b, l, q, o, NBW, len0, bar, smem, sh TRACE_PASS);
         bar.arrive();
         TRACE(13);
         xch_clear<2>(a.xch, att_used);
         {
-            DirectGemm g{(global_w_ptr)lp.wo, o, d, nq / 32, a.m, ncb, d / 16, groups, 1, nq / 32, base, a.xch, a.fail};
+            DirectGemm g{(global_w_ptr)lp.wo, o, d, nq / 32, a.m, d / 16, 1, nq / 32, base, a.xch, a.fail};
             g.e.h_in = h0;
             g.e.h = h1;
-            if (g.units * groups <= FUSED_G) {
-                direct_phase<HD, NBW, 1, 6, NBW <= 3 ? 6 : 3, EPI_RESID>(g, bar, smem, sh TRACE_PASS);
+            if (g.units <= FUSED_G) {
+                direct_phase<HD, NBW, 1, 6, 6, EPI_RESID>(g, bar, smem, sh TRACE_PASS);
             } else {
                 g.units = (g.units + 1) / 2;
                 direct_phase<HD, NBW, 2, 6, 3, EPI_RESID>(g, bar, smem, sh TRACE_PASS);
@@ -295,23 +291,23 @@ __global__ __launch_bounds__(FT, 2) void layers_direct_kernel(FusedArgs a, Batch
         }
         bar.arrive();
         TRACE(14);
-        norm_phase(h1, lp.ffn_norm, x1, a.m, ncb, d, a.inv_d, a.eps, bar, sh TRACE_PASS);
+        norm_phase(h1, lp.ffn_norm, x1, a.m, NBW, d, a.inv_d, a.eps, bar, sh TRACE_PASS);
         bar.arrive();
         TRACE(18);
         {
-            DirectGemm g{(global_w_ptr)lp.wgu, x1, 2 * F, d / 32, a.m, ncb, (F / 8 + 3) / 4, groups, 1, d / 32, base, a.xch, a.fail};
+            DirectGemm g{(global_w_ptr)lp.wgu, x1, 2 * F, d / 32, a.m, (F / 8 + 3) / 4, 1, d / 32, base, a.xch, a.fail};
             g.e.a_out = act;
-            direct_phase<HD, NBW, 4, NBW == 4 ? 2 : 4, 2, EPI_SWIGLU>(g, bar, smem, sh TRACE_PASS);
+            direct_phase<HD, NBW, 4, 4, 2, EPI_SWIGLU>(g, bar, smem, sh TRACE_PASS);
         }
         bar.arrive();
         TRACE(15);
         XchUsed down_used;
         {
-            DirectGemm g{(global_w_ptr)lp.wd, act, d, F / 32, a.m, ncb, (d / 16 + a.down_ub - 1) / a.down_ub, groups, a.ks_down,
+            DirectGemm g{(global_w_ptr)lp.wd, act, d, F / 32, a.m, (d / 16 + a.down_ub - 1) / a.down_ub, a.ks_down,
                          (F / 32 + a.ks_down - 1) / a.ks_down, base, a.xch, a.fail};
             g.e.h_in = h1;
             g.e.h = h2;
-            if (a.down_ub == 4) down_used = direct_phase<HD, NBW, 4, NBW == 4 ? 2 : 4, 2, EPI_RESID>(g, bar, smem, sh TRACE_PASS);
+            if (a.down_ub == 4) down_used = direct_phase<HD, NBW, 4, 4, 2, EPI_RESID>(g, bar, smem, sh TRACE_PASS);
             else down_used = direct_phase<HD, NBW, 2, 6, 3, EPI_RESID>(g, bar, smem, sh TRACE_PASS);
         }
         bar.arrive();
@@ -325,11 +321,11 @@ __global__ __launch_bounds__(FT, 2) void layers_direct_kernel(FusedArgs a, Batch
 
 // K split and weight blocks an item of the down projection: operand fragments through the cache at 154 GB/s a compute
 // unit, an exchange at about 1.3 us.
-static void plan_down(const vf_config &c, int nbw, int groups, FusedArgs &a) {
+static void plan_down(const vf_config &c, int nbw, FusedArgs &a) {
     const int KB = c.d_ffn / 32;
     float best = 0.f;
     for (int ub = 2; ub <= 4; ub += 2) {
-        const int items = (c.d_model / 16 + ub - 1) / ub * groups;
+        const int items = (c.d_model / 16 + ub - 1) / ub;
         for (int ks = 1; ks <= MAX_DOWN_SPLITS; ++ks) {
             const int kbps = (KB + ks - 1) / ks;
             if (ks > 1 && (items * ks > FUSED_G || kbps < FW || (KB + kbps - 1) / kbps != ks)) continue;
@@ -340,40 +336,28 @@ static void plan_down(const vf_config &c, int nbw, int groups, FusedArgs &a) {
     }
 }
 
-// Up to 64 rows (FROWS), one row group.  Chunks of a sequence of 1024 tokens, this kernel / a launch per operation, us:
-//   0.5B  9 rows 730 / 945, 33 819 / 946, 64 892 / 974, 80 1030 / 1026, 128 1113 / 1054
-//   1.5B  9 rows 1234 / 1486, 33 1468 / 1509, 64 1483 / 1568, 80 1919 / 1647, 128 1930 / 1734
-//   3B    9 rows 1605 / 2119, 33 1936 / 2123, 64 2093 / 2224, 80 2977 / 2426, 128 3294 / 2671
-// Of vf_verify's calls alone: a chunk of a prompt keeps a launch per operation, which shares the GPU with whatever runs
-// on other streams; this kernel needs all of it.
-// (more rows: tiles as large as the accumulators take cost more in the sum over the wavefronts than the launches do)
-bool vf_direct_ok(const vf_model *m, const Batch &b) {
-    const vf_config &c = m->cfg;
-    return m->fz_h && fused_shape_ok(c) && b.total_rows <= fused_rows(c) && c.d_model <= 8192;
-}
+// Calls of vf_verify with up to 48 rows (FROWS) that the staging does not take.  More rows get a launch per operation, and
+// so does a chunk of a prompt whatever its rows: launches share the GPU with what runs on other streams, another model's
+// calls among them, and a persistent kernel needs all of it.
+bool vf_direct_ok(const vf_config &c, int rows) { return fused_shape_ok(c) && rows <= FROWS && c.d_model <= 8192; }
 
 int vf_run_direct(vf_model *m, const Batch &b, const int32_t *tokens, bool tree, hipStream_t st) {
     const vf_config &c = m->cfg;
-    if (!vf_direct_ok(m, b)) return vf_fail(VF_ERR_UNSUPPORTED, "persistent kernel does not apply to this call");
+    if (!vf_direct_ok(c, b.total_rows)) return vf_fail(VF_ERR_UNSUPPORTED, "persistent kernel does not apply to this call");
     FusedArgs a;
     memset(&a, 0, sizeof a);
     fused_args(m, b, tokens, tree, a);
     a.h_last = m->h;
     a.logits = m->logits;   // phase timelines go behind its first 64 rows
-    // row blocks an item: what covers the rows with the fewest dead blocks
-    const int ncb = (b.total_rows + 15) / 16;
-    int nbw = 4;
-    for (int n = 4; n >= 2; --n)
-        if ((ncb + n - 1) / n * n < (ncb + nbw - 1) / nbw * nbw) nbw = n;
-    if (ncb == 1) nbw = 2;
-    plan_down(c, nbw, (ncb + nbw - 1) / nbw, a);
+    const int nb = (b.total_rows + 15) / 16;
+    plan_down(c, std::max(2, nb), a);   // one row block: timed with the plan of two
     ProfScope ps(m, VF_SITE_STEP, st);
     if (c.head_dim == 128) {
-        if (nbw == 2) return fused_launch<&layers_direct_kernel<2, 128>>(a, b, st);
-        if (nbw == 3) return fused_launch<&layers_direct_kernel<3, 128>>(a, b, st);
-        return fused_launch<&layers_direct_kernel<4, 128>>(a, b, st);
+        if (nb == 1) return fused_launch<&layers_direct_kernel<1, 128>>(a, b, st);
+        if (nb == 2) return fused_launch<&layers_direct_kernel<2, 128>>(a, b, st);
+        return fused_launch<&layers_direct_kernel<3, 128>>(a, b, st);
     }
-    if (nbw == 2) return fused_launch<&layers_direct_kernel<2, 64>>(a, b, st);
-    if (nbw == 3) return fused_launch<&layers_direct_kernel<3, 64>>(a, b, st);
-    return fused_launch<&layers_direct_kernel<4, 64>>(a, b, st);
+    if (nb == 1) return fused_launch<&layers_direct_kernel<1, 64>>(a, b, st);
+    if (nb == 2) return fused_launch<&layers_direct_kernel<2, 64>>(a, b, st);
+    return fused_launch<&layers_direct_kernel<3, 64>>(a, b, st);
 }

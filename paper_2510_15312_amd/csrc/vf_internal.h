@@ -376,12 +376,12 @@ int vf_run_layers_f32(vf_model *m, const Batch &b, const int32_t *tokens, bool t
 int vf_run_head_f32(vf_model *m, int row_lo, int row_hi, float *out, hipStream_t st);
 size_t vf_fused_workspace_bytes(const vf_config &c);
 int vf_fused_init(vf_model *m, char *ws, hipStream_t st);
-bool vf_fused_ok(const vf_model *m, const Batch &b);
+bool vf_fused_ok(const vf_config &c, int rows);
 // tree: rows take position and visibility from the model's tree_depth / tree_anc tables
 int vf_run_fused(vf_model *m, const Batch &b, const int32_t *tokens, float *logits_out, bool tree, hipStream_t st);
 int vf_fused_check(vf_model *m);
-// the decoder layers alone, for more rows (fused_direct.hip); leaves the residual stream in m->h
-bool vf_direct_ok(const vf_model *m, const Batch &b);
+// the decoder layers alone, for rows that do not fit LDS (fused_direct.hip); leaves the residual stream in m->h
+bool vf_direct_ok(const vf_config &c, int rows);
 int vf_run_direct(vf_model *m, const Batch &b, const int32_t *tokens, bool tree, hipStream_t st);
 // per-row top-k of logits: candidates per vocabulary slice into the model's candidate buffers, then the merge
 int vf_launch_topk_slices(const vf_model *m, const float *logits, int rows, int K, hipStream_t st);

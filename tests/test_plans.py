@@ -8,7 +8,7 @@ import paper_2510_15312_amd as vf
 import workloads as wl
 import test_gpu_attn_items as items
 from test_gpu_rows import MODELS, candidates, config_of
-from util_plan import GEMMS, attention_plan, gemm_plan
+from util_plan import GEMMS, attention_plan, gemm_plan, persistent_plan
 
 FULL = ["0.5b_k8", "1.5b_k16", "3b_k32"]
 
@@ -77,3 +77,20 @@ def test_attention_of_few_items_stays_with_their_kernel(name):
     cfg = vf.config_from(wl.CONFIGS[name], 4096, 8192)
     assert attention_plan(cfg, [1000], [64]) == (0, False)
     assert attention_plan(cfg, [7000] * 16, [33] * 16)[0] > 0
+
+
+# (whole pass up to, layers up to): a row's d * 2 bytes and 8 KB for each 16 rows in 152 KB of LDS; no more than 48 rows, whose
+# kernels need the whole GPU, which a call of more rows shares with other models' calls
+@pytest.mark.parametrize("name,whole", [("0.5b_k8", 48), ("1.5b_k16", 42), ("3b_k32", 22)])
+def test_calls_of_the_persistent_kernels(name, whole):
+    cfg = vf.config_from(wl.CONFIGS[name], 128, 8192)
+    for rows in range(1, 129):
+        kernel, barriers = persistent_plan(cfg, rows)
+        assert kernel == ("pass" if rows <= whole else "layers" if rows <= 48 else None), rows
+        assert barriers == {"pass": 1 + 5 * cfg.n_layers, "layers": 1 + 7 * cfg.n_layers, None: 0}[kernel]
+
+
+def test_models_without_a_persistent_kernel():
+    for kw in (dict(dtype="f32"), dict(d_model=288)):
+        cfg = vf.config_from(wl.scaled(wl.CONFIGS["1.5b_k16"], **kw), 64, 1024)
+        assert all(persistent_plan(cfg, rows)[0] is None for rows in range(1, 65))

@@ -22,3 +22,10 @@ def attention_plan(cfg, lens, rows):
     arr = C.c_int32 * n
     vf.binding._check(vf.lib.vf_debug_attention_plan(C.byref(cfg), n, arr(*[int(x) for x in lens]), arr(*[int(x) for x in rows]), out))
     return out[0], bool(out[1])
+
+
+def persistent_plan(cfg, rows):
+    """(which persistent kernel a vf_verify of so many rows takes, grid barriers of its launch)."""
+    out = (C.c_int32 * 2)()
+    vf.binding._check(vf.lib.vf_debug_persistent_plan(C.byref(cfg), rows, out))
+    return [None, "pass", "layers"][out[0]], out[1]
