@@ -178,10 +178,11 @@ __device__ __forceinline__ XchUsed direct_phase(const DirectGemm &g, GridBar &ba
     return used;
 }
 
-// x = bf16(h / rms * gain) in operand order, one row a workgroup; eight columns a thread
+// x = bf16(h / rms * gain) in operand order, one row a workgroup; eight columns a thread.  The first P passes stay in
+// registers between the sum and the products; what a wider row has beyond them is read twice.
 __device__ __forceinline__ void norm_phase(const float *h, const float *gain, bf16_t *x, int m, int ncb, int d, float inv_d, float eps, GridBar &bar,
                                            FusedShared &sh TRACE_ARG) {
-    constexpr int P = 2;   // passes of 4096 columns (vf_direct_takes)
+    constexpr int P = 2;   // passes of 4096 columns
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), row = blockIdx.x, n = d >> 3;
@@ -209,6 +210,12 @@ __device__ __forceinline__ void norm_phase(const float *h, const float *gain, bf
             for (int j = 0; j < 4; ++j) s += v[p][0][j] * v[p][0][j] + v[p][1][j] * v[p][1][j];
             if (p * FT + tid < n) sq += s;
         }
+    const float *hrow = h + (size_t)row * d;
+    for (int i = P * FT + tid; i < n; i += FT) {
+        const floatx4 a = ssa_load_f4(hrow + i * 8), b = ssa_load_f4(hrow + i * 8 + 4);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) sq += a[j] * a[j] + b[j] * b[j];
+    }
 #pragma unroll
     for (int o = 32; o; o >>= 1) sq += __shfl_xor(sq, o, 64);
     if (lane == 0) sh.rs_tmp[wave][0] = sq;
@@ -217,13 +224,16 @@ __device__ __forceinline__ void norm_phase(const float *h, const float *gain, bf
 #pragma unroll
     for (int i = 0; i < FW; ++i) tot += sh.rs_tmp[i][0];
     const float r = 1.0f / sqrtf(tot * inv_d + eps);
+    auto put = [&](int i, floatx4 a, floatx4 b, floatx4 ga, floatx4 gb) {
+        const u32x2 lo = pack4_bf16(a[0] * r * ga[0], a[1] * r * ga[1], a[2] * r * ga[2], a[3] * r * ga[3]);
+        const u32x2 hi = pack4_bf16(b[0] * r * gb[0], b[1] * r * gb[1], b[2] * r * gb[2], b[3] * r * gb[3]);
+        st_f32x4<true>(reinterpret_cast<float *>(x + xfrag_index(row, i * 8, ncb)), __builtin_bit_cast(floatx4, u32x4{lo[0], lo[1], hi[0], hi[1]}));
+    };
 #pragma unroll
     for (int p = 0; p < P; ++p)
-        if (p * FT + tid < n) {
-            const u32x2 lo = pack4_bf16(v[p][0][0] * r * g[p][0][0], v[p][0][1] * r * g[p][0][1], v[p][0][2] * r * g[p][0][2], v[p][0][3] * r * g[p][0][3]);
-            const u32x2 hi = pack4_bf16(v[p][1][0] * r * g[p][1][0], v[p][1][1] * r * g[p][1][1], v[p][1][2] * r * g[p][1][2], v[p][1][3] * r * g[p][1][3]);
-            st_f32x4<true>(reinterpret_cast<float *>(x + xfrag_index(row, (p * FT + tid) * 8, ncb)), __builtin_bit_cast(floatx4, u32x4{lo[0], lo[1], hi[0], hi[1]}));
-        }
+        if (p * FT + tid < n) put(p * FT + tid, v[p][0], v[p][1], g[p][0], g[p][1]);
+    for (int i = P * FT + tid; i < n; i += FT)
+        put(i, ssa_load_f4(hrow + i * 8), ssa_load_f4(hrow + i * 8 + 4), load_global_f4(gain + i * 8), load_global_f4(gain + i * 8 + 4));
     // rs_tmp is written again two barriers from here at the earliest
 }
 
@@ -339,7 +349,7 @@ static void plan_down(const vf_config &c, int nbw, FusedArgs &a) {
 // Calls of vf_verify with up to 48 rows (FROWS) that the staging does not take.  More rows get a launch per operation, and
 // so does a chunk of a prompt whatever its rows: launches share the GPU with what runs on other streams, another model's
 // calls among them, and a persistent kernel needs all of it.
-bool vf_direct_ok(const vf_config &c, int rows) { return fused_shape_ok(c) && rows <= FROWS && c.d_model <= 8192; }
+bool vf_direct_ok(const vf_config &c, int rows) { return fused_shape_ok(c) && rows <= FROWS; }
 
 int vf_run_direct(vf_model *m, const Batch &b, const int32_t *tokens, bool tree, hipStream_t st) {
     const vf_config &c = m->cfg;

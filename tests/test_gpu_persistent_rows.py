@@ -21,6 +21,8 @@ MODELS = {
     "narrow": (dict(d_model=320, n_q_heads=5, n_kv_heads=1, head_dim=64, d_ffn=992, vocab=1040), 600),
     "two_passes_64": (dict(d_model=1600, n_q_heads=10, n_kv_heads=2, head_dim=64, d_ffn=2080, vocab=1040), 70),
     "two_passes_128": (dict(d_model=2048, n_q_heads=12, n_kv_heads=4, head_dim=128, d_ffn=4128, vocab=2064), 300),
+    # rows of the residual stream of more than two passes of the norm: up to 8 of them fit LDS
+    "widest": (dict(d_model=8256, n_q_heads=6, n_kv_heads=2, head_dim=64, d_ffn=992, vocab=1040), 70),
 }
 VERIFY = (1, 7, 8, 9, 16, 17, 24, 25, 32, 33)   # two_passes_128: 32 rows are the most that LDS takes
 BATCH = (34, 47, 48, 49, 63, 64, 65, 66)        # two sequences; from 65 rows on a launch per operation

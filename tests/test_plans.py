@@ -90,6 +90,13 @@ def test_calls_of_the_persistent_kernels(name, whole):
         assert barriers == {"pass": 1 + 5 * cfg.n_layers, "layers": 1 + 7 * cfg.n_layers, None: 0}[kernel]
 
 
+def test_any_width_has_a_persistent_kernel():
+    for d, whole in ((8192, 9), (8256, 8), (16384, 4)):
+        cfg = vf.make_config(2, d, 6, 2, 64, 992, 1040, "bf16", 1e6, 1e-6, 64, 1024)
+        for rows in range(1, 65):
+            assert persistent_plan(cfg, rows)[0] == ("pass" if rows <= whole else "layers" if rows <= 48 else None), (d, rows)
+
+
 def test_models_without_a_persistent_kernel():
     for kw in (dict(dtype="f32"), dict(d_model=288)):
         cfg = vf.config_from(wl.scaled(wl.CONFIGS["1.5b_k16"], **kw), 64, 1024)
