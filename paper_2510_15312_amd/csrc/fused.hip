@@ -621,13 +621,7 @@ __global__ __launch_bounds__(FT, FUSED_MINW) void verify_fused_kernel(FusedArgs 
     const int len0 = launch_tables(a, b, sh);
     TRACE(0);
     embed_phase(a, b);
-#ifdef FUSED_ARRIVALS
-    // debug build: stamps go behind the first 64 rows of the logits buffer (the model workspace's, when the caller passes none)
-    GridBar bar{a.bar, a.fail, (unsigned)__builtin_amdgcn_readfirstlane(start), gridDim.x / BAR_COUNTERS, false,
-                reinterpret_cast<unsigned long long *>(a.logits + (size_t)64 * a.vocab), 0, 0};
-#else
-    GridBar bar{a.bar, a.fail, (unsigned)__builtin_amdgcn_readfirstlane(start), gridDim.x / BAR_COUNTERS, false};
-#endif
+    GridBar bar = grid_bar(a.bar, a.fail, __builtin_amdgcn_readfirstlane(start));
     bar.arrive();   // (a workgroup barrier inside: the row table is visible to every wavefront from here on)
 
     FastGemm base;
@@ -727,6 +721,15 @@ int fill_split(int G, int units, int KB) {
 // an attention part with their (max, sum) pairs.  One item per workgroup.
 static size_t xch_bytes(const vf_config &c) { return (size_t)FUSED_G * std::max(4 * 3, c.head_dim / 16 * 2) * 1024; }
 
+// [barrier][arrival | release][workgroup]
+static size_t stamp_bytes(const vf_config &c) {
+#ifdef FUSED_ARRIVALS
+    return (size_t)(2 + 7 * c.n_layers) * 2 * FUSED_G * 8;
+#else
+    return 0;
+#endif
+}
+
 struct FusedBuffers { size_t h, ss, q, o, a, x, xch, bar, total; };
 static FusedBuffers fused_buffers(const vf_config &c) {
     const size_t L = c.n_layers, d = c.d_model, nq = (size_t)c.n_q_heads * c.head_dim, F = c.d_ffn, R = fused_rows(c);
@@ -740,7 +743,7 @@ static FusedBuffers fused_buffers(const vf_config &c) {
     f.a = add(L * R * F * 2);
     f.x = add(2 * L * R * d * 2);
     f.xch = add(xch_bytes(c));
-    f.bar = add(65536);
+    f.bar = add(BAR_WORDS * 4 + stamp_bytes(c));
     f.total = n;
     return f;
 }
@@ -814,7 +817,7 @@ int vf_fused_check(vf_model *m) {
     VF_HIP(hipMemcpy(&flag, m->fz_bar + BAR_FAIL, 4, hipMemcpyDeviceToHost));
     if (flag) {
         // counters and their start value are out of step now: start over from zero
-        VF_HIP(hipMemset(m->fz_bar, 0, 65536));
+        VF_HIP(hipMemset(m->fz_bar, 0, BAR_WORDS * 4));
         VF_HIP(hipMemset(m->fz_xch, 0xff, xch_bytes(m->cfg)));
         return vf_fail(VF_ERR_HIP, "persistent verify kernel: a grid barrier timed out; results of that call are invalid");
     }
@@ -822,10 +825,11 @@ int vf_fused_check(vf_model *m) {
 }
 
 #ifdef FUSED_ARRIVALS
-// Copies the arrival / release stamps of the last launch (logits left in the model workspace): [barrier][2][workgroup].
+// Copies the arrival / release stamps of the last launch: [barrier][2][workgroup].
 extern "C" int vf_debug_arrivals(vf_model *m, unsigned long long *out_host, int n_barriers) {
+    if (!m->fz_bar || n_barriers < 0 || (size_t)n_barriers * 2 * FUSED_G * 8 > stamp_bytes(m->cfg)) return vf_fail(VF_ERR_ARG, "vf_debug_arrivals");
     VF_HIP(hipDeviceSynchronize());
-    VF_HIP(hipMemcpy(out_host, m->logits + (size_t)64 * m->cfg.vocab, (size_t)n_barriers * 2 * FUSED_G * 8, hipMemcpyDeviceToHost));
+    VF_HIP(hipMemcpy(out_host, m->fz_bar + BAR_WORDS, (size_t)n_barriers * 2 * FUSED_G * 8, hipMemcpyDeviceToHost));
     return VF_OK;
 }
 #endif

@@ -17,7 +17,7 @@ constexpr int MAX_DOWN_SPLITS = 9;   // K splits of the down projection
 #define BAR_COUNTERS 64           // counters a barrier's arrivals are spread over
 #endif
 // words of the barrier block behind the counters, in memory lines of their own (from word 8192 on: phase timelines)
-constexpr int BAR_START = 7936, BAR_FAIL = 8000;
+constexpr int BAR_START = 7936, BAR_FAIL = 8000, BAR_WORDS = 16384;
 static_assert(BAR_COUNTERS * 64 <= BAR_START, "counters end below");
 constexpr int LDS_BYTES = 152 * 1024;  // dynamic LDS of the one workgroup a CU holds (160 KB less the static part)
 constexpr long long SPIN_LIMIT = 4000000;  // polls before a barrier gives up (seconds, not microseconds)
@@ -144,6 +144,15 @@ struct GridBar {
 
 // The counters' value at launch start: requested first thing in a kernel, used when its first phase is done.
 __device__ __forceinline__ unsigned barrier_start(const unsigned *start) { return __hip_atomic_load(start, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+// Debug build FUSED_ARRIVALS: the stamps' place is behind the barrier block, room for every barrier of either kernel and
+// the end of the output head.
+__device__ __forceinline__ GridBar grid_bar(unsigned *mem, unsigned *fail, unsigned start) {
+    return GridBar{mem, fail, start, gridDim.x / BAR_COUNTERS, false,
+#ifdef FUSED_ARRIVALS
+                   reinterpret_cast<unsigned long long *>(mem + BAR_WORDS), 0, 0
+#endif
+    };
+}
 // For the next launch: what the counters have grown to when all arrivals of this one are in.  Anywhere behind this
 // workgroup's first wait, when every workgroup has read the old value, and its last arrival.
 __device__ __forceinline__ void barrier_advance(unsigned *start, const GridBar &bar) {

@@ -249,7 +249,7 @@ __global__ __launch_bounds__(FT, 2) void layers_direct_kernel(FusedArgs a, Batch
     const size_t hstride = (size_t)a.frows * d;
     const int len0 = launch_tables(a, b, sh);
     embed_phase(a, b);
-    GridBar bar{a.bar, a.fail, (unsigned)__builtin_amdgcn_readfirstlane(start), gridDim.x / BAR_COUNTERS, false};
+    GridBar bar = grid_bar(a.bar, a.fail, __builtin_amdgcn_readfirstlane(start));
     bar.arrive();
     FastGemm base;
     base.m = a.m;
@@ -358,7 +358,6 @@ int vf_run_direct(vf_model *m, const Batch &b, const int32_t *tokens, bool tree,
     memset(&a, 0, sizeof a);
     fused_args(m, b, tokens, tree, a);
     a.h_last = m->h;
-    a.logits = m->logits;   // phase timelines go behind its first 64 rows
     const int nb = (b.total_rows + 15) / 16;
     plan_down(c, std::max(2, nb), a);   // one row block: timed with the plan of two
     ProfScope ps(m, VF_SITE_STEP, st);

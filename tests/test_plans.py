@@ -101,3 +101,13 @@ def test_models_without_a_persistent_kernel():
     for kw in (dict(dtype="f32"), dict(d_model=288)):
         cfg = vf.config_from(wl.scaled(wl.CONFIGS["1.5b_k16"], **kw), 64, 1024)
         assert all(persistent_plan(cfg, rows)[0] is None for rows in range(1, 65))
+
+
+def test_phase_timeline_knows_every_barrier():
+    from paper_2510_15312_amd import phase_timeline as pt
+    for name, rows in (("0.5b_k8", 9), ("1.5b_k16", 17), ("3b_k32", 33), ("3b_k32", 49)):
+        cfg = vf.config_from(wl.CONFIGS[name], 64, 8192)
+        kernel, barriers = persistent_plan(cfg, rows)
+        assert pt.kernel_of(cfg, rows) == kernel
+        if kernel:   # every barrier, and behind the whole pass's last one the output head
+            assert len(pt.phases(kernel, cfg.n_layers)) == barriers + (kernel == "pass")
