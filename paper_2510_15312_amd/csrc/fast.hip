@@ -244,10 +244,10 @@ __global__ __launch_bounds__(NW * 64) VF_MFMA_KERNEL void gemm_fast_kernel(FastG
         const int row = c * 16 + (lane & 15);
         const bool live = row < m && nb < NBt;
         if (EPI == EPI_RESID) {
-            epi_resid<false>(g, row, live, nb, lane, v0[it]);
+            epi_resid(g, row, live, nb, lane, v0[it]);
         } else if (live) {
-            if (EPI == EPI_QKV) epi_qkv<false>(g, b, row, nb, lane, v0[it]);
-            else if (EPI == EPI_SWIGLU) epi_swiglu<false>(g, row, nb, lane, v0[it], v1[it]);
+            if (EPI == EPI_QKV) epi_qkv(g, b, row, nb, lane, v0[it]);
+            else if (EPI == EPI_SWIGLU) epi_swiglu(g, row, nb, lane, v0[it], v1[it]);
             else *reinterpret_cast<floatx4 *>(g.logits + (size_t)row * g.N + nb * 16 + (lane >> 4) * 4) = v0[it];
         }
     }

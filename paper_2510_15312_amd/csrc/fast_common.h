@@ -64,12 +64,8 @@ template <bool COH> __device__ inline void st_u32x2(void *p, u32x2 v) {
                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     else *reinterpret_cast<u32x2 *>(p) = v;
 }
-#ifndef VF_STORE16_WT
-#define VF_STORE16_WT 1   // 16-byte write-through stores as one instruction (0: two 8-byte atomic stores)
-#endif
 template <bool COH> __device__ inline void st_f32x4(float *p, floatx4 v) {
     if (COH) {
-#if VF_STORE16_WT
         // one 16-byte store with the agent-scope (write-through) cache policy: what the 8-byte atomic
         // stores compile to, at twice the width.  Readers never depend on the 16 bytes arriving together.
         // A store of more than 8 bytes reads its data registers for some cycles after it has issued, and
@@ -77,11 +73,6 @@ template <bool COH> __device__ inline void st_f32x4(float *p, floatx4 v) {
         // not look inside this statement: the two idle cycles the hardware asks for are part of it.
         typedef float __attribute__((address_space(1))) *global_f32_ptr;
         asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" : : "v"((global_f32_ptr)p), "v"(v) : "memory");
-#else
-        const u32x4 r = __builtin_bit_cast(u32x4, v);
-        st_u32x2<true>(p, u32x2{r[0], r[1]});
-        st_u32x2<true>(p + 2, u32x2{r[2], r[3]});
-#endif
     } else {
         *reinterpret_cast<floatx4 *>(p) = v;
     }
@@ -99,21 +90,15 @@ __device__ inline void stores_done() {
     __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0)
     asm volatile("" ::: "memory");
 }
-#ifndef VF_COH_LOAD_SCOPE
-#define VF_COH_LOAD_SCOPE __HIP_MEMORY_SCOPE_AGENT
-#endif
 __device__ inline floatx4 load_coherent(const float *p) {
     const unsigned long long *q = reinterpret_cast<const unsigned long long *>(p);
-    const unsigned long long a = __hip_atomic_load(q, __ATOMIC_RELAXED, VF_COH_LOAD_SCOPE);
-    const unsigned long long b = __hip_atomic_load(q + 1, __ATOMIC_RELAXED, VF_COH_LOAD_SCOPE);
+    const unsigned long long a = __hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const unsigned long long b = __hip_atomic_load(q + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const u32x2 lo = __builtin_bit_cast(u32x2, a), hi = __builtin_bit_cast(u32x2, b);
     return __builtin_bit_cast(floatx4, u32x4{lo[0], lo[1], hi[0], hi[1]});
 }
 __device__ inline u32x4 load_coherent16(const void *p) {
     return __builtin_bit_cast(u32x4, load_coherent(reinterpret_cast<const float *>(p)));
-}
-__device__ inline float load_coherent1(const float *p) {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, VF_COH_LOAD_SCOPE);
 }
 
 __device__ inline u32x2 pack4_bf16(float a, float b, float c, float d) {
@@ -128,22 +113,20 @@ __device__ inline unsigned pack2_bf16(float a, float b) {
 
 // ---- epilogues: thread holds Y[row][n0 .. n0+3] ------------------------------------------------
 
-template <bool COH>
 __device__ inline void epi_resid(const FastGemm &g, int row, bool live, int nb, int lane, floatx4 v) {
     const int n0 = nb * 16 + (lane >> 4) * 4;
     floatx4 hv = {0.f, 0.f, 0.f, 0.f};
     if (live) {
         const float *hp = g.h_in + (size_t)row * g.N + n0;
         hv = *reinterpret_cast<const floatx4 *>(hp) + v;  // a buffer other workgroups wrote in an earlier phase, never rewritten
-        st_f32x4<COH>(g.h + (size_t)row * g.N + n0, hv);
+        st_f32x4<false>(g.h + (size_t)row * g.N + n0, hv);
     }
     float ssq = hv[0] * hv[0] + hv[1] * hv[1] + hv[2] * hv[2] + hv[3] * hv[3];
     ssq += __shfl_xor(ssq, 16, 64);
     ssq += __shfl_xor(ssq, 32, 64);
-    if (live && (lane >> 4) == 0) st_f32<COH>(g.ss_out + nb * 64 + row, ssq);
+    if (live && (lane >> 4) == 0) st_f32<false>(g.ss_out + nb * 64 + row, ssq);
 }
 
-template <bool COH>
 __device__ inline void epi_qkv(const FastGemm &g, const Batch &b, int row, int nb, int lane, floatx4 v) {
     const int n0 = nb * 16 + (lane >> 4) * 4;
     const int hd = g.hd, half = hd >> 1;
@@ -173,14 +156,14 @@ __device__ inline void epi_qkv(const FastGemm &g, const Batch &b, int row, int n
             d0 = kv + kv_k_index(g.layer, s.n_pages, page, g.hkv, head - g.hq, tin, i0, hd);
             d1 = kv + kv_k_index(g.layer, s.n_pages, page, g.hkv, head - g.hq, tin, i0 + half, hd);
         }
-        st_u32<COH>(d0, pack2_bf16(a0, a1));
-        st_u32<COH>(d1, pack2_bf16(b0, b1));
+        st_u32<false>(d0, pack2_bf16(a0, a1));
+        st_u32<false>(d1, pack2_bf16(b0, b1));
     } else {
         const int vh = head - g.hq - g.hkv;
         const int page = kv_page(s, slot), tin = slot % VF_TILE;
         for (int i = 0; i < 4; ++i) {
             const bf16_t x = (bf16_t)v[i];
-            st_u16<COH>(kv + kv_v_index(g.layer, s.n_pages, page, g.hkv, vh, tin, p0 + i, hd),
+            st_u16<false>(kv + kv_v_index(g.layer, s.n_pages, page, g.hkv, vh, tin, p0 + i, hd),
                         __builtin_bit_cast(unsigned short, x));
         }
     }
@@ -188,12 +171,11 @@ __device__ inline void epi_qkv(const FastGemm &g, const Batch &b, int row, int n
 
 // v0, v1: tiles of the weight blocks nb (even) and nb + 1; gate row f is packed column 2 f, up row f column
 // 2 f + 1, so a lane holds two (gate, up) pairs of either block
-template <bool COH>
 __device__ inline void epi_swiglu(const FastGemm &g, int row, int nb, int lane, floatx4 v0, floatx4 v1) {
     bf16_t *out = g.a_out + (size_t)row * g.F + nb * 8 + (lane >> 4) * 2;
     auto act = [](float gt, float up) { return gt / (1.0f + expf(-gt)) * up; };
-    st_u32<COH>(out, pack2_bf16(act(v0[0], v0[1]), act(v0[2], v0[3])));
-    st_u32<COH>(out + 8, pack2_bf16(act(v1[0], v1[1]), act(v1[2], v1[3])));
+    st_u32<false>(out, pack2_bf16(act(v0[0], v0[1]), act(v0[2], v0[3])));
+    st_u32<false>(out + 8, pack2_bf16(act(v1[0], v1[1]), act(v1[2], v1[3])));
 }
 
 // ---- attention ----------------------------------------------------------------------------------
@@ -212,58 +194,6 @@ template <int HD> struct AttLds {
     static constexpr int KROW = HD + 8, VROW = ATT_KEYS + 8;  // padded rows: conflict-free fragment reads
     bf16_t Ks[ATT_KEYS * KROW];
     bf16_t Vs[HD * VROW];
-};
-
-// Copy of keys [k_begin, k_begin + 128) of one kv head into LDS: K as [key][d], V^T as [d][key];
-// keys at or past kmax read as zero.  THREADS threads take part; load() issues every global load,
-// store() writes them to LDS, so other work can sit between the two.
-template <int HD, int THREADS> struct AttStage {
-    static constexpr int KROW = AttLds<HD>::KROW, VROW = AttLds<HD>::VROW;
-    static constexpr int KP = HD / 8;                   // 16-byte pieces per key row
-    static constexpr int NK = ATT_KEYS * KP / THREADS;  // pieces per thread
-    u32x4 kreg[NK], vreg[NK];
-
-    __device__ inline void load(const SeqDesc &s, int layer, int hkv, int kvh, int k_begin, int kmax, int tid) {
-        const bf16_t *kv = reinterpret_cast<const bf16_t *>(s.kv);
-        const u32x4 zero4 = {0u, 0u, 0u, 0u};
-#pragma unroll
-        for (int i = 0; i < NK; ++i) {
-            const int pidx = i * THREADS + tid, key = pidx / KP, piece = pidx % KP, t = k_begin + key;
-            kreg[i] = zero4;
-            if (t < kmax)
-                kreg[i] = *reinterpret_cast<const u32x4 *>(
-                    kv + kv_k_index(layer, s.n_pages, kv_page(s, t), hkv, kvh, t % VF_TILE, piece * 8, HD));
-        }
-#pragma unroll
-        for (int i = 0; i < NK; ++i) {
-            // V^T tiles: per 64-key page [d][64]; piece = 8 consecutive keys of one d
-            const int pidx = i * THREADS + tid, d = pidx / (ATT_KEYS / 8), piece = pidx % (ATT_KEYS / 8);
-            const int t = k_begin + piece * 8;
-            vreg[i] = zero4;
-            if (t < kmax)
-                vreg[i] = *reinterpret_cast<const u32x4 *>(
-                    kv + kv_v_index(layer, s.n_pages, kv_page(s, t), hkv, kvh, t % VF_TILE, d, HD));
-        }
-    }
-    __device__ inline void store(AttLds<HD> &L, int k_begin, int kmax, int tid) const {
-#pragma unroll
-        for (int i = 0; i < NK; ++i) {
-            const int pidx = i * THREADS + tid, key = pidx / KP, piece = pidx % KP;
-            *reinterpret_cast<u32x4 *>(L.Ks + key * KROW + piece * 8) = kreg[i];
-        }
-#pragma unroll
-        for (int i = 0; i < NK; ++i) {
-            const int pidx = i * THREADS + tid, d = pidx / (ATT_KEYS / 8), piece = pidx % (ATT_KEYS / 8);
-            const int t = k_begin + piece * 8;
-            bf16x8 v = __builtin_bit_cast(bf16x8, vreg[i]);
-            if (t + 8 > kmax) {  // cache rows past the last key may hold anything: zero them
-#pragma unroll
-                for (int j = 0; j < 8; ++j)
-                    if (t + j >= kmax) v[j] = (bf16_t)0.f;
-            }
-            *reinterpret_cast<bf16x8 *>(L.Vs + d * VROW + piece * 8) = v;
-        }
-    }
 };
 
 // Copies keys [k_begin, k_begin + 128) of one kv head into LDS: K as [key][d], V^T as [d][key];

@@ -415,12 +415,6 @@ __device__ __forceinline__ XchUsed resid_phase(const ResidGemm &g, GridBar &bar,
 //            wavefront q of the unit adds the halves of row block q and applies SwiGLU.
 //   head:    blocks w, w + W, ... (W = wavefronts of the grid) per wavefront, full K, one after
 //            the other through the same ring; logits are stored from the accumulators.
-#ifndef FUSED_GU_LIGHT
-#define FUSED_GU_LIGHT 1        // gate/up: workgroups busy in the O projection take one unit, the others share the rest
-#endif
-#ifndef FUSED_GU_REV
-#define FUSED_GU_REV 1          // gate/up: the units of a partial last range go to the workgroups at the top of the grid
-#endif
 constexpr int wave_tail_bytes(int nb) { return FW * nb * 1024; }   // LDS behind the staged activations: the tiles of a pass
 template <int NB, int HD, int EPI>
 __device__ __forceinline__ void wave_phase(const FastGemm &g, int n_light, GridBar &bar, unsigned char *smem, int lds_total,
@@ -470,7 +464,7 @@ __device__ __forceinline__ void wave_phase(const FastGemm &g, int n_light, GridB
                 const int start = (2 * j + slot) * G, left = n_units - start;
                 if (left >= G) ++n_task;
                 else if (left > 0) {
-                    const int idx = FUSED_GU_REV ? G - 1 - wg : wg;
+                    const int idx = G - 1 - wg;
                     if (idx < left) { blk_last = 2 * (start + idx) + sub; ++n_task; }
                 }
             }
@@ -604,11 +598,8 @@ __device__ __forceinline__ void wave_phase(const FastGemm &g, int n_light, GridB
     }
 }
 
-#ifndef FUSED_MINW
-#define FUSED_MINW 2
-#endif
 template <int NB, int HD>
-__global__ __launch_bounds__(FT, FUSED_MINW) void verify_fused_kernel(FusedArgs a, Batch b) {
+__global__ __launch_bounds__(FT, 2) void verify_fused_kernel(FusedArgs a, Batch b) {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ FusedShared sh;
     const unsigned start = barrier_start(a.bar_start);
@@ -796,7 +787,7 @@ int vf_run_fused(vf_model *m, const Batch &b, const int32_t *tokens, float *logi
         // one unit for each workgroup of the O projection, if the others can take the rest in at most
         // three units each (two passes)
         const int n_o = c.d_model / 16, units = c.d_ffn / 16, H = FUSED_G - n_o;
-        a.gu_light = (FUSED_GU_LIGHT && H > 0 && n_o < units && units - n_o <= 3 * H && units - n_o > H) ? n_o : 0;
+        a.gu_light = (H > 0 && n_o < units && units - n_o <= 3 * H && units - n_o > H) ? n_o : 0;
     }
     ProfScope ps(m, VF_SITE_STEP, st);
     const int nb = (b.total_rows + 15) / 16;

@@ -42,16 +42,9 @@ typedef const u32x4 __attribute__((address_space(1))) *global_w_ptr;
 
 // Loads from the single-assignment buffers (one version per phase and layer, written once per launch
 // before they are read): no cache can hold an older copy of such a line, so an ordinary load will do.
-#ifndef FUSED_SSA_PLAIN
-#define FUSED_SSA_PLAIN 1
-#endif
-__device__ __forceinline__ floatx4 ssa_load_f4(const float *p) {
-    return FUSED_SSA_PLAIN ? *reinterpret_cast<const floatx4 *>(p) : load_coherent(p);
-}
-__device__ __forceinline__ u32x4 ssa_load_16(const void *p) {
-    return FUSED_SSA_PLAIN ? *reinterpret_cast<const u32x4 *>(p) : load_coherent16(p);
-}
-__device__ __forceinline__ float ssa_load_f1(const float *p) { return FUSED_SSA_PLAIN ? *p : load_coherent1(p); }
+__device__ __forceinline__ floatx4 ssa_load_f4(const float *p) { return *reinterpret_cast<const floatx4 *>(p); }
+__device__ __forceinline__ u32x4 ssa_load_16(const void *p) { return *reinterpret_cast<const u32x4 *>(p); }
+__device__ __forceinline__ float ssa_load_f1(const float *p) { return *p; }
 
 struct FusedLayer {
     const u32x4 *wqkv, *wo, *wgu, *wd;
