@@ -358,8 +358,8 @@ int vf_set_option(vf_model *m, int option, int value);
 /* ---- measurement hook (not part of the method) ---------------------------------------------- */
 
 /* Kernel sites timed by vf_profile: the five GEMMs of the forward pass, attention (both
- * kernels), the small norm / epilogue kernels together, acceptance, and the persistent whole-pass kernel
- * (which replaces the first six when it runs). */
+ * kernels), the small norm / epilogue kernels together, acceptance, and the persistent kernels (the whole pass
+ * replaces the first seven when it runs, the decoder layers alone all of them but the output head and its norm). */
 #define VF_SITE_QKV     0
 #define VF_SITE_O       1
 #define VF_SITE_GATEUP  2

@@ -14,12 +14,12 @@
 // Memory protocol between workgroups (different compute dies have separate L2 caches):
 //   * everything one workgroup writes and another reads later in the launch is stored through
 //     to memory (agent-scope stores), and a workgroup waits until its stores have completed
-//     before it signals anything (a barrier arrival, a counter) to other workgroups;
+//     before it arrives at a barrier (partial tiles in the exchange are their own signal);
 //   * bulk data is read with ordinary loads from single-assignment buffers -- one version of
 //     the residual stream per half layer, one q / attention output / SwiGLU buffer per
 //     layer -- so no cache can hold a stale line of it: a line is never read before its only
 //     write in a launch, and caches start clean at every launch;
-//   * data in reused buffers (the exchange of partial tiles, counters) is read with agent-scope loads.
+//   * data in reused buffers (the exchange of partial tiles, the barrier's counters) is read with agent-scope loads.
 // The KV cache is written (new rows) and read (all rows) once per layer and launch, in that
 // order; tiles that hold new rows are read with agent-scope loads.
 //

@@ -24,9 +24,9 @@ constexpr long long SPIN_LIMIT = 4000000;  // polls before a barrier gives up (s
 
 #ifndef FUSED_MAXP
 #define FUSED_MAXP 6              // most key parts per attention block (verify step of 1.5B, 17 rows, 2048 keys: 9 parts 1135 us, 6 1126, 5 1143,
-                                  // 4 1157; the 0.5B shape at 1024 keys takes five: 4 577 for 582; every setting gives the same mean logit
-                                  // error at the full 1.5B size, 1.3e-2, but with 4 and 5 parts one row of 136 landed at 2.12e-2 and 2.005e-2,
-                                  // past the stated 2e-2)
+                                  // 4 1157; the 0.5B shape at 1024 keys takes five: 4 577 for 582; with parts merged by the last of them every setting gave
+                                  // the same mean logit error at the full 1.5B size, 1.3e-2, but with 4 and 5 parts one row of 136 landed at
+                                  // 2.12e-2 and 2.005e-2, past the stated 2e-2)
 #endif
 // One workgroup of 8 wavefronts per CU: two wavefronts per SIMD, so each may use up to 256 vector
 // registers (weight ring + staging loads in flight) without spilling.

@@ -3,9 +3,9 @@
 //   embed | per layer: norm, QKV, attention, O, norm, gate/up, down
 // The normalised rows go through memory as MFMA fragments, written once by the norm phases, and every GEMM phase
 // reads both operands in operand order straight into registers: no staging in LDS, no limit on the rows from it, no
-// K split for its sake.  A norm phase costs a barrier and a round trip (about 2.5 us); staging costs every workgroup
-// the loads and conversions of all its rows (at 33 rows of 3072 columns 8 us twice a layer, and K splits that meet in
-// memory on top).
+// K split for its sake.  A norm phase costs a barrier and a round trip (3.8 and 5.0 us a layer at 33 rows of 3072
+// columns); staging costs every workgroup the loads and conversions of all its rows (there 8 us twice a layer, and K
+// splits that meet in memory on top).
 // The output head is the many-row path's.
 #include "fused_core.h"
 
