@@ -103,6 +103,11 @@ size_t carve_model(vf_model *m, char *base) {
     m->scratch_i32 = (int32_t *)cv.take(64 * 4);
     m->ss_ld = c.dtype == VF_F32 ? (int)std::max(R, (size_t)64) : 64;
     m->ss = (float *)cv.take((d / 16) * (size_t)m->ss_ld * 4);
+    if (c.dtype == VF_BF16) {
+        m->row_place = (RowPlace *)cv.take(R * sizeof(RowPlace));
+        m->row_cos = (float *)cv.take(R * (hd / 2) * 4);
+        m->row_sin = (float *)cv.take(R * (hd / 2) * 4);
+    }
     m->counters = (int32_t *)cv.take(VF_N_COUNTERS * 4);
     m->topk_cand_v = (float *)cv.take((size_t)R * vf_topk_max_slices(c) * VF_TOPK_MAX * 4);
     m->topk_cand_i = (int32_t *)cv.take((size_t)R * vf_topk_max_slices(c) * VF_TOPK_MAX * 4);
@@ -142,20 +147,19 @@ int run_layers(vf_model *m, const Batch &b, const int32_t *tokens, int *tail_par
     const GemmPlan qkv = vf_gemm_plan(m, nq + 2 * nkv, d, rows, GEMM_QKV), po = vf_gemm_plan(m, d, nq, rows, GEMM_SPLIT);
     const GemmPlan gu = vf_gemm_plan(m, 2 * F, d, rows, GEMM_SWIGLU), down = vf_gemm_plan(m, d, F, rows, GEMM_SPLIT);
     const bool act_in_gemm = gu.epi == GEMM_SWIGLU;  // the activation function is the gate/up GEMM's epilogue
-    if ((rc = vf_launch_embed(m, b, tokens, st))) return rc;
+    if ((rc = vf_launch_embed(m, b, tokens, tree ? m->tree_depth : nullptr, st))) return rc;
     int nparts = 0;
     for (int l = 0; l < c.n_layers; ++l) {
         const LayerPacked &lp = m->layers[l];
         { ProfScope ps(m, VF_SITE_SMALL, st);
           if ((rc = vf_launch_norm(m, lp.attn_norm, m->x, m->part, nparts, rows, R, st))) return rc; }
-        const QkvEpilogue epi = vf_qkv_epilogue(m, b, l, tree ? m->tree_depth : nullptr);
         { ProfScope ps(m, VF_SITE_QKV, st);
-          if (qkv.epi == GEMM_QKV) rc = vf_launch_gemm_qkv(m, lp.wqkv, m->x, nq + 2 * nkv, d, epi, qkv, st);
+          if (qkv.epi == GEMM_QKV) rc = vf_launch_gemm_qkv(m, lp.wqkv, m->x, nq + 2 * nkv, d, rows, l, qkv, st);
           else rc = vf_launch_gemm(m, lp.wqkv, m->x, m->part, nq + 2 * nkv, d, rows, 0, rows, R, qkv, st);
           if (rc) return rc; }
         if (qkv.epi != GEMM_QKV) {
             ProfScope ps(m, VF_SITE_SMALL, st);
-            if ((rc = vf_launch_qkv_finish(m, epi, m->part, qkv.ks, R, st))) return rc;
+            if ((rc = vf_launch_qkv_finish(m, vf_qkv_epilogue(m, b, l, tree ? m->tree_depth : nullptr), m->part, qkv.ks, R, st))) return rc;
         }
         { ProfScope ps(m, VF_SITE_ATTN, st);
           if ((rc = vf_launch_attention(m, b, l, tree ? m->tree_anc : nullptr, st))) return rc; }

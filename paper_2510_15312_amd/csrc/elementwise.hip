@@ -61,13 +61,28 @@ __global__ void rope_table_kernel(float *__restrict__ cosv, float *__restrict__ 
 
 // ---- forward pass helpers -----------------------------------------------------------------------
 
-__global__ void embed_kernel(const bf16_t *__restrict__ E, const int32_t *__restrict__ tokens, Batch b,
-                             float *__restrict__ h, int d, int vocab) {
-    const int row = blockIdx.x;
+// One workgroup per row.  The first wavefronts gather, pieces of eight elements that lie together in the packed matrix; the
+// last finds the row's place (place: NULL if nothing reads it).
+__global__ __launch_bounds__(256) void embed_kernel(const bf16_t *__restrict__ E, const int32_t *__restrict__ tokens, Batch b,
+                                                    float *__restrict__ h, int d, int vocab, const int32_t *__restrict__ depth, int hkv, int hd,
+                                                    const float *__restrict__ cosv, const float *__restrict__ sinv, RowPlace *__restrict__ place,
+                                                    float *__restrict__ row_cos, float *__restrict__ row_sin) {
+    const int row = blockIdx.x, half = hd / 2, i = threadIdx.x - 192;
+    if (place && i >= 0 && i < half) {
+        const RowPlace p = row_place(b, depth, hkv, hd, row);
+        if (i == 0) place[row] = p;
+        row_cos[(size_t)row * half + i] = cosv[(size_t)p.pos * half + i];
+        row_sin[(size_t)row * half + i] = sinv[(size_t)p.pos * half + i];
+    }
     int tok = tokens[row];
     if (tok == VF_PENDING) tok = b.s[find_seq(b, row)].state[1];
     if (tok < 0 || tok >= vocab) tok = 0;
-    for (int k = threadIdx.x; k < d; k += blockDim.x) h[(size_t)row * d + k] = (float)E[wfrag_index(tok, k, d)];
+    for (int k = threadIdx.x * 8; k < d; k += 2048) {
+        const bf16x8 e = *reinterpret_cast<const bf16x8 *>(E + wfrag_index(tok, k, d));
+        float *p = h + (size_t)row * d + k;
+        *reinterpret_cast<floatx4 *>(p) = floatx4{(float)e[0], (float)e[1], (float)e[2], (float)e[3]};
+        *reinterpret_cast<floatx4 *>(p + 4) = floatx4{(float)e[4], (float)e[5], (float)e[6], (float)e[7]};
+    }
 }
 
 __device__ inline float block_sum(float v, float *red) {
@@ -181,8 +196,9 @@ __global__ __launch_bounds__(256) void qkv_finish_kernel(const float *__restrict
     if (idx >= e.b.total_rows * per_row) return;
     const int row = idx / per_row, n0 = (idx % per_row) * 4;
     const int nb = n0 >> 4, g4 = n0 >> 2 & 3;
-    const QkvPlace at = qkv_place(e, row, g4);
-    const QkvAngles angles = qkv_angles(e, at, nb);
+    const RowPlace place = row_place(e.b, e.depth, e.hkv, e.hd, row);
+    const QkvPlace at = qkv_place(e, place, g4);
+    const QkvAngles angles = qkv_angles(e, place.pos, nb, g4);
     floatx4 v = {0.f, 0.f, 0.f, 0.f};
     for (int q0 = 0; q0 < nparts; q0 += 4) {   // requested together, added in order
         floatx4 t[4];
@@ -327,9 +343,10 @@ int vf_launch_rope_table(const vf_model *m, hipStream_t st) {
     return VF_OK;
 }
 
-int vf_launch_embed(const vf_model *m, const Batch &b, const int32_t *tokens, hipStream_t st) {
-    hipLaunchKernelGGL(embed_kernel, dim3(b.total_rows), dim3(256), 0, st, (const bf16_t *)m->embed, tokens, b, m->h,
-                       m->cfg.d_model, m->cfg.vocab);
+int vf_launch_embed(const vf_model *m, const Batch &b, const int32_t *tokens, const int32_t *depth, hipStream_t st) {
+    const vf_config &c = m->cfg;
+    hipLaunchKernelGGL(embed_kernel, dim3(b.total_rows), dim3(256), 0, st, (const bf16_t *)m->embed, tokens, b, m->h, c.d_model, c.vocab,
+                       depth, c.n_kv_heads, c.head_dim, m->rope_cos, m->rope_sin, m->row_place, m->row_cos, m->row_sin);
     VF_LAUNCH_CHECK("embed");
     return VF_OK;
 }
@@ -360,10 +377,13 @@ int vf_launch_norm(const vf_model *m, const float *gain, void *x_out, const floa
     return VF_OK;
 }
 
-QkvEpilogue vf_qkv_epilogue(const vf_model *m, const Batch &b, int layer, const int32_t *depth) {
+QkvColumns vf_qkv_columns(const vf_model *m, int layer) {
     const vf_config &c = m->cfg;
-    return {b, layer, c.n_q_heads, c.n_kv_heads, c.head_dim, c.qkv_bias ? m->layers[layer].bqkv : nullptr,
-            m->rope_cos, m->rope_sin, (bf16_t *)m->q, depth};
+    return {layer, c.n_q_heads, c.n_kv_heads, c.head_dim, c.qkv_bias ? m->layers[layer].bqkv : nullptr, m->rope_cos, m->rope_sin,
+            (bf16_t *)m->q};
+}
+QkvEpilogue vf_qkv_epilogue(const vf_model *m, const Batch &b, int layer, const int32_t *depth) {
+    return {vf_qkv_columns(m, layer), b, depth};
 }
 
 int vf_launch_qkv_finish(const vf_model *m, const QkvEpilogue &e, const float *part, int nparts, int ld_rows, hipStream_t st) {

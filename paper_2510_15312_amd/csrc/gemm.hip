@@ -304,11 +304,13 @@ static RowsGemm rows_gemm(const RowsShape &s, const void *W, const void *X, floa
     return p;
 }
 
-int vf_launch_gemm_qkv(const vf_model *m, const void *W, const void *X, int N, int K, const QkvEpilogue &e, const GemmPlan &plan,
+int vf_launch_gemm_qkv(const vf_model *m, const void *W, const void *X, int N, int K, int rows, int layer, const GemmPlan &plan,
                        hipStream_t st) {
-    const int rows = e.b.total_rows;
+    QkvColumns e = vf_qkv_columns(m, layer);
+    e.cosv = m->row_cos;
+    e.sinv = m->row_sin;
     if (plan.epi != GEMM_QKV || plan.ks != 1 || N != (e.hq + 2 * e.hkv) * e.hd) return vf_fail(VF_ERR_ARG, "QKV GEMM: not its plan");
-    RowsGemmQkv p{rows_gemm(ROWS_SHAPES[plan.shape], W, X, nullptr, N, K, (rows + 15) >> 4, 0, rows, rows, 1), e};
+    RowsGemmQkv p{rows_gemm(ROWS_SHAPES[plan.shape], W, X, nullptr, N, K, (rows + 15) >> 4, 0, rows, rows, 1), e, m->row_place};
     return launch_rows_as<ROWS_EPI_QKV>(plan.shape, p, p.nx * p.ny, st);
 }
 

@@ -36,19 +36,38 @@ struct RowsGemm {
     int32_t *cand_i;
     int topk;
 };
-struct RowsGemmQkv : RowsGemm { QkvEpilogue e; };
-// QKV: where a wavefront's rows go, looked up ahead of the products
-template <int EPI, int WMB> struct RowsQkv {
-    __device__ __forceinline__ void request(const RowsGemm &, int, int) {}
-};
-template <int WMB> struct RowsQkv<ROWS_EPI_QKV, WMB> {
-    QkvPlace at[WMB];
-    __device__ __forceinline__ void request(const RowsGemmQkv &p, int cb0, int lane) {
-#pragma unroll
-        for (int c = 0; c < WMB; ++c) at[c] = qkv_place(p.e, min((cb0 + c) * 16 + (lane & 15), p.row_hi - 1), lane >> 4);
-    }
+struct RowsGemmQkv : RowsGemm {
+    QkvColumns e;             // cosv, sinv: by row of the call
+    const RowPlace *place;
 };
 template <int EPI> using RowsArgs = std::conditional_t<EPI == ROWS_EPI_QKV, RowsGemmQkv, RowsGemm>;
+// QKV: where a wavefront's rows go and, of tiles of up to five blocks a wavefront, the rotary angles of its first row block:
+// requested behind the first activations, ahead of the products (behind those each is a memory round trip, in front of
+// the activations these wait).
+template <int EPI, int WNB, int WMB> struct RowsQkv {
+    __device__ __forceinline__ void request(const RowsGemm &, int, int, int) {}
+};
+template <int WNB, int WMB> struct RowsQkv<ROWS_EPI_QKV, WNB, WMB> {
+    static constexpr bool EARLY = WNB * WMB <= 5;
+    u32x4 place[WMB][2];
+    QkvAngles an[2][WNB];
+    static __device__ __forceinline__ int row_of(const RowsGemmQkv &p, int cb0, int c, int lane) { return min((cb0 + c) * 16 + (lane & 15), p.row_hi - 1); }
+    __device__ __forceinline__ void request_angles(const RowsGemmQkv &p, int nb0, int cb0, int c, int lane) {
+#pragma unroll
+        for (int n = 0; n < WNB; ++n) an[c & 1][n] = qkv_angles(p.e, row_of(p, cb0, c, lane), min(nb0 + n, (p.N >> 4) - 1), lane >> 4);
+    }
+    __device__ __forceinline__ void request(const RowsGemmQkv &p, int nb0, int cb0, int lane) {
+#pragma unroll
+        for (int c = 0; c < WMB; ++c)
+#pragma unroll
+            for (int i = 0; i < 2; ++i) place[c][i] = reinterpret_cast<const u32x4 *>(p.place + row_of(p, cb0, c, lane))[i];
+        if constexpr (EARLY) request_angles(p, nb0, cb0, 0, lane);
+    }
+    __device__ __forceinline__ QkvPlace at(const RowsGemmQkv &p, int c, int lane) const {
+        const u32x4 a = place[c][0], b = place[c][1];
+        return qkv_place(p.e, {(unsigned long long)a[1] << 32 | a[0], (unsigned long long)a[3] << 32 | a[2], (int)b[0], (int)b[1], {0, 0}}, lane >> 4);
+    }
+};
 
 // Workgroup -> (row tile, column tile, split).  Neighbours in the order (split, column tile, row tile)
 // share a compute die, so that its L2 serves all but the first reader of a weight tile.
@@ -78,7 +97,7 @@ __device__ __forceinline__ float silu_mul(float g, float u) { return g / (1.0f +
 //            equal values by rising id, as list `list` of n_lists.  The four lanes that share a row run one
 //            round per result: every lane offers its best remaining value, two shuffles pick the row's.
 template <int EPI, int WNB, int WMB>
-__device__ __forceinline__ void rows_epilogue(const RowsArgs<EPI> &p, const RowsQkv<EPI, WMB> &qkv, const floatx4 (&acc)[WNB][WMB], int nb0,
+__device__ __forceinline__ void rows_epilogue(const RowsArgs<EPI> &p, RowsQkv<EPI, WNB, WMB> &qkv, const floatx4 (&acc)[WNB][WMB], int nb0,
                                               int cb0, int split, int list, int n_lists, int lane) {
     const int NBt = p.N >> 4, g4 = lane >> 4;
     if constexpr (EPI == ROWS_EPI_SWIGLU) {
@@ -99,21 +118,17 @@ __device__ __forceinline__ void rows_epilogue(const RowsArgs<EPI> &p, const Rows
         }
     } else if constexpr (EPI == ROWS_EPI_QKV) {
         // the next row block's angles are on their way while one is stored
-        QkvAngles an[2][WNB];
-        auto request = [&](int c) {
-#pragma unroll
-            for (int n = 0; n < WNB; ++n) an[c & 1][n] = qkv_angles(p.e, qkv.at[c], min(nb0 + n, NBt - 1));
-        };
-        request(0);
+        if constexpr (!RowsQkv<EPI, WNB, WMB>::EARLY) qkv.request_angles(p, nb0, cb0, 0, lane);
 #pragma unroll
         for (int c = 0; c < WMB; ++c) {
-            if (c + 1 < WMB) request(c + 1);
+            if (c + 1 < WMB) qkv.request_angles(p, nb0, cb0, c + 1, lane);
             const int row = (cb0 + c) * 16 + (lane & 15);
             if (row < p.row_lo || row >= p.row_hi) continue;
+            const QkvPlace at = qkv.at(p, c, lane);
 #pragma unroll
             for (int n = 0; n < WNB; ++n) {
                 if (nb0 + n >= NBt) break;
-                qkv_store(p.e, qkv.at[c], an[c & 1][n], row, nb0 + n, g4, acc[n][c]);
+                qkv_store(p.e, at, qkv.an[c & 1][n], row, nb0 + n, g4, acc[n][c]);
             }
         }
     } else if constexpr (EPI == ROWS_EPI_TOPK) {
@@ -246,10 +261,10 @@ __global__ __launch_bounds__((CW + 1) * 64) VF_MFMA_KERNEL void gemm_stream_kern
             for (int c = 0; c < WMB; ++c)
                 acc[n][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[n], __builtin_bit_cast(bf16x8, r[c]), acc[n][c], 0, 0, 0);
     };
-    RowsQkv<EPI, WMB> qkv;
-    qkv.request(p, cb0 + wave * WMB, lane);
 #pragma unroll
     for (int d = 0; d < D; ++d) fetch(x[d]);
+    RowsQkv<EPI, NB, WMB> qkv;
+    qkv.request(p, nb0, cb0 + wave * WMB, lane);
     read(w[0], 0);
     const int groups = (nk - 1) / D;
     for (int g = 0; g < groups; ++g) {
@@ -346,8 +361,8 @@ __global__ __launch_bounds__(WM *WN * 64) VF_MFMA_KERNEL void gemm_tile_kernel(R
         static_for<0, LPW>([&](auto i) { issue1((unsigned)(s * FR) * 1024u, i); });
         --left;
     }
-    RowsQkv<EPI, WMB> qkv;
-    qkv.request(p, cb0 + wm * WMB, lane);
+    RowsQkv<EPI, WNB, WMB> qkv;
+    qkv.request(p, nb0 + wn * WNB, cb0 + wm * WMB, lane);
     Frags f0, f1;
     vm_wait<(S - 1) * LPW>();
     lds_sync();

@@ -92,6 +92,8 @@ struct vf_model {
     int32_t *scratch_i32;       // [64]
     float *ss;                  // per-16-column sums of squares of h rows, [d/16][ss_ld]
     int ss_ld;                  // 64 (few-row kernels), float32 model: rows of the largest call
+    struct RowPlace *row_place; // many-row kernels: where the rows of the call go, [R]
+    float *row_cos, *row_sin;   // their rotary angles, [R][hd/2]
     int32_t *counters;          // split-K arrival counters, [VF_N_COUNTERS], zero between kernels
     float *topk_cand_v;         // top-k candidates per (row, vocabulary slice), [R, slices, VF_TOPK_MAX]
     int32_t *topk_cand_i;
@@ -240,39 +242,50 @@ static_assert(VF_MAX_BATCH % 8 == 0, "find_seq_many reads descriptors in eights"
 // Columns of the packed QKV matrix: heads 0..hq-1 are q, then hkv k heads, then hkv v heads (v is not
 // rotated).  Packed columns 2i, 2i+1 of a q or k head are elements i and i + hd/2, so four columns are the
 // two rotary pairs i, i + 1 and every store is two elements.
-struct QkvEpilogue {
-    Batch b;
+struct QkvColumns {
     int32_t layer, hq, hkv, hd;
     const float *bias, *cosv, *sinv;   // bias: NULL without one
     bf16_t *q;
+};
+struct QkvEpilogue : QkvColumns {
+    Batch b;
     const int32_t *depth;              // tree verify: depth of every row; NULL: row r of a sequence has depth r
 };
 // Where a row goes: offsets (elements) of lane group g4's share, columns 16 nb + 4 g4 .. + 3 of any block
 // nb.  What depends on nb alone is added per block, by the scalar unit where nb is the same for the wavefront.
-struct QkvPlace { unsigned rope, k, v; bf16_t *page; };   // page: NULL for a row that is not stored
+struct QkvPlace { unsigned k, v; bf16_t *page; };   // page: NULL for a row that is not stored
 struct QkvAngles { float2 c, s; };
+// What of that is the same in every layer, found once a call (embed_kernel) and kept per row, with the row's rotary angles
+// next to one another: sequence, length and block table are a chain of three or four memory round trips, which the QKV
+// GEMM of every layer waited out ahead of its first products (a pass of 104 rows of 0.5B in 12 sequences 1269 -> 1216 us,
+// a prompt of 777 tokens in chunks of 128 6723 -> 6591, of 2048 at 1.5B in chunks of 256 16854 -> 16647).
+struct RowPlace {
+    unsigned long long page;         // of layer 0; 0: the row is not stored
+    unsigned long long layer_bytes;  // from a layer's page to the next one's
+    int32_t pos, tin;                // position of the rotary angle, token within the page
+    int32_t pad[2];                  // two 16-byte loads
+};
 // The rotary angle is that of the token's position; the cache row is the call's row (the two differ for
 // tree-structured drafts, where a node stands at the position of its depth).
-__device__ __forceinline__ QkvPlace qkv_place_in(const QkvEpilogue &e, const SeqDesc &s, int row, int g4) {
-    const int len = s.state[0], r = row - s.row0, slot = len + r, tin = slot % VF_TILE, hd = e.hd;
-    if (slot < 0 || slot >= s.capacity) return {0, 0, 0, nullptr};
-    return {(unsigned)((len + (e.depth ? e.depth[row] : r)) * (hd >> 1) + g4 * 2),
-            (unsigned)kv_k_index(0, 0, 0, 0, 0, tin, 0, hd) + g4 * 2, (unsigned)kv_v_index(0, 0, 0, 0, 0, tin, 0, hd) + g4 * 32,
-            reinterpret_cast<bf16_t *>(s.kv) + ((size_t)e.layer * s.n_pages + kv_page(s, slot)) * 2 * e.hkv * VF_TILE * hd};
+__device__ __forceinline__ RowPlace row_place(const Batch &b, const int32_t *depth, int hkv, int hd, int row) {
+    const SeqDesc &s = b.s[find_seq_many(b, row)];
+    const int len = s.state[0], r = row - s.row0, slot = len + r;
+    if (slot < 0 || slot >= s.capacity) return {0, 0, 0, 0, {0, 0}};
+    const size_t page_bytes = (size_t)2 * hkv * VF_TILE * hd * sizeof(bf16_t);
+    return {(unsigned long long)(s.kv + (size_t)kv_page(s, slot) * page_bytes), (unsigned long long)s.n_pages * page_bytes,
+            len + (depth ? depth[row] : r), slot % VF_TILE, {0, 0}};
 }
-// One sequence (a prefill chunk): its descriptor is read by the scalar unit.  Several: per lane, a wavefront's
-// rows may belong to more than one (a loop over all sequences with scalar reads: 8.2 -> 10.8 us the QKV GEMM of
-// 104 rows in 12 sequences).
-__device__ __forceinline__ QkvPlace qkv_place(const QkvEpilogue &e, int row, int g4) {
-    if (e.b.n_seqs == 1) return qkv_place_in(e, e.b.s[0], row, g4);
-    return qkv_place_in(e, e.b.s[find_seq_many(e.b, row)], row, g4);
+__device__ __forceinline__ QkvPlace qkv_place(const QkvColumns &e, const RowPlace &p, int g4) {
+    const unsigned long long page = p.page ? p.page + p.layer_bytes * (unsigned)e.layer : 0;
+    return {(unsigned)kv_k_index(0, 0, 0, 0, 0, p.tin, 0, e.hd) + g4 * 2, (unsigned)kv_v_index(0, 0, 0, 0, 0, p.tin, 0, e.hd) + g4 * 32,
+            reinterpret_cast<bf16_t *>(page)};
 }
-// the angles of the lane's columns of block nb (any, for a v head)
-__device__ __forceinline__ QkvAngles qkv_angles(const QkvEpilogue &e, const QkvPlace &p, int nb) {
-    const unsigned at = p.rope + ((nb * 16 & (e.hd - 1)) >> 1);
+// the angles of the lane's columns of block nb (any, for a v head); `at`: the row's place in e.cosv and e.sinv
+__device__ __forceinline__ QkvAngles qkv_angles(const QkvColumns &e, int at, int nb, int g4) {
+    at = at * (e.hd >> 1) + ((nb * 16 & (e.hd - 1)) >> 1) + g4 * 2;
     return {*reinterpret_cast<const float2 *>(e.cosv + at), *reinterpret_cast<const float2 *>(e.sinv + at)};
 }
-__device__ __forceinline__ void qkv_store(const QkvEpilogue &e, const QkvPlace &p, const QkvAngles &a, int row, int nb, int g4, floatx4 v) {
+__device__ __forceinline__ void qkv_store(const QkvColumns &e, const QkvPlace &p, const QkvAngles &a, int row, int nb, int g4, floatx4 v) {
     if (!p.page) return;
     const int hd = e.hd, half = hd >> 1, head = nb * 16 >> (hd == 128 ? 7 : 6), p0 = nb * 16 & (hd - 1), i0 = p0 >> 1;
     if (e.bias) v += *reinterpret_cast<const floatx4 *>(e.bias + nb * 16 + g4 * 4);
@@ -326,13 +339,15 @@ int vf_launch_pack(const vf_model *m, const void *src, const void *src2, void *d
                    int perm_hd, hipStream_t st);
 int vf_launch_pack_vec(const float *src, float *dst, int n, int perm_hd, hipStream_t st);
 int vf_launch_rope_table(const vf_model *m, hipStream_t st);
-int vf_launch_embed(const vf_model *m, const Batch &b, const int32_t *tokens, hipStream_t st);
+// gathers the rows' embeddings and finds their places; depth as below
+int vf_launch_embed(const vf_model *m, const Batch &b, const int32_t *tokens, const int32_t *depth, hipStream_t st);
 int vf_launch_norm(const vf_model *m, const float *gain, void *x_out, const float *part, int nparts,
                    int rows, int ld_rows, hipStream_t st);
 // the QKV GEMM of a GEMM_QKV plan
-int vf_launch_gemm_qkv(const vf_model *m, const void *W, const void *X, int N, int K, const QkvEpilogue &e, const GemmPlan &plan,
+int vf_launch_gemm_qkv(const vf_model *m, const void *W, const void *X, int N, int K, int rows, int layer, const GemmPlan &plan,
                        hipStream_t st);
 // depth != NULL (tree verify): row r stands at position len + depth[row], not len + r
+QkvColumns vf_qkv_columns(const vf_model *m, int layer);
 QkvEpilogue vf_qkv_epilogue(const vf_model *m, const Batch &b, int layer, const int32_t *depth);
 int vf_launch_qkv_finish(const vf_model *m, const QkvEpilogue &e, const float *part, int nparts, int ld_rows, hipStream_t st);
 // ancestor masks and depths of every row of the call from the parent table, into the model workspace
