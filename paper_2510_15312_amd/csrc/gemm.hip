@@ -137,12 +137,16 @@ int launch_bf16(const vf_model *m, const void *W, const void *X, float *part, in
 //     start + step * k-blocks per split * rounds of the chip + written * MB + hbm * MB of weights
 // (us; rounds: workgroups / 256 rounded up while there are few, fractional beyond) plus the time the
 // consumer takes to read the partial sums, and the cheapest (shape, split) is taken.  The constants are
-// least-squares fits, shape by shape, to 8,800 timings on the MI355X with cold weights (thirteen
-// matrices of the 0.5B, 1.5B and 3B shapes, 49 to 2048 rows, every split): mean error 6 %, and the choice
-// is 1.2 % slower on average than the best of all timed, 16 % at worst.  What decides is visible in them: a
+// least-squares fits to the time of a layer of the model with one of its four matrices forced to each shape and
+// split: 16,000 timings on the MI355X (0.5B, 1.5B and 3B shapes, twenty row counts of 16 to 1500), those within
+// 15 % of the best.  The choice costs a layer 0.2 % on average against the best of all timed, 3 % at worst; constants
+// fitted to single kernels, with an error of 6 % each, chose 0.5 % and 7 % worse, most of it in the down projection (256
+// rows of 1.5B, a layer: 73.6 us, now 71.5).  What decides is visible in them: a
 // shape of few weight blocks per tile (stream) wins while its column tiles fill the chip once, the square tiles
-// once there are several rounds of them anyway (their step covers more products).
-enum RowsKernel { RK_T16x16, RK_T16x8, RK_T8x8, RK_S4x2, RK_S4x4, RK_S4x5, RK_S8x4, RK_S8x5, RK_S16x5, RK_S24x5, RK_COUNT };
+// once there are several rounds of them anyway (their step covers more products).  Activations four k-blocks ahead
+// serve as well as eight (RK_S16x5, gate/up of 256 rows at 1.5B, a layer 73.3 -> 72.5), twelve and sixteen are no
+// better, nor are rings of shorter slots.
+enum RowsKernel { RK_T16x16, RK_T16x8, RK_T8x8, RK_S4x2, RK_S4x4, RK_S4x5, RK_S8x4, RK_S8x5, RK_S16x5, RK_S24x5, RK_S8x3, RK_S16x5W4, RK_COUNT };
 struct RowsShape {
     int mb, nb;                        // 16-row blocks x weight blocks of a tile
     float start, step, written, hbm;
@@ -150,16 +154,18 @@ struct RowsShape {
     int lists;                         // top-k candidate lists per tile and row
 };
 constexpr RowsShape ROWS_SHAPES[RK_COUNT] = {
-    {16, 16, 4.93f, 0.5881f, 0.192f, 0.0463f, true, true, true, true, 2},     // RK_T16x16: square tile, 8 wavefronts of 64 x 128
-    {16, 8, 3.70f, 0.3476f, 0.220f, 0.0478f, true, true, true, true, 2},      // RK_T16x8 : square tile, 8 wavefronts of 64 x 64
-    {8, 8, 3.06f, 0.2053f, 0.210f, 0.0841f, true, true, true, true, 2},       // RK_T8x8  : square tile, 4 wavefronts of 64 x 64
-    {4, 2, 2.00f, 0.0566f, 0.311f, 0.1253f, true, true, false, false, 0},     // RK_S4x2  : stream, 4 wavefronts of 16 rows
-    {4, 4, 2.20f, 0.0826f, 0.239f, 0.1143f, true, true, true, false, 0},      // RK_S4x4
-    {4, 5, 2.88f, 0.1332f, 0.368f, 0.0598f, true, false, true, false, 0},     // RK_S4x5
-    {8, 4, 2.42f, 0.1244f, 0.264f, 0.0947f, true, true, true, false, 0},      // RK_S8x4  : stream, 8 wavefronts of 16 rows
-    {8, 5, 2.79f, 0.1839f, 0.331f, 0.0406f, true, true, true, true, 1},       // RK_S8x5
-    {16, 5, 2.77f, 0.3189f, 0.281f, 0.0091f, false, false, true, false, 0},   // RK_S16x5 : stream, 8 wavefronts of 32 rows
-    {24, 5, 1.17f, 0.3889f, 0.803f, 0.0203f, false, false, true, false, 0},   // RK_S24x5 : stream, 8 wavefronts of 48 rows
+    {16, 16, 4.99f, 0.4876f, 0.182f, 0.0377f, true, true, true, true, 2},     // RK_T16x16 : square tile, 8 wavefronts of 64 x 128
+    {16, 8, 3.54f, 0.2849f, 0.228f, 0.0505f, true, true, true, true, 2},      // RK_T16x8  : square tile, 8 wavefronts of 64 x 64
+    {8, 8, 3.21f, 0.1769f, 0.183f, 0.0964f, true, true, true, true, 2},       // RK_T8x8   : square tile, 4 wavefronts of 64 x 64
+    {4, 2, 2.09f, 0.0571f, 0.325f, 0.0910f, true, true, false, false, 0},     // RK_S4x2   : stream, 4 wavefronts of 16 rows
+    {4, 4, 2.46f, 0.0795f, 0.220f, 0.0868f, true, true, true, false, 0},      // RK_S4x4
+    {4, 5, 2.35f, 0.1088f, 0.371f, 0.0626f, true, false, true, false, 0},     // RK_S4x5
+    {8, 4, 2.47f, 0.1248f, 0.232f, 0.0618f, true, true, true, false, 0},      // RK_S8x4   : stream, 8 wavefronts of 16 rows
+    {8, 5, 2.51f, 0.1477f, 0.277f, 0.0451f, true, true, true, true, 1},       // RK_S8x5
+    {16, 5, 2.30f, 0.2643f, 0.256f, 0.0094f, false, false, true, false, 0},   // RK_S16x5  : stream, 8 wavefronts of 32 rows
+    {24, 5, 1.20f, 0.3275f, 0.618f, 0.0203f, false, false, true, false, 0},   // RK_S24x5  : stream, 8 wavefronts of 48 rows
+    {8, 3, 2.59f, 0.1066f, 0.330f, 0.0681f, false, true, false, false, 0},    // RK_S8x3   : stream, 8 wavefronts of 16 rows
+    {16, 5, 2.86f, 0.2717f, 0.214f, 0.0122f, true, true, false, false, 0},    // RK_S16x5W4: stream, 4 wavefronts of 64 rows
 };
 // ROWS_EPI_*
 constexpr bool rows_built(const RowsShape &s, int epi) {
@@ -187,9 +193,11 @@ template <int EPI, typename F> int with_rows_kernel(int k, F fn) {
         VF_STREAM_KERNEL(RK_S4x4, 4, 1, 4, 8, 4, 5)
         VF_STREAM_KERNEL(RK_S4x5, 4, 1, 5, 8, 4, 5)
         VF_STREAM_KERNEL(RK_S8x4, 8, 1, 4, 8, 4, 5)
-        VF_STREAM_KERNEL(RK_S8x5, 8, 1, 5, 8, 4, 5)
-        VF_STREAM_KERNEL(RK_S16x5, 8, 2, 5, 8, 4, 5)
+        VF_STREAM_KERNEL(RK_S8x5, 8, 1, 5, 4, 4, 5)
+        VF_STREAM_KERNEL(RK_S16x5, 8, 2, 5, 4, 4, 5)
         VF_STREAM_KERNEL(RK_S24x5, 8, 3, 5, 4, 4, 5)
+        VF_STREAM_KERNEL(RK_S8x3, 8, 1, 3, 8, 4, 5)
+        VF_STREAM_KERNEL(RK_S16x5W4, 4, 4, 5, 4, 4, 5)
         default: break;
     }
 #undef VF_ROWS_CASE
@@ -243,6 +251,9 @@ GemmPlan vf_gemm_plan(const vf_model *m, int N, int K, int rows, GemmUse use) {
         for (int k = 0; k < RK_COUNT; ++k) {
             const RowsShape &s = ROWS_SHAPES[k];
             const int whole = use == GEMM_SWIGLU ? ROWS_EPI_SWIGLU : use == GEMM_TOPK ? ROWS_EPI_TOPK : use == GEMM_QKV ? ROWS_EPI_QKV : ROWS_EPI_PARTIAL;
+            // Output heads are far wider than what the constants are fitted to.  Up to 128 rows half of a tile of 256 would be
+            // padding (80 rows: 65 us more than RK_S8x5 at 3B, 100 at 1.5B).
+            if ((use == GEMM_PARTIAL || use == GEMM_TOPK) && cbs <= 8 && s.mb >= 16) continue;
             const float mb_w = (float)N * K * 2e-6f;
             const int tiles = (NBt + s.nb - 1) / s.nb * ((cbs + s.mb - 1) / s.mb);
             for (int ks : {1, 2, 3, 4, 6, 8, 10, 12, 16}) {
@@ -252,11 +263,11 @@ GemmPlan vf_gemm_plan(const vf_model *m, int N, int K, int rows, GemmUse use) {
                 const float rounds = wgs <= 768 ? (float)((wgs + 255) / 256) : (float)wgs / 256.f + 0.2f;
                 const float mb_out = (use == GEMM_SWIGLU ? 1.f : use == GEMM_TOPK ? 0.5f : 4.f * splits) * rows * N * 1e-6f;
                 float t = s.start + s.step * nk * rounds + s.written * mb_out + s.hbm * mb_w;
-                if (use == GEMM_SPLIT) t += 0.2f * mb_out;   // the consumer reads the partial sums at about 5 TB/s
+                if (use == GEMM_SPLIT) t += 0.18f * mb_out;   // the consumer reads the partial sums at about 5 TB/s
                 // Unsplit, the QKV epilogue runs in the GEMM, at the end of every wavefront; split, it is a launch of its own.
                 // Measured, GEMM and epilogue together, in one launch / in two: 256 rows at 1.5B 8.2 / 12.1 us, 128 at 0.5B
                 // 6.9 / 8.9, 104 in 12 sequences 8.0 / 10, 277 in 16 at 1.5B 12.2 / 15.3, 1024 at 3B 52 / 55.
-                if (use == GEMM_QKV) t += splits == 1 ? 1.0f : 4.0f + 0.2f * mb_out;
+                if (use == GEMM_QKV) t += splits == 1 ? 0.f : 2.9f + 0.13f * mb_out;
                 if (t < best) {
                     best = t;
                     p.shape = k;

@@ -205,13 +205,19 @@ __global__ __launch_bounds__((CW + 1) * 64) VF_MFMA_KERNEL void gemm_stream_kern
         const char *src[NB];
 #pragma unroll
         for (int n = 0; n < NB; ++n) src[n] = (const char *)p.W + ((size_t)min(nb0 + n, NBt - 1) * p.KB + kb_begin) * 1024;
-        auto issue = [&](int s, int slot) {
+        auto issue_as = [&](int s, int slot, auto once) {
             static_for<0, KS>([&](auto h) {
                 const unsigned kb = min(s * KS + (int)h, nk - 1);   // past the end: the last k-block again, not used
                 static_for<0, NB>([&](auto n) {
-                    fragment_to_lds<((int)h * NB + (int)n) * 1024>(src[n] + (size_t)kb * 1024, lane_off, lds0 + (unsigned)slot * (KS * NB * 1024));
+                    fragment_to_lds<((int)h * NB + (int)n) * 1024, decltype(once)::value>(src[n] + (size_t)kb * 1024, lane_off,
+                                                                                          lds0 + (unsigned)slot * (KS * NB * 1024));
                 });
             });
+        };
+        // weights that no other row tile reads are not kept
+        auto issue = [&](int s, int slot) {
+            if (p.ny == 1) issue_as(s, slot, std::true_type{});
+            else issue_as(s, slot, std::false_type{});
         };
         const int first = min(SW - 1, ns);
         for (int s = 0; s < first; ++s) issue(s, s);

@@ -19,9 +19,14 @@ template <int LO, int HI, typename F> __device__ __forceinline__ void static_for
 // lane_off: 16 * lane).  Inline because the compiler makes every LDS read wait for all such loads in
 // flight; the kernels count them themselves (vm_wait).  The destination goes through m0, which needs one
 // idle cycle before the load.
-template <int LDS_OFF> __device__ __forceinline__ void fragment_to_lds(const void *src, unsigned lane_off, unsigned lds) {
-    asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-                 : : "s"(lds), "v"(lane_off), "s"(src), "n"(LDS_OFF) : "memory", "scc");
+// ONCE: nobody else reads it (non-temporal).
+template <int LDS_OFF, bool ONCE = false> __device__ __forceinline__ void fragment_to_lds(const void *src, unsigned lane_off, unsigned lds) {
+    if constexpr (ONCE)
+        asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt"
+                     : : "s"(lds), "v"(lane_off), "s"(src), "n"(LDS_OFF) : "memory", "scc");
+    else
+        asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                     : : "s"(lds), "v"(lane_off), "s"(src), "n"(LDS_OFF) : "memory", "scc");
 }
 // until at most N of this wavefront's vector memory operations are outstanding
 template <int N> __device__ __forceinline__ void vm_wait() { asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory"); }

@@ -25,9 +25,9 @@ _cache = {}
 MODELS = {
     "wide": (dict(d_model=512, n_q_heads=4, n_kv_heads=2, head_dim=128, d_ffn=8960, vocab=16400), False,
              (1, 17, 49, 128, 144, 272, 384, 512, 777, 1030, 1500)),
-    "narrow": (dict(d_model=288, n_q_heads=3, n_kv_heads=1, head_dim=64, d_ffn=4128, vocab=4112), False, (33, 65, 448, 1499)),
+    "narrow": (dict(d_model=288, n_q_heads=3, n_kv_heads=1, head_dim=64, d_ffn=4128, vocab=4112), False, (33, 65, 448, 1499, 200)),
     "deep": (dict(d_model=3072, n_q_heads=48, n_kv_heads=16, head_dim=128, d_ffn=2048, vocab=40000), True,
-             (33, 65, 129, 300, 511, 777, 1000, 1030, 1281)),
+             (33, 65, 129, 300, 511, 777, 1000, 1030, 1281, 100, 600)),
 }
 MAX_ROWS = 1500
 

@@ -4,7 +4,7 @@ import ctypes as C
 import paper_2510_15312_amd as vf
 
 GEMMS = ["qkv", "o", "gateup", "down", "head", "topk"]
-SHAPES = ["T16x16", "T16x8", "T8x8", "S4x2", "S4x4", "S4x5", "S8x4", "S8x5", "S16x5", "S24x5"]
+SHAPES = ["T16x16", "T16x8", "T8x8", "S4x2", "S4x4", "S4x5", "S8x4", "S8x5", "S16x5", "S24x5", "S8x3", "S16x5W4"]
 EPILOGUES = ["partial", "split", "qkv", "swiglu", "topk"]
 
 
