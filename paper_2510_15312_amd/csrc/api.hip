@@ -147,6 +147,8 @@ int run_layers(vf_model *m, const Batch &b, const int32_t *tokens, int *tail_par
     const GemmPlan qkv = vf_gemm_plan(m, nq + 2 * nkv, d, rows, GEMM_QKV), po = vf_gemm_plan(m, d, nq, rows, GEMM_SPLIT);
     const GemmPlan gu = vf_gemm_plan(m, 2 * F, d, rows, GEMM_SWIGLU), down = vf_gemm_plan(m, d, F, rows, GEMM_SPLIT);
     const bool act_in_gemm = gu.epi == GEMM_SWIGLU;  // the activation function is the gate/up GEMM's epilogue
+    AttnPlan attn;
+    vf_attention_plan(m, b, &attn);
     if ((rc = vf_launch_embed(m, b, tokens, tree ? m->tree_depth : nullptr, st))) return rc;
     int nparts = 0;
     for (int l = 0; l < c.n_layers; ++l) {
@@ -162,7 +164,7 @@ int run_layers(vf_model *m, const Batch &b, const int32_t *tokens, int *tail_par
             if ((rc = vf_launch_qkv_finish(m, vf_qkv_epilogue(m, b, l, tree ? m->tree_depth : nullptr), m->part, qkv.ks, R, st))) return rc;
         }
         { ProfScope ps(m, VF_SITE_ATTN, st);
-          if ((rc = vf_launch_attention(m, b, l, tree ? m->tree_anc : nullptr, st))) return rc; }
+          if ((rc = vf_launch_attention(m, b, attn, l, tree ? m->tree_anc : nullptr, st))) return rc; }
         { ProfScope ps(m, VF_SITE_O, st);
           if ((rc = vf_launch_gemm(m, lp.wo, m->o, m->part, d, nq, rows, 0, rows, R, po, st))) return rc; }
         { ProfScope ps(m, VF_SITE_SMALL, st);

@@ -134,12 +134,10 @@ int launch(const vf_model *m, const Batch &b, int layer, const tree_mask_t *anc,
 
 }  // namespace
 
-int vf_launch_attention(const vf_model *m, const Batch &b, int layer, const tree_mask_t *anc, hipStream_t st) {
+int vf_launch_attention(const vf_model *m, const Batch &b, const AttnPlan &plan, int layer, const tree_mask_t *anc, hipStream_t st) {
     const vf_config &c = m->cfg;
-    if (m->fast_path && !anc) {  // MFMA kernels
-        const int rc = vf_launch_attention_items(m, b, layer, st);
-        return rc < 0 ? rc : rc > 0 ? VF_OK : vf_launch_attention_rows(m, b, layer, st);
-    }
+    if (m->fast_path && !anc)  // MFMA kernels
+        return plan.workgroups ? vf_launch_attention_items(m, b, plan, layer, st) : vf_launch_attention_rows(m, b, layer, st);
     if (c.head_dim == 64) return launch<64>(m, b, layer, anc, st);
     if (c.head_dim == 128) return launch<128>(m, b, layer, anc, st);
     return vf_fail(VF_ERR_UNSUPPORTED, "head_dim %d (built for 64 and 128)", c.head_dim);

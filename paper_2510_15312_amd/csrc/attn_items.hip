@@ -18,10 +18,6 @@ namespace {
 
 constexpr int ITEMS_WAVES = 4, ITEMS_GROUP = ITEMS_WAVES * 16, ITEMS_STAGES = 2;
 
-// Shape of a launch: workgroups of the sequences before sequence i (a huge number past the last one),
-// records per head before its own, pages of a part.  merge: some sequence has more than one part.
-struct ItemsGrid { int first[VF_MAX_BATCH], record[VF_MAX_BATCH], part_pages, merge; };
-
 __host__ __device__ inline int items_parts(const SeqDesc &s, int part_pages) {
     const int keys = s.len_ub + s.nrows < s.capacity ? s.len_ub + s.nrows : s.capacity;
     return ((keys + VF_TILE - 1) / VF_TILE + part_pages - 1) / part_pages;
@@ -183,38 +179,53 @@ __global__ __launch_bounds__(ITEMS_WAVES * 64) VF_MFMA_KERNEL void attn_items_ke
     }
 }
 
-// Merge of the key parts by log-sum-exp: HD / 4 threads per (row, head), four output values each.
+// Merge of the key parts by log-sum-exp: HD / 4 threads per (row, head), four output values each.  What bounds it is the
+// chain of memory round trips: where a row's records lie comes from the kernel arguments (a descriptor looked up per lane
+// and its sequence's length behind it were two trips more), eight records are requested together without knowing how many
+// there are, and the row's last key, which says that, with them.
+struct ItemsMerge { int row0[VF_MAX_BATCH], parts[VF_MAX_BATCH], record[VF_MAX_BATCH], rows, part_keys; };   // row0: a huge number past the last sequence
+
 template <int HD>
-__global__ __launch_bounds__(256) void attn_items_merge_kernel(Batch b, ItemsGrid grid, const float *__restrict__ part,
+__global__ __launch_bounds__(256) void attn_items_merge_kernel(ItemsMerge g, const RowPlace *__restrict__ place, const float *__restrict__ part,
                                                                bf16_t *__restrict__ o, int hq, int ncb) {
-    constexpr int REC = HD + ATTF_STRIDE_PAD, TH = HD / 4;
+    constexpr int REC = HD + ATTF_STRIDE_PAD, TH = HD / 4, NR = 8;
     const int idx = blockIdx.x * (256 / TH) + threadIdx.x / TH, d0 = threadIdx.x % TH * 4;
-    if (idx >= b.total_rows * hq) return;
+    if (idx >= g.rows * hq) return;
     const int row = idx / hq, head = idx % hq;
-    const int seq = find_seq_many(b, row);
-    const SeqDesc &s = b.s[seq];
-    const int parts = items_parts(s, grid.part_pages), last = min(s.state[0] + row - s.row0, s.capacity - 1);
-    const int used = min(parts, last / VF_TILE / grid.part_pages + 1);   // parts with keys of this row
-    const float *p = part + ((size_t)(grid.record[seq] + (row - s.row0) * parts) * hq + head) * REC;
+    int row0 = 0, parts = g.parts[0], record = g.record[0];
+#pragma unroll
+    for (int i = 1; i < VF_MAX_BATCH; ++i)
+        if (row >= g.row0[i]) { row0 = g.row0[i]; parts = g.parts[i]; record = g.record[i]; }
+    const int last_key = place[row].last_key;
+    const float *p = part + ((size_t)(record + (row - row0) * parts) * hq + head) * REC;
     float M = -1e30f, L = 0.f;
     floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-    for (int i0 = 0; i0 < used; i0 += 4) {   // four records requested together
-        float2 ml[4];
-        floatx4 v[4];
+    int used = parts;
+    for (int i0 = 0; i0 < used; i0 += NR) {
+        float2 ml[NR];
+        floatx4 v[NR];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const float *r = p + (size_t)min(i0 + i, used - 1) * hq * REC;
+        for (int i = 0; i < NR; ++i) {
+            const float *r = p + (size_t)min(i0 + i, parts - 1) * hq * REC;
             ml[i] = *reinterpret_cast<const float2 *>(r);
             v[i] = *reinterpret_cast<const floatx4 *>(r + ATTF_STRIDE_PAD + d0);
         }
+        used = min(parts, last_key / g.part_keys + 1);   // parts with keys of this row: the records of others hold anything
+        float m = M;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            if (i0 + i >= used) break;
-            const float m = fmaxf(M, ml[i].x), keep = exp2f(M - m), add = exp2f(ml[i].x - m);
-            L = L * keep + ml[i].y * add;
-            acc = acc * keep + v[i] * add;
-            M = m;
-        }
+        for (int i = 0; i < NR; ++i)
+            if (i0 + i < used) m = fmaxf(m, ml[i].x);
+        const float keep = exp2f(M - m);
+        L *= keep;
+        acc *= keep;
+        M = m;
+#pragma unroll
+        for (int i = 0; i < NR; ++i)
+            if (i0 + i < used) {
+                const float add = exp2f(ml[i].x - m);
+                L += ml[i].y * add;
+                acc += v[i] * add;
+            }
     }
     const float inv = 1.0f / L;
     *reinterpret_cast<u32x2 *>(o + xfrag_index(row, head * HD + d0, ncb)) =
@@ -231,8 +242,17 @@ int launch_items(const vf_model *m, const Batch &b, const ItemsGrid &grid, int l
     VF_LAUNCH_CHECK("attn_items");
     if (grid.merge) {
         constexpr int PER = 256 / (HD / 4);
-        hipLaunchKernelGGL(attn_items_merge_kernel<HD>, dim3((b.total_rows * c.n_q_heads + PER - 1) / PER), dim3(256), 0, st, b,
-                           grid, m->attn_part, (bf16_t *)m->o, c.n_q_heads, ncb);
+        ItemsMerge g;
+        g.rows = b.total_rows;
+        g.part_keys = grid.part_pages * VF_TILE;
+        for (int i = 0; i < VF_MAX_BATCH; ++i) {
+            const bool is = i < b.n_seqs;
+            g.row0[i] = is ? b.s[i].row0 : 0x7fffffff;
+            g.parts[i] = is ? items_parts(b.s[i], grid.part_pages) : 1;
+            g.record[i] = is ? grid.record[i] : 0;
+        }
+        hipLaunchKernelGGL(attn_items_merge_kernel<HD>, dim3((b.total_rows * c.n_q_heads + PER - 1) / PER), dim3(256), 0, st, g,
+                           m->row_place, m->attn_part, (bf16_t *)m->o, c.n_q_heads, ncb);
         VF_LAUNCH_CHECK("attn_items_merge");
     }
     return VF_OK;
@@ -240,28 +260,30 @@ int launch_items(const vf_model *m, const Batch &b, const ItemsGrid &grid, int l
 
 }  // namespace
 
-// Which kernel, and how many pages make a part.  Both are modelled (us, one launch and its merge) and this
-// file's is taken where it is a tenth cheaper:
-//   here:      8.0 + 1.27 a thousand group pages (64 items x 64 keys; 0.67 for head_dim 64) + 0.97 a page of
-//              a part (0.60) + 1.13 a chip full of workgroups + with a merge 4.2 and 0.30 a MB of records
-//              + 0.20 a MB of keys and values
-//   attn_rows: 6.3 + 0.86 a thousand block tiles (16 items x 32 keys; 0.43) + 0.12 a tile of a part (0.06)
-//              + 2.2 with a merge + 0.60 a MB of keys and values (its blocks of 16 items read them on
-//              every die)
-// The constants are least-squares fits to 18 calls (0.5B, 1.5B and 3B shapes; chunks of 128 to 1024 rows and
-// batches of 8 to 16 sequences), every part size of a power of two: mean errors 6 and 7 %.  Measured, here
-// against attn_rows with launch gaps: 16 sequences of 512 to 8192 keys at the 1.5B shape, 277 rows, 45 / 67;
-// 8 of about 2000 keys, 22 / 28; 1900 rows of 3B in two chunks, 39 / 59 a layer and chunk; 256 rows over up to
-// 2048 keys at 1.5B, 19 / 13.5; 12 sequences of about 800 keys at 0.5B, 17 / 14.
-// Workgroups of the launch; 0: left to attn_rows.
-static int plan_items(const vf_model *m, const Batch &b, ItemsGrid &best) {
+// Which kernel, and how many pages make a part: once a call, the same for every layer.  Both kernels are modelled (us):
+//   here:      c1 a page of a part while a compute unit has one workgroup; two on one are hardly faster together than one
+//              after the other, so c2 a page for each of them; with more workgroups than the chip holds (512) c2 a page of
+//              a compute unit's share of all of them and a third of a part for the ones left at the end; with a merge 0.4
+//              for eight parts and 0.3 a MB of records, and 0.1 a MB of keys and values
+//   attn_rows: 0.35 a thousand block tiles (16 items x 32 keys; 0.39 for head_dim 64) + 2.7 with a merge + 0.4 a MB of keys
+//              and values (its blocks of 16 items read them on every die)
+// The constants are fits to the time of a layer of 74 calls (0.5B, 1.5B and 3B shapes and three with other heads; chunks of 64
+// to 1056 rows, batches of 5 to 16 sequences) with attn_rows and up to 23 sizes of a part: the choice costs a layer 0.3 %
+// on average against the best of them, 4.8 % at worst; powers of two and a workgroup's cost whatever the chip holds chose 2.0 and 10 %: 554 workgroups
+// where 512 fit (16 sequences of 512 to 8192 keys, 277 rows of 1.5B, parts of 8 pages: 3386 us a pass; of 9 pages 3191).
+// Measured, a layer, here / attn_rows: those 16 sequences 102 / 121 us, 8 sequences of about 2000 keys at 0.5B 54 / 60, 400
+// rows over 4000 keys at 1.5B 118 / 131, 1024 over 1000 at 3B 275 / 299, 256 over 1792 at 1.5B 79 / 75.
+static void plan_items(const vf_model *m, const Batch &b, AttnPlan &best) {
+    best.workgroups = 0;
     const vf_config &c = m->cfg;
     const int group = c.n_q_heads / c.n_kv_heads;
-    const float w = c.head_dim / 128.f, kv_mb_key = c.n_kv_heads * c.head_dim * 4e-6f;
+    const bool wide = c.head_dim == 128;
+    const float c1 = wide ? 0.493f : 0.65f, c2 = wide ? 0.30f : 0.55f;
+    const float kv_mb_key = c.n_kv_heads * c.head_dim * 4e-6f;
     float kv_mb = 0.f, group_pages = 0.f, block_tiles = 0.f;
     int max_keys = 0;
     for (int i = 0; i < b.n_seqs; ++i) {
-        if ((uintptr_t)b.s[i].kv & 15) return 0;   // the direct loads move 16 bytes a lane
+        if ((uintptr_t)b.s[i].kv & 15) return;   // the direct loads move 16 bytes a lane
         const int items = b.s[i].nrows * group, keys = b.s[i].len_ub + b.s[i].nrows;
         const float seen = b.s[i].len_ub + 0.5f * b.s[i].nrows;   // keys an item sees on average
         group_pages += (float)((items + ITEMS_GROUP - 1) / ITEMS_GROUP) * c.n_kv_heads * (seen / VF_TILE + 1.f);
@@ -270,14 +292,15 @@ static int plan_items(const vf_model *m, const Batch &b, ItemsGrid &best) {
         max_keys = max(max_keys, keys);
     }
     const int rows_parts = vf_attention_rows_parts(m, b);
-    const float rows_cost = 6.3f + w * (0.86e-3f * block_tiles + 0.122f * max_keys / (ATT_TILE * rows_parts)) +
-                            (rows_parts > 1 ? 2.2f : 0.f) + 0.60f * kv_mb;
+    float best_cost = (wide ? 0.352e-3f : 0.389e-3f) * block_tiles + (wide ? 0.015f * max_keys / (ATT_TILE * rows_parts) : 0.f) +
+                      (rows_parts > 1 ? 2.67f : 0.f) + 0.404f * kv_mb;
     const size_t record_floats = (size_t)c.n_q_heads * (c.head_dim + ATTF_STRIDE_PAD), room = m->attn_part_floats / record_floats;
+    const int max_pages = (max_keys + VF_TILE - 1) / VF_TILE;
     ItemsGrid grid;
-    int best_workgroups = 0;
-    float best_cost = 0.9f * rows_cost;
-    for (grid.part_pages = 4;; grid.part_pages *= 2) {
-        int records = 0, workgroups = 0;
+    // sizes of a part: every one up to 14, then an eighth to a quarter apart, and no parts
+    for (grid.part_pages = 3;; grid.part_pages += grid.part_pages < 14 ? 1 : grid.part_pages < 32 ? 2 + grid.part_pages / 20 * 2 : grid.part_pages / 4) {
+        int records = 0, workgroups = 0, parts_max = 1;
+        grid.part_pages = min(grid.part_pages, max_pages);
         grid.merge = 0;
         for (int i = 0; i < VF_MAX_BATCH; ++i) {
             grid.first[i] = i < b.n_seqs ? workgroups : 0x7fffffff;
@@ -286,33 +309,35 @@ static int plan_items(const vf_model *m, const Batch &b, ItemsGrid &best) {
             const int parts = items_parts(b.s[i], grid.part_pages);
             workgroups += (b.s[i].nrows * group + ITEMS_GROUP - 1) / ITEMS_GROUP * c.n_kv_heads * parts;
             records += b.s[i].nrows * parts;
-            grid.merge |= parts > 1;
+            parts_max = max(parts_max, parts);
         }
-        const int pages = min(grid.part_pages, (max_keys + VF_TILE - 1) / VF_TILE);
-        const float cost = 8.0f + 1.27e-3f * (0.35f + 0.65f * w) * group_pages + (0.23f + 0.74f * w) * pages + 1.13f / 256.f * workgroups +
-                           (grid.merge ? 4.2f + 0.30f * 4e-6f * records * record_floats : 0.f) + 0.20f * kv_mb;
+        grid.merge = parts_max > 1;
+        const float pages = grid.part_pages, mean = min(pages, group_pages / workgroups);
+        float cost = workgroups > 512   ? c2 * group_pages / 256.f + 0.316f * c1 * pages
+                     : workgroups > 256 ? c2 * (pages + mean)
+                                        : c1 * pages;
+        cost += 0.10f * kv_mb;
+        if (grid.merge) cost += 0.37f * ((parts_max + 7) / 8) + 0.297f * 4e-6f * records * record_floats;
         if (cost < best_cost && (!grid.merge || (size_t)records <= room)) {
             best_cost = cost;
-            best = grid;
-            best_workgroups = workgroups;
+            best.grid = grid;
+            best.workgroups = workgroups;
         }
-        if (!grid.merge) break;
+        if (grid.part_pages == max_pages) break;
     }
-    return best_workgroups;
 }
 
 int vf_attention_items_plan(const vf_model *m, const Batch &b, int *merge) {
-    ItemsGrid grid;
-    if (!plan_items(m, b, grid)) return 0;
-    *merge = grid.merge;
-    return grid.part_pages;
+    AttnPlan plan;
+    plan_items(m, b, plan);
+    if (!plan.workgroups) return 0;
+    *merge = plan.grid.merge;
+    return plan.grid.part_pages;
 }
 
-// 1: launched, 0: left to attn_rows, < 0: an error
-int vf_launch_attention_items(const vf_model *m, const Batch &b, int layer, hipStream_t st) {
-    ItemsGrid grid;
-    const int workgroups = plan_items(m, b, grid);
-    if (!workgroups) return 0;
-    const int rc = m->cfg.head_dim == 128 ? launch_items<128>(m, b, grid, layer, workgroups, st) : launch_items<64>(m, b, grid, layer, workgroups, st);
-    return rc ? rc : 1;
+void vf_attention_plan(const vf_model *m, const Batch &b, AttnPlan *plan) { plan_items(m, b, *plan); }
+
+int vf_launch_attention_items(const vf_model *m, const Batch &b, const AttnPlan &plan, int layer, hipStream_t st) {
+    return m->cfg.head_dim == 128 ? launch_items<128>(m, b, plan.grid, layer, plan.workgroups, st)
+                                  : launch_items<64>(m, b, plan.grid, layer, plan.workgroups, st);
 }

@@ -263,17 +263,17 @@ struct RowPlace {
     unsigned long long page;         // of layer 0; 0: the row is not stored
     unsigned long long layer_bytes;  // from a layer's page to the next one's
     int32_t pos, tin;                // position of the rotary angle, token within the page
-    int32_t pad[2];                  // two 16-byte loads
+    int32_t last_key, pad;           // last key the row may see (of a row that is not stored too); two 16-byte loads
 };
 // The rotary angle is that of the token's position; the cache row is the call's row (the two differ for
 // tree-structured drafts, where a node stands at the position of its depth).
 __device__ __forceinline__ RowPlace row_place(const Batch &b, const int32_t *depth, int hkv, int hd, int row) {
     const SeqDesc &s = b.s[find_seq_many(b, row)];
-    const int len = s.state[0], r = row - s.row0, slot = len + r;
-    if (slot < 0 || slot >= s.capacity) return {0, 0, 0, 0, {0, 0}};
+    const int len = s.state[0], r = row - s.row0, slot = len + r, last = min(slot, s.capacity - 1);
+    if (slot < 0 || slot >= s.capacity) return {0, 0, 0, 0, last, 0};
     const size_t page_bytes = (size_t)2 * hkv * VF_TILE * hd * sizeof(bf16_t);
     return {(unsigned long long)(s.kv + (size_t)kv_page(s, slot) * page_bytes), (unsigned long long)s.n_pages * page_bytes,
-            len + (depth ? depth[row] : r), slot % VF_TILE, {0, 0}};
+            len + (depth ? depth[row] : r), slot % VF_TILE, last, 0};
 }
 __device__ __forceinline__ QkvPlace qkv_place(const QkvColumns &e, const RowPlace &p, int g4) {
     const unsigned long long page = p.page ? p.page + p.layer_bytes * (unsigned)e.layer : 0;
@@ -360,8 +360,13 @@ int vf_launch_accept_tree(const vf_model *m, const Batch &b, const AcceptBatch &
                           const int32_t *tokens, const float *logits, int32_t *n_accept, int32_t *out_tokens,
                           int32_t *y, int32_t *path, hipStream_t st);
 int vf_launch_swiglu(const vf_model *m, const float *part, int nparts, int rows, int ld_rows, hipStream_t st);
-// anc != NULL: rows of the call see, among the call's rows, only those in their ancestor mask
-int vf_launch_attention(const vf_model *m, const Batch &b, int layer, const tree_mask_t *anc, hipStream_t st);
+// Shape of a launch of the attention kernel for many items: workgroups of the sequences before sequence i (a huge number
+// past the last one), records per head before its own, pages of a part.  merge: some sequence has more than one part.
+struct ItemsGrid { int first[VF_MAX_BATCH], record[VF_MAX_BATCH], part_pages, merge; };
+struct AttnPlan { int workgroups; ItemsGrid grid; };   // workgroups 0: the kernel for few items
+void vf_attention_plan(const vf_model *m, const Batch &b, AttnPlan *plan);
+// anc != NULL: rows of the call see, among the call's rows, only those in their ancestor mask (without `plan`)
+int vf_launch_attention(const vf_model *m, const Batch &b, const AttnPlan &plan, int layer, const tree_mask_t *anc, hipStream_t st);
 int vf_launch_state_set(int32_t *state, int idx, int32_t value, hipStream_t st);
 int vf_launch_state_add(int32_t *state, int idx, int32_t delta, hipStream_t st);
 int vf_launch_kv_read(const vf_model *m, const SeqDesc &s, int layer, int t0, int n, float *k_out,
@@ -378,8 +383,8 @@ int vf_launch_accept_static(const vf_model *m, const Batch &b, const AcceptBatch
 int vf_accept_static_init();
 int vf_attention_rows_parts(const vf_model *m, const Batch &b);
 int vf_launch_attention_rows(const vf_model *m, const Batch &b, int layer, hipStream_t st);
-// the same for many items over long contexts; 1: launched, 0: vf_launch_attention_rows is the faster one
-int vf_launch_attention_items(const vf_model *m, const Batch &b, int layer, hipStream_t st);
+// the same for many items over long contexts, as planned
+int vf_launch_attention_items(const vf_model *m, const Batch &b, const AttnPlan &plan, int layer, hipStream_t st);
 // its choice: pages of a part (merge: whether a sequence has several), 0: vf_launch_attention_rows
 int vf_attention_items_plan(const vf_model *m, const Batch &b, int *merge);
 bool vf_fast_path_ok(const vf_model *m, int total_rows);
