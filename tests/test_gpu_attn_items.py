@@ -112,6 +112,27 @@ def test_paged_batch(hd, n_seqs, lo, hi):
     assert err < 1e-2
 
 
+# more parts than the merge requests together (eight), and rows that do not see the last one, whose records for them hold anything
+@pytest.mark.parametrize("hd,ctx", [(64, 5720), (128, 5740)])
+def test_merge_of_many_parts(hd, ctx):
+    pair, rows = _pair(hd), 64
+    pages, _ = attention_plan(pair.vcfg, [ctx], [rows])
+    parts = -(-(-(-(ctx + rows) // 64)) // pages)
+    assert parts > 8 and ctx < (parts - 1) * pages * 64 < ctx + rows
+    seq = pair.new_seq(9000)
+    _fill(pair, seq, ctx, torch.Generator(device=DEV).manual_seed(ctx))
+    ids = i32(wl.make_context(pair.cfg.vocab, rows, np.random.default_rng(ctx)))
+    logits = torch.empty((rows, pair.cfg.vocab), dtype=torch.float32, device=DEV)
+
+    def run():
+        vf.vf_seq_set_len(seq, ctx)
+        vf.vf_prefill_chunk(pair.model, seq, ids, logits_mode=2, logits_out=logits)
+        return logits
+    err = _both(pair, run)
+    print(f"hd {hd}, {parts} parts: {err:.2e}", flush=True)
+    assert err < 1e-2
+
+
 # A value that is not finite may reach the rows of its own 32 keys and of the items (16 to a wavefront, 3 to a
 # row here) that share them, as in the kernel for few items, and no row further up.
 @pytest.mark.parametrize("at", [44, 70, 703])   # second half of the chunk's first page, first half, a later page
