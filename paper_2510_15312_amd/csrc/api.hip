@@ -706,6 +706,9 @@ int vf_debug_gemm_plan(const vf_config *cfg, int use, int rows, int32_t *out) {
     return VF_OK;
 }
 
+// Whether a kernel (as in out[0] above) is built with an epilogue (GemmUse; GEMM_PARTIAL and GEMM_SPLIT share one).
+int vf_debug_gemm_built(int kernel, int epilogue) { return vf_gemm_built(kernel, (GemmUse)epilogue); }
+
 // Which persistent kernel a call of vf_verify takes (options at their defaults).  out: 0 none, 1 the whole pass, 2 the
 // layers; grid barriers of its launch.
 int vf_debug_persistent_plan(const vf_config *cfg, int rows, int32_t *out) {

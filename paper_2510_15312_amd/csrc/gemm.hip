@@ -136,36 +136,53 @@ int launch_bf16(const vf_model *m, const void *W, const void *X, float *part, in
 // A call's time on a shape of tile is modelled as
 //     start + step * k-blocks per split * rounds of the chip + written * MB + hbm * MB of weights
 // (us; rounds: workgroups / 256 rounded up while there are few, fractional beyond) plus the time the
-// consumer takes to read the partial sums, and the cheapest (shape, split) is taken.  The constants are
-// least-squares fits to the time of a layer of the model with one of its four matrices forced to each shape and
-// split: 16,000 timings on the MI355X (0.5B, 1.5B and 3B shapes, twenty row counts of 16 to 1500), those within
-// 15 % of the best.  The choice costs a layer 0.2 % on average against the best of all timed, 3 % at worst; constants
-// fitted to single kernels, with an error of 6 % each, chose 0.5 % and 7 % worse, most of it in the down projection (256
-// rows of 1.5B, a layer: 73.6 us, now 71.5).  What decides is visible in them: a
+// consumer takes to read the partial sums, and the cheapest (shape, split) is taken.
+// Layers: the constants are least-squares fits to the time of a layer of the model with one of its four matrices forced to
+// each shape and split (0.5B, 1.5B and 3B shapes, twenty row counts of 16 to 1500), the timings within 15 % of the
+// best.  On 17 other row counts of the same models the choice costs a layer 0.4 % on average against the best shape and split, 5.8 % at
+// worst (down of 320 rows at 1.5B; profiles/layer_gemm_plan_timings.txt).  What decides is visible in them: a
 // shape of few weight blocks per tile (stream) wins while its column tiles fill the chip once, the square tiles
 // once there are several rounds of them anyway (their step covers more products).  Activations four k-blocks ahead
 // serve as well as eight (RK_S16x5, gate/up of 256 rows at 1.5B, a layer 73.3 -> 72.5), twelve and sixteen are no
 // better, nor are rings of shorter slots.
+// Output heads of WIDE_HEAD columns and more (dozens of rounds of column tiles) have constants of their own: the layers'
+// choose badly for them, 104 rows of 0.5B 89 us in RK_S8x5 where RK_T8x8 takes 72.5.  Fitted to the time of the head
+// alone (0.5B, 1.5B and 3B and four other widths and vocabularies of 32000 to 262144, up to 60 row counts of 1 to 1500, every
+// shape; profiles/output_head_timings.txt); the choice is 0.4 % slower than the best of all shapes on average, 13 % at worst (264
+// rows of 0.5B, whose second tile of 256 is nearly empty), with the top-k epilogue, whose time also depends on k, 0.5 and 12 %.
+// Heads of 4096 and 16384 columns are like the layers' matrices: 0.8 % with the layers' constants, 55 % at worst with these.
 enum RowsKernel { RK_T16x16, RK_T16x8, RK_T8x8, RK_S4x2, RK_S4x4, RK_S4x5, RK_S8x4, RK_S8x5, RK_S16x5, RK_S24x5, RK_S8x3, RK_S16x5W4, RK_COUNT };
+constexpr int WIDE_HEAD = 24576;
+struct RowsCost { float start, step, written, hbm; };
+constexpr RowsCost NEVER{0.f, 0.f, 0.f, 0.f};
 struct RowsShape {
     int mb, nb;                        // 16-row blocks x weight blocks of a tile
-    float start, step, written, hbm;
-    bool partial, qkv, swiglu, topk;   // epilogues it is built with: those that rows of the three full-size shapes take
+    RowsCost layer;
+    bool partial, qkv, swiglu, topk;   // epilogues it is built with: those that rows of the three full-size shapes, or a narrow head's, take
     int lists;                         // top-k candidate lists per tile and row
+    RowsCost head, head_topk;          // of wide heads
 };
 constexpr RowsShape ROWS_SHAPES[RK_COUNT] = {
-    {16, 16, 4.99f, 0.4876f, 0.182f, 0.0377f, true, true, true, true, 2},     // RK_T16x16 : square tile, 8 wavefronts of 64 x 128
-    {16, 8, 3.54f, 0.2849f, 0.228f, 0.0505f, true, true, true, true, 2},      // RK_T16x8  : square tile, 8 wavefronts of 64 x 64
-    {8, 8, 3.21f, 0.1769f, 0.183f, 0.0964f, true, true, true, true, 2},       // RK_T8x8   : square tile, 4 wavefronts of 64 x 64
-    {4, 2, 2.09f, 0.0571f, 0.325f, 0.0910f, true, true, false, false, 0},     // RK_S4x2   : stream, 4 wavefronts of 16 rows
-    {4, 4, 2.46f, 0.0795f, 0.220f, 0.0868f, true, true, true, false, 0},      // RK_S4x4
-    {4, 5, 2.35f, 0.1088f, 0.371f, 0.0626f, true, false, true, false, 0},     // RK_S4x5
-    {8, 4, 2.47f, 0.1248f, 0.232f, 0.0618f, true, true, true, false, 0},      // RK_S8x4   : stream, 8 wavefronts of 16 rows
-    {8, 5, 2.51f, 0.1477f, 0.277f, 0.0451f, true, true, true, true, 1},       // RK_S8x5
-    {16, 5, 2.30f, 0.2643f, 0.256f, 0.0094f, false, false, true, false, 0},   // RK_S16x5  : stream, 8 wavefronts of 32 rows
-    {24, 5, 1.20f, 0.3275f, 0.618f, 0.0203f, false, false, true, false, 0},   // RK_S24x5  : stream, 8 wavefronts of 48 rows
-    {8, 3, 2.59f, 0.1066f, 0.330f, 0.0681f, false, true, false, false, 0},    // RK_S8x3   : stream, 8 wavefronts of 16 rows
-    {16, 5, 2.86f, 0.2717f, 0.214f, 0.0122f, true, true, false, false, 0},    // RK_S16x5W4: stream, 4 wavefronts of 64 rows
+    // RK_T16x16: square tile, 8 wavefronts of 64 x 128
+    {16, 16, {4.99f, 0.4876f, 0.182f, 0.0377f}, true, true, true, true, 2, {5.36f, 0.5984f, 0.211f, 0.0788f}, {7.13f, 0.7503f, 2.291f, 0.0153f}},
+    // RK_T16x8: square tile, 8 wavefronts of 64 x 64
+    {16, 8, {3.54f, 0.2849f, 0.228f, 0.0505f}, true, true, true, true, 2, {3.99f, 0.3404f, 0.292f, 0.0598f}, {15.40f, 0.3998f, 2.336f, 0.0141f}},
+    // RK_T8x8: square tile, 4 wavefronts of 64 x 64
+    {8, 8, {3.21f, 0.1769f, 0.183f, 0.0964f}, true, true, true, true, 2, {2.39f, 0.1847f, 0.362f, 0.0873f}, {10.70f, 0.2174f, 1.742f, 0.0785f}},
+    // RK_S4x2, RK_S4x4, RK_S4x5: stream, 4 wavefronts of 16 rows
+    {4, 2, {2.09f, 0.0571f, 0.325f, 0.0910f}, true, true, false, false, 0, NEVER, NEVER},
+    {4, 4, {2.46f, 0.0795f, 0.220f, 0.0868f}, true, true, true, false, 0, {12.95f, 0.0548f, 0.471f, 0.0919f}, NEVER},
+    {4, 5, {2.35f, 0.1088f, 0.371f, 0.0626f}, true, false, true, false, 0, NEVER, NEVER},
+    // RK_S8x4, RK_S8x5: stream, 8 wavefronts of 16 rows
+    {8, 4, {2.47f, 0.1248f, 0.232f, 0.0618f}, true, true, true, false, 0, NEVER, NEVER},
+    {8, 5, {2.51f, 0.1477f, 0.277f, 0.0451f}, true, true, true, true, 1, NEVER, NEVER},
+    // RK_S16x5, RK_S24x5: stream, 8 wavefronts of 32 and of 48 rows
+    {16, 5, {2.30f, 0.2643f, 0.256f, 0.0094f}, false, false, true, false, 0, NEVER, NEVER},
+    {24, 5, {1.20f, 0.3275f, 0.618f, 0.0203f}, false, false, true, false, 0, NEVER, NEVER},
+    // RK_S8x3: stream, 8 wavefronts of 16 rows
+    {8, 3, {2.59f, 0.1066f, 0.330f, 0.0681f}, false, true, false, false, 0, NEVER, NEVER},
+    // RK_S16x5W4: stream, 4 wavefronts of 64 rows
+    {16, 5, {2.86f, 0.2717f, 0.214f, 0.0122f}, true, true, false, false, 0, NEVER, NEVER},
 };
 // ROWS_EPI_*
 constexpr bool rows_built(const RowsShape &s, int epi) {
@@ -242,27 +259,30 @@ int vf_gemm_init() {
     return rc;
 }
 
+static int epilogue_of(GemmUse use) {
+    return use == GEMM_SWIGLU ? ROWS_EPI_SWIGLU : use == GEMM_TOPK ? ROWS_EPI_TOPK : use == GEMM_QKV ? ROWS_EPI_QKV : ROWS_EPI_PARTIAL;
+}
+
 GemmPlan vf_gemm_plan(const vf_model *m, int N, int K, int rows, GemmUse use) {
     GemmPlan p{1, 1, -1, GEMM_PARTIAL, 0, nullptr};
     const int NBt = N >> 4, KB = K >> 5;
     if (m->fast_path) {
         const int cbs = (rows + 15) >> 4;
+        const bool wide = (use == GEMM_PARTIAL || use == GEMM_TOPK) && N >= WIDE_HEAD;
         float best = 1e30f;
         for (int k = 0; k < RK_COUNT; ++k) {
             const RowsShape &s = ROWS_SHAPES[k];
-            const int whole = use == GEMM_SWIGLU ? ROWS_EPI_SWIGLU : use == GEMM_TOPK ? ROWS_EPI_TOPK : use == GEMM_QKV ? ROWS_EPI_QKV : ROWS_EPI_PARTIAL;
-            // Output heads are far wider than what the constants are fitted to.  Up to 128 rows half of a tile of 256 would be
-            // padding (80 rows: 65 us more than RK_S8x5 at 3B, 100 at 1.5B).
-            if ((use == GEMM_PARTIAL || use == GEMM_TOPK) && cbs <= 8 && s.mb >= 16) continue;
+            const RowsCost &cost = !wide ? s.layer : use == GEMM_TOPK ? s.head_topk : s.head;
+            if (cost.step <= 0.f) continue;
             const float mb_w = (float)N * K * 2e-6f;
             const int tiles = (NBt + s.nb - 1) / s.nb * ((cbs + s.mb - 1) / s.mb);
             for (int ks : {1, 2, 3, 4, 6, 8, 10, 12, 16}) {
                 if (ks > 1 && ((use != GEMM_SPLIT && use != GEMM_QKV) || KB / ks < 4 || (size_t)ks * rows * N > m->part_floats)) break;
                 const int nk = (KB + ks - 1) / ks, splits = (KB + nk - 1) / nk, wgs = tiles * splits;
-                if (!rows_built(s, splits > 1 ? ROWS_EPI_PARTIAL : whole)) continue;
+                if (!rows_built(s, splits > 1 ? ROWS_EPI_PARTIAL : epilogue_of(use))) continue;
                 const float rounds = wgs <= 768 ? (float)((wgs + 255) / 256) : (float)wgs / 256.f + 0.2f;
                 const float mb_out = (use == GEMM_SWIGLU ? 1.f : use == GEMM_TOPK ? 0.5f : 4.f * splits) * rows * N * 1e-6f;
-                float t = s.start + s.step * nk * rounds + s.written * mb_out + s.hbm * mb_w;
+                float t = cost.start + cost.step * nk * rounds + cost.written * mb_out + cost.hbm * mb_w;
                 if (use == GEMM_SPLIT) t += 0.18f * mb_out;   // the consumer reads the partial sums at about 5 TB/s
                 // Unsplit, the QKV epilogue runs in the GEMM, at the end of every wavefront; split, it is a launch of its own.
                 // Measured, GEMM and epilogue together, in one launch / in two: 256 rows at 1.5B 8.2 / 12.1 us, 128 at 0.5B
@@ -290,6 +310,8 @@ GemmPlan vf_gemm_plan(const vf_model *m, int N, int K, int rows, GemmUse use) {
     p.ks = ks;
     return p;
 }
+
+bool vf_gemm_built(int shape, GemmUse epi) { return shape >= 0 && shape < RK_COUNT && rows_built(ROWS_SHAPES[shape], epilogue_of(epi)); }
 
 int vf_gemm_topk_lists(const GemmPlan &p, int N) {
     const RowsShape &s = ROWS_SHAPES[p.shape];

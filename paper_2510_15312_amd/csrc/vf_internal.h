@@ -327,6 +327,7 @@ struct GemmPlan {
 };
 int vf_gemm_init();
 GemmPlan vf_gemm_plan(const vf_model *m, int N, int K, int rows, GemmUse use);
+bool vf_gemm_built(int shape, GemmUse epi);
 // candidate lists per row a GEMM_TOPK plan leaves
 int vf_gemm_topk_lists(const GemmPlan &p, int N);
 // Y partials [ks][R][N] (R = ld_rows) for rows [row_lo, row_hi) of X.
