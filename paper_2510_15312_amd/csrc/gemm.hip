@@ -284,10 +284,11 @@ GemmPlan vf_gemm_plan(const vf_model *m, int N, int K, int rows, GemmUse use) {
                 const float mb_out = (use == GEMM_SWIGLU ? 1.f : use == GEMM_TOPK ? 0.5f : 4.f * splits) * rows * N * 1e-6f;
                 float t = cost.start + cost.step * nk * rounds + cost.written * mb_out + cost.hbm * mb_w;
                 if (use == GEMM_SPLIT) t += 0.18f * mb_out;   // the consumer reads the partial sums at about 5 TB/s
-                // Unsplit, the QKV epilogue runs in the GEMM, at the end of every wavefront; split, it is a launch of its own.
-                // Measured, GEMM and epilogue together, in one launch / in two: 256 rows at 1.5B 8.2 / 12.1 us, 128 at 0.5B
-                // 6.9 / 8.9, 104 in 12 sequences 8.0 / 10, 277 in 16 at 1.5B 12.2 / 15.3, 1024 at 3B 52 / 55.
-                if (use == GEMM_QKV) t += splits == 1 ? 0.f : 2.9f + 0.13f * mb_out;
+                // Unsplit, the QKV epilogue runs in the GEMM, at the end of every wavefront; split, it is a launch of its own, and
+                // no call of the full-size shapes gains by that: a layer of 3B, unsplit / the best split, 9 rows 60.6 / 62.5
+                // us, 48 65.8 / 68.1, 72 76.9 / 79.2 (a smaller term than this split it there), 128 87.6 / 90.2; of 1.5B 72
+                // rows 50.8 / 53.7, of 0.5B 37.3 / 40.0.
+                if (use == GEMM_QKV) t += splits == 1 ? 0.f : 5.5f + 0.13f * mb_out;
                 if (t < best) {
                     best = t;
                     p.shape = k;
