@@ -11,6 +11,8 @@
 // (nothing, and one workgroup a compute unit: 10 to 30 % slower), eight wavefronts and 128 items (0 to 20 %
 // slower), pages of 32 keys (two softmax chains for one: 53 -> 45 us on the mix of 16 sequences), 32 items a
 // wavefront on those (slower: half the wavefronts, each 1.1 us a tile).
+#include <algorithm>
+
 #include "fast_common.h"
 #include "lds_stream.h"
 
@@ -260,48 +262,57 @@ int launch_items(const vf_model *m, const Batch &b, const ItemsGrid &grid, int l
 
 }  // namespace
 
-// Which kernel, and how many pages make a part: once a call, the same for every layer.  Both kernels are modelled (us):
-//   here:      c1 a page of a part while a compute unit has one workgroup; two on one are hardly faster together than one
-//              after the other, so c2 a page for each of them; with more workgroups than the chip holds (512) c2 a page of
-//              a compute unit's share of all of them and a third of a part for the ones left at the end; with a merge 0.4
-//              for eight parts and 0.3 a MB of records, and 0.1 a MB of keys and values
-//   attn_rows: 0.35 a thousand block tiles (16 items x 32 keys; 0.39 for head_dim 64) + 2.7 with a merge + 0.4 a MB of keys
-//              and values (its blocks of 16 items read them on every die)
-// The constants are fits to the time of a layer of 74 calls (0.5B, 1.5B and 3B shapes and three with other heads; chunks of 64
-// to 1056 rows, batches of 5 to 16 sequences) with attn_rows and up to 23 sizes of a part: the choice costs a layer 0.3 %
-// on average against the best of them, 4.8 % at worst; powers of two and a workgroup's cost whatever the chip holds chose 2.0 and 10 %: 554 workgroups
-// where 512 fit (16 sequences of 512 to 8192 keys, 277 rows of 1.5B, parts of 8 pages: 3386 us a pass; of 9 pages 3191).
-// Measured, a layer, here / attn_rows: those 16 sequences 102 / 121 us, 8 sequences of about 2000 keys at 0.5B 54 / 60, 400
-// rows over 4000 keys at 1.5B 118 / 131, 1024 over 1000 at 3B 275 / 299, 256 over 1792 at 1.5B 79 / 75.
+// Which kernel, and how many pages make a part: once a call, the same for every layer.  Both kernels are modelled (us a
+// layer; what is the same for both left out):
+//   here:      what a page of a part costs while a compute unit has one workgroup, or two; with more workgroups than the chip
+//              holds (512) their mean for each full round of the chip, and for the rest (of up to 256 workgroups, or more) a
+//              round of theirs; a merge is a launch, and reads eight parts at a time and the records
+//   attn_rows: its wavefronts' chain of tiles, or where that is longer the chip's share of all tiles (16 items x 32 keys) and
+//              workgroups; a merge, records, and keys and values (its blocks of 16 items read them on every die)
+// The constants are fits to whole layers of 3610 calls of eleven models (chunks of 49 to 1056 rows over up to 7600 keys, batches of
+// 2 to 32 sequences) with attn_rows and every size of a part (profiles/attention_plan_timings.txt): the choice costs a
+// layer 0.4 % on average against the best of them.  Without the launch of a merge, and with constants fitted to few
+// calls, it was 1.3 %: few rows over long contexts came here for a merge more (64 rows over 2048 keys at 0.5B 42.3 us a
+// layer, attn_rows 39.6), many over longer ones ran in parts of uneven rounds (1024 over 7600 at 1.5B 289 where parts of 28
+// pages take 257).
+struct AttnCost {
+    float page1, page2, mean2, round, last, rest1, rest2, rest_mean2, merge, merge8, record_mb;                    // here
+    float rows, chain, tile, workgroup, rows_merge, rows_record_mb, rows_kv_mb;                                    // attn_rows
+};
+constexpr AttnCost COST_64 = {0.68f, 0.50f, 0.49f, 1.07f, 0.07f, 0.26f, 0.40f, 0.64f, 5.13f, 1.03f, 0.21f,
+                              -1.38f, 0.65f, 0.24e-3f, 4.2e-3f, 3.64f, 1.36f, 0.38f};
+constexpr AttnCost COST_128 = {1.08f, 0.94f, 0.66f, 1.90f, 0.22f, 0.89f, 1.07f, 0.06f, 4.55f, 1.02f, 0.34f,
+                               -2.44f, 1.09f, 0.58e-3f, 11.7e-3f, 4.02f, 0.92f, 0.37f};
+
 static void plan_items(const vf_model *m, const Batch &b, AttnPlan &best) {
     best.workgroups = 0;
     const vf_config &c = m->cfg;
     const int group = c.n_q_heads / c.n_kv_heads;
-    const bool wide = c.head_dim == 128;
-    const float c1 = wide ? 0.493f : 0.65f, c2 = wide ? 0.30f : 0.55f;
-    const float kv_mb_key = c.n_kv_heads * c.head_dim * 4e-6f;
-    float kv_mb = 0.f, group_pages = 0.f, block_tiles = 0.f;
-    int max_keys = 0;
+    const AttnCost &t = c.head_dim == 128 ? COST_128 : COST_64;
+    float seen_keys = 0.f, group_pages = 0.f, block_tiles = 0.f;
+    int max_keys = 0, blocks = 0;
     for (int i = 0; i < b.n_seqs; ++i) {
         if ((uintptr_t)b.s[i].kv & 15) return;   // the direct loads move 16 bytes a lane
-        const int items = b.s[i].nrows * group, keys = b.s[i].len_ub + b.s[i].nrows;
+        const int items = b.s[i].nrows * group, item_blocks = (items + 15) / 16 * c.n_kv_heads;
         const float seen = b.s[i].len_ub + 0.5f * b.s[i].nrows;   // keys an item sees on average
         group_pages += (float)((items + ITEMS_GROUP - 1) / ITEMS_GROUP) * c.n_kv_heads * (seen / VF_TILE + 1.f);
-        block_tiles += (float)((items + 15) / 16) * c.n_kv_heads * (seen / ATT_TILE + 1.f);
-        kv_mb += kv_mb_key * keys;
-        max_keys = max(max_keys, keys);
+        block_tiles += item_blocks * (seen / ATT_TILE + 0.5f);
+        blocks += item_blocks;
+        seen_keys += b.s[i].len_ub + b.s[i].nrows;
+        max_keys = max(max_keys, b.s[i].len_ub + b.s[i].nrows);
     }
-    const int rows_parts = vf_attention_rows_parts(m, b);
-    float best_cost = (wide ? 0.352e-3f : 0.389e-3f) * block_tiles + (wide ? 0.015f * max_keys / (ATT_TILE * rows_parts) : 0.f) +
-                      (rows_parts > 1 ? 2.67f : 0.f) + 0.404f * kv_mb;
     const size_t record_floats = (size_t)c.n_q_heads * (c.head_dim + ATTF_STRIDE_PAD), room = m->attn_part_floats / record_floats;
+    const float record_mb = 4e-6f * record_floats;
+    const int rows_parts = vf_attention_rows_parts(m, b), tiles = (max_keys + ATT_TILE - 1) / ATT_TILE;
+    float best_cost = t.rows + std::max(t.chain * tiles / (8 * rows_parts), t.tile * block_tiles + t.workgroup * blocks * rows_parts) +
+                      t.rows_kv_mb * 4e-6f * c.n_kv_heads * c.head_dim * seen_keys;
+    if (rows_parts > 1) best_cost += t.rows_merge + t.rows_record_mb * record_mb * b.total_rows * rows_parts;
     const int max_pages = (max_keys + VF_TILE - 1) / VF_TILE;
     ItemsGrid grid;
     // sizes of a part: every one up to 14, then an eighth to a quarter apart, and no parts
     for (grid.part_pages = 3;; grid.part_pages += grid.part_pages < 14 ? 1 : grid.part_pages < 32 ? 2 + grid.part_pages / 20 * 2 : grid.part_pages / 4) {
         int records = 0, workgroups = 0, parts_max = 1;
         grid.part_pages = min(grid.part_pages, max_pages);
-        grid.merge = 0;
         for (int i = 0; i < VF_MAX_BATCH; ++i) {
             grid.first[i] = i < b.n_seqs ? workgroups : 0x7fffffff;
             grid.record[i] = records;
@@ -312,12 +323,13 @@ static void plan_items(const vf_model *m, const Batch &b, AttnPlan &best) {
             parts_max = max(parts_max, parts);
         }
         grid.merge = parts_max > 1;
-        const float pages = grid.part_pages, mean = min(pages, group_pages / workgroups);
-        float cost = workgroups > 512   ? c2 * group_pages / 256.f + 0.316f * c1 * pages
-                     : workgroups > 256 ? c2 * (pages + mean)
-                                        : c1 * pages;
-        cost += 0.10f * kv_mb;
-        if (grid.merge) cost += 0.37f * ((parts_max + 7) / 8) + 0.297f * 4e-6f * records * record_floats;
+        const float pages = grid.part_pages, mean = std::min(pages, group_pages / workgroups);   // (the unqualified one is int here)
+        const int rest = workgroups % 512;
+        float cost = workgroups <= 256   ? t.page1 * pages
+                     : workgroups <= 512 ? t.page2 * pages + t.mean2 * mean
+                                         : t.round * mean * (workgroups / 512) + t.last * pages +
+                                               (rest == 0 ? 0.f : rest <= 256 ? t.rest1 * pages : t.rest2 * pages + t.rest_mean2 * mean);
+        if (grid.merge) cost += t.merge + t.merge8 * ((parts_max - 1) / 8) + t.record_mb * record_mb * records;
         if (cost < best_cost && (!grid.merge || (size_t)records <= room)) {
             best_cost = cost;
             best.grid = grid;
