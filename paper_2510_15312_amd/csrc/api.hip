@@ -720,10 +720,7 @@ int vf_debug_persistent_plan(const vf_config *cfg, int rows, int32_t *out) {
     return VF_OK;
 }
 
-// Sequences of the given lengths and rows, caches aligned.  out: pages of a part (0: the kernel for few items),
-// whether parts are merged.
-int vf_debug_attention_plan(const vf_config *cfg, int n_seqs, const int32_t *len, const int32_t *rows, int32_t *out) {
-    vf_model m;
+static int debug_batch(const vf_config *cfg, int n_seqs, const int32_t *len, const int32_t *rows, vf_model &m, Batch &b) {
     memset(&m, 0, sizeof m);
     const int rc = check_config(cfg);
     if (rc) return rc;
@@ -732,7 +729,6 @@ int vf_debug_attention_plan(const vf_config *cfg, int n_seqs, const int32_t *len
     m.es = 2;
     m.fast_path = 1;
     carve_model(&m, nullptr);
-    Batch b;
     memset(&b, 0, sizeof b);
     b.n_seqs = n_seqs;
     for (int i = 0; i < n_seqs; ++i) {
@@ -742,8 +738,28 @@ int vf_debug_attention_plan(const vf_config *cfg, int n_seqs, const int32_t *len
         b.s[i].capacity = cfg->max_positions;
         b.total_rows += rows[i];
     }
+    return VF_OK;
+}
+
+// Sequences of the given lengths and rows, caches aligned.  out: pages of a part (0: the kernel for few items),
+// whether parts are merged.
+int vf_debug_attention_plan(const vf_config *cfg, int n_seqs, const int32_t *len, const int32_t *rows, int32_t *out) {
+    vf_model m;
+    Batch b;
+    const int rc = debug_batch(cfg, n_seqs, len, rows, m, b);
+    if (rc) return rc;
     out[1] = 0;
     out[0] = vf_attention_items_plan(&m, b, &out[1]);
+    return VF_OK;
+}
+
+// Whether the kernel for few items reads the output projection's weights ahead.
+int vf_debug_attention_reads_ahead(const vf_config *cfg, int n_seqs, const int32_t *len, const int32_t *rows, int32_t *out) {
+    vf_model m;
+    Batch b;
+    const int rc = debug_batch(cfg, n_seqs, len, rows, m, b);
+    if (rc) return rc;
+    out[0] = vf_attention_reads_ahead(&m, b);
     return VF_OK;
 }
 

@@ -342,31 +342,33 @@ __global__ __launch_bounds__(256) VF_MFMA_KERNEL void attn_fast_kernel(Batch b, 
 #endif
 constexpr int ROWS_QB = ROWS_QB_N, ROWS_WAVES = 8;
 
-// The first weights that the GEMMs behind attention read (the output projection's, then gate/up's), brought to the
-// last-level cache by workgroups of its launch that have no items: attention is a chain of latencies that leaves the memory
-// idle, and those GEMMs' first products wait for weights.  256 rows a call of 1.5B, a pass of 2048 tokens 15,850 -> 15,560 us, 512
-// rows 1.9 % faster, 128 rows of 0.5B 6270 -> 6193, 104 rows in 12 sequences 1198 -> 1191; 3B and other chunks of 0.5B within
-// 0.3 %.  5 MB: with 8 chunks of 256 of 0.5B are 1 % slower, with 12 those and 3B's of 128; all of gate/up makes attention
-// longer by what the GEMM gains and more.  64 to 160 workgroups are the same.  In the norms it does not pay: down's weights 1
-// to 3 % slower, QKV's 0.5 % faster at 0.5B and 1 to 5 % slower at 1.5B and 3B.
-struct NextWeights { const char *src[2]; unsigned bytes[2]; };
-constexpr int NEXT_WGS = 96;   // a multiple of eight
-constexpr unsigned NEXT_BYTES = 5u << 20;
+// The output projection's weights, brought to the last-level cache by workgroups of attention's launch that have no items:
+// attention is a chain of latencies that leaves the memory idle, and that GEMM's first products wait for weights.  Where
+// (vf_attention_reads_ahead), and what a layer takes without / with it (profiles/attention_read_ahead_timings.txt):
+//   more than 32 rows: with fewer there is too little attention to hide it behind (9 rows of 0.5B 29.1 / 29.9 us, 49 rows 31.9 / 31.9,
+//     with 1000 keys 34.9 / 34.6);
+//   all of it in 5 MB: of a larger matrix only the first columns' are read, and all workgroups of the GEMM start at once
+//     (16 heads of 128 and d 1536, 80 rows over 1000 keys 52.6 / 53.1; 2048 wide 0 to 2 % slower, 3B the same);
+//   a sixteenth of the compute units without attention's workgroups in the launch's last round: the readers take turns with
+//     it otherwise (256 workgroups: 64.9 / 65.7, 43.1 / 43.6, where 192 are 66.8 / 66.1, 226 80.0 / 79.9 and 384 102.7 / 100.9).
+// Gate/up's first weights as well, 5 MB in all, gained 0.2 us more at 112 rows of 0.5B and lost 0.3 to 0.5 at 256 and with 16 key
+// heads.  In the norms it does not pay: down's weights 1 to 3 % slower, QKV's 0.5 % faster at 0.5B and 1 to 5 % slower at
+// 1.5B and 3B.
+struct NextWeights { const char *src; unsigned bytes; };
+constexpr int NEXT_WGS = 64;   // a multiple of eight; 96 are the same
+constexpr size_t NEXT_BYTES = 5u << 20;
 
 // workgroup i of NEXT_WGS, on compute die `die`: a share of the die's eighth
 __device__ __forceinline__ void read_next_weights(const NextWeights &w, int i, int die) {
     constexpr int NL = 8;   // 16-byte loads in flight a lane
     constexpr unsigned STEP = ROWS_WAVES * 64 * 16;
+    const unsigned slice = (w.bytes / 8 + 15) & ~15u, end = min(w.bytes, slice * (die + 1));
+    for (unsigned at = slice * die + (unsigned)(i >> 3) * (NL * STEP) + threadIdx.x * 16; at < end; at += NEXT_WGS / 8 * NL * STEP) {
+        u32x4 v[NL];
 #pragma unroll
-    for (int m = 0; m < 2; ++m) {
-        const unsigned slice = (w.bytes[m] / 8 + 15) & ~15u, end = min(w.bytes[m], slice * (die + 1));
-        for (unsigned at = slice * die + (unsigned)(i >> 3) * (NL * STEP) + threadIdx.x * 16; at < end; at += NEXT_WGS / 8 * NL * STEP) {
-            u32x4 v[NL];
+        for (int j = 0; j < NL; ++j) v[j] = *reinterpret_cast<const u32x4 *>(w.src + min(at + j * STEP, end - 16));
 #pragma unroll
-            for (int j = 0; j < NL; ++j) v[j] = *reinterpret_cast<const u32x4 *>(w.src[m] + min(at + j * STEP, end - 16));
-#pragma unroll
-            for (int j = 0; j < NL; ++j) asm volatile("" : : "v"(v[j]));
-        }
+        for (int j = 0; j < NL; ++j) asm volatile("" : : "v"(v[j]));
     }
 }
 
@@ -691,17 +693,27 @@ int vf_attention_rows_parts(const vf_model *m, const Batch &b) {
     return n_parts;
 }
 
-int vf_launch_attention_rows(const vf_model *m, const Batch &b, int layer, hipStream_t st) {
+static dim3 rows_grid(const vf_model *m, const Batch &b) {
     const vf_config &c = m->cfg;
-    const int group = c.n_q_heads / c.n_kv_heads, n_parts = vf_attention_rows_parts(m, b);
+    const int group = c.n_q_heads / c.n_kv_heads;
     int max_items = 0;
     for (int i = 0; i < b.n_seqs; ++i) max_items = max(max_items, b.s[i].nrows * group);
-    dim3 grid((max_items + 16 * ROWS_QB - 1) / (16 * ROWS_QB), c.n_kv_heads, b.n_seqs * n_parts);
-    const LayerPacked &lp = m->layers[layer];
-    const size_t wo = (size_t)c.n_q_heads * c.head_dim * c.d_model * 2, wgu = (size_t)c.d_ffn * c.d_model * 4;
-    NextWeights next = {{(const char *)lp.wo, (const char *)lp.wgu}, {(unsigned)min(wo, (size_t)NEXT_BYTES), 0}};
-    next.bytes[1] = (unsigned)min(wgu, (size_t)(NEXT_BYTES - next.bytes[0]));
-    grid.z += (NEXT_WGS + grid.x * grid.y - 1) / (grid.x * grid.y);
+    return dim3((max_items + 16 * ROWS_QB - 1) / (16 * ROWS_QB), c.n_kv_heads, b.n_seqs * vf_attention_rows_parts(m, b));
+}
+
+bool vf_attention_reads_ahead(const vf_model *m, const Batch &b) {
+    const vf_config &c = m->cfg;
+    const dim3 grid = rows_grid(m, b);
+    const unsigned last_round = grid.x * grid.y * grid.z % 256;
+    return b.total_rows > 32 && (size_t)c.n_q_heads * c.head_dim * c.d_model * 2 <= NEXT_BYTES && last_round && last_round <= 240;
+}
+
+int vf_launch_attention_rows(const vf_model *m, const Batch &b, int layer, hipStream_t st) {
+    const vf_config &c = m->cfg;
+    const int n_parts = vf_attention_rows_parts(m, b);
+    dim3 grid = rows_grid(m, b);
+    NextWeights next = {(const char *)m->layers[layer].wo, (unsigned)((size_t)c.n_q_heads * c.head_dim * c.d_model * 2)};
+    if (vf_attention_reads_ahead(m, b)) grid.z += (NEXT_WGS + grid.x * grid.y - 1) / (grid.x * grid.y);
     const int ncb = (b.total_rows + 15) >> 4;
     const float scale_log2e = 1.4426950408889634f / sqrtf((float)c.head_dim);
     const int lds = ROWS_WAVES * (c.head_dim / 16) * 64 * 16 + ROWS_WAVES * 2 * 16 * 4;

@@ -383,6 +383,8 @@ int vf_launch_accept_static(const vf_model *m, const Batch &b, const AcceptBatch
                             hipStream_t st);
 int vf_accept_static_init();
 int vf_attention_rows_parts(const vf_model *m, const Batch &b);
+// whether its launch reads the output projection's weights ahead
+bool vf_attention_reads_ahead(const vf_model *m, const Batch &b);
 int vf_launch_attention_rows(const vf_model *m, const Batch &b, int layer, hipStream_t st);
 // the same for many items over long contexts, as planned
 int vf_launch_attention_items(const vf_model *m, const Batch &b, const AttnPlan &plan, int layer, hipStream_t st);

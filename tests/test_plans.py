@@ -10,7 +10,7 @@ import paper_2510_15312_amd as vf
 import workloads as wl
 import test_gpu_attn_items as items
 from test_gpu_rows import MODELS, candidates, config_of
-from util_plan import EPILOGUES, GEMMS, SHAPES, attention_plan, gemm_plan, persistent_plan
+from util_plan import EPILOGUES, GEMMS, SHAPES, attention_plan, attention_reads_ahead, gemm_plan, persistent_plan
 
 FULL = ["0.5b_k8", "1.5b_k16", "3b_k32"]
 
@@ -97,6 +97,22 @@ def test_attention_takes_a_fast_kernel():
             best = min(us.values())
             cost.append(us.get(str(pages) if pages else "rows", 1.15 * best) / best)
     assert sum(cost) / len(cost) < 1.0065 and sum(c > 1.03 for c in cost) < 0.07 * len(cost)
+
+
+# Where attention's launch reads the output projection's weights ahead, against timings with and without: nowhere at a loss of
+# more than the spread of two runs (1.5 %), and with a gain on average.
+def test_read_ahead_where_it_pays():
+    added, configs = [], {}
+    with open(os.path.join(os.path.dirname(__file__), "..", "profiles", "attention_read_ahead_timings.txt")) as f:
+        for line in f:
+            if line.startswith("#"):
+                continue
+            d, hq, hkv, hd, ffn, rows, ctx, without, more = line.split()
+            cfg = vf.make_config(1, int(d), int(hq), int(hkv), int(hd), int(ffn), 4096, "bf16", 1e6, 1e-6, 1056, 8704)
+            if attention_reads_ahead(cfg, [int(ctx)], [int(rows)]):
+                added.append((float(more) / float(without), line))
+    assert len(added) > 400 and max(added)[0] < 0.015, max(added)
+    assert sum(a for a, _ in added) < 0
 
 
 def test_splits_leave_no_part_empty():

@@ -24,6 +24,14 @@ def attention_plan(cfg, lens, rows):
     return out[0], bool(out[1])
 
 
+def attention_reads_ahead(cfg, lens, rows):
+    """Whether the kernel for few items reads the output projection's weights ahead."""
+    n, out = len(lens), (C.c_int32 * 1)()
+    arr = C.c_int32 * n
+    vf.binding._check(vf.lib.vf_debug_attention_reads_ahead(C.byref(cfg), n, arr(*[int(x) for x in lens]), arr(*[int(x) for x in rows]), out))
+    return bool(out[0])
+
+
 def persistent_plan(cfg, rows):
     """(which persistent kernel a vf_verify of so many rows takes, grid barriers of its launch)."""
     out = (C.c_int32 * 2)()
