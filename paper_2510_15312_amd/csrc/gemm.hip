@@ -139,8 +139,9 @@ int launch_bf16(const vf_model *m, const void *W, const void *X, float *part, in
 // consumer takes to read the partial sums, and the cheapest (shape, split) is taken.
 // Layers: the constants are least-squares fits to the time of a layer of the model with one of its four matrices forced to
 // each shape and split (0.5B, 1.5B and 3B shapes, twenty row counts of 16 to 1500), the timings within 15 % of the
-// best.  On 17 other row counts of the same models the choice costs a layer 0.4 % on average against the best shape and split, 5.8 % at
-// worst (down of 320 rows at 1.5B; profiles/layer_gemm_plan_timings.txt).  What decides is visible in them: a
+// best.  Timed anew (20 row counts of 7 to 1300, and a model 2048 wide), the choice costs a layer 0.4 % on average against the
+// best kernel and split, 3.4 % at worst of the three (down of 250 rows at 3B), 5 % of the fourth;
+// profiles/layer_gemm_plan_timings.txt.  What decides is visible in them: a
 // shape of few weight blocks per tile (stream) wins while its column tiles fill the chip once, the square tiles
 // once there are several rounds of them anyway (their step covers more products).  Activations four k-blocks ahead
 // serve as well as eight (RK_S16x5, gate/up of 256 rows at 1.5B, a layer 73.3 -> 72.5), twelve and sixteen are no

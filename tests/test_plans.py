@@ -71,6 +71,21 @@ def test_output_heads_take_a_fast_kernel(epilogue, mean, worst):
     assert sum(c for c, _ in cost) / len(cost) < mean and max(cost)[0] < worst, max(cost)
 
 
+# and those of a layer, on timings that their constants are not fitted to
+def test_layers_take_fast_kernels():
+    cost = []
+    with open(os.path.join(os.path.dirname(__file__), "..", "profiles", "layer_gemm_plan_timings.txt")) as f:
+        for line in f:
+            if line.startswith("#"):
+                continue
+            d, hq, hkv, hd, ffn, gemm, rows, *times = line.split()
+            cfg = vf.make_config(1, int(d), int(hq), int(hkv), int(hd), int(ffn), 4096, "bf16", 1e6, 1e-6, 1536, 4096)
+            us = {t.split(":")[0]: float(t.split(":")[1]) for t in times}
+            kernel, splits, _ = gemm_plan(cfg, gemm, int(rows))
+            cost.append((us[f"{kernel}/{splits}"] / min(us.values()), line))
+    assert sum(c for c, _ in cost) / len(cost) < 1.006 and max(cost)[0] < 1.06, max(cost)
+
+
 # a split QKV is a launch more, and slower at every row count that was timed (by 2 to 4 % of a layer up to 128 rows of 3B)
 @pytest.mark.parametrize("name", FULL)
 def test_qkv_of_the_full_shapes_is_one_launch(name):
