@@ -133,6 +133,37 @@ def test_merge_of_many_parts(hd, ctx):
     assert err < 1e-2
 
 
+# The same with records that would show: a call before it, whose rows all see the last part, leaves there the records of
+# keys and values far above all others, which outweigh a row's own by any number of orders if they are added to it.
+@pytest.mark.parametrize("hd,ctx", [(64, 5720), (128, 5720)])
+def test_merge_drops_the_parts_a_row_does_not_see(hd, ctx):
+    pair, rows = _pair(hd), 64
+    pages, merged = attention_plan(pair.vcfg, [ctx], [rows])
+    parts = -(-(-(-(ctx + rows) // 64)) // pages)
+    last = (parts - 1) * pages * 64
+    # the first 64 items, 21 rows of three heads, see nothing of the last part
+    assert merged and ctx + 22 < last < ctx + rows
+    assert attention_plan(pair.vcfg, [last + 32], [rows]) == (pages, True) and -(-(-(-(last + 32 + rows) // 64)) // pages) == parts
+    seq, gen = pair.new_seq(9000), torch.Generator(device=DEV).manual_seed(ctx)
+    _fill(pair, seq, last, gen)
+    far = torch.empty((2, 32, pair.cfg.n_kv_heads, hd), dtype=torch.float32, device=DEV).normal_(0.0, 100.0, generator=gen)
+    far[1] = 1e4
+    vf.vf_kv_write(pair.model, seq, 0, last, far[0], far[1])
+    ids = i32(wl.make_context(pair.cfg.vocab, rows, np.random.default_rng(ctx)))
+    logits = torch.empty((rows, pair.cfg.vocab), dtype=torch.float32, device=DEV)
+
+    def run_at(n):
+        vf.vf_seq_set_len(seq, n)
+        vf.vf_prefill_chunk(pair.model, seq, ids, logits_mode=2, logits_out=logits)
+        return logits
+    before = run_at(last + 32).cpu().numpy()
+    err = _both(pair, lambda: run_at(ctx))   # the kernel for many items first
+    own = logits.cpu().numpy()
+    print(f"hd {hd}, {parts} parts: {err:.2e}", flush=True)
+    assert np.isfinite(own).all() and rel_inf(before, own).min() > 0.1   # every row of the call before saw the far values
+    assert err < 1e-2
+
+
 # A value that is not finite may reach the rows of its own 32 keys and of the items (16 to a wavefront, 3 to a
 # row here) that share them, as in the kernel for few items, and no row further up.
 @pytest.mark.parametrize("at", [44, 70, 703])   # second half of the chunk's first page, first half, a later page
