@@ -13,6 +13,7 @@ import workloads as wl
 import paper_2510_15312_amd as vf
 from util_oracle import rel_inf
 from util_gpu import DEV, Pair, tol_of, i32, f32
+from util_plan import gemm_plan, persistent_plan
 
 pytestmark = pytest.mark.gpu
 C = wl.CONFIGS
@@ -296,4 +297,39 @@ def test_tree_verify_on_paged_sequences_compacts_across_pages(fast):
         oracle.compact(cache, n_ctx, wp)
         for layer in (0, cfg.n_layers - 1):
             (kg, vg), (ko, vo) = pair.kv_both(seq, cache, layer, n_ctx - 3, a + 4)
+            assert np.abs(kg - ko).max() <= 1e-2 * np.abs(ko).max() and np.abs(vg - vo).max() <= 1e-2 * np.abs(vo).max()
+
+
+# More rows than the persistent kernels take: a launch per operation, with the rotary angles of a row's depth found once a call
+# and applied in the QKV GEMM's epilogue.
+@pytest.mark.parametrize("name", ["0.5b_k8", "1.5b_k16"])
+def test_trees_of_many_rows_on_paged_sequences(name):
+    cfg = wl.scaled(C[name], n_layers=2, vocab=4096)
+    pair = Pair(cfg, max_rows=128, max_positions=400)
+    rng = np.random.default_rng(23)
+    ctxs, ks = [120, 61, 200], [32, 24, 21]
+    row_off = [0] + [int(x) for x in np.cumsum([k + 1 for k in ks])]
+    rows = row_off[-1]
+    assert persistent_plan(pair.vcfg, rows)[0] is None and gemm_plan(pair.vcfg, "qkv", rows)[2] == "qkv"
+    need = [-(-(n + k + 1) // 64) for n, k in zip(ctxs, ks)]
+    pool = torch.empty(vf.vf_kv_bytes(pair.model, 64, sum(need)), dtype=torch.uint8, device=DEV)
+    perm = np.split(rng.permutation(sum(need)), np.cumsum(need)[:-1])
+    seqs, caches, toks, pars = [], [], [], []
+    for bt, n_ctx, k in zip(perm, ctxs, ks):
+        seqs.append(pair.new_seq(len(bt) * 64, pool=pool, block_table=i32(bt)))
+        caches.append(oracle.KVCache(pair.spec, len(bt) * 64))
+        pair.prefill_both(seqs[-1], caches[-1], wl.make_context(cfg.vocab, n_ctx, rng), 64)
+        t, p = _random_tree(rng, k, cfg.vocab)
+        assert max(oracle.transformer.tree_depths(p)) < k   # depth and row differ
+        toks.append(t); pars.append(p)
+    logits = torch.empty((rows, cfg.vocab), dtype=torch.float32, device=DEV)
+    vf.vf_verify_tree(pair.model, seqs, i32(np.concatenate(toks)), row_off, [p for ps in pars for p in ps], logits)
+    torch.cuda.synchronize()
+    z = np.concatenate([oracle.verify_tree(pair.spec, pair.ow, c, t, p) for c, t, p in zip(caches, toks, pars)])
+    err = rel_inf(logits.cpu().numpy(), z).max()
+    print(f"{name}, {rows} rows: max rel-inf logit error {err:.3e}", flush=True)
+    assert err < tol_of(cfg)
+    for seq, cache, n_ctx, k in zip(seqs, caches, ctxs, ks):
+        for layer in range(cfg.n_layers):
+            (kg, vg), (ko, vo) = pair.kv_both(seq, cache, layer, n_ctx, k + 1)
             assert np.abs(kg - ko).max() <= 1e-2 * np.abs(ko).max() and np.abs(vg - vo).max() <= 1e-2 * np.abs(vo).max()
