@@ -147,8 +147,8 @@ int run_layers(vf_model *m, const Batch &b, const int32_t *tokens, int *tail_par
     const GemmPlan qkv = vf_gemm_plan(m, nq + 2 * nkv, d, rows, GEMM_QKV), po = vf_gemm_plan(m, d, nq, rows, GEMM_SPLIT);
     const GemmPlan gu = vf_gemm_plan(m, 2 * F, d, rows, GEMM_SWIGLU), down = vf_gemm_plan(m, d, F, rows, GEMM_SPLIT);
     const bool act_in_gemm = gu.epi == GEMM_SWIGLU;  // the activation function is the gate/up GEMM's epilogue
-    AttnPlan attn;
-    vf_attention_plan(m, b, &attn);
+    AttnPlan attn{};
+    if (m->fast_path && !tree) vf_attention_plan(m, b, &attn);
     if ((rc = vf_launch_embed(m, b, tokens, tree ? m->tree_depth : nullptr, st))) return rc;
     int nparts = 0;
     for (int l = 0; l < c.n_layers; ++l) {

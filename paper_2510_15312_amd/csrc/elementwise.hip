@@ -64,13 +64,13 @@ __global__ void rope_table_kernel(float *__restrict__ cosv, float *__restrict__ 
 // ---- forward pass helpers -----------------------------------------------------------------------
 
 // One workgroup per row.  The first wavefronts gather, pieces of eight elements that lie together in the packed matrix; the
-// last finds the row's place (place: NULL if nothing reads it).
+// last finds the row's place.
 __global__ __launch_bounds__(256) void embed_kernel(const bf16_t *__restrict__ E, const int32_t *__restrict__ tokens, Batch b,
                                                     float *__restrict__ h, int d, int vocab, const int32_t *__restrict__ depth, int hkv, int hd,
                                                     const float *__restrict__ cosv, const float *__restrict__ sinv, RowPlace *__restrict__ place,
                                                     float *__restrict__ row_cos, float *__restrict__ row_sin) {
     const int row = blockIdx.x, half = hd / 2, i = threadIdx.x - 192;
-    if (place && i >= 0 && i < half) {
+    if (i >= 0 && i < half) {
         const RowPlace p = row_place(b, depth, hkv, hd, row);
         if (i == 0) place[row] = p;
         row_cos[(size_t)row * half + i] = cosv[(size_t)p.pos * half + i];
