@@ -477,7 +477,7 @@ int vf_prefill_chunk_topk(vf_model *m, vf_seq *s, const int32_t *tokens_dev, int
     const float *last_row;
     GemmPlan p;
     p.epi = GEMM_PARTIAL;
-    if (c.dtype == VF_BF16 && topk_in_gemm(c, n_tokens, top_k)) p = vf_gemm_plan(m, c.vocab, c.d_model, n_tokens, GEMM_TOPK);
+    if (c.dtype == VF_BF16 && topk_in_gemm(c, n_tokens, top_k)) p = vf_gemm_plan(m, c.vocab, c.d_model, n_tokens, GEMM_TOPK, top_k);
     if (p.epi == GEMM_TOPK) {
         { ProfScope ps(m, VF_SITE_SMALL, st);
           if ((rc = vf_launch_norm(m, m->final_norm, m->x, m->part, tail, n_tokens, n_tokens, st))) return rc; }
@@ -682,7 +682,7 @@ int vf_stream_read(vf_model *m, size_t *bytes_host, void *stream) {
 
 // Which kernels a many-row call takes: not part of the interface, exported so that the tests can state what they
 // run and check that nothing chosen goes untested.  Host only.
-//   use: a GemmUse-like number: 0 QKV, 1 O, 2 gate/up, 3 down, 4 output head, 5 output head with the top-k epilogue
+//   use: a GemmUse-like number: 0 QKV, 1 O, 2 gate/up, 3 down, 4 output head, 4 + k output head with the top-k epilogue
 //   out: kernel of gemm_rows.h (index into the shapes of gemm.hip), K splits, epilogue (GemmUse), and whether the
 //   partial sums, where it leaves some, fit their workspace
 int vf_debug_gemm_plan(const vf_config *cfg, int use, int rows, int32_t *out) {
@@ -690,15 +690,16 @@ int vf_debug_gemm_plan(const vf_config *cfg, int use, int rows, int32_t *out) {
     memset(&m, 0, sizeof m);
     const int rc = check_config(cfg);
     if (rc) return rc;
-    if (cfg->dtype != VF_BF16 || rows < 1 || rows > cfg->max_rows || use < 0 || use > 5) return vf_fail(VF_ERR_ARG, "vf_debug_gemm_plan");
+    if (cfg->dtype != VF_BF16 || rows < 1 || rows > cfg->max_rows || use < 0 || use > 4 + VF_TOPK_MAX) return vf_fail(VF_ERR_ARG, "vf_debug_gemm_plan");
     m.cfg = *cfg;
     m.es = 2;
     m.fast_path = 1;
     carve_model(&m, nullptr);
     const int d = cfg->d_model, nq = cfg->n_q_heads * cfg->head_dim, nkv = cfg->n_kv_heads * cfg->head_dim, F = cfg->d_ffn;
-    const int N[] = {nq + 2 * nkv, d, 2 * F, d, cfg->vocab, cfg->vocab}, K[] = {d, nq, d, F, d, d};
+    const int N[] = {nq + 2 * nkv, d, 2 * F, d, cfg->vocab, cfg->vocab}, K[] = {d, nq, d, F, d, d}, top_k = use > 4 ? use - 4 : 1;
     const GemmUse as[] = {GEMM_QKV, GEMM_SPLIT, GEMM_SWIGLU, GEMM_SPLIT, GEMM_PARTIAL, GEMM_TOPK};
-    const GemmPlan p = vf_gemm_plan(&m, N[use], K[use], rows, as[use]);
+    use = std::min(use, 5);
+    const GemmPlan p = vf_gemm_plan(&m, N[use], K[use], rows, as[use], top_k);
     out[0] = p.shape;
     out[1] = p.ks;
     out[2] = p.epi;

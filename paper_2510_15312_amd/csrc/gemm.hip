@@ -150,11 +150,13 @@ int launch_bf16(const vf_model *m, const void *W, const void *X, float *part, in
 // choose badly for them, 104 rows of 0.5B 89 us in RK_S8x5 where RK_T8x8 takes 72.5.  Fitted to the time of the head
 // alone (0.5B, 1.5B and 3B and four other widths and vocabularies of 32000 to 262144, up to 60 row counts of 1 to 1500, every
 // shape; profiles/output_head_timings.txt); the choice is 0.4 % slower than the best of all shapes on average, 13 % at worst (264
-// rows of 0.5B, whose second tile of 256 is nearly empty), with the top-k epilogue, whose time also depends on k, 0.5 and 12 %.
+// rows of 0.5B, whose second tile of 256 is nearly empty).  With the top-k epilogue a call's time goes on with the merge of its lists,
+// twice as many in RK_T16x8 as in RK_T16x16 (240 rows of 1.5B, top 4: 209 and 221 us the GEMM, 284 and 268 with norm and merge): fitted to
+// both, for 1 to 8 candidates; 0.3 % slower than the best on average, 11 % at worst (7 % of the three full-size shapes).
 // Heads of 4096 and 16384 columns are like the layers' matrices: 0.8 % with the layers' constants, 55 % at worst with these.
 enum RowsKernel { RK_T16x16, RK_T16x8, RK_T8x8, RK_S4x2, RK_S4x4, RK_S4x5, RK_S8x4, RK_S8x5, RK_S16x5, RK_S24x5, RK_S8x3, RK_S16x5W4, RK_COUNT };
 constexpr int WIDE_HEAD = 24576;
-struct RowsCost { float start, step, written, hbm; };
+struct RowsCost { float start, step, written, hbm, again = 0.f; };   // again: a round of the chip, for each candidate after the first
 constexpr RowsCost NEVER{0.f, 0.f, 0.f, 0.f};
 struct RowsShape {
     int mb, nb;                        // 16-row blocks x weight blocks of a tile
@@ -165,18 +167,18 @@ struct RowsShape {
 };
 constexpr RowsShape ROWS_SHAPES[RK_COUNT] = {
     // RK_T16x16: square tile, 8 wavefronts of 64 x 128
-    {16, 16, {4.99f, 0.4876f, 0.182f, 0.0377f}, true, true, true, true, 2, {5.36f, 0.5984f, 0.211f, 0.0788f}, {7.13f, 0.7503f, 2.291f, 0.0153f}},
+    {16, 16, {4.99f, 0.4876f, 0.182f, 0.0377f}, true, true, true, true, 2, {5.36f, 0.5984f, 0.211f, 0.0788f}, {10.03f, 0.5180f, 2.491f, 0.0604f, 10.60f}},
     // RK_T16x8: square tile, 8 wavefronts of 64 x 64
-    {16, 8, {3.54f, 0.2849f, 0.228f, 0.0505f}, true, true, true, true, 2, {3.99f, 0.3404f, 0.292f, 0.0598f}, {15.40f, 0.3998f, 2.336f, 0.0141f}},
+    {16, 8, {3.54f, 0.2849f, 0.228f, 0.0505f}, true, true, true, true, 2, {3.99f, 0.3404f, 0.292f, 0.0598f}, {11.13f, 0.3468f, 2.699f, 0.0368f, 4.58f}},
     // RK_T8x8: square tile, 4 wavefronts of 64 x 64
-    {8, 8, {3.21f, 0.1769f, 0.183f, 0.0964f}, true, true, true, true, 2, {2.39f, 0.1847f, 0.362f, 0.0873f}, {10.70f, 0.2174f, 1.742f, 0.0785f}},
+    {8, 8, {3.21f, 0.1769f, 0.183f, 0.0964f}, true, true, true, true, 2, {2.39f, 0.1847f, 0.362f, 0.0873f}, {11.59f, 0.1955f, 1.711f, 0.0521f, 2.34f}},
     // RK_S4x2, RK_S4x4, RK_S4x5: stream, 4 wavefronts of 16 rows
     {4, 2, {2.09f, 0.0571f, 0.325f, 0.0910f}, true, true, false, false, 0, NEVER, NEVER},
     {4, 4, {2.46f, 0.0795f, 0.220f, 0.0868f}, true, true, true, false, 0, {12.95f, 0.0548f, 0.471f, 0.0919f}, NEVER},
     {4, 5, {2.35f, 0.1088f, 0.371f, 0.0626f}, true, false, true, false, 0, NEVER, NEVER},
     // RK_S8x4, RK_S8x5: stream, 8 wavefronts of 16 rows
     {8, 4, {2.47f, 0.1248f, 0.232f, 0.0618f}, true, true, true, false, 0, NEVER, NEVER},
-    {8, 5, {2.51f, 0.1477f, 0.277f, 0.0451f}, true, true, true, true, 1, NEVER, NEVER},
+    {8, 5, {2.51f, 0.1477f, 0.277f, 0.0451f}, true, true, true, true, 1, NEVER, {0.f, 0.f, 0.f, 0.f, 2.2f}},
     // RK_S16x5, RK_S24x5: stream, 8 wavefronts of 32 and of 48 rows
     {16, 5, {2.30f, 0.2643f, 0.256f, 0.0094f}, false, false, true, false, 0, NEVER, NEVER},
     {24, 5, {1.20f, 0.3275f, 0.618f, 0.0203f}, false, false, true, false, 0, NEVER, NEVER},
@@ -264,7 +266,7 @@ static int epilogue_of(GemmUse use) {
     return use == GEMM_SWIGLU ? ROWS_EPI_SWIGLU : use == GEMM_TOPK ? ROWS_EPI_TOPK : use == GEMM_QKV ? ROWS_EPI_QKV : ROWS_EPI_PARTIAL;
 }
 
-GemmPlan vf_gemm_plan(const vf_model *m, int N, int K, int rows, GemmUse use) {
+GemmPlan vf_gemm_plan(const vf_model *m, int N, int K, int rows, GemmUse use, int top_k) {
     GemmPlan p{1, 1, -1, GEMM_PARTIAL, 0, nullptr};
     const int NBt = N >> 4, KB = K >> 5;
     if (m->fast_path) {
@@ -284,6 +286,10 @@ GemmPlan vf_gemm_plan(const vf_model *m, int N, int K, int rows, GemmUse use) {
                 const float rounds = wgs <= 768 ? (float)((wgs + 255) / 256) : (float)wgs / 256.f + 0.2f;
                 const float mb_out = (use == GEMM_SWIGLU ? 1.f : use == GEMM_TOPK ? 0.5f : 4.f * splits) * rows * N * 1e-6f;
                 float t = cost.start + cost.step * nk * rounds + cost.written * mb_out + cost.hbm * mb_w;
+                if (use == GEMM_TOPK) {   // the merge reads a row's lists once per candidate
+                    const float lists = (NBt + s.nb - 1) / s.nb * s.lists, read = lists * top_k * top_k;
+                    t += s.head_topk.again * (top_k - 1) * rounds + 2.38e-3f * read + 1.44e-6f * read * rows;
+                }
                 if (use == GEMM_SPLIT) t += 0.18f * mb_out;   // the consumer reads the partial sums at about 5 TB/s
                 // Unsplit, the QKV epilogue runs in the GEMM, at the end of every wavefront; split, it is a launch of its own, and
                 // no call of the full-size shapes gains by that: a layer of 3B, unsplit / the best split, 9 rows 60.6 / 62.5
@@ -364,6 +370,7 @@ int vf_launch_gemm(const vf_model *m, const void *W, const void *X, float *out, 
         const int epi = plan.epi == GEMM_SWIGLU ? ROWS_EPI_SWIGLU : plan.epi == GEMM_TOPK ? ROWS_EPI_TOPK : ROWS_EPI_PARTIAL;
         return launch_rows(epi, plan.shape, p, p.nx * p.ny * plan.ks, st);
     }
+    if (plan.epi == GEMM_TOPK) return vf_fail(VF_ERR_ARG, "top-k epilogue: no many-row kernel");
     if (cbs <= 1) return launch_bf16<1>(m, W, X, out, N, K, ncb, row_lo, row_hi, ld_rows, plan, st);
     if (cbs == 2) return launch_bf16<2>(m, W, X, out, N, K, ncb, row_lo, row_hi, ld_rows, plan, st);
     if (cbs == 3) return launch_bf16<3>(m, W, X, out, N, K, ncb, row_lo, row_hi, ld_rows, plan, st);

@@ -326,7 +326,8 @@ struct GemmPlan {
     int32_t *topk_ids;  // their ids (the values go where the partials would)
 };
 int vf_gemm_init();
-GemmPlan vf_gemm_plan(const vf_model *m, int N, int K, int rows, GemmUse use);
+// top_k: candidates a row that a GEMM_TOPK plan is for
+GemmPlan vf_gemm_plan(const vf_model *m, int N, int K, int rows, GemmUse use, int top_k = 1);
 bool vf_gemm_built(int shape, GemmUse epi);
 // candidate lists per row a GEMM_TOPK plan leaves
 int vf_gemm_topk_lists(const GemmPlan &p, int N);

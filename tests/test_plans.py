@@ -21,7 +21,7 @@ def _taken(cfg, rows, top_k):
     for g in GEMMS:
         if g == "topk" and (rows <= 64 or rows < (28 if cfg.d_model >= 2048 else 40) * top_k):
             continue   # the candidates come from the logits
-        kernel, splits, epilogue = gemm_plan(cfg, g, rows)
+        kernel, splits, epilogue = gemm_plan(cfg, g, rows, top_k)
         out.add((kernel, epilogue, splits > 1))
     return out
 
@@ -67,7 +67,7 @@ def test_output_heads_take_a_fast_kernel(epilogue, mean, worst):
                 continue
             cfg = vf.make_config(1, int(d), 2, 2, 64, 64, int(vocab), "bf16", 1e4, 1e-6, 1504, 2048)
             us = {t.split(":")[0]: float(t.split(":")[1]) for t in times}
-            cost.append((us[gemm_plan(cfg, "topk" if epilogue == "top" else "head", int(rows))[0]] / min(us.values()), line))
+            cost.append((us[gemm_plan(cfg, *(("topk", int(rows), int(what[3:])) if epilogue == "top" else ("head", int(rows))))[0]] / min(us.values()), line))
     assert sum(c for c, _ in cost) / len(cost) < mean and max(cost)[0] < worst, max(cost)
 
 

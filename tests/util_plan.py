@@ -8,10 +8,10 @@ SHAPES = ["T16x16", "T16x8", "T8x8", "S4x2", "S4x4", "S4x5", "S8x4", "S8x5", "S1
 EPILOGUES = ["partial", "split", "qkv", "swiglu", "topk"]
 
 
-def gemm_plan(cfg, gemm, rows):
+def gemm_plan(cfg, gemm, rows, top_k=1):
     """(kernel, K splits, epilogue) of a GEMM of a vf_config at a number of rows."""
     out = (C.c_int32 * 4)()
-    vf.binding._check(vf.lib.vf_debug_gemm_plan(C.byref(cfg), GEMMS.index(gemm), rows, out))
+    vf.binding._check(vf.lib.vf_debug_gemm_plan(C.byref(cfg), GEMMS.index(gemm) + (top_k - 1 if gemm == "topk" else 0), rows, out))
     assert out[3], f"{gemm} of {rows} rows: the partial sums do not fit"
     return SHAPES[out[0]], out[1], EPILOGUES[out[2]]
 
