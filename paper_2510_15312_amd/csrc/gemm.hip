@@ -278,6 +278,10 @@ GemmPlan vf_gemm_plan(const vf_model *m, int N, int K, int rows, GemmUse use, in
             const RowsCost &cost = !wide ? s.layer : use == GEMM_TOPK ? s.head_topk : s.head;
             if (cost.step <= 0.f) continue;
             const float mb_w = (float)N * K * 2e-6f;
+            // Up to 64 rows the stream kernels read each weight once and past the caches.  A head that the last-level cache (256
+            // MB) does not hold, read through it by a square tile, costs the layers of the next pass more than the tile gains:
+            // one row of 0.5B, RK_T8x8 44.6 us and RK_S4x4 50.4, a prefill of 51 tokens 840 and 817.
+            if (use == GEMM_PARTIAL && cbs <= 4 && mb_w > 256.f && s.lists == 2) continue;
             const int tiles = (NBt + s.nb - 1) / s.nb * ((cbs + s.mb - 1) / s.mb);
             for (int ks : {1, 2, 3, 4, 6, 8, 10, 12, 16}) {
                 if (ks > 1 && ((use != GEMM_SPLIT && use != GEMM_QKV) || KB / ks < 4 || (size_t)ks * rows * N > m->part_floats)) break;
