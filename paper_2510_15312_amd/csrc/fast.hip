@@ -349,8 +349,9 @@ constexpr int ROWS_QB = ROWS_QB_N, ROWS_WAVES = 8;
 //     with 1000 keys 34.9 / 34.6);
 //   all of it in 5 MB: of a larger matrix only the first columns' are read, and all workgroups of the GEMM start at once
 //     (16 heads of 128 and d 1536, 80 rows over 1000 keys 52.6 / 53.1; 2048 wide 0 to 2 % slower, 3B the same);
-//   a sixteenth of the compute units without attention's workgroups in the launch's last round: the readers take turns with
-//     it otherwise (256 workgroups: 64.9 / 65.7, 43.1 / 43.6, where 192 are 66.8 / 66.1, 226 80.0 / 79.9 and 384 102.7 / 100.9).
+//   a sixteenth of the compute units without attention's workgroups in the round of 256 that is the launch's last, or more
+//     workgroups than the chip holds (512): the readers take turns with attention otherwise (256 workgroups: 64.9 / 65.7, 43.1 /
+//     43.6, 512: 119.5 / 120.0, where 192 are 66.8 / 66.1, 384 102.7 / 100.9 and 768 165.7 / 164.0).
 // Gate/up's first weights as well, 5 MB in all, gained 0.2 us more at 112 rows of 0.5B and lost 0.3 to 0.5 at 256 and with 16 key
 // heads.  In the norms it does not pay: down's weights 1 to 3 % slower, QKV's 0.5 % faster at 0.5B and 1 to 5 % slower at
 // 1.5B and 3B.
@@ -704,8 +705,8 @@ static dim3 rows_grid(const vf_model *m, const Batch &b) {
 bool vf_attention_reads_ahead(const vf_model *m, const Batch &b) {
     const vf_config &c = m->cfg;
     const dim3 grid = rows_grid(m, b);
-    const unsigned last_round = grid.x * grid.y * grid.z % 256;
-    return b.total_rows > 32 && (size_t)c.n_q_heads * c.head_dim * c.d_model * 2 <= NEXT_BYTES && last_round && last_round <= 240;
+    const unsigned workgroups = grid.x * grid.y * grid.z;
+    return b.total_rows > 32 && (size_t)c.n_q_heads * c.head_dim * c.d_model * 2 <= NEXT_BYTES && (workgroups > 512 || (workgroups - 1) % 256 < 240);
 }
 
 int vf_launch_attention_rows(const vf_model *m, const Batch &b, int layer, hipStream_t st) {
